@@ -124,8 +124,8 @@ __global__ __launch_bounds__(256) void bwd_dispatch_kernel(BwdDispatchParams p) 
   for (int t = blockIdx.x * n_waves + wave; t < p.T; t += n_blocks * n_waves) bwd_dispatch_token<BF16>(p, t);
 }
 
-// ---- fp32 backward GEMMs: one 64 x 64 x 16 LDS-tiled kernel with element strides,
-// every bound checked, K zero-padded.  Exactness path, not a throughput path. ----
+// ---- fp32 backward GEMMs on the tile of gemm_f32.h (H and I are multiples of 64: every tile is full in N, and in M
+// except for the last rows of an expert's segment) ----
 struct GemmBwdParamsF32 {
   const float* A;     // dgrad: [rows, lda]; wgrad: [rows, lda] read transposed
   const float* B;     // dgrad: per expert [N, ldb] (weights, read transposed); wgrad: [rows, ldb]
@@ -139,77 +139,39 @@ struct GemmBwdParamsF32 {
   TileMap tiles;
 };
 
-// acc[i][j] += sum_k A(m0 + ty*4 + i, k) * B(k, n0 + tx*4 + j); A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn];
-// m < M, n < N, k < K else 0.
-__device__ __forceinline__ void gemm_tile_f32_strided(const float* A, long sam, long sak, const float* B, long sbk,
-                                                      long sbn, int M, int N, int K, float* smem,
-                                                      float (&acc)[4][4]) {
-  float(*As)[kFBM] = reinterpret_cast<float(*)[kFBM]>(smem);                  // [k][m]
-  float(*Bs)[kFBN] = reinterpret_cast<float(*)[kFBN]>(smem + kFBK * kFBM);    // [k][n]
-  const int tid = threadIdx.x;
-  const int ty = tid >> 4, tx = tid & 15;
-  for (int k0 = 0; k0 < K; k0 += kFBK) {
-    float av[4], bv[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int idx = tid + q * 256;              // 1024 elements of each 64 x 16 operand tile
-      const int k = idx & 15, x = idx >> 4;       // x = m (A) or n (B)
-      av[q] = (x < M && k0 + k < K) ? A[(long)x * sam + (long)(k0 + k) * sak] : 0.f;
-      bv[q] = (x < N && k0 + k < K) ? B[(long)(k0 + k) * sbk + (long)x * sbn] : 0.f;
-    }
-    __syncthreads();   // previous step's reads are done
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int idx = tid + q * 256;
-      As[idx & 15][idx >> 4] = av[q];
-      Bs[idx & 15][idx >> 4] = bv[q];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kFBK; ++k) {
-      const float4 a = *reinterpret_cast<const float4*>(&As[k][ty * 4]);
-      const float4 b = *reinterpret_cast<const float4*>(&Bs[k][tx * 4]);
-      const float ar[4] = {a.x, a.y, a.z, a.w};
-      const float br[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(ar[i], br[j], acc[i][j]);
-    }
-  }
-  __syncthreads();   // LDS free for the next tile
-}
-
 // act_grad (+ SwiGLU_grad) and gate_grad: C[rows, N] = A[rows, K] * W_e[N, K]^T per M tile.
 template <int EPI>
 __global__ __launch_bounds__(256) void grouped_dgrad_f32_kernel(GemmBwdParamsF32 p) {
-  __shared__ __attribute__((aligned(16))) float smem[kFBK * kFBM + kFBK * kFBN];
+  __shared__ __attribute__((aligned(16))) float smem[kFLdsFloats1];
   const int total = p.tiles.meta[kMetaMTiles] * p.n_ntiles;
-  const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-  for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  const int G = gridDim.x;
+  for (int it = 0; it * G < total; ++it) {
+    const int tile = xcd_spread_tile(it, blockIdx.x, G, total);
+    if (tile < 0) continue;
     const int mtile = tile / p.n_ntiles, n0 = (tile % p.n_ntiles) * kFBN;
     const int e = p.tiles.expert[mtile], row0 = p.tiles.row0[mtile], rows = p.tiles.rows[mtile];
     if (rows <= 0) continue;   // the empty half of a pair slot (block-uniform)
-    float acc[4][4] = {};
-    gemm_tile_f32_strided(p.A + (size_t)row0 * p.lda, p.lda, 1, p.B + (size_t)e * p.strideB + (size_t)n0 * p.ldb, 1,
-                          p.ldb, rows, p.N - n0, p.K, smem, acc);
+    f32x16 acc[1];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = ty * 4 + i;
+    for (int r = 0; r < 16; ++r) acc[0][r] = 0.f;
+    gemm_rows_f32<true, true, 1>(acc, p.A + (size_t)(row0 + min(tid >> 2, rows - 1)) * p.lda + (tid & 3) * 4, 1,
+                                 p.B + (size_t)e * p.strideB + (size_t)(n0 + (tid >> 2)) * p.ldb + (tid & 3) * 4, 1, 0, p.K,
+                                 wm * 32 < rows, smem);
+    const int c = n0 + wn * 32 + (lane & 31);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = wm * 32 + f32_acc_row(r, lane);
       if (m >= rows) continue;
       const size_t grow = (size_t)(row0 + m);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = n0 + tx * 4 + j;
-        if (c >= p.N) continue;
-        if (EPI == kEpiSwigluGrad) {
-          const float g = p.G[grow * (size_t)(2 * p.N) + c], u = p.G[grow * (size_t)(2 * p.N) + p.N + c];
-          const float s = sigmoidf_(g), da = acc[i][j];
-          p.C[grow * p.ldc + c] = da * u * s * (1.f + g * (1.f - s));
-          p.C[grow * p.ldc + p.N + c] = da * g * s;
-        } else {
-          p.C[grow * p.ldc + c] = acc[i][j];
-        }
+      if (EPI == kEpiSwigluGrad) {
+        const float g = p.G[grow * (size_t)(2 * p.N) + c], u = p.G[grow * (size_t)(2 * p.N) + p.N + c];
+        const float s = sigmoidf_(g), da = acc[0][r];
+        p.C[grow * p.ldc + c] = da * u * s * (1.f + g * (1.f - s));
+        p.C[grow * p.ldc + p.N + c] = da * g * s;
+      } else {
+        p.C[grow * p.ldc + c] = acc[0][r];
       }
     }
   }
@@ -217,25 +179,27 @@ __global__ __launch_bounds__(256) void grouped_dgrad_f32_kernel(GemmBwdParamsF32
 
 // w2_grad and w1_grad: C_e[M, N] = A_e[rows_e, M]^T * B_e[rows_e, N]; zeros for experts without rows.
 __global__ __launch_bounds__(256) void grouped_wgrad_f32_kernel(GemmBwdParamsF32 p) {
-  __shared__ __attribute__((aligned(16))) float smem[kFBK * kFBM + kFBK * kFBN];
+  __shared__ __attribute__((aligned(16))) float smem[kFLdsFloats1];
   const int per_e = p.n_mtiles * p.n_ntiles;
   const int total = p.E_local * per_e;
-  const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-  for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  const int G = gridDim.x;
+  for (int it = 0; it * G < total; ++it) {
+    const int tile = xcd_spread_tile(it, blockIdx.x, G, total);
+    if (tile < 0) continue;
     const int e = tile / per_e, rem = tile % per_e;
     const int m0 = (rem / p.n_ntiles) * kFBM, n0 = (rem % p.n_ntiles) * kFBN;
     const int seg0 = p.offsets[e], cnt = p.offsets[e + 1] - seg0;
-    float acc[4][4] = {};
-    gemm_tile_f32_strided(p.A + (size_t)seg0 * p.lda + m0, 1, p.lda, p.B + (size_t)seg0 * p.ldb + n0, p.ldb, 1,
-                          p.M - m0, p.N - n0, cnt, smem, acc);
-    float* c_base = p.C + (size_t)e * p.strideC;
+    f32x16 acc[1];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int r = 0; r < 16; ++r) acc[0][r] = 0.f;
+    const size_t k0 = (size_t)(seg0 + (tid >> 4));
+    gemm_core_f32<false, false, 1, true, true>(acc, p.A + k0 * p.lda + m0 + (tid & 15) * 4, p.lda,
+                                               p.B + k0 * p.ldb + n0 + (tid & 15) * 4, p.ldb, 0, cnt, smem);
+    float* c_base = p.C + (size_t)e * p.strideC + (size_t)(m0 + wm * 32) * p.ldc + n0 + wn * 32 + (lane & 31);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int m = m0 + ty * 4 + i, c = n0 + tx * 4 + j;
-        if (m < p.M && c < p.N) c_base[(size_t)m * p.ldc + c] = acc[i][j];
-      }
+    for (int r = 0; r < 16; ++r) c_base[(size_t)f32_acc_row(r, lane) * p.ldc] = acc[0][r];
   }
 }
 

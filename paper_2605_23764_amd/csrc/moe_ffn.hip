@@ -481,7 +481,7 @@ int run_backward(const BwdCtx& c, const void* dy, const void* x, const void* w_g
   const int bm = tile_bm(s);
   const int tn = BF16 ? kBN : kFBN;
   auto ceil_div = [](int a, int b) { return (a + b - 1) / b; };
-  const int grid = BF16 ? (c.n_cu + 7) / 8 * 8 : c.n_cu * 4;
+  const int grid = (c.n_cu + 7) / 8 * 8 * (BF16 ? 1 : 4);   // fp32: four 256-thread workgroups per CU
 
   uint32_t* tickets = reinterpret_cast<uint32_t*>(c.ws + c.L.tickets);   // [0, 8): w2_grad, [8, 16): w1_grad
 

@@ -1,0 +1,32 @@
+"""fp32 grouped GEMMs on the matrix pipe at the edges of their tiles: 64 rows (two wave rows of 32), 64 columns, a
+reduction in steps of 16 that the weight gradients cut at an expert's last row.  Against the fp64 oracle; the bound is
+the fp32 one of the other tests (1e-5 of the largest element; sums of at most 320 products)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_23764_amd as moe
+from workloads import make_inputs
+
+pytestmark = pytest.mark.gpu
+
+# rows per expert: none, one, around 16, 32 and 64, and three tiles
+ROWS = [0, 1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 130]
+
+
+@pytest.mark.parametrize("H,I,keep_xp", [(64, 64, True), (320, 192, False)])
+def test_edges_of_the_fp32_tiles(H, I, keep_xp):
+    from gpu_common import check_backward, check_forward, check_routing, run_backward, run_forward, small_config
+    cfg = small_config("f32_edges", sum(ROWS), H, I, len(ROWS), len(ROWS), 0, 1, "f32", 71)
+    inp = make_inputs(cfg, with_dy=True)
+    inp["logits"][:] = -10.0
+    inp["logits"][np.arange(cfg.T), np.random.default_rng(3).permutation(np.repeat(np.arange(len(ROWS)), ROWS))] = 1.0
+    ref = oracle.forward(inp["x"], inp["logits"], inp["w_gate_up"], inp["w_down"], cfg.k)
+    assert ref["counts"].tolist() == ROWS
+    run = run_forward(cfg, inp, store_h1=True, keep_xp=keep_xp)
+    check_routing(run, ref)
+    check_forward(run, ref, "f32", store_h1=True)
+    single = run_forward(cfg, inp, mode=moe.MODE_PERSISTENT, store_h1=True, keep_xp=keep_xp)
+    assert torch.equal(single.out, run.out)
+    check_backward(run_backward(cfg, inp, run), oracle.backward(inp["dy"], ref, inp["w_gate_up"], inp["w_down"]), ref["counts"], "f32")

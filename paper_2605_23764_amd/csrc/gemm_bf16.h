@@ -807,12 +807,14 @@ __device__ __forceinline__ bool pair_work_item(const GemmParams& p, int m0, int 
   return mtile < n_m && __builtin_amdgcn_readfirstlane(p.tiles.rows[mtile]) > 0;
 }
 
-// Tile id for workgroup b in sweep `it` of a grid of G workgroups (G % 8 == 0).
-// Workgroups are dealt to the 8 XCDs round-robin by id, so giving XCD x the
-// contiguous ids [x*G/8, (x+1)*G/8) keeps tiles that share an operand panel
-// (same M tile, neighbouring N tiles) behind the same L2.
-__device__ __forceinline__ int xcd_tile_id(int it, int b, int G) {
-  return it * G + (b & 7) * (G >> 3) + (b >> 3);
+// Tile of workgroup b in sweep `it` of a grid of G workgroups (G % 8 == 0) over `total` tiles, -1 if it has none.
+// Workgroups are dealt to the 8 XCDs round-robin by id; an XCD takes a contiguous eighth of the sweep, so that tiles that
+// share an operand panel sit behind the same L2, and of a partly filled sweep an eighth of what there is: with a fixed
+// G / 8 tiles per XCD the 72 tiles of a small fp32 layer sat on one of the eight (GEMM-1 44 us), and the last 256 of 2816
+// weight-gradient tiles ran two to a CU on half of the chip.
+__device__ __forceinline__ int xcd_spread_tile(int it, int b, int G, int total) {
+  const int n = min(G, total - it * G), per = (n + 7) >> 3, i = b >> 3, t = (b & 7) * per + i;
+  return i < per && t < n ? it * G + t : -1;
 }
 
 // Activation x weight GEMMs over the M-tile map.  The map lists M tiles in pairs

@@ -20,7 +20,7 @@
 // pipe is 83 % busy on a busy CU (GEMM-1); the rest is the last round: 1056 tiles on 256 CUs are 4.1 per CU.
 #pragma once
 #include "common.h"
-#include "gemm_bf16.h"  // GemmEpilogue
+#include "gemm_bf16.h"  // GemmEpilogue, xcd_spread_tile
 
 namespace moe {
 
@@ -183,15 +183,6 @@ __device__ __forceinline__ void gemm_tile_f32(const GemmParamsF32& p, int mtile,
       p.C[grow * p.ldc + c] = acc[0][r];
     }
   }
-}
-
-// Tile of workgroup b in sweep `it` of a grid of G workgroups over `total` tiles, -1 if it has none: an XCD takes a
-// contiguous eighth of the sweep, of a partly filled one too, so that neighbouring tiles share operands behind one L2
-// and the last tiles are spread over the whole chip (a fixed G / 8 tiles per XCD would put the 72 tiles of a small layer
-// on one of the eight: its GEMM-1 took 44 us).
-__device__ __forceinline__ int xcd_spread_tile(int it, int b, int G, int total) {
-  const int n = min(G, total - it * G), per = (n + 7) >> 3, i = b >> 3, t = (b & 7) * per + i;
-  return i < per && t < n ? it * G + t : -1;
 }
 
 template <int EPI>

@@ -79,16 +79,26 @@ __global__ __launch_bounds__(256) void permute_kernel(PermuteParams p) {
 // The same copy for the rows of experts with at least k_lo rows only (offsets: E_local + 1 prefix sums of
 // the rows per expert).  Used by the backward when the forward kept no permuted copy: the register-
 // stationary weight-gradient kernel reads x through the permutation itself, the general kernel (experts
-// above its row limit) reads this partial copy.
+// above its row limit) reads this partial copy.  A wave walks all rows in strides and finds each row's expert by
+// counting the segment ends at or below it, 64 to a ballot: the rows of all experts are under way together (expert after
+// expert, ten experts of 100 rows took ten dependent copies, 18 us instead of 5).
 __global__ __launch_bounds__(256) void permute_large_experts_kernel(PermuteParams p, const int32_t* offsets, int E_local,
                                                                     int k_lo) {
   const int n_waves = blockDim.x / kWave;
   const int wave = threadIdx.x / kWave;
-  for (int e = 0; e < E_local; ++e) {
-    const int seg0 = offsets[e], seg1 = offsets[e + 1];
-    if (seg1 - seg0 < k_lo) continue;
-    for (int r0 = seg0 + blockIdx.x * n_waves; r0 < seg1; r0 += gridDim.x * n_waves)
-      permute_rows<4>(p, r0, min(seg1, r0 + n_waves), wave, n_waves);
+  const int lane = lane_id();
+  int end[kMaxE / kWave];
+#pragma unroll
+  for (int i = 0; i < kMaxE / kWave; ++i) {
+    const int e = i * kWave + lane;
+    end[i] = e < E_local ? offsets[e + 1] : 0x7fffffff;
+  }
+  const int R = offsets[E_local];
+  for (int r = blockIdx.x * n_waves + wave; r < R; r += gridDim.x * n_waves) {
+    int e = 0;
+#pragma unroll
+    for (int i = 0; i < kMaxE / kWave; ++i) e += __popcll(__ballot(end[i] <= r));
+    if (offsets[e + 1] - offsets[e] >= k_lo) permute_rows<4>(p, r, r + 1, 0, 1);
   }
 }
 

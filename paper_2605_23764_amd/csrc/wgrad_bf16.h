@@ -237,7 +237,7 @@ __device__ __forceinline__ void wgrad_tile_of(int r, int n_mt, int n_nt, int& mt
 // expert by expert (wgrad_tile_of inside an expert), without gaps and with neighbours of equal cost: a sweep of
 // G consecutive tiles over the G workgroups is then balanced by construction (all tiles of a sweep belong to
 // one expert or to two of neighbouring size), and the last, partly filled sweep holds the cheapest tiles.  An
-// XCD takes a contiguous range of every sweep, so the CUs that share operand panels sit behind one L2.
+// XCD takes a contiguous eighth of every sweep, so the CUs that share operand panels sit behind one L2.
 __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void grouped_wgrad2_bf16_kernel(GemmParams p) {
   __shared__ __attribute__((aligned(1024))) char smem[kWgLdsBytes];
@@ -271,8 +271,8 @@ void grouped_wgrad2_bf16_kernel(GemmParams p) {
   const int total = s_box[0] * per_e;
   const int G = gridDim.x;
   for (int it = 0; it * G < total; ++it) {
-    const int tile = xcd_tile_id(it, blockIdx.x, G);
-    if (tile >= total) continue;
+    const int tile = xcd_spread_tile(it, blockIdx.x, G, total);
+    if (tile < 0) continue;
     const int r = tile / per_e;
     const int e = __builtin_amdgcn_readfirstlane(s_order[r]);
     int mt, nt;

@@ -432,8 +432,8 @@ void grouped_wgrad_panel_bf16_kernel(GemmParams p, int want_items) {
       mp = ticket - k * n_mp;
     } else {
       if (it * G >= total) break;
-      const int id = xcd_tile_id(it, blockIdx.x, G);
-      if (id >= total) continue;
+      const int id = xcd_spread_tile(it, blockIdx.x, G, total);
+      if (id < 0) continue;
       // items of one expert and column range are neighbours: they share the B chunks through the L2
       e = __builtin_amdgcn_readfirstlane(id / per_e);
       const int r = id - e * per_e;

@@ -67,6 +67,7 @@ constexpr int kMaxMT = kBM / 64;                     // 32-row MFMA sub-tiles pe
 // those of a 256-row tile, and the MFMA work grows by the real rows only.
 constexpr int kWideRows = kBM + 64;
 constexpr int kBLinesPerWave = kBLines / 4;          // 8
+constexpr int kStreamMaxRows = 64;                   // rows of the largest expert up to which a launch runs as a weight stream
 
 struct GemmParams {
   const __bf16* A;    // [rows, lda] activations, expert-contiguous rows, k-contiguous
@@ -89,9 +90,9 @@ struct GemmParams {
   int M;              // weight gradients: output rows
   int lda, ldb, ldc;
   int n_ntiles;       // ceil(N / 256) (SwiGLU: ceil(N / 128))
-  int E_local;        // weight gradients
+  int E_local;        // NN, NT: local experts (weight stream); weight gradients
   int k_lo;           // weight gradients, general kernel: experts with fewer rows are left to the register-stationary kernel
-  const int32_t* offsets;   // weight gradients: [E_local + 1] segment boundaries
+  const int32_t* offsets;   // [E_local + 1] segment boundaries
   uint32_t* tickets;        // weight gradients, register-stationary kernel: 8 zeroed counters (one per XCD) from which
                             // the workgroups draw their items; nullptr = fixed round-robin assignment
   TileMap tiles;      // NN, NT
@@ -118,11 +119,19 @@ __device__ __forceinline__ void wait_vmcnt() {
 // vmcnt(0) before every operand read (which would serialise the pipeline); ordering
 // is done by hand with wait_vmcnt + s_barrier.  The "memory" clobber keeps LDS reads
 // from moving across.
+// STREAM: non-temporal, for bytes that nobody reads a second time.
+template <bool STREAM = false>
 __device__ __forceinline__ void lds_dma16(const char* sbase, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(lds_addr), "v"(voff), "s"(sbase)
-               : "memory", "m0");
+  if constexpr (STREAM)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                 :
+                 : "s"(lds_addr), "v"(voff), "s"(sbase)
+                 : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(lds_addr), "v"(voff), "s"(sbase)
+                 : "memory", "m0");
 }
 
 // One slice of the register-fed row block: lane (row l32, half lh) fetches the 16 bytes that are its MFMA operand
@@ -530,6 +539,19 @@ __device__ __forceinline__ void scatter_block_via_lds(char* region, const u32x2 
   __builtin_amdgcn_wave_barrier();
 }
 
+// SwiGLU_grad on four elements of act_grad (Section 2.2, Figure 2b): with the saved pre-activations (g, u), packed bf16,
+// d_gate = dA*u*s*(1 + g*(1 - s)), d_up = dA*g*s, s = sigmoid(g).
+__device__ __forceinline__ void swiglu_grad4(const float (&da)[4], u32x2 gv, u32x2 uv, float (&dg)[4], float (&du)[4]) {
+  const float g[4] = {bf16_lo(gv.x), bf16_hi(gv.x), bf16_lo(gv.y), bf16_hi(gv.y)};
+  const float u[4] = {bf16_lo(uv.x), bf16_hi(uv.x), bf16_lo(uv.y), bf16_hi(uv.y)};
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    const float sg = sigmoid_bf16_(g[x]);
+    dg[x] = da[x] * u[x] * sg * (1.f + g[x] * (1.f - sg));
+    du[x] = da[x] * g[x] * sg;
+  }
+}
+
 // One output tile: (t0, t1) = (M tile of the tile map, N tile of TileShape<TALL>::kCols
 // columns; SwiGLU: half as many output columns).  X5: a wide tile of 257..320 rows (rows past 256 go
 // through the register-fed block of each wave row).
@@ -723,8 +745,7 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmParams& p, int t0, int 
         store_block_via_lds<4, false, true>(region, ph, h, 2 * p.N, rows_valid, p.N - c0, h + p.N);
       }
     } else if (EPI == kEpiSwigluGrad) {
-      // SwiGLU_grad on the act_grad tile (Section 2.2, Figure 2b): the accumulators hold dA; with the saved
-      // pre-activations (g, u): d_gate = dA*u*s*(1 + g*(1 - s)), d_up = dA*g*s, s = sigmoid(g)
+      // SwiGLU_grad on the act_grad tile: the accumulators hold dA
       const int c0 = ntile * S::kCols + wn * 128;
       u32x2 pdg[4][4], pdu[4][4];
       const bool row_ok = l32 < rows_valid;
@@ -739,16 +760,9 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmParams& p, int t0, int 
             gv = *reinterpret_cast<const u32x2*>(h + c);
             uv = *reinterpret_cast<const u32x2*>(h + p.N + c);
           }
-          const float g[4] = {bf16_lo(gv.x), bf16_hi(gv.x), bf16_lo(gv.y), bf16_hi(gv.y)};
-          const float u[4] = {bf16_lo(uv.x), bf16_hi(uv.x), bf16_lo(uv.y), bf16_hi(uv.y)};
           float dg[4], du[4];
-#pragma unroll
-          for (int x = 0; x < 4; ++x) {
-            const float da = am[nt][q * 4 + x];
-            const float sg = sigmoid_bf16_(g[x]);
-            dg[x] = da * u[x] * sg * (1.f + g[x] * (1.f - sg));
-            du[x] = da * g[x] * sg;
-          }
+          const float da[4] = {am[nt][q * 4], am[nt][q * 4 + 1], am[nt][q * 4 + 2], am[nt][q * 4 + 3]};
+          swiglu_grad4(da, gv, uv, dg, du);
           pdg[nt][q] = u32x2{pack_bf16(dg[0], dg[1]), pack_bf16(dg[2], dg[3])};
           pdu[nt][q] = u32x2{pack_bf16(du[0], du[1]), pack_bf16(du[2], du[3])};
         }
@@ -822,11 +836,21 @@ __device__ __forceinline__ int xcd_spread_tile(int it, int b, int G, int total) 
 // XCD j % 8 (workgroups are dealt to the XCDs round-robin by id); inside an XCD
 // the work items run N-tile-major with the two siblings adjacent, so the CUs that
 // stream the same weight panel do so at the same time behind the same L2.
+// A launch whose largest expert has at most kStreamMaxRows rows runs as a weight stream instead (gemm_stream.h).
+template <int LAY, int EPI>
+__device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_rows, char* smem);
+
 template <int LAY, int EPI>
 __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void grouped_gemm_bf16_kernel(GemmParams p) {
   __shared__ __attribute__((aligned(1024))) char smem[kGemmLdsBytes];
-  const int n_m = p.tiles.meta[kMetaMTiles];
+  const int n_m = p.tiles.meta[kMetaMTiles], max_rows = p.tiles.meta[kMetaMaxRows];   // both fetched at once
+  if constexpr (EPI != kEpiScatter) {
+    if (max_rows <= kStreamMaxRows) {
+      stream_gemm_bf16<LAY, EPI>(p, max_rows, smem);
+      return;
+    }
+  }
   const int xcd = blockIdx.x & 7, lw = blockIdx.x >> 3, W = gridDim.x >> 3;
   const int n_pairs = (n_m + 1) >> 1;
   const int pairs_x = n_pairs > xcd ? (n_pairs - xcd + 7) >> 3 : 0;

@@ -1,0 +1,320 @@
+// Grouped bf16 GEMMs for a few rows per expert (serving batches, small training batches): the weight stream.
+//
+// With at most 64 rows per expert a weight element meets one or two MFMA row blocks, so the launch is a read of the
+// weights at HBM rate and nothing else; the tile of gemm_bf16.h (256 weight columns, 64 KB of weights under way per CU)
+// then has too few work items to fill the chip evenly (T = 1 at H = 2048, I = 1408: 44 items on four of the eight dies)
+// and too little in flight.  Here
+//   * an item is 128 or 64 weight columns of one expert over the whole K (never split: results are the same bits as the
+//     other kernel's, whose MFMAs sum in the same order), dealt evenly to all workgroups; 64 columns where that makes the
+//     rounds come out shorter;
+//   * a workgroup runs its items as ONE stream of 16 KB weight stages (64 k x 128 columns or 128 k x 64) through an LDS
+//     ring of 6 or 7 stages, 80..96 KB of weights under way; the next item's first stages are requested while the last
+//     ones of this item are multiplied, so nothing drains between items;
+//   * activation rows ride along in the same stage (4 or 8 KB, from the L2), gathered through the permutation if need be;
+//   * one barrier per stage; each of the four waves multiplies one 32-column block (two of them with 64 columns).
+//     For SwiGLU a wave's block is 16 gate and the 16 matching up columns: both meet in one lane's accumulators.
+// Results are written straight from the accumulators (8 bytes per lane): they are a thousandth of the bytes read.
+// The weights are read non-temporally (each line once, by one workgroup): 5 to 9 % of a launch.
+// What bounds it: the rate at which HBM serves 256-byte pieces of rows 8..14 KB apart.  A loop that only loads them
+// reaches 6.2 TB/s (5.7 without the non-temporal hint), 1 KB pieces 6.3..6.7, one linear stream 7.1; with the MFMAs
+// taken out the launch is no faster, without the activation loads 2 %.
+// Measured, layer (routing and Combine included), against the tiles of gemm_bf16.h: H = 7168, I = 2048, 32 of 256 experts,
+// k = 8: T = 4 168 -> 101 us, T = 32 428 -> 354, T = 256 527 -> 499, T = 1000 548 -> 527; H = 2048, I = 1408, 16 experts,
+// k = 4: T = 1 60 -> 38.5, T = 8 74 -> 68, T = 64 76 -> 73.  Above 64 rows the activations' share of a stage grows past a
+// third and the other kernel's 256 rows per weight fetch win.
+#pragma once
+#include "gemm_bf16.h"
+
+namespace moe {
+
+constexpr int kStreamGather = 2048;                  // token indices kept in LDS (rows beyond are looked up in memory)
+constexpr int kStreamTables = 6 * 24 * 1024;         // LDS offset of the tables, behind the larger ring
+constexpr int kStreamGatherOff = kStreamTables + 3 * kMaxE * 4;
+static_assert(kStreamGatherOff + kStreamGather * 4 <= kGemmLdsBytes, "LDS budget");
+
+// CW weight columns per item; AL activation lines (8 rows x 64 k) per wave and stage.
+template <int CW, int AL>
+struct StreamShape {
+  static constexpr int kKB = 8192 / CW;                          // k per stage
+  static constexpr int kRows = (CW == 128 ? 32 : 16) * AL;       // activation rows a stage holds
+  static constexpr int kMT = kRows > 32 ? 2 : 1;                 // 32-row blocks
+  static constexpr int kStage = (16 + 4 * AL) * kLine;
+  static constexpr int kDepth = AL == 1 ? 7 : 6;
+  static constexpr int kLoads = 4 + AL;                          // wave-wide loads per wave and stage
+  static_assert(kDepth * kStage <= kStreamTables, "ring");
+};
+
+typedef __attribute__((address_space(3))) int32_t* lds_i32_ptr;
+// Waits until at most `stages` stages requested after the wanted one are under way (fewer near the end of the stream).
+template <int LPS, int MOST>
+__device__ __forceinline__ void stream_wait(int stages) {
+  if constexpr (MOST == 0) {
+    wait_vmcnt<0>();
+  } else {
+    if (stages >= MOST) wait_vmcnt<LPS * MOST>();
+    else stream_wait<LPS, MOST - 1>(stages);
+  }
+}
+
+template <int LAY, int EPI, int CW, int AL>
+__device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, char* smem) {
+  typedef StreamShape<CW, AL> S;
+  constexpr int kOut = EPI == kEpiSwiglu ? CW / 2 : CW;          // output columns per item
+  constexpr int kRPL = CW == 128 ? 4 : 8;                        // NN: k-rows per 1 KB line
+  const int G = gridDim.x;
+  const int n_ct = (p.N + kOut - 1) / kOut;
+  const int total = n_act * n_ct;
+  // 128 columns: neighbouring items on different dies, as the dispatcher deals them; 64 columns: on one die, whose L2 then
+  // serves both halves of a line that two items share
+  auto tile_of = [&](int it) __attribute__((always_inline)) {
+    const int id = it * G + (int)blockIdx.x;
+    return CW == 128 ? (id < total ? id : -1) : xcd_spread_tile(it, blockIdx.x, G, total);
+  };
+  int n_items = (total + G - 1) / G;
+  if (n_items > 0 && tile_of(n_items - 1) < 0) --n_items;
+  if (n_items <= 0) return;
+  const int n_steps = (p.K + S::kKB - 1) / S::kKB;
+  const int n_total = __builtin_amdgcn_readfirstlane(n_items * n_steps);
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lh = lane >> 5;
+  const lds_i32_ptr s_expert = (lds_i32_ptr)(smem + kStreamTables), s_row0 = s_expert + kMaxE, s_rows = s_row0 + kMaxE;
+  const lds_i32_ptr s_tok = (lds_i32_ptr)(smem + kStreamGatherOff);
+  const uint32_t lds0 = lds_addr_of(smem);
+  const int ldb_bytes = p.ldb * 2;
+
+  // ---- request side: item and step of the next stage to request ----
+  const int r8 = lane >> 3;                                      // row of this lane inside an 8-row line
+  struct { const char *a_base, *b_base; uint32_t a_off[AL], b_off[LAY == kLayNT ? 4 : 1]; int step, item, slot; } q;
+  q.step = 0; q.item = 0; q.slot = 0;
+  auto item_of = [&](int it, int& ae, int& ct) __attribute__((always_inline)) {
+    const int id = tile_of(it);
+    ae = __builtin_amdgcn_readfirstlane(id / n_ct);
+    ct = __builtin_amdgcn_readfirstlane(id - ae * n_ct);
+  };
+  auto set_item = [&]() __attribute__((always_inline)) {
+    int ae, ct;
+    item_of(q.item, ae, ct);
+    const int e = __builtin_amdgcn_readfirstlane(s_expert[ae]), row0 = __builtin_amdgcn_readfirstlane(s_row0[ae]);
+    const int rows = __builtin_amdgcn_readfirstlane(s_rows[ae]);
+    const bool gathered = LAY == kLayNN && p.gather != nullptr;
+    q.a_base = uniform_ptr(reinterpret_cast<const char*>(gathered ? p.A : p.A + (size_t)row0 * p.lda));
+    q.b_base = uniform_ptr(reinterpret_cast<const char*>(p.B + (size_t)e * p.strideB));
+#pragma unroll
+    for (int i = 0; i < AL; ++i) {
+      // activation line wave + 4 i: CW = 128: rows 8 (wave + 4 i) ..; CW = 64: rows 8 ((wave + 4 i) / 2) .., k half wave & 1
+      const int rl = CW == 128 ? wave + 4 * i : (wave + 4 * i) >> 1;
+      const int row = min(rl * 8 + r8, rows - 1);                // rows past the end repeat the last one; never stored
+      int arow = row;
+      if (gathered) arow = row0 + row < kStreamGather ? s_tok[row0 + row] : p.gather[row0 + row];
+      const int chunk = (lane & 7) ^ ((4 * (rl & 1) + (r8 >> 1)) & 7);
+      q.a_off[i] = (uint32_t)(((long)arow * p.lda + chunk * 8) * 2);
+    }
+    if constexpr (LAY == kLayNN) {
+      int kk, col;
+      if (CW == 128) {
+        kk = lane >> 4;
+        const int c = ((lane & 15) - 4 * kk) & 15;               // staged chunk of 8 columns, k-rows rotated by 64 bytes
+        if (EPI == kEpiSwiglu) col = c < 8 ? ct * 64 + c * 8 : p.N + ct * 64 + ((c - 8) ^ 2) * 8;
+        else col = min(ct * 128 + c * 8, p.N - 8);
+      } else {
+        kk = r8;
+        const int c = (lane & 7) ^ (4 * ((kk >> 1) & 1));
+        if (EPI == kEpiSwiglu) col = c < 4 ? ct * 32 + c * 8 : p.N + ct * 32 + ((c - 4) ^ 2) * 8;
+        else col = ct * 64 + c * 8;
+      }
+      q.b_off[0] = (uint32_t)((kk * p.ldb + col) * 2);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        // weight line wave * 4 + i: 8 output columns x 64 k; CW = 64: column group (line / 2), k half line & 1
+        const int nl = CW == 128 ? wave * 4 + i : wave * 2 + (i >> 1);
+        const int n = min(ct * CW + nl * 8 + r8, p.N - 1);
+        const int chunk = (lane & 7) ^ ((4 * (nl & 1) + (r8 >> 1)) & 7);
+        q.b_off[i] = (uint32_t)(((size_t)n * p.ldb + chunk * 8) * 2);
+      }
+    }
+  };
+  auto request = [&]() __attribute__((always_inline)) {
+    if (q.step == 0) set_item();
+    const int k0 = q.step * S::kKB;
+    const uint32_t st = uniform_u32(lds0 + (uint32_t)(q.slot * S::kStage));
+    // k past the end (an odd number of 64s with 128 to a stage): the last 64 again, not multiplied
+    const char* a_k = uniform_ptr(q.a_base + (size_t)(CW == 128 ? k0 : min(k0 + (wave & 1) * 64, p.K - 64)) * 2);
+#pragma unroll
+    for (int i = 0; i < AL; ++i) lds_dma16(a_k, q.a_off[i], st + 16 * kLine + (wave + 4 * i) * kLine);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const char* b_k;
+      if (LAY == kLayNN) b_k = q.b_base + (size_t)min(k0 + (wave * 4 + i) * kRPL, p.K - kRPL) * ldb_bytes;
+      else b_k = q.b_base + (size_t)(CW == 128 ? k0 : min(k0 + (i & 1) * 64, p.K - 64)) * 2;
+      lds_dma16<CW == 128>(uniform_ptr(b_k), q.b_off[LAY == kLayNT ? i : 0], st + (wave * 4 + i) * kLine);
+    }
+    q.slot = q.slot == S::kDepth - 1 ? 0 : q.slot + 1;
+    if (++q.step == n_steps) { q.step = 0; ++q.item; }
+  };
+
+  // ---- operand reads: offsets of this lane inside a stage ----
+  const int blk = CW == 128 ? wave : wave & 1;                   // this wave's 32-column block
+  const bool active = CW == 128 || wave < 2;
+  uint32_t b_rd;
+  if (LAY == kLayNN) {
+    const int g = lane >> 4, i = lane & 15, kk = i >> 2;
+    int c;                                                       // staged chunk of this 16-lane group's columns
+    if (EPI == kEpiSwiglu) c = (g & 1) ? CW / 16 + ((2 * blk + ((i & 3) >> 1)) ^ 2) : 2 * blk + ((i & 3) >> 1);
+    else c = 4 * blk + (g & 1) * 2 + ((i & 3) >> 1);
+    if (CW == 128) b_rd = (uint32_t)((g >> 1) * 2 * kLine + kk * 256 + ((c + 4 * kk) & 15) * 16 + (i & 1) * 8);
+    else b_rd = (uint32_t)((g >> 1) * kLine + kk * 128 + (c ^ (4 * ((kk >> 1) & 1))) * 16 + (i & 1) * 8);
+  } else {
+    b_rd = (uint32_t)((blk * 4 + (l32 >> 3)) * (CW == 128 ? 1 : 2) * kLine + (l32 & 7) * 128);
+  }
+  const int ar = l32 & (S::kRows - 1);                           // 16-row stages: the upper lanes repeat the rows
+  const uint32_t a_rd = (uint32_t)(16 * kLine + (ar >> 3) * (CW == 128 ? 1 : 2) * kLine + (ar & 7) * 128);
+  const int a_sw = (ar >> 1) & 7, b_sw = (l32 >> 1) & 7;
+
+  f32x16 acc[S::kMT];
+#pragma unroll
+  for (int mt = 0; mt < S::kMT; ++mt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
+
+  auto half_stage = [&](lds_cptr st, int h) __attribute__((always_inline)) {   // 64 k: four MFMA slices
+    bf16x8 wf[4], xf[4][S::kMT];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int ks = h * 4 + s;
+      if (LAY == kLayNN) {
+        const lds_cptr b = st + b_rd + ks * (CW == 128 ? 4 : 2) * kLine;
+        wf[s] = join_tr(__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)b),
+                        __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(b + (CW == 128 ? kLine : kLine / 2))));
+      } else {
+        wf[s] = *(lds_bf16x8_cptr)(st + b_rd + h * kLine + (uint32_t)(((s * 2 + lh) ^ b_sw) << 4));
+      }
+#pragma unroll
+      for (int mt = 0; mt < S::kMT; ++mt)
+        xf[s][mt] = *(lds_bf16x8_cptr)(st + a_rd + h * kLine + mt * 4 * kLine + (uint32_t)(((s * 2 + lh) ^ a_sw) << 4));
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int mt = 0; mt < S::kMT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s], xf[s][mt], acc[mt], 0, 0, 0);
+  };
+
+  for (int g = 0; g < S::kDepth - 1 && g < n_total; ++g) request();
+  int step = 0, item = 0, slot = 0;
+  for (int g = 0; g < n_total; ++g) {
+    stream_wait<S::kLoads, S::kDepth - 2>(n_total - 1 - g);      // this wave's part of stage g has landed
+    wait_lgkmcnt0();
+    __builtin_amdgcn_s_barrier();                                // ... and everybody's; stage g - 1 has been read by all
+    if (g + S::kDepth - 1 < n_total) request();                  // into the slot of stage g - 1
+    if (active) {
+      const lds_cptr st = (lds_cptr)smem + slot * S::kStage;
+      half_stage(st, 0);
+      if (CW == 64 && step * S::kKB + 64 < p.K) half_stage(st, 1);
+    }
+    slot = slot == S::kDepth - 1 ? 0 : slot + 1;
+    if (++step < n_steps) continue;
+    step = 0;
+    int ae, ct;
+    item_of(item++, ae, ct);
+    if (!active) continue;
+    const int row0 = __builtin_amdgcn_readfirstlane(s_row0[ae]), rows = __builtin_amdgcn_readfirstlane(s_rows[ae]);
+    // lane: row l32 of each 32-row block; register group q: staged columns q * 8 + lh * 4 .. + 3 of the wave's block
+#pragma unroll
+    for (int mt = 0; mt < S::kMT; ++mt) {
+      const int m = mt * 32 + l32;
+      const size_t grow = (size_t)(row0 + m);
+      if (m < rows) {
+        if (EPI == kEpiSwiglu) {
+#pragma unroll
+          for (int qg = 0; qg < 2; ++qg) {
+            const int c = ct * kOut + blk * 16 + qg * 8 + lh * 4;
+            float gt[4], u[4], a[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+              gt[x] = acc[mt][qg * 4 + x];
+              u[x] = acc[mt][qg * 4 + 8 + x];
+              a[x] = gt[x] * sigmoid_bf16_(gt[x]) * u[x];
+            }
+            *reinterpret_cast<u32x2*>(p.C + grow * p.ldc + c) = u32x2{pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3])};
+            if (p.C2) {
+              __bf16* h = p.C2 + grow * (size_t)(2 * p.N) + c;
+              *reinterpret_cast<u32x2*>(h) = u32x2{pack_bf16(gt[0], gt[1]), pack_bf16(gt[2], gt[3])};
+              *reinterpret_cast<u32x2*>(h + p.N) = u32x2{pack_bf16(u[0], u[1]), pack_bf16(u[2], u[3])};
+            }
+          }
+        } else {
+#pragma unroll
+          for (int qg = 0; qg < 4; ++qg) {
+            const int c = ct * kOut + blk * 32 + qg * 8 + lh * 4;
+            if (c >= p.N) continue;
+            float v[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) v[x] = acc[mt][qg * 4 + x];
+            if (EPI == kEpiSwigluGrad) {
+              const __bf16* h = p.G + grow * (size_t)(2 * p.N) + c;
+              float dg[4], du[4];
+              swiglu_grad4(v, *reinterpret_cast<const u32x2*>(h), *reinterpret_cast<const u32x2*>(h + p.N), dg, du);
+              __bf16* o = p.C + grow * p.ldc + c;
+              *reinterpret_cast<u32x2*>(o) = u32x2{pack_bf16(dg[0], dg[1]), pack_bf16(dg[2], dg[3])};
+              *reinterpret_cast<u32x2*>(o + p.N) = u32x2{pack_bf16(du[0], du[1]), pack_bf16(du[2], du[3])};
+            } else {
+              *reinterpret_cast<u32x2*>(p.C + grow * p.ldc + c) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+            }
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int mt = 0; mt < S::kMT; ++mt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
+  }
+}
+
+// Whole launch of a grouped GEMM whose largest expert has max_rows <= kStreamMaxRows rows.
+template <int LAY, int EPI>
+__device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_rows, char* smem) {
+  // experts with rows, in expert order (every wave counts, wave 0 writes), and the tokens of the first rows
+  const int lane = lane_id();
+  const lds_i32_ptr s_expert = (lds_i32_ptr)(smem + kStreamTables), s_row0 = s_expert + kMaxE, s_rows = s_row0 + kMaxE;
+  int n_act = 0, R = 0;
+  int lo[kMaxE / kWave], hi[kMaxE / kWave];
+#pragma unroll
+  for (int i = 0; i < kMaxE / kWave; ++i) {
+    const int e = i * kWave + lane;
+    lo[i] = e < p.E_local ? p.offsets[e] : 0;
+    hi[i] = e < p.E_local ? p.offsets[e + 1] : 0;
+  }
+#pragma unroll
+  for (int i = 0; i < kMaxE / kWave; ++i) {
+    const uint64_t bal = __ballot(hi[i] > lo[i]);
+    const int at = n_act + __popcll(bal & ((1ull << lane) - 1));
+    if (threadIdx.x < kWave && hi[i] > lo[i]) {
+      s_expert[at] = i * kWave + lane;
+      s_row0[at] = lo[i];
+      s_rows[at] = hi[i] - lo[i];
+    }
+    n_act += __popcll(bal);
+  }
+  if (LAY == kLayNN && p.gather) {
+    R = p.offsets[p.E_local];
+    const lds_i32_ptr s_tok = (lds_i32_ptr)(smem + kStreamGatherOff);
+    for (int i = threadIdx.x; i < min(R, kStreamGather); i += kGemmThreads) s_tok[i] = p.gather[i];
+  }
+  __syncthreads();
+  n_act = __builtin_amdgcn_readfirstlane(n_act);
+  // 128 columns per item; 64 only where that still is a single round, i.e. where the chip would be at most half full
+  // (T = 1, H = 2048, I = 1408, four experts: GEMM-1 88 items -> 176): 64 columns are 128-byte pieces of a row, 64-byte
+  // pieces for SwiGLU (half gate, half up), which stream 10..30 % slower once all CUs are busy (T = 64: 84 us a layer
+  // against 73).
+  constexpr int kOut64 = EPI == kEpiSwiglu ? 32 : 64;
+  const bool narrow = n_act * ((p.N + kOut64 - 1) / kOut64) <= (int)gridDim.x;
+  if (max_rows > 32) stream_items<LAY, EPI, 128, 2>(p, n_act, smem);
+  else if (!narrow) stream_items<LAY, EPI, 128, 1>(p, n_act, smem);
+  else if (max_rows > 16) stream_items<LAY, EPI, 64, 2>(p, n_act, smem);
+  else stream_items<LAY, EPI, 64, 1>(p, n_act, smem);
+}
+
+}  // namespace moe

@@ -12,6 +12,7 @@
 #include "common.h"
 #include "gemm_bf16.h"
 #include "gemm_f32.h"
+#include "gemm_stream.h"
 #include "microbench.h"
 #include "permute_combine.h"
 #include "persistent.h"
@@ -244,6 +245,7 @@ P gemm2_params(const Ctx& c, const void* w_down) {
 int run_gemm1(const Ctx& c, const void* w_gate_up, const void* x_gather = nullptr) {
   if (c.s.dtype == MOE_BF16) {
     GemmParams p = gemm1_params<GemmParams, __bf16>(c, w_gate_up);
+    p.offsets = c.sv.offsets; p.E_local = c.s.E_local;
     if (x_gather) {
       p.A = static_cast<const __bf16*>(x_gather);
       p.gather = c.sv.token_of;
@@ -256,10 +258,11 @@ int run_gemm1(const Ctx& c, const void* w_gate_up, const void* x_gather = nullpt
 }
 
 int run_gemm2(const Ctx& c, const void* w_down) {
-  if (c.s.dtype == MOE_BF16)
-    hipLaunchKernelGGL((grouped_gemm_bf16_kernel<kLayNN, kEpiStore>), dim3(gemm_grid(c)), dim3(kGemmThreads), 0, c.stream,
-                       gemm2_params<GemmParams, __bf16>(c, w_down));
-  else
+  if (c.s.dtype == MOE_BF16) {
+    GemmParams p = gemm2_params<GemmParams, __bf16>(c, w_down);
+    p.offsets = c.sv.offsets; p.E_local = c.s.E_local;
+    hipLaunchKernelGGL((grouped_gemm_bf16_kernel<kLayNN, kEpiStore>), dim3(gemm_grid(c)), dim3(kGemmThreads), 0, c.stream, p);
+  } else
     hipLaunchKernelGGL(grouped_gemm_f32_kernel<kEpiStore>, dim3(gemm_grid(c) * 4), dim3(256), 0, c.stream,
                        gemm2_params<GemmParamsF32, float>(c, w_down));
   return launch_status();
@@ -522,6 +525,7 @@ int run_backward(const BwdCtx& c, const void* dy, const void* x, const void* w_g
   pa.lda = s.H; pa.ldb = s.H; pa.ldc = 2 * s.I;
   pa.n_ntiles = ceil_div(s.I, tn);
   pa.tiles = c.tiles;
+  pa.offsets = c.sv.offsets; pa.E_local = s.E_local;
   // gate_grad: dXp = dH1 W_gate_up^T
   P pg{};
   pg.A = dH1; pg.B = static_cast<const T*>(w_gate_up); pg.C = dXp;
@@ -529,6 +533,7 @@ int run_backward(const BwdCtx& c, const void* dy, const void* x, const void* w_g
   pg.lda = 2 * s.I; pg.ldb = 2 * s.I; pg.ldc = s.H;
   pg.n_ntiles = ceil_div(s.H, tn);
   pg.tiles = c.tiles;
+  pg.offsets = c.sv.offsets; pg.E_local = s.E_local;
 
   // w2_grad: dW_down[e] = A_e^T dYp_e (needs only dYp: runs first, while dYp is fresh in the caches)
   auto launch_w2 = [&](hipStream_t st) {

@@ -32,6 +32,8 @@
 // matching up columns, placed so each wave owns both halves of its columns and
 // applies A = g*sigmoid(g)*u to the fp32 accumulators in registers.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 namespace moe {
@@ -132,6 +134,15 @@ __device__ __forceinline__ void lds_dma16(const char* sbase, uint32_t voff, uint
                  :
                  : "s"(lds_addr), "v"(voff), "s"(sbase)
                  : "memory", "m0");
+}
+
+// The same copy to lds_base + OFF: the LDS address goes straight into M0 (three instructions in all).
+template <int OFF>
+__device__ __forceinline__ void lds_dma16_at(const char* sbase, uint32_t voff, uint32_t lds_base) {
+  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(lds_base), "v"(voff), "s"(sbase), "n"(OFF)
+               : "memory", "m0", "scc");
 }
 
 // One slice of the register-fed row block: lane (row l32, half lh) fetches the 16 bytes that are its MFMA operand
@@ -325,6 +336,63 @@ __device__ __forceinline__ void gemm_read_frags(GemmFrags<LAY, NMT>& f, lds_cptr
   for (int a = 0; a < GemmSliceShape<LAY, NMT>::n_reads; ++a) gemm_read_one<LAY, NMT, TALL>(f, a, as, bs, ks, t);
 }
 
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
+// The slice of a wave with four row blocks (tiles of more than 192 rows, matrix bound), with the copies LOAD0 ..
+// LOAD0 + 3 of the load group.  A wave is alone on its SIMD and issues one instruction every four clocks, eight under a
+// 32-clock MFMA, so what stands between two MFMAs decides: here at most one operand read or one copy, the copies evenly
+// among the reads, the reads in the order in which the next slice asks for them, and no branch: 230 instructions per K
+// step instead of 380.  The general slice guards every copy (five to eight instructions and a branch, four copies in a
+// row), and the general loop copies 64 fragment registers per step because its last step differs.
+// Measured, same bits (T = 8192, H = 7168, I = 2048, 32 of 256 experts): forward 869 -> 833 us, with skewed routing as one
+// launch 1320 -> 1250; T = 4096, H = 2048, I = 1408, 16 experts: forward 401 -> 386, backward 731 -> 705.  With the copies
+// masked through exec instead of repeated past the end: 10 % slower than the general loop.  Waves with fewer row blocks
+// keep the general loop: those launches wait for the weights (this slice: 0 to 2 % slower at 64..125 rows per expert).
+template <int LAY, int NX, int LOAD0>
+__device__ __forceinline__ void gemm_slice_full(f32x16 (&acc)[kMaxMT][4], const GemmFrags<LAY, kMaxMT>& cur, GemmFrags<LAY, kMaxMT>& nxt,
+                                                lds_cptr as_n, lds_cptr bs_n, int ks_n, const GemmTileCtx& t,
+                                                const GemmLoadGroup& g, const uint32_t (&b_off)[8], f32x16 (&accx)[4],
+                                                const bf16x8& xblk) {
+  typedef TileShape<false> S;
+  constexpr int NMT = kMaxMT;
+  constexpr int n_w = GemmSliceShape<LAY, NMT>::n_wreads, n_reads = GemmSliceShape<LAY, NMT>::n_reads;
+  constexpr int n_mfma = (NMT + NX) * 4, n_act = n_reads + 4;
+  bf16x8 wf[4], xf[NMT];
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) wf[nt] = LAY == kLayNT ? cur.wk[nt] : join_tr(cur.w[nt][0], cur.w[nt][1]);
+#pragma unroll
+  for (int mt = 0; mt < NMT; ++mt) xf[mt] = cur.xf[mt];
+  static_for<0, n_mfma>([&](auto jc) __attribute__((always_inline)) {
+    constexpr int j = decltype(jc)::value;
+    if constexpr (j < NMT * 4) acc[j >> 2][j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j & 3], xf[j >> 2], acc[j >> 2][j & 3], 0, 0, 0);
+    else mfma_vgpr_acc(accx[j & 3], wf[j & 3], xblk);
+    // actions: reads 0 .. n_reads - 1 with copy c behind read ceil((c + 1) * n_reads / 4) - 1
+    static_for<0, n_act>([&](auto ac) __attribute__((always_inline)) {
+      constexpr int a = decltype(ac)::value;
+      if constexpr ((a * n_mfma) / n_act == j) {
+        constexpr int c = (a + 1) * 4 / n_act;               // copies among actions 0 .. a
+        if constexpr (c > a * 4 / n_act) {
+          constexpr int i = LOAD0 + c - 1;
+          if constexpr (i >= S::kALoads) lds_dma16_at<(LAY == kLayNN ? 1 : 4) * (i - S::kALoads) * kLine>(g.b_k, b_off[i - S::kALoads], g.b_st);
+          else lds_dma16_at<4 * i * kLine>(g.a_k, t.a_off[i], g.a_st);
+        } else {
+          constexpr int r = a - c;                           // read number: weight 0, activation 0, weights 1..3, activations 1..3
+          constexpr int w0 = n_w / 4;
+          constexpr int num = r < w0 ? r : r == w0 ? n_w : r <= n_w ? r - 1 : r;
+          gemm_read_one<LAY, NMT, false>(nxt, num, as_n, bs_n, ks_n, t);
+        }
+      }
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  });
+}
+
 // K loop of one tile for a wave with NMT active row sub-tiles.
 //
 // Step s computes from A stage s%2 and B stage s%3.  Its barrier sits in front of
@@ -382,6 +450,41 @@ __device__ __forceinline__ void gemm_k_loop(f32x16 (&acc)[kMaxMT][4], f32x16 (&a
   if (NMT > 0) gemm_read_frags<LAY, NMT, TALL>(cur, lds, lds + S::kBReg, 0, t);
 
   int bs_i = 0;
+  if constexpr (NMT == kMaxMT && !TALL) {
+    // One body for every step.  Past the end the copies fetch the last step again into stages that are free, and the last
+    // step's barrier takes the place of the closing one (its reads of a further step's operands are never used).  Copies
+    // that the last barrier does not cover must stay clear of the epilogue's staging (weight stage 2, and 16 KB and more
+    // into activation stage 1): they are the last step's weight lines, which therefore go to stage 0 or 1, and the first
+    // four activation lines behind that barrier (the first 16 KB of a stage); a wave's own have landed before it goes on.
+    uint32_t b_off[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b_off[i] = LAY == kLayNN ? t.b_off[i & 1] + (uint32_t)((i >> 1) * 4 * t.ldb_bytes) : t.b_off[i];
+    if (n_steps <= 2) g = gemm_load_group<LAY, TALL>(t, n_steps - 1, 1, n_steps - 1, n_steps);
+    for (int s = 0; s < n_steps; ++s) {
+      const lds_cptr as = lds + (s & 1) * S::kAStage, as_n = lds + ((s + 1) & 1) * S::kAStage;
+      const lds_cptr bs = lds + S::kBReg + bs_i * S::kBStage;
+      const int bs_next = bs_i == kBStages - 1 ? 0 : bs_i + 1;
+      if (NX) load_x(xn, min(s + 1, n_steps - 1));
+      gemm_slice_full<LAY, NX, 4>(acc, cur, nxt, as, bs, 1, t, g, b_off, accx, xb[0]);
+      gemm_slice_full<LAY, NX, 8>(acc, nxt, cur, as, bs, 2, t, g, b_off, accx, xb[1]);
+      gemm_slice_full<LAY, NX, 12>(acc, cur, nxt, as, bs, 3, t, g, b_off, accx, xb[2]);
+      wait_lgkmcnt0();
+      wait_vmcnt<S::kBLoads>();
+      __builtin_amdgcn_s_barrier();
+      if (NX) wait_xblock<S::kBLoads>(xn);   // see the general loop below
+      g = gemm_load_group<LAY, TALL>(t, min(s + 2, n_steps - 1), s & 1, min(s + 3, n_steps - 1), s == n_steps - 2 && bs_i == 2 ? 1 : bs_i);
+      gemm_slice_full<LAY, NX, 0>(acc, nxt, cur, as_n, lds + S::kBReg + bs_next * S::kBStage, 0, t, g, b_off, accx,
+                                  xb[3]);
+      if (NX) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) xb[ks] = xn[ks];
+      }
+      bs_i = bs_next;
+    }
+    wait_vmcnt<0>();   // ... so that the next tile's copies, to the same lines, come behind them
+    if (NX) asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");   // the last assembly MFMA's result before any read of it
+    return;
+  }
   for (int s = 0; s < n_steps; ++s) {
     const lds_cptr as = lds + (s & 1) * S::kAStage;
     const lds_cptr bs = lds + S::kBReg + bs_i * S::kBStage;

@@ -215,6 +215,10 @@ int run_permute(const Ctx& c, const void* x) {
 
 int gemm_grid(const Ctx& c) { return (c.n_cu + 7) / 8 * 8; }
 
+// Rows of every expert (the bf16 kernels look at them beside the tile map).
+void set_segments(GemmParams& p, const Ctx& c) { p.offsets = c.sv.offsets; p.E_local = c.s.E_local; }
+void set_segments(GemmParamsF32&, const Ctx&) {}
+
 template <typename P, typename T>
 P gemm1_params(const Ctx& c, const void* w_gate_up) {
   const MoeShape& s = c.s;
@@ -225,6 +229,7 @@ P gemm1_params(const Ctx& c, const void* w_gate_up) {
   p.lda = s.H; p.ldb = 2 * s.I; p.ldc = s.I;
   p.n_ntiles = gemm1_ntiles(s);
   p.tiles = tile_map(c);
+  set_segments(p, c);
   return p;
 }
 
@@ -238,6 +243,7 @@ P gemm2_params(const Ctx& c, const void* w_down) {
   p.lda = s.I; p.ldb = s.H; p.ldc = s.H;
   p.n_ntiles = gemm2_ntiles(s);
   p.tiles = tile_map(c);
+  set_segments(p, c);
   return p;
 }
 
@@ -245,7 +251,6 @@ P gemm2_params(const Ctx& c, const void* w_down) {
 int run_gemm1(const Ctx& c, const void* w_gate_up, const void* x_gather = nullptr) {
   if (c.s.dtype == MOE_BF16) {
     GemmParams p = gemm1_params<GemmParams, __bf16>(c, w_gate_up);
-    p.offsets = c.sv.offsets; p.E_local = c.s.E_local;
     if (x_gather) {
       p.A = static_cast<const __bf16*>(x_gather);
       p.gather = c.sv.token_of;
@@ -260,7 +265,6 @@ int run_gemm1(const Ctx& c, const void* w_gate_up, const void* x_gather = nullpt
 int run_gemm2(const Ctx& c, const void* w_down) {
   if (c.s.dtype == MOE_BF16) {
     GemmParams p = gemm2_params<GemmParams, __bf16>(c, w_down);
-    p.offsets = c.sv.offsets; p.E_local = c.s.E_local;
     hipLaunchKernelGGL((grouped_gemm_bf16_kernel<kLayNN, kEpiStore>), dim3(gemm_grid(c)), dim3(kGemmThreads), 0, c.stream, p);
   } else
     hipLaunchKernelGGL(grouped_gemm_f32_kernel<kEpiStore>, dim3(gemm_grid(c) * 4), dim3(256), 0, c.stream,

@@ -137,12 +137,18 @@ __device__ __forceinline__ void lds_dma16(const char* sbase, uint32_t voff, uint
 }
 
 // The same copy to lds_base + OFF: the LDS address goes straight into M0 (three instructions in all).
-template <int OFF>
+template <int OFF, bool STREAM = false>
 __device__ __forceinline__ void lds_dma16_at(const char* sbase, uint32_t voff, uint32_t lds_base) {
-  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(lds_base), "v"(voff), "s"(sbase), "n"(OFF)
-               : "memory", "m0", "scc");
+  if constexpr (STREAM)
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                 :
+                 : "s"(lds_base), "v"(voff), "s"(sbase), "n"(OFF)
+                 : "memory", "m0", "scc");
+  else
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(lds_base), "v"(voff), "s"(sbase), "n"(OFF)
+                 : "memory", "m0", "scc");
 }
 
 // One slice of the register-fed row block: lane (row l32, half lh) fetches the 16 bytes that are its MFMA operand
@@ -233,7 +239,7 @@ __device__ __forceinline__ GemmLoadGroup gemm_load_group(const GemmTileCtx& t, i
   return g;
 }
 
-template <int LAY, bool TALL>
+template <int LAY, bool TALL, bool STREAM = false>
 __device__ __forceinline__ void gemm_issue_one(const GemmTileCtx& t, const GemmLoadGroup& g, int idx) {
   typedef TileShape<TALL> S;
   if (idx < S::kALoads) {
@@ -243,9 +249,9 @@ __device__ __forceinline__ void gemm_issue_one(const GemmTileCtx& t, const GemmL
     if (g.b_k == nullptr) return;
     if (LAY == kLayNN) {
       // line i of this wave: k-row group i / halves, column half i % halves
-      lds_dma16(g.b_k + (size_t)((i / S::kHalves) * 4) * t.ldb_bytes, t.b_off[i % S::kHalves], g.b_st + i * kLine);
+      lds_dma16<STREAM>(g.b_k + (size_t)((i / S::kHalves) * 4) * t.ldb_bytes, t.b_off[i % S::kHalves], g.b_st + i * kLine);
     } else {
-      lds_dma16(g.b_k, t.b_off[i], g.b_st + 4 * i * kLine);
+      lds_dma16<STREAM>(g.b_k, t.b_off[i], g.b_st + 4 * i * kLine);
     }
   }
 }
@@ -300,7 +306,7 @@ __device__ __forceinline__ void mfma_vgpr_acc(f32x16& acc, const bf16x8& a, cons
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
 
-template <int LAY, int NMT, bool TALL, int NX = 0>
+template <int LAY, int NMT, bool TALL, int NX = 0, bool STREAM = false>
 __device__ __forceinline__ void gemm_slice(f32x16 (&acc)[kMaxMT][4], const GemmFrags<LAY, NMT>& cur,
                                            GemmFrags<LAY, NMT>& nxt, bool read_next, lds_cptr as_n, lds_cptr bs_n,
                                            int ks_n, const GemmTileCtx& t, const GemmLoadGroup& g, int load0,
@@ -322,7 +328,7 @@ __device__ __forceinline__ void gemm_slice(f32x16 (&acc)[kMaxMT][4], const GemmF
       if (a < S::n_reads) {
         if (read_next) gemm_read_one<LAY, NMT, TALL>(nxt, a, as_n, bs_n, ks_n, t);
       } else {
-        gemm_issue_one<LAY, TALL>(t, g, load0 + (a - S::n_reads));
+        gemm_issue_one<LAY, TALL, STREAM>(t, g, load0 + (a - S::n_reads));
       }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -354,7 +360,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 // launch 1320 -> 1250; T = 4096, H = 2048, I = 1408, 16 experts: forward 401 -> 386, backward 731 -> 705.  With the copies
 // masked through exec instead of repeated past the end: 10 % slower than the general loop.  Waves with fewer row blocks
 // keep the general loop: those launches wait for the weights (this slice: 0 to 2 % slower at 64..125 rows per expert).
-template <int LAY, int NX, int LOAD0>
+template <int LAY, int NX, int LOAD0, bool STREAM>
 __device__ __forceinline__ void gemm_slice_full(f32x16 (&acc)[kMaxMT][4], const GemmFrags<LAY, kMaxMT>& cur, GemmFrags<LAY, kMaxMT>& nxt,
                                                 lds_cptr as_n, lds_cptr bs_n, int ks_n, const GemmTileCtx& t,
                                                 const GemmLoadGroup& g, const uint32_t (&b_off)[8], f32x16 (&accx)[4],
@@ -379,7 +385,7 @@ __device__ __forceinline__ void gemm_slice_full(f32x16 (&acc)[kMaxMT][4], const 
         constexpr int c = (a + 1) * 4 / n_act;               // copies among actions 0 .. a
         if constexpr (c > a * 4 / n_act) {
           constexpr int i = LOAD0 + c - 1;
-          if constexpr (i >= S::kALoads) lds_dma16_at<(LAY == kLayNN ? 1 : 4) * (i - S::kALoads) * kLine>(g.b_k, b_off[i - S::kALoads], g.b_st);
+          if constexpr (i >= S::kALoads) lds_dma16_at<(LAY == kLayNN ? 1 : 4) * (i - S::kALoads) * kLine, STREAM>(g.b_k, b_off[i - S::kALoads], g.b_st);
           else lds_dma16_at<4 * i * kLine>(g.a_k, t.a_off[i], g.a_st);
         } else {
           constexpr int r = a - c;                           // read number: weight 0, activation 0, weights 1..3, activations 1..3
@@ -414,7 +420,7 @@ __device__ __forceinline__ void gemm_slice_full(f32x16 (&acc)[kMaxMT][4], const 
 // lies inside ONE loop trip (a value carried around the loop may be copied by the compiler at the back
 // edge, which must only happen to retired values) and ends, right behind the barrier's wait, in a statement
 // that names the registers, so that the compiler can neither use nor copy them earlier.
-template <int LAY, int NMT, bool TALL, int NX = 0>
+template <int LAY, int NMT, bool TALL, int NX = 0, bool STREAM = false>
 __device__ __forceinline__ void gemm_k_loop(f32x16 (&acc)[kMaxMT][4], f32x16 (&accx)[4], const GemmTileCtx& t, char* smem,
                                             int n_steps) {
   typedef TileShape<TALL> S;
@@ -431,11 +437,11 @@ __device__ __forceinline__ void gemm_k_loop(f32x16 (&acc)[kMaxMT][4], f32x16 (&a
   {
     const GemmLoadGroup g0 = gemm_load_group<LAY, TALL>(t, 0, 0, 0, 0);                       // A(0), B(0)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) gemm_issue_one<LAY, TALL>(t, g0, i);
+    for (int i = 0; i < 16; ++i) gemm_issue_one<LAY, TALL, STREAM>(t, g0, i);
     if (n_steps > 1) {
       const GemmLoadGroup g1 = gemm_load_group<LAY, TALL>(t, -1, 0, 1, 1);                    // B(1)
 #pragma unroll
-      for (int i = S::kALoads; i < 16; ++i) gemm_issue_one<LAY, TALL>(t, g1, i);
+      for (int i = S::kALoads; i < 16; ++i) gemm_issue_one<LAY, TALL, STREAM>(t, g1, i);
       wait_vmcnt<S::kBLoads>();
     } else {
       wait_vmcnt<0>();
@@ -445,7 +451,7 @@ __device__ __forceinline__ void gemm_k_loop(f32x16 (&acc)[kMaxMT][4], f32x16 (&a
   }
   GemmLoadGroup g = gemm_load_group<LAY, TALL>(t, n_steps > 1 ? 1 : -1, 1, n_steps > 2 ? 2 : -1, 2);   // A(1), B(2)
 #pragma unroll
-  for (int i = 0; i < 4; ++i) gemm_issue_one<LAY, TALL>(t, g, i);
+  for (int i = 0; i < 4; ++i) gemm_issue_one<LAY, TALL, STREAM>(t, g, i);
   GemmFrags<LAY, NMT> cur, nxt;
   if (NMT > 0) gemm_read_frags<LAY, NMT, TALL>(cur, lds, lds + S::kBReg, 0, t);
 
@@ -465,15 +471,15 @@ __device__ __forceinline__ void gemm_k_loop(f32x16 (&acc)[kMaxMT][4], f32x16 (&a
       const lds_cptr bs = lds + S::kBReg + bs_i * S::kBStage;
       const int bs_next = bs_i == kBStages - 1 ? 0 : bs_i + 1;
       if (NX) load_x(xn, min(s + 1, n_steps - 1));
-      gemm_slice_full<LAY, NX, 4>(acc, cur, nxt, as, bs, 1, t, g, b_off, accx, xb[0]);
-      gemm_slice_full<LAY, NX, 8>(acc, nxt, cur, as, bs, 2, t, g, b_off, accx, xb[1]);
-      gemm_slice_full<LAY, NX, 12>(acc, cur, nxt, as, bs, 3, t, g, b_off, accx, xb[2]);
+      gemm_slice_full<LAY, NX, 4, STREAM>(acc, cur, nxt, as, bs, 1, t, g, b_off, accx, xb[0]);
+      gemm_slice_full<LAY, NX, 8, STREAM>(acc, nxt, cur, as, bs, 2, t, g, b_off, accx, xb[1]);
+      gemm_slice_full<LAY, NX, 12, STREAM>(acc, cur, nxt, as, bs, 3, t, g, b_off, accx, xb[2]);
       wait_lgkmcnt0();
       wait_vmcnt<S::kBLoads>();
       __builtin_amdgcn_s_barrier();
       if (NX) wait_xblock<S::kBLoads>(xn);   // see the general loop below
       g = gemm_load_group<LAY, TALL>(t, min(s + 2, n_steps - 1), s & 1, min(s + 3, n_steps - 1), s == n_steps - 2 && bs_i == 2 ? 1 : bs_i);
-      gemm_slice_full<LAY, NX, 0>(acc, nxt, cur, as_n, lds + S::kBReg + bs_next * S::kBStage, 0, t, g, b_off, accx,
+      gemm_slice_full<LAY, NX, 0, STREAM>(acc, nxt, cur, as_n, lds + S::kBReg + bs_next * S::kBStage, 0, t, g, b_off, accx,
                                   xb[3]);
       if (NX) {
 #pragma unroll
@@ -494,11 +500,11 @@ __device__ __forceinline__ void gemm_k_loop(f32x16 (&acc)[kMaxMT][4], f32x16 (&a
 #pragma unroll
     for (int ks = 0; ks < 3; ++ks) {
       if (NMT > 0) {
-        gemm_slice<LAY, NMT, TALL, NX>(acc, cur, nxt, true, as, bs, ks + 1, t, g, 4 + 4 * ks, accx, xb[ks]);
+        gemm_slice<LAY, NMT, TALL, NX, STREAM>(acc, cur, nxt, true, as, bs, ks + 1, t, g, 4 + 4 * ks, accx, xb[ks]);
         cur = nxt;
       } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) gemm_issue_one<LAY, TALL>(t, g, 4 + 4 * ks + i);
+        for (int i = 0; i < 4; ++i) gemm_issue_one<LAY, TALL, STREAM>(t, g, 4 + 4 * ks + i);
       }
     }
     if (more) {
@@ -512,12 +518,12 @@ __device__ __forceinline__ void gemm_k_loop(f32x16 (&acc)[kMaxMT][4], f32x16 (&a
     }
     if (NMT > 0) {
       // `more` false: no loads left (both sources null) and nothing further to read
-      gemm_slice<LAY, NMT, TALL, NX>(acc, cur, nxt, more, lds + ((s + 1) & 1) * S::kAStage,
+      gemm_slice<LAY, NMT, TALL, NX, STREAM>(acc, cur, nxt, more, lds + ((s + 1) & 1) * S::kAStage,
                                      lds + S::kBReg + bs_next * S::kBStage, 0, t, g, 0, accx, xb[3]);
       if (more) cur = nxt;
     } else if (more) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) gemm_issue_one<LAY, TALL>(t, g, i);
+      for (int i = 0; i < 4; ++i) gemm_issue_one<LAY, TALL, STREAM>(t, g, i);
     }
     if (NX && more) {
 #pragma unroll
@@ -658,7 +664,7 @@ __device__ __forceinline__ void swiglu_grad4(const float (&da)[4], u32x2 gv, u32
 // One output tile: (t0, t1) = (M tile of the tile map, N tile of TileShape<TALL>::kCols
 // columns; SwiGLU: half as many output columns).  X5: a wide tile of 257..320 rows (rows past 256 go
 // through the register-fed block of each wave row).
-template <int LAY, int EPI, bool TALL, int X5 = 0>
+template <int LAY, int EPI, bool TALL, int X5 = 0, bool NT_OK = false>
 __device__ __forceinline__ void gemm_tile_bf16(const GemmParams& p, int t0, int t1, char* smem) {
   typedef TileShape<TALL> S;
   static_assert(!(TALL && X5), "one shape at a time");
@@ -765,27 +771,44 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmParams& p, int t0, int 
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  if constexpr (X5) {
-    // 256 staged rows: every wave row is full; the fifth block exists for wave row 0, and for wave row 1 above 288 rows
-    if (has_x) {
+  // The expert's only tile reads each of its weight lines once on the chip, and reads them non-temporally where the launch
+  // waits for them: forward waves of up to three row blocks (T = 2000, H = 7168, I = 2048, 32 of 256 experts: forward
+  // 583 -> 567 us; T = 400, H = 2048, I = 1408, 16 experts: 100.4 -> 95.9; with four blocks, T = 8192, 838 and 849), and
+  // gate_grad where all experts' weights exceed the 256 MB memory-side cache, in which the forward has left smaller ones
+  // (T = 8192, 1.9 GB: 501 -> 474 us; T = 400, 185 MB: 48 and 54.5).  Tiles that share an expert's weights read them plainly:
+  // non-temporal they cost the skewed forward 2 %.  SwiGLU_grad and the single launches (NT_OK false) have no registers for
+  // a second loop (43 and 49 spilled).
+  auto k_loop = [&](auto stream) __attribute__((always_inline)) {
+    constexpr bool ST = decltype(stream)::value, ST4 = ST && LAY == kLayNT;
+    if constexpr (X5) {
+      // 256 staged rows: every wave row is full; the fifth block exists for wave row 0, and for wave row 1 above 288 rows
+      if (has_x) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) accx[j][r] = 0.f;
-      gemm_k_loop<LAY, kMaxMT, false, 1>(acc, accx, t, smem, n_steps);
+          for (int r = 0; r < 16; ++r) accx[j][r] = 0.f;
+        gemm_k_loop<LAY, kMaxMT, false, 1, ST4>(acc, accx, t, smem, n_steps);
+      } else {
+        gemm_k_loop<LAY, kMaxMT, false, 0, ST4>(acc, accx, t, smem, n_steps);
+      }
     } else {
-      gemm_k_loop<LAY, kMaxMT, false, 0>(acc, accx, t, smem, n_steps);
+      switch (n_mt) {
+        case 0: gemm_k_loop<LAY, 0, TALL, 0, ST>(acc, accx, t, smem, n_steps); break;
+        case 1: gemm_k_loop<LAY, 1, TALL, 0, ST>(acc, accx, t, smem, n_steps); break;
+        case 2: gemm_k_loop<LAY, 2, TALL, 0, ST>(acc, accx, t, smem, n_steps); break;
+        case 3: gemm_k_loop<LAY, 3, TALL, 0, ST>(acc, accx, t, smem, n_steps); break;
+        default:
+          if constexpr (!TALL) gemm_k_loop<LAY, 4, TALL, 0, ST4>(acc, accx, t, smem, n_steps);   // a tall wave row has at most 96 rows
+          break;
+      }
     }
+  };
+  if constexpr (TALL || EPI == kEpiSwigluGrad || !NT_OK || (LAY == kLayNN && X5)) {
+    k_loop(std::false_type{});
   } else {
-    switch (n_mt) {
-      case 0: gemm_k_loop<LAY, 0, TALL>(acc, accx, t, smem, n_steps); break;
-      case 1: gemm_k_loop<LAY, 1, TALL>(acc, accx, t, smem, n_steps); break;
-      case 2: gemm_k_loop<LAY, 2, TALL>(acc, accx, t, smem, n_steps); break;
-      case 3: gemm_k_loop<LAY, 3, TALL>(acc, accx, t, smem, n_steps); break;
-      default:
-        if constexpr (!TALL) gemm_k_loop<LAY, 4, TALL>(acc, accx, t, smem, n_steps);   // a tall wave row has at most 96 rows
-        break;
-    }
+    const bool only = __builtin_amdgcn_readfirstlane(p.offsets[e + 1] - p.offsets[e]) == __builtin_amdgcn_readfirstlane(rows);
+    if (only && (LAY == kLayNN || (size_t)p.strideB * p.E_local * 2 > ((size_t)256 << 20))) k_loop(std::true_type{});
+    else k_loop(std::false_type{});
   }
 
   // ---- epilogue: lane holds row l32 of each 32 x 32 block and, per register group q,
@@ -901,11 +924,11 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmParams& p, int t0, int 
 // tall above (the map builder makes such tiles only with <= 384 rows and gives each a pair slot of its own).
 __device__ __forceinline__ bool tile_is_tall(int rows) { return rows > kWideRows; }
 
-template <int LAY, int EPI>
+template <int LAY, int EPI, bool NT_OK = false>
 __device__ __forceinline__ void gemm_map_tile_bf16(const GemmParams& p, int mtile, int ntile, bool tall, char* smem) {
   if (tall) gemm_tile_bf16<LAY, EPI, true>(p, mtile, ntile, smem);
-  else if (__builtin_amdgcn_readfirstlane(p.tiles.rows[mtile]) > kBM) gemm_tile_bf16<LAY, EPI, false, 1>(p, mtile, ntile, smem);
-  else gemm_tile_bf16<LAY, EPI, false>(p, mtile, ntile, smem);
+  else if (__builtin_amdgcn_readfirstlane(p.tiles.rows[mtile]) > kBM) gemm_tile_bf16<LAY, EPI, false, 1, NT_OK>(p, mtile, ntile, smem);
+  else gemm_tile_bf16<LAY, EPI, false, 0, NT_OK>(p, mtile, ntile, smem);
 }
 
 // Work item `rem` (0 .. 2*n_ntiles-1) of tile pair (m0, m0+1): a tall tile owns the whole slot as
@@ -973,7 +996,7 @@ void grouped_gemm_bf16_kernel(GemmParams p) {
     int mtile, ntile;
     bool tall;
     if (!pair_work_item(p, 2 * (pl * 8 + xcd), rem, n_m, kOutCols, mtile, ntile, tall)) continue;
-    gemm_map_tile_bf16<LAY, EPI>(p, mtile, ntile, tall, smem);
+    gemm_map_tile_bf16<LAY, EPI, true>(p, mtile, ntile, tall, smem);
   }
   if (split_tail && lw < 2 * tail) {
     const int i = n_whole + (lw >> 1), half = lw & 1;

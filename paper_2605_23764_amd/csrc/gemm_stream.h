@@ -19,8 +19,8 @@
 // reaches 6.2 TB/s (5.7 without the non-temporal hint), 1 KB pieces 6.3..6.7, one linear stream 7.1; with the MFMAs
 // taken out the launch is no faster, without the activation loads 2 %.
 // Measured, layer (routing and Combine included), against the tiles of gemm_bf16.h: H = 7168, I = 2048, 32 of 256 experts,
-// k = 8: T = 4 168 -> 101 us, T = 32 428 -> 354, T = 256 527 -> 499, T = 1000 548 -> 527; H = 2048, I = 1408, 16 experts,
-// k = 4: T = 1 60 -> 38.5, T = 8 74 -> 68, T = 64 76 -> 73.  Above 64 rows the activations' share of a stage grows past a
+// k = 8: T = 4 168 -> 101 us, T = 32 428 -> 354, T = 256 527 -> 470, T = 1000 548 -> 505; H = 2048, I = 1408, 16 experts,
+// k = 4: T = 1 60 -> 38.5, T = 8 74 -> 63, T = 64 76 -> 67.  Above 64 rows the activations' share of a stage grows past a
 // third and the other kernel's 256 rows per weight fetch win.
 #pragma once
 #include "gemm_bf16.h"
@@ -35,12 +35,15 @@ static_assert(kStreamGatherOff + kStreamGather * 4 <= kGemmLdsBytes, "LDS budget
 // CW weight columns per item; AL activation lines (8 rows x 64 k) per wave and stage.
 template <int CW, int AL>
 struct StreamShape {
-  static constexpr int kKB = 8192 / CW;                          // k per stage
-  static constexpr int kRows = (CW == 128 ? 32 : 16) * AL;       // activation rows a stage holds
+  static constexpr int kKB = CW == 64 ? 128 : 64;                // k per stage
+  static constexpr int kRows = (CW == 64 ? 16 : 32) * AL;        // activation rows a stage holds
   static constexpr int kMT = kRows > 32 ? 2 : 1;                 // 32-row blocks
-  static constexpr int kStage = (16 + 4 * AL) * kLine;
-  static constexpr int kDepth = AL == 1 ? 7 : 6;
-  static constexpr int kLoads = 4 + AL;                          // wave-wide loads per wave and stage
+  static constexpr int kNB = CW == 256 ? 2 : 1;                  // 32-column blocks per wave
+  static constexpr int kBLoads = CW == 256 ? 8 : 4;              // weight lines per wave and stage
+  static constexpr int kALine0 = 4 * kBLoads;                    // the stage's activation lines follow its weight lines
+  static constexpr int kStage = (kALine0 + 4 * AL) * kLine;
+  static constexpr int kDepth = CW == 256 ? (AL == 1 ? 4 : 3) : AL == 1 ? 7 : 6;
+  static constexpr int kLoads = kBLoads + AL;                    // wave-wide loads per wave and stage
   static_assert(kDepth * kStage <= kStreamTables, "ring");
 };
 
@@ -60,7 +63,8 @@ template <int LAY, int EPI, int CW, int AL>
 __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, char* smem) {
   typedef StreamShape<CW, AL> S;
   constexpr int kOut = EPI == kEpiSwiglu ? CW / 2 : CW;          // output columns per item
-  constexpr int kRPL = CW == 128 ? 4 : 8;                        // NN: k-rows per 1 KB line
+  constexpr int kRPL = CW == 64 ? 8 : 4;                         // NN: k-rows per 1 KB line
+  static_assert(CW != 256 || (LAY == kLayNN && EPI == kEpiSwiglu), "256 columns: gate and up halves");
   const int G = gridDim.x;
   const int n_ct = (p.N + kOut - 1) / kOut;
   const int total = n_act * n_ct;
@@ -68,7 +72,7 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
   // serves both halves of a line that two items share
   auto tile_of = [&](int it) __attribute__((always_inline)) {
     const int id = it * G + (int)blockIdx.x;
-    return CW == 128 ? (id < total ? id : -1) : xcd_spread_tile(it, blockIdx.x, G, total);
+    return CW != 64 ? (id < total ? id : -1) : xcd_spread_tile(it, blockIdx.x, G, total);
   };
   int n_items = (total + G - 1) / G;
   if (n_items > 0 && tile_of(n_items - 1) < 0) --n_items;
@@ -86,7 +90,7 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
 
   // ---- request side: item and step of the next stage to request ----
   const int r8 = lane >> 3;                                      // row of this lane inside an 8-row line
-  struct { const char *a_base, *b_base; uint32_t a_off[AL], b_off[LAY == kLayNT ? 4 : 1]; int step, item, slot; } q;
+  struct { const char *a_base, *b_base; uint32_t a_off[AL], b_off[LAY == kLayNT ? 4 : S::kNB]; int step, item, slot; } q;
   q.step = 0; q.item = 0; q.slot = 0;
   auto item_of = [&](int it, int& ae, int& ct) __attribute__((always_inline)) {
     const int id = tile_of(it);
@@ -104,7 +108,7 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
 #pragma unroll
     for (int i = 0; i < AL; ++i) {
       // activation line wave + 4 i: CW = 128: rows 8 (wave + 4 i) ..; CW = 64: rows 8 ((wave + 4 i) / 2) .., k half wave & 1
-      const int rl = CW == 128 ? wave + 4 * i : (wave + 4 * i) >> 1;
+      const int rl = CW != 64 ? wave + 4 * i : (wave + 4 * i) >> 1;
       const int row = min(rl * 8 + r8, rows - 1);                // rows past the end repeat the last one; never stored
       int arow = row;
       if (gathered) arow = row0 + row < kStreamGather ? s_tok[row0 + row] : p.gather[row0 + row];
@@ -113,7 +117,13 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
     }
     if constexpr (LAY == kLayNN) {
       int kk, col;
-      if (CW == 128) {
+      if (CW == 256) {
+        // two lines per four k-rows: 128 gate columns, 128 up columns (chunks in the order that keeps the reads apart)
+        kk = lane >> 4;
+        const int c = ((lane & 15) - 4 * kk) & 15;
+        col = min(ct * 128 + c * 8, p.N - 8);
+        q.b_off[S::kNB - 1] = (uint32_t)((kk * p.ldb + p.N + min(ct * 128 + (c ^ 2) * 8, p.N - 8)) * 2);
+      } else if (CW == 128) {
         kk = lane >> 4;
         const int c = ((lane & 15) - 4 * kk) & 15;               // staged chunk of 8 columns, k-rows rotated by 64 bytes
         if (EPI == kEpiSwiglu) col = c < 8 ? ct * 64 + c * 8 : p.N + ct * 64 + ((c - 8) ^ 2) * 8;
@@ -141,55 +151,67 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
     const int k0 = q.step * S::kKB;
     const uint32_t st = uniform_u32(lds0 + (uint32_t)(q.slot * S::kStage));
     // k past the end (an odd number of 64s with 128 to a stage): the last 64 again, not multiplied
-    const char* a_k = uniform_ptr(q.a_base + (size_t)(CW == 128 ? k0 : min(k0 + (wave & 1) * 64, p.K - 64)) * 2);
+    const char* a_k = uniform_ptr(q.a_base + (size_t)(CW != 64 ? k0 : min(k0 + (wave & 1) * 64, p.K - 64)) * 2);
 #pragma unroll
-    for (int i = 0; i < AL; ++i) lds_dma16(a_k, q.a_off[i], st + 16 * kLine + (wave + 4 * i) * kLine);
+    for (int i = 0; i < AL; ++i) lds_dma16(a_k, q.a_off[i], st + (S::kALine0 + wave + 4 * i) * kLine);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < S::kBLoads; ++i) {
       const char* b_k;
-      if (LAY == kLayNN) b_k = q.b_base + (size_t)min(k0 + (wave * 4 + i) * kRPL, p.K - kRPL) * ldb_bytes;
+      if (CW == 256) b_k = q.b_base + (size_t)(k0 + (wave * 4 + (i >> 1)) * 4) * ldb_bytes;
+      else if (LAY == kLayNN) b_k = q.b_base + (size_t)min(k0 + (wave * 4 + i) * kRPL, p.K - kRPL) * ldb_bytes;
       else b_k = q.b_base + (size_t)(CW == 128 ? k0 : min(k0 + (i & 1) * 64, p.K - 64)) * 2;
-      lds_dma16<CW == 128>(uniform_ptr(b_k), q.b_off[LAY == kLayNT ? i : 0], st + (wave * 4 + i) * kLine);
+      lds_dma16<CW != 64>(uniform_ptr(b_k), q.b_off[LAY == kLayNT ? i : CW == 256 ? i & 1 : 0], st + (wave * S::kBLoads + i) * kLine);
     }
     q.slot = q.slot == S::kDepth - 1 ? 0 : q.slot + 1;
     if (++q.step == n_steps) { q.step = 0; ++q.item; }
   };
 
   // ---- operand reads: offsets of this lane inside a stage ----
-  const int blk = CW == 128 ? wave : wave & 1;                   // this wave's 32-column block
-  const bool active = CW == 128 || wave < 2;
+  const int blk = CW != 64 ? wave : wave & 1;                    // this wave's (first) 32-column block; the second: blk + 4
+  const bool active = CW != 64 || wave < 2;
   uint32_t b_rd;
   if (LAY == kLayNN) {
     const int g = lane >> 4, i = lane & 15, kk = i >> 2;
     int c;                                                       // staged chunk of this 16-lane group's columns
-    if (EPI == kEpiSwiglu) c = (g & 1) ? CW / 16 + ((2 * blk + ((i & 3) >> 1)) ^ 2) : 2 * blk + ((i & 3) >> 1);
+    if (CW == 256) c = (2 * blk + ((i & 3) >> 1)) ^ ((g & 1) * 2);   // gate line, up line
+    else if (EPI == kEpiSwiglu) c = (g & 1) ? CW / 16 + ((2 * blk + ((i & 3) >> 1)) ^ 2) : 2 * blk + ((i & 3) >> 1);
     else c = 4 * blk + (g & 1) * 2 + ((i & 3) >> 1);
-    if (CW == 128) b_rd = (uint32_t)((g >> 1) * 2 * kLine + kk * 256 + ((c + 4 * kk) & 15) * 16 + (i & 1) * 8);
+    if (CW == 256) b_rd = (uint32_t)(((g >> 1) * 4 + (g & 1)) * kLine + kk * 256 + ((c + 4 * kk) & 15) * 16 + (i & 1) * 8);
+    else if (CW == 128) b_rd = (uint32_t)((g >> 1) * 2 * kLine + kk * 256 + ((c + 4 * kk) & 15) * 16 + (i & 1) * 8);
     else b_rd = (uint32_t)((g >> 1) * kLine + kk * 128 + (c ^ (4 * ((kk >> 1) & 1))) * 16 + (i & 1) * 8);
   } else {
-    b_rd = (uint32_t)((blk * 4 + (l32 >> 3)) * (CW == 128 ? 1 : 2) * kLine + (l32 & 7) * 128);
+    b_rd = (uint32_t)((blk * 4 + (l32 >> 3)) * (CW != 64 ? 1 : 2) * kLine + (l32 & 7) * 128);
   }
   const int ar = l32 & (S::kRows - 1);                           // 16-row stages: the upper lanes repeat the rows
-  const uint32_t a_rd = (uint32_t)(16 * kLine + (ar >> 3) * (CW == 128 ? 1 : 2) * kLine + (ar & 7) * 128);
+  const uint32_t a_rd = (uint32_t)(S::kALine0 * kLine + (ar >> 3) * (CW != 64 ? 1 : 2) * kLine + (ar & 7) * 128);
   const int a_sw = (ar >> 1) & 7, b_sw = (l32 >> 1) & 7;
 
-  f32x16 acc[S::kMT];
+  f32x16 acc[S::kNB][S::kMT];
+  auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int mt = 0; mt < S::kMT; ++mt)
+    for (int nb = 0; nb < S::kNB; ++nb)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
+      for (int mt = 0; mt < S::kMT; ++mt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[nb][mt][r] = 0.f;
+  };
+  clear();
 
   auto half_stage = [&](lds_cptr st, int h) __attribute__((always_inline)) {   // 64 k: four MFMA slices
-    bf16x8 wf[4], xf[4][S::kMT];
+    bf16x8 wf[S::kNB][4], xf[4][S::kMT];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int ks = h * 4 + s;
       if (LAY == kLayNN) {
-        const lds_cptr b = st + b_rd + ks * (CW == 128 ? 4 : 2) * kLine;
-        wf[s] = join_tr(__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)b),
-                        __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(b + (CW == 128 ? kLine : kLine / 2))));
+#pragma unroll
+        for (int nb = 0; nb < S::kNB; ++nb) {
+          // the second block's 64 columns further on are 8 chunks on, and a line's 16 chunks wrap around
+          const lds_cptr b = st + (nb ? b_rd ^ 128u : b_rd) + ks * (CW == 256 ? 8 : CW == 128 ? 4 : 2) * kLine;
+          wf[nb][s] = join_tr(__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)b),
+                              __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(b + (CW == 256 ? 2 * kLine : CW == 128 ? kLine : kLine / 2))));
+        }
       } else {
-        wf[s] = *(lds_bf16x8_cptr)(st + b_rd + h * kLine + (uint32_t)(((s * 2 + lh) ^ b_sw) << 4));
+        wf[0][s] = *(lds_bf16x8_cptr)(st + b_rd + h * kLine + (uint32_t)(((s * 2 + lh) ^ b_sw) << 4));
       }
 #pragma unroll
       for (int mt = 0; mt < S::kMT; ++mt)
@@ -198,7 +220,9 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int mt = 0; mt < S::kMT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s], xf[s][mt], acc[mt], 0, 0, 0);
+      for (int mt = 0; mt < S::kMT; ++mt)
+#pragma unroll
+        for (int nb = 0; nb < S::kNB; ++nb) acc[nb][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[nb][s], xf[s][mt], acc[nb][mt], 0, 0, 0);
   };
 
   for (int g = 0; g < S::kDepth - 1 && g < n_total; ++g) request();
@@ -228,13 +252,15 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
       if (m < rows) {
         if (EPI == kEpiSwiglu) {
 #pragma unroll
-          for (int qg = 0; qg < 2; ++qg) {
-            const int c = ct * kOut + blk * 16 + qg * 8 + lh * 4;
+          for (int qb = 0; qb < 2 * S::kNB; ++qb) {
+            const int nb = qb >> 1, qg = qb & 1;
+            const int c = ct * kOut + (blk + 4 * nb) * 16 + qg * 8 + lh * 4;
+            if (CW == 256 && c >= p.N) continue;
             float gt[4], u[4], a[4];
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
-              gt[x] = acc[mt][qg * 4 + x];
-              u[x] = acc[mt][qg * 4 + 8 + x];
+              gt[x] = acc[nb][mt][qg * 4 + x];
+              u[x] = acc[nb][mt][qg * 4 + 8 + x];
               a[x] = gt[x] * sigmoid_bf16_(gt[x]) * u[x];
             }
             *reinterpret_cast<u32x2*>(p.C + grow * p.ldc + c) = u32x2{pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3])};
@@ -251,7 +277,7 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
             if (c >= p.N) continue;
             float v[4];
 #pragma unroll
-            for (int x = 0; x < 4; ++x) v[x] = acc[mt][qg * 4 + x];
+            for (int x = 0; x < 4; ++x) v[x] = acc[0][mt][qg * 4 + x];
             if (EPI == kEpiSwigluGrad) {
               const __bf16* h = p.G + grow * (size_t)(2 * p.N) + c;
               float dg[4], du[4];
@@ -266,10 +292,7 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
         }
       }
     }
-#pragma unroll
-    for (int mt = 0; mt < S::kMT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
+    clear();
   }
 }
 
@@ -311,6 +334,15 @@ __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_ro
   // against 73).
   constexpr int kOut64 = EPI == kEpiSwiglu ? 32 : 64;
   const bool narrow = n_act * ((p.N + kOut64 - 1) / kOut64) <= (int)gridDim.x;
+  if constexpr (LAY == kLayNN && EPI == kEpiSwiglu) {
+    // GEMM-1: 256 columns (128 gate, 128 up: 256-byte pieces instead of 128; T = 256, H = 7168 515 -> 475 us a layer, T = 64,
+    // H = 2048 73 -> 67)
+    if (!narrow) {
+      if (max_rows > 32) stream_items<LAY, EPI, 256, 2>(p, n_act, smem);
+      else stream_items<LAY, EPI, 256, 1>(p, n_act, smem);
+      return;
+    }
+  }
   if (max_rows > 32) stream_items<LAY, EPI, 128, 2>(p, n_act, smem);
   else if (!narrow) stream_items<LAY, EPI, 128, 1>(p, n_act, smem);
   else if (max_rows > 16) stream_items<LAY, EPI, 64, 2>(p, n_act, smem);

@@ -336,8 +336,11 @@ __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_ro
   const bool narrow = n_act * ((p.N + kOut64 - 1) / kOut64) <= (int)gridDim.x;
   if constexpr (LAY == kLayNN && EPI == kEpiSwiglu) {
     // GEMM-1: 256 columns (128 gate, 128 up: 256-byte pieces instead of 128; T = 256, H = 7168 515 -> 475 us a layer, T = 64,
-    // H = 2048 73 -> 67)
-    if (!narrow) {
+    // H = 2048 73 -> 67), unless 128 make shorter rounds (20 experts with rows, 320 items of 256 on 256 workgroups: 352 against
+    // 356 at T = 32; a round costs its columns)
+    const int G = gridDim.x;
+    const int rounds256 = (n_act * ((p.N + 127) / 128) + G - 1) / G, rounds128 = (n_act * ((p.N + 63) / 64) + G - 1) / G;
+    if (!narrow && 2 * rounds256 <= rounds128) {
       if (max_rows > 32) stream_items<LAY, EPI, 256, 2>(p, n_act, smem);
       else stream_items<LAY, EPI, 256, 1>(p, n_act, smem);
       return;

@@ -461,7 +461,15 @@ __device__ __forceinline__ void gemm_k_loop(f32x16 (&acc)[kMaxMT][4], f32x16 (&a
     // step's barrier takes the place of the closing one (its reads of a further step's operands are never used).  Copies
     // that the last barrier does not cover must stay clear of the epilogue's staging (weight stage 2, and 16 KB and more
     // into activation stage 1): they are the last step's weight lines, which therefore go to stage 0 or 1, and the first
-    // four activation lines behind that barrier (the first 16 KB of a stage); a wave's own have landed before it goes on.
+    // four activation lines behind that barrier (the first 16 KB of a stage).  A wave waits for its own before it goes on,
+    // but no barrier tells the others: the next tile's first copies may go to the same lines only if the same wave makes
+    // them.  Activation lines (line L of the staging area: wave L % 4, in both shapes) and NT weights (likewise) are safe; NN
+    // weights only from wide to wide: a wide wave owns 8 KB of a stage in a row, a tall wave 4 KB, and tall stages 0 and 1
+    // lie in wide stage 1.  So a workgroup passes a barrier before every tall NN tile:
+    // grouped_gemm_bf16_kernel has it (no launch is slower for it: T = 11000, H = 7168, half of the experts tall, 1317 us before
+    // this loop and 1299..1317 with it; remembering the shape of the tile before instead cost every launch 0.5 us of scalar
+    // spills), and in the single launches drawing a task has two (the words it hands round lie in line 0 of the staging area,
+    // which wave 0 alone copies to and writes to).
     uint32_t b_off[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) b_off[i] = LAY == kLayNN ? t.b_off[i & 1] + (uint32_t)((i >> 1) * 4 * t.ldb_bytes) : t.b_off[i];
@@ -487,7 +495,7 @@ __device__ __forceinline__ void gemm_k_loop(f32x16 (&acc)[kMaxMT][4], f32x16 (&a
       }
       bs_i = bs_next;
     }
-    wait_vmcnt<0>();   // ... so that the next tile's copies, to the same lines, come behind them
+    wait_vmcnt<0>();   // ... so that this wave's copies of the next tile come behind them
     if (NX) asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");   // the last assembly MFMA's result before any read of it
     return;
   }
@@ -996,6 +1004,7 @@ void grouped_gemm_bf16_kernel(GemmParams p) {
     int mtile, ntile;
     bool tall;
     if (!pair_work_item(p, 2 * (pl * 8 + xcd), rem, n_m, kOutCols, mtile, ntile, tall)) continue;
+    if (LAY == kLayNN && tall) __builtin_amdgcn_s_barrier();   // see gemm_k_loop, full tiles
     gemm_map_tile_bf16<LAY, EPI, true>(p, mtile, ntile, tall, smem);
   }
   if (split_tail && lw < 2 * tail) {
@@ -1005,6 +1014,7 @@ void grouped_gemm_bf16_kernel(GemmParams p) {
     int mtile, ntile;
     bool tall;
     if (pair_work_item(p, 2 * (pl * 8 + xcd), rem, n_m, kOutCols, mtile, ntile, tall)) {
+      if (LAY == kLayNN) __builtin_amdgcn_s_barrier();
       if (tall) {                                   // already a 128-column item
         if (half == 0) gemm_tile_bf16<LAY, EPI, true>(p, mtile, ntile, smem);
       } else if ((2 * ntile + half) * (kOutCols / 2) < p.N) {

@@ -16,7 +16,7 @@ CASES = [
     ("one_row", 128, 64, [1, 0, 0]),                        # one expert; 64 columns per item, a single stage
     ("narrow_16", 320, 192, [16, 1, 0, 9]),                 # 16-row stages; K = 2.5 and 1.5 stages of 128
     ("narrow_32", 192, 320, [17, 32, 3]),                   # 32-row stages with 64 columns
-    ("wide_32", 448, 832, [32, 2, 31, 0] * 12),             # 128 columns, several items per workgroup, N = 3.5 and 6.5 tiles
+    ("wide_32", 448, 832, [32, 2, 31, 0] * 12),             # 256 columns (GEMM-1), 128 (act_grad), 64; N = 3.5 and 6.5 tiles of 128
     ("wide_64", 320, 448, [64, 33, 1, 0, 50]),              # two row blocks
     ("many_rows", 128, 192, [40] * 64),                     # more rows than the token table in LDS holds
     ("above", 192, 128, [65, 3]),                           # the first size that takes the ordinary tiles
@@ -26,8 +26,52 @@ CASES = [
 @pytest.mark.parametrize("keep_xp", [True, False])
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_weight_stream(case, keep_xp):
+    _run(*case, keep_xp)
+
+
+# rows of nine experts, eight of each: 64 experts have rows, 880 and 2072 in all (the token table in LDS holds 2048)
+ONE_32, ONE_64 = [32, 3, 17, 1, 0, 9, 26, 2, 20], [64, 50, 1, 33, 0, 7, 52, 18, 34]
+
+DEEP = [
+    # name, H, I, rows per expert, columns per item of GEMM-1, GEMM-2, act_grad, gate_grad
+    ("gemm1_256_rows_32", 576, 832, ONE_32 * 8, (256, 128, 128, 128)),
+    ("gemm1_256_rows_64", 576, 832, ONE_64 * 8, (256, 128, 128, 128)),
+    ("gemm1_128_rows_32", 576, 576, ONE_32 * 8, (128, 128, 128, 128)),
+    ("gemm1_128_rows_64", 576, 576, ONE_64 * 8, (128, 128, 128, 128)),
+    # two stages to an item, fewer than any ring holds: GEMM-1 and act_grad (K = H) ...
+    ("short_k_h", 128, 832, ONE_64 * 8, (256, None, 128, None)),
+    # ... GEMM-2 (K = I, one stage) and gate_grad (K = 2 I)
+    ("short_k_i", 1088, 64, ONE_32 * 8, (None, 128, None, 128)),
+]
+
+
+def _columns(n_act, N, swiglu, G):
+    """Columns per item and number of items that the launch's rule (csrc/gemm_stream.h, stream_gemm_bf16) gives."""
+    items = {cw: n_act * -(-N // (cw // 2 if swiglu else cw)) for cw in (64, 128, 256)}
+    if items[64] <= G:
+        cw = 64
+    else:
+        cw = 256 if swiglu and 2 * -(-items[256] // G) <= -(-items[128] // G) else 128
+    return cw, items[cw]
+
+
+@pytest.mark.parametrize("keep_xp", [True, False])
+@pytest.mark.parametrize("case", DEEP, ids=[c[0] for c in DEEP])
+def test_several_items_per_workgroup(case, keep_xp):
+    """Each workgroup runs more than one item: stages of the next one requested while the last ones of this one are
+    multiplied, stores between the loads, and a last round that only some workgroups have an item in."""
+    name, H, I, rows, columns = case
+    G = -(-torch.cuda.get_device_properties(0).multi_processor_count // 8) * 8
+    n_act = sum(r > 0 for r in rows)
+    for want, (N, swiglu) in zip(columns, ((I, True), (H, False), (I, False), (H, False))):
+        if want is not None:
+            cw, items = _columns(n_act, N, swiglu, G)
+            assert cw == want and items > G and items % G, (name, N, cw, items, G)
+    _run(name, H, I, rows, keep_xp)
+
+
+def _run(name, H, I, rows, keep_xp):
     from gpu_common import check_backward, check_forward, check_routing, run_backward, run_forward, small_config
-    name, H, I, rows = case
     E = len(rows)
     cfg = small_config("stream_" + name, sum(rows), H, I, E, E, 0, 1, "bf16", 81)
     inp = make_inputs(cfg, with_dy=True)

@@ -11,6 +11,7 @@ wait), but nothing in the language enforces it; this module checks the generated
 """
 from __future__ import annotations
 
+import functools
 import os
 import re
 import subprocess
@@ -31,6 +32,7 @@ def _vregs(text: str) -> set:
     return regs
 
 
+@functools.lru_cache(maxsize=None)
 def device_assembly() -> str:
     """Device-only assembly of csrc/moe_ffn.hip with the library's own flags."""
     from .build import HIPCC_FLAGS, SOURCES
@@ -82,6 +84,22 @@ def check_register_fed_loads(asm: str):
             if touched:
                 bad.append((no, line, sorted(touched)))
     return n_loads, bad
+
+
+def loads_ahead_of_first_branch(asm: str, kernel: str):
+    """Scalar loads (base, offset) of the kernel ahead of its first branch, in the groups that one wait covers."""
+    start = asm.index(f"\n{kernel}:")
+    groups = [[]]
+    for raw in asm[start + 1:].splitlines()[1:]:
+        line = raw.split(";")[0].strip()
+        if line.startswith("s_cbranch") or line.startswith("s_branch"):
+            break
+        m = re.match(r"s_load_dword\w*\s+[^,]+,\s*(s\[\d+:\d+\])\s*,\s*(\w+)", line)
+        if m:
+            groups[-1].append((m.group(1), int(m.group(2), 0)))
+        elif line.startswith("s_waitcnt") and "lgkmcnt" in line:
+            groups.append([])
+    return groups
 
 
 def main():

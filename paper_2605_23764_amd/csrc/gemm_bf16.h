@@ -978,14 +978,18 @@ template <int LAY, int EPI>
 __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void grouped_gemm_bf16_kernel(GemmParams p) {
   __shared__ __attribute__((aligned(1024))) char smem[kGemmLdsBytes];
-  const int n_m = p.tiles.meta[kMetaMTiles], max_rows = p.tiles.meta[kMetaMaxRows];   // both fetched at once
+  // Both words of the map and the grid size are fetched together: left to itself the compiler sinks what only the tiles need
+  // below the branch, where it waits for memory a second time.  Layers of 33..144 MB of weights, 40 and 100 rows per expert:
+  // 1 us of a forward of 40..70 us, streams included (with the two words alone: nothing gained).
+  int n_m = p.tiles.meta[kMetaMTiles], max_rows = p.tiles.meta[kMetaMaxRows], G = gridDim.x;
+  asm volatile("" : "+s"(n_m), "+s"(max_rows), "+s"(G));
   if constexpr (EPI != kEpiScatter) {
     if (max_rows <= kStreamMaxRows) {
       stream_gemm_bf16<LAY, EPI>(p, max_rows, smem);
       return;
     }
   }
-  const int xcd = blockIdx.x & 7, lw = blockIdx.x >> 3, W = gridDim.x >> 3;
+  const int xcd = blockIdx.x & 7, lw = blockIdx.x >> 3, W = G >> 3;
   const int n_pairs = (n_m + 1) >> 1;
   const int pairs_x = n_pairs > xcd ? (n_pairs - xcd + 7) >> 3 : 0;
   const int per_pair = 2 * p.n_ntiles;

@@ -5,7 +5,7 @@ import os
 
 import pytest
 
-from paper_2605_23764_amd.asm_check import check_register_fed_loads, device_assembly
+from paper_2605_23764_amd.asm_check import check_register_fed_loads, device_assembly, loads_ahead_of_first_branch
 
 GOOD = """
 \t.amdhsa_kernel k
@@ -49,3 +49,13 @@ def test_generated_code_keeps_the_window_closed():
     # four fragments per request, two requests (prologue, loop) per instantiation of the register-fed tile
     assert n >= 8 and n % 4 == 0, n
     assert not bad, bad[:5]
+
+
+@pytest.mark.skipif(not os.path.exists(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")), reason="needs hipcc")
+@pytest.mark.parametrize("lay,epi", [(0, 1), (0, 0), (1, 2), (1, 0)])
+def test_launch_head_waits_for_the_tile_map_once(lay, epi):
+    """The number of M tiles (word 0) and the rows of the largest expert (word 3), between which the grouped GEMM kernel
+    decides what it runs as, are fetched together."""
+    groups = loads_ahead_of_first_branch(device_assembly(), f"_ZN3moe24grouped_gemm_bf16_kernelILi{lay}ELi{epi}EEEvNS_10GemmParamsE")
+    # kernel arguments come from s[0:1]
+    assert any({(base, 0), (base, 12)} <= set(g) for g in groups for base, _ in g if base != "s[0:1]"), groups

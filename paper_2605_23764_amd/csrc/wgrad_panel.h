@@ -32,9 +32,18 @@ namespace moe {
 // phase of the tile sweep, summed over all items.  Per wave 8 words: vmcnt wait, barrier, next request (the three
 // steps of an entry hand-over), everything between two hand-overs (16 MFMAs and their operand reads), epilogues,
 // number of hand-overs, number of tiles, unused.
+// The clocks are read inside the kernel's own code (MOE_WG_MARK, MOE_WG_SUM), nothing else differs.
 #if defined(MOE_SCHED_TRACE)
 __device__ unsigned long long g_wgrad_cycles[16];
-#define MOE_WG_CLOCK() ((long long)__builtin_amdgcn_s_memtime())
+__device__ inline void trace_add(unsigned long long* sum, const long long (&cy)[6], int n_tiles) {
+  for (int i = 0; i < 6; ++i) atomicAdd(sum + i, (unsigned long long)cy[i]);
+  atomicAdd(sum + 6, (unsigned long long)n_tiles);
+}
+#define MOE_WG_MARK(i) trace_at[i] = (long long)__builtin_amdgcn_s_memtime();
+#define MOE_WG_SUM(phase, from, to) trace_cy[phase] += trace_at[to] - trace_at[from];
+#else
+#define MOE_WG_MARK(i)
+#define MOE_WG_SUM(phase, from, to)
 #endif
 
 constexpr int kWpM = 256;                          // output rows per panel
@@ -319,8 +328,9 @@ __device__ __forceinline__ void wp_item(const WpCtx& t, int row0, char* smem) {
   // Hand-over to chunk kcn of tile tile_n inside the sweep: as next_entry, but what is requested next follows from kcn, so
   // a request is two copies from a scalar base with row offsets that sit in registers (wp_issue_entry computes them, with
   // a division and a multiplication per line), and the wait is one instruction once enough of the sweep lies behind it
-  // (wp_wait_entry: a switch).  Together they were 239 clocks of the hand-over's 471; training step at T = 8192, H = 7168,
-  // I = 2048, 32 of 256 experts: 2669 -> 2650 us.
+  // (wp_wait_entry: a switch).  Of the later wave of a SIMD (c3 shapes, tracing build) wait and request take 321 clocks of a
+  // hand-over instead of 408, a tile 8 780 instead of 9 460; training step at T = 8192, H = 7168, I = 2048, 32 of 256 experts:
+  // 2669 -> 2650 us.
   static_assert(kWpLoads == 2, "two copies per wave and entry");
   uint32_t b_row[2], b_row_last[2];                             // last chunk: rows past the segment repeat its last one
 #pragma unroll
@@ -330,12 +340,20 @@ __device__ __forceinline__ void wp_item(const WpCtx& t, int row0, char* smem) {
     b_row[i] = (uint32_t)(r * t.ldb_bytes) + col;
     b_row_last[i] = (uint32_t)(min((KC - 1) * kWpBK + r, t.k_rows - 1) * t.ldb_bytes) + col;
   }
+#if defined(MOE_SCHED_TRACE)
+  long long trace_cy[6], trace_at[5];                           // trace_at[4]: end of the hand-over or epilogue before
+  for (long long& trace_c : trace_cy) trace_c = 0;
+#endif
+  MOE_WG_MARK(4)
   auto next_chunk = [&](int tile_n, int kcn) __attribute__((always_inline)) {   // kcn: known at compile time
     constexpr int K1 = KC > 0 ? KC : 1;
     const int h = tile_n * K1 + kcn;
+    MOE_WG_MARK(0)
     if (h > kWpAhead && h + kWpAhead - 1 < K1 * t.NT) wait_vmcnt_uniform(2 * (kWpAhead - 1) + kWpEpiStores * wp_steady_epilogues(kcn, K1));
     else wp_wait_entry(g, n_entries, epi_mask);
+    MOE_WG_MARK(1)
     __builtin_amdgcn_s_barrier();
+    MOE_WG_MARK(2)
     const int kcr = (kcn + kWpAhead) % K1, tile_r = tile_n + (kcn + kWpAhead) / K1;
     if (tile_r < t.NT) {
       const uint32_t st = uniform_u32(t.lds0 + (uint32_t)(slot == 0 ? kWpDepth - 1 : slot - 1) * kWpSlot + (uint32_t)t.wave * (2 * kLine));
@@ -344,11 +362,13 @@ __device__ __forceinline__ void wp_item(const WpCtx& t, int row0, char* smem) {
       lds_dma16_at<0>(base, kcr == K1 - 1 ? b_row_last[0] : b_row[0], st);
       lds_dma16_at<kLine>(base, kcr == K1 - 1 ? b_row_last[1] : b_row[1], st);
     }
-  };
+    MOE_WG_MARK(3)
+    MOE_WG_SUM(0, 0, 1) MOE_WG_SUM(1, 1, 2) MOE_WG_SUM(2, 2, 3) MOE_WG_SUM(3, 4, 0)
+    MOE_WG_MARK(4)
 #if defined(MOE_SCHED_TRACE)
-  long long cy[6] = {0, 0, 0, 0, 0, 0};
-  long long c_prev = MOE_WG_CLOCK();
+    trace_cy[5] += 1;
 #endif
+  };
 #pragma unroll 1
   for (int tile = 0; tile < t.NT; ++tile) {
 #pragma unroll
@@ -364,18 +384,7 @@ __device__ __forceinline__ void wp_item(const WpCtx& t, int row0, char* smem) {
       const bool more = g < n_entries;
       if (more) {
         wait_lgkmcnt0();                   // this wave holds everything it needs from the entry it leaves
-#if defined(MOE_SCHED_TRACE)
-        const long long c0 = MOE_WG_CLOCK();
-        wp_wait_entry(g, n_entries, epi_mask);
-        const long long c1 = MOE_WG_CLOCK();
-        __builtin_amdgcn_s_barrier();
-        const long long c2 = MOE_WG_CLOCK();
-        if (g + kWpAhead < n_entries) wp_issue_entry<KC>(t, g + kWpAhead);
-        const long long c3 = MOE_WG_CLOCK();
-        cy[0] += c1 - c0; cy[1] += c2 - c1; cy[2] += c3 - c2; cy[3] += c0 - c_prev; cy[5] += 1; c_prev = c3;
-#else
         next_chunk(kc + 1 == KC ? tile + 1 : tile, kc + 1 == KC ? 0 : kc + 1);
-#endif
       }
       slice(xa[kc * 4 + 3], false, more, slot, 0);
     }
@@ -395,19 +404,15 @@ __device__ __forceinline__ void wp_item(const WpCtx& t, int row0, char* smem) {
         }
       wp_store_block(region, pk, c_row + tile * kWpN, t.ldc);
     }
-#if defined(MOE_SCHED_TRACE)
-    { const long long ce = MOE_WG_CLOCK(); cy[4] += ce - c_prev; c_prev = ce; }
-#endif
+    MOE_WG_MARK(0)
+    MOE_WG_SUM(4, 4, 0)
+    MOE_WG_MARK(4)
     epi_mask |= 1u;
   }
   wait_lgkmcnt0();
   __builtin_amdgcn_s_barrier();            // ring and staging space are quiet before the next item's first loads
 #if defined(MOE_SCHED_TRACE)
-  if (lane == 0 && (wm == 0 || wm == 5)) {
-    unsigned long long* d = g_wgrad_cycles + (wm == 0 ? 0 : 8);
-    for (int i = 0; i < 6; ++i) atomicAdd(d + i, (unsigned long long)cy[i]);
-    atomicAdd(d + 6, (unsigned long long)t.NT);
-  }
+  if (lane == 0 && (wm == 0 || wm == 5)) trace_add(g_wgrad_cycles + (wm == 0 ? 0 : 8), trace_cy, t.NT);
 #endif
 }
 

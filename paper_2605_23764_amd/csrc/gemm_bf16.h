@@ -786,6 +786,10 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmParams& p, int t0, int 
   // (T = 8192, 1.9 GB: 501 -> 474 us; T = 400, 185 MB: 48 and 54.5).  Tiles that share an expert's weights read them plainly:
   // non-temporal they cost the skewed forward 2 %.  SwiGLU_grad and the single launches (NT_OK false) have no registers for
   // a second loop (43 and 49 spilled).
+  // What the forward pays for a backward that follows at once (T = 400, w_gate_up 185 MB): gate_grad finds less of the weights
+  // in the memory-side cache, 47 -> 53 us.  With GEMM-1 reading plainly where H1 is kept and the weights fit that cache the
+  // step gains 1 % (304.6 -> 302.3; T = 256 268 -> 266) and the forward loses 6 % (95.7 -> 101.1; T = 256 89 -> 94); with weights
+  // of 138 MB, T = 300, the step loses too (272.8 -> 275.0).  Behind several layers the backward finds nothing either way.
   auto k_loop = [&](auto stream) __attribute__((always_inline)) {
     constexpr bool ST = decltype(stream)::value, ST4 = ST && LAY == kLayNT;
     if constexpr (X5) {

@@ -4,23 +4,27 @@
 // weights at HBM rate and nothing else; the tile of gemm_bf16.h (256 weight columns, 64 KB of weights under way per CU)
 // then has too few work items to fill the chip evenly (T = 1 at H = 2048, I = 1408: 44 items on four of the eight dies)
 // and too little in flight.  Here
-//   * an item is 128 or 64 weight columns of one expert over the whole K (never split: results are the same bits as the
-//     other kernel's, whose MFMAs sum in the same order), dealt evenly to all workgroups; 64 columns where that makes the
-//     rounds come out shorter;
-//   * a workgroup runs its items as ONE stream of 16 KB weight stages (64 k x 128 columns or 128 k x 64) through an LDS
-//     ring of 6 or 7 stages, 80..96 KB of weights under way; the next item's first stages are requested while the last
-//     ones of this item are multiplied, so nothing drains between items;
+//   * an item is some weight columns of one expert over the whole K (never split: results are the same bits as the other
+//     kernel's, whose MFMAs sum in the same order), dealt evenly to all workgroups.  Three widths (stream_gemm_bf16 has the rule):
+//       columns              a stage holds              ring: up to 32 rows / up to 64    weights under way
+//       256 (GEMM-1 only)    64 k x 256 = 32 KB         4 / 3 stages                      96 / 64 KB
+//       128                  64 k x 128 = 16 KB         7 / 6                             96 / 80 KB
+//       64 (up to 32 rows)   128 k x 64 = 16 KB         7 (up to 16 rows) / 6             96 / 80 KB
+//   * a workgroup runs its items as ONE stream of such stages through the ring in LDS; the next item's first stages are
+//     requested while the last ones of this item are multiplied, so nothing drains between items;
 //   * activation rows ride along in the same stage (4 or 8 KB, from the L2), gathered through the permutation if need be;
-//   * one barrier per stage; each of the four waves multiplies one 32-column block (two of them with 64 columns).
-//     For SwiGLU a wave's block is 16 gate and the 16 matching up columns: both meet in one lane's accumulators.
+//   * one barrier per stage; each of the four waves multiplies one 32-column block (256 columns: two; 64 columns: two of the
+//     waves one each).  For SwiGLU a block is 16 gate and the 16 matching up columns: both meet in one lane's accumulators.
 // Results are written straight from the accumulators (8 bytes per lane): they are a thousandth of the bytes read.
-// The weights are read non-temporally (each line once, by one workgroup): 5 to 9 % of a launch.
-// What bounds it: the rate at which HBM serves 256-byte pieces of rows 8..14 KB apart.  A loop that only loads them
-// reaches 6.2 TB/s (5.7 without the non-temporal hint), 1 KB pieces 6.3..6.7, one linear stream 7.1; with the MFMAs
-// taken out the launch is no faster, without the activation loads 2 %.
+// The weights are read non-temporally (each line once, by one workgroup; 64 columns: not, two items share a line): 5 to 9 %
+// of a launch.
+// What bounds it: the rate at which HBM serves short pieces of rows 4..14 KB apart: 256 bytes, 128 where a SwiGLU item of 128
+// columns reads 64 gate and 64 up columns.  A loop that only loads pieces of 256 bytes reaches 6.2 TB/s (5.7 without the
+// non-temporal hint; 128 bytes 5.1), 1 KB pieces 6.3..6.7, one linear stream 7.1; with the MFMAs taken out the launch is no
+// faster, without the activation loads 2 %.
 // Measured, layer (routing and Combine included), against the tiles of gemm_bf16.h: H = 7168, I = 2048, 32 of 256 experts,
-// k = 8: T = 4 168 -> 101 us, T = 32 428 -> 354, T = 256 527 -> 470, T = 1000 548 -> 505; H = 2048, I = 1408, 16 experts,
-// k = 4: T = 1 60 -> 38.5, T = 8 74 -> 63, T = 64 76 -> 67.  Above 64 rows the activations' share of a stage grows past a
+// k = 8: T = 4 168 -> 101 us, T = 32 428 -> 354, T = 256 524 -> 461, T = 1000 548 -> 505; H = 2048, I = 1408, 16 experts,
+// k = 4: T = 1 60 -> 38.5, T = 8 74 -> 62, T = 64 76 -> 67.  Above 64 rows the activations' share of a stage grows past a
 // third and the other kernel's 256 rows per weight fetch win.
 #pragma once
 #include "gemm_bf16.h"
@@ -28,9 +32,6 @@
 namespace moe {
 
 constexpr int kStreamGather = 2048;                  // token indices kept in LDS (rows beyond are looked up in memory)
-constexpr int kStreamTables = 6 * 24 * 1024;         // LDS offset of the tables, behind the larger ring
-constexpr int kStreamGatherOff = kStreamTables + 3 * kMaxE * 4;
-static_assert(kStreamGatherOff + kStreamGather * 4 <= kGemmLdsBytes, "LDS budget");
 
 // CW weight columns per item; AL activation lines (8 rows x 64 k) per wave and stage.
 template <int CW, int AL>
@@ -44,8 +45,16 @@ struct StreamShape {
   static constexpr int kStage = (kALine0 + 4 * AL) * kLine;
   static constexpr int kDepth = CW == 256 ? (AL == 1 ? 4 : 3) : AL == 1 ? 7 : 6;
   static constexpr int kLoads = kBLoads + AL;                    // wave-wide loads per wave and stage
-  static_assert(kDepth * kStage <= kStreamTables, "ring");
+  static constexpr int kRing = kDepth * kStage;
 };
+
+constexpr int stream_max(int a, int b) { return a > b ? a : b; }
+// LDS offset of the tables, behind the largest ring (144 KB)
+constexpr int kStreamTables = stream_max(stream_max(StreamShape<256, 1>::kRing, StreamShape<256, 2>::kRing),
+                                         stream_max(stream_max(StreamShape<128, 1>::kRing, StreamShape<128, 2>::kRing),
+                                                    stream_max(StreamShape<64, 1>::kRing, StreamShape<64, 2>::kRing)));
+constexpr int kStreamGatherOff = kStreamTables + 3 * kMaxE * 4;
+static_assert(kStreamGatherOff + kStreamGather * 4 <= kGemmLdsBytes, "LDS budget");
 
 typedef __attribute__((address_space(3))) int32_t* lds_i32_ptr;
 // Waits until at most `stages` stages requested after the wanted one are under way (fewer near the end of the stream).

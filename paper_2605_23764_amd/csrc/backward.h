@@ -140,19 +140,28 @@ struct GemmBwdParamsF32 {
 };
 
 // act_grad (+ SwiGLU_grad) and gate_grad: C[rows, N] = A[rows, K] * W_e[N, K]^T per M tile.
+// One result v of a data gradient (SwiGLU-grad: v = dA).
+template <int EPI>
+__device__ __forceinline__ void store_dgrad_f32(const GemmBwdParamsF32& p, size_t grow, int c, float v) {
+  if (EPI == kEpiSwigluGrad) {
+    const float g = p.G[grow * (size_t)(2 * p.N) + c], u = p.G[grow * (size_t)(2 * p.N) + p.N + c];
+    const float s = sigmoidf_(g);
+    p.C[grow * p.ldc + c] = v * u * s * (1.f + g * (1.f - s));
+    p.C[grow * p.ldc + p.N + c] = v * g * s;
+  } else {
+    p.C[grow * p.ldc + c] = v;
+  }
+}
+
 template <int EPI>
 __global__ __launch_bounds__(256) void grouped_dgrad_f32_kernel(GemmBwdParamsF32 p) {
   __shared__ __attribute__((aligned(16))) float smem[kFLdsFloats1];
-  const int total = p.tiles.meta[kMetaMTiles] * p.n_ntiles;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
-  const int G = gridDim.x;
-  for (int it = 0; it * G < total; ++it) {
-    const int tile = xcd_spread_tile(it, blockIdx.x, G, total);
-    if (tile < 0) continue;
+  auto whole = [&](int tile) __attribute__((always_inline)) {
     const int mtile = tile / p.n_ntiles, n0 = (tile % p.n_ntiles) * kFBN;
     const int e = p.tiles.expert[mtile], row0 = p.tiles.row0[mtile], rows = p.tiles.rows[mtile];
-    if (rows <= 0) continue;   // the empty half of a pair slot (block-uniform)
+    if (rows <= 0) return;   // the empty half of a pair slot (block-uniform)
     f32x16 acc[1];
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[0][r] = 0.f;
@@ -163,31 +172,34 @@ __global__ __launch_bounds__(256) void grouped_dgrad_f32_kernel(GemmBwdParamsF32
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int m = wm * 32 + f32_acc_row(r, lane);
-      if (m >= rows) continue;
-      const size_t grow = (size_t)(row0 + m);
-      if (EPI == kEpiSwigluGrad) {
-        const float g = p.G[grow * (size_t)(2 * p.N) + c], u = p.G[grow * (size_t)(2 * p.N) + p.N + c];
-        const float s = sigmoidf_(g), da = acc[0][r];
-        p.C[grow * p.ldc + c] = da * u * s * (1.f + g * (1.f - s));
-        p.C[grow * p.ldc + p.N + c] = da * g * s;
-      } else {
-        p.C[grow * p.ldc + c] = acc[0][r];
-      }
+      if (m < rows) store_dgrad_f32<EPI>(p, (size_t)(row0 + m), c, acc[0][r]);
     }
-  }
+  };
+  auto quarter = [&](int tile, int qm, int qn) __attribute__((always_inline)) {
+    const int mtile = tile / p.n_ntiles, n0 = (tile % p.n_ntiles) * kFBN + qn * 32;
+    const int e = p.tiles.expert[mtile], row0 = p.tiles.row0[mtile] + qm * 32, rows = p.tiles.rows[mtile] - qm * 32;
+    if (rows <= 0) return;
+    f32x4 acc[1] = {{0.f, 0.f, 0.f, 0.f}};
+    gemm_core_f32_quarter<true, true, 1, false>(acc, p.A + (size_t)(row0 + min(tid >> 3, rows - 1)) * p.lda + (tid & 7) * 4, 1,
+                                                p.B + (size_t)e * p.strideB + (size_t)(n0 + (tid >> 3)) * p.ldb + (tid & 7) * 4,
+                                                1, 0, p.K, smem);
+    const int c = n0 + wn * 16 + (lane & 15);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = wm * 16 + 4 * (lane >> 4) + r;
+      if (m < rows) store_dgrad_f32<EPI>(p, (size_t)(row0 + m), c, acc[0][r]);
+    }
+  };
+  f32_sweeps(p.tiles.meta[kMetaMTiles] * p.n_ntiles, p.K, whole, quarter);
 }
 
 // w2_grad and w1_grad: C_e[M, N] = A_e[rows_e, M]^T * B_e[rows_e, N]; zeros for experts without rows.
 __global__ __launch_bounds__(256) void grouped_wgrad_f32_kernel(GemmBwdParamsF32 p) {
   __shared__ __attribute__((aligned(16))) float smem[kFLdsFloats1];
   const int per_e = p.n_mtiles * p.n_ntiles;
-  const int total = p.E_local * per_e;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
-  const int G = gridDim.x;
-  for (int it = 0; it * G < total; ++it) {
-    const int tile = xcd_spread_tile(it, blockIdx.x, G, total);
-    if (tile < 0) continue;
+  auto whole = [&](int tile) __attribute__((always_inline)) {
     const int e = tile / per_e, rem = tile % per_e;
     const int m0 = (rem / p.n_ntiles) * kFBM, n0 = (rem % p.n_ntiles) * kFBN;
     const int seg0 = p.offsets[e], cnt = p.offsets[e + 1] - seg0;
@@ -200,7 +212,20 @@ __global__ __launch_bounds__(256) void grouped_wgrad_f32_kernel(GemmBwdParamsF32
     float* c_base = p.C + (size_t)e * p.strideC + (size_t)(m0 + wm * 32) * p.ldc + n0 + wn * 32 + (lane & 31);
 #pragma unroll
     for (int r = 0; r < 16; ++r) c_base[(size_t)f32_acc_row(r, lane) * p.ldc] = acc[0][r];
-  }
+  };
+  auto quarter = [&](int tile, int qm, int qn) __attribute__((always_inline)) {
+    const int e = tile / per_e, rem = tile % per_e;
+    const int m0 = (rem / p.n_ntiles) * kFBM + qm * 32, n0 = (rem % p.n_ntiles) * kFBN + qn * 32;
+    const int seg0 = p.offsets[e], cnt = p.offsets[e + 1] - seg0;
+    f32x4 acc[1] = {{0.f, 0.f, 0.f, 0.f}};
+    const size_t k0 = (size_t)(seg0 + (tid >> 3));
+    gemm_core_f32_quarter<false, false, 1, true>(acc, p.A + k0 * p.lda + m0 + (tid & 7) * 4, p.lda,
+                                                 p.B + k0 * p.ldb + n0 + (tid & 7) * 4, p.ldb, 0, cnt, smem);
+    float* c_base = p.C + (size_t)e * p.strideC + (size_t)(m0 + wm * 16 + 4 * (lane >> 4)) * p.ldc + n0 + wn * 16 + (lane & 15);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) c_base[(size_t)r * p.ldc] = acc[0][r];
+  };
+  f32_sweeps(p.E_local * per_e, p.offsets[p.E_local] / p.E_local, whole, quarter);
 }
 
 }  // namespace moe

@@ -17,7 +17,12 @@
 // Measured, T = 1500, H = 1024, I = 704, 16 experts, k = 4 (25.9 GFLOP forward, 51.9 backward), against 64 x 64 tiles with
 // 4 x 4 outputs per thread on the vector ALU: GEMM-1 418 -> 190 us (91 TFLOP/s), GEMM-2 173 -> 97, act_grad 277 -> 112,
 // gate_grad 521 -> 185, the two weight gradients 371 -> 144 each; error against 64 bits unchanged (1.0e-6).  The matrix
-// pipe is 83 % busy on a busy CU (GEMM-1); the rest is the last round: 1056 tiles on 256 CUs are 4.1 per CU.
+// pipe is 83 % busy on a busy CU (GEMM-1).  With quarter tiles for the last round (1111 tiles on 256 CUs are 4.3 per CU):
+// GEMM-1 190 -> 178, act_grad 114 -> 102; where a whole launch has few tiles more: T = 256, H = 256, I = 128, 8 experts, a
+// training step 72.7 -> 52 (GEMM-1 14.4 -> 7.1, act_grad 14.4 -> 7.2, gate_grad 8.3 -> 5.3); T = 300, H = 512, I = 448, 10 of 16
+// experts 116.7 -> 91.5; T = 20, H = 2048, I = 1408, forward 168 -> 150.  Same bits.
+// No gain from deeper prefetch (four steps in registers), operand fragments read a step ahead, or wave priorities by what
+// a workgroup has left.
 #pragma once
 #include "common.h"
 #include "gemm_bf16.h"  // GemmEpilogue, xcd_spread_tile
@@ -29,6 +34,10 @@ constexpr int kFKcLd = kFBK + 4;                  // k-contiguous stage: floats 
 constexpr int kFXcLd = kFBN + 8;                  // x-contiguous stage: floats per k
 constexpr int kFStage = kFBM * kFKcLd;            // floats per operand stage (1280 >= 16 * 72)
 static_assert(kFStage >= kFBK * kFXcLd, "stage size");
+constexpr int kFQK = 32, kFQLd = 32 + 4;          // a quarter tile's K step; floats per row (either orientation)
+constexpr int kFQFixed = 64;                      // what a tile of either size costs beside its K loop, in k of a quarter
+constexpr int kFQStage = 32 * kFQLd;
+static_assert(kFQStage <= kFStage, "a quarter's stages fit where a tile's do");
 constexpr int kFLdsFloats1 = 2 * 2 * kFStage;     // two stages of two operands (20 KB)
 constexpr int kFLdsFloats2 = 2 * 3 * kFStage;     // two weight column blocks (30 KB)
 
@@ -46,6 +55,8 @@ struct GemmParamsF32 {
 
 typedef __attribute__((address_space(3))) float* lds_f32_ptr;
 typedef __attribute__((address_space(3))) f32x4* lds_f32x4_ptr;
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) f32x2* lds_f32x2_ptr;
 
 // acc[h] += A * B_h over n_steps K steps of 16 (rounded up to an even count) for this wave's 32 x 32 block (wm, wn).
 // A_KC / B_KC: operand k-contiguous (a thread fetches row tid / 4, k = tid % 4 * 4 .. + 3) or x-contiguous (k = tid / 16,
@@ -145,8 +156,136 @@ __device__ __forceinline__ void gemm_rows_f32(f32x16 (&acc)[NB], const float* a_
   else gemm_core_f32<A_KC, B_KC, NB, false, false>(acc, a_ptr, a_k, b_ptr, b_k, b_half, K, smem);
 }
 
+// A quarter of a tile, 32 x 32, for launches and last rounds with too few tiles: wave (wm, wn) owns a 16 x 16 block (GEMM-1:
+// twice) on v_mfma_f32_16x16x4_f32, K step 32, two LDS stages and four more steps in registers.  Both MFMA shapes add one
+// product after the other, in the order of their k slots (bit for bit the chain of fmaf: 204 800 random results), so with the
+// slots 0 4 1 5, then 2 6 3 7 of every eight k the quarter gives the same bits as the whole tile, whose slots are 0 4, 1 5,
+// 2 6, 3 7.  The k-contiguous stage keeps a lane group's eight k of a step together (group g = lane / 16 holds k = 4 * (g & 1)
+// + g / 2, + 2 of every eight): rows of 4 x 8 + 4 floats, read as two 16-byte fragments without conflicts.
+template <bool A_KC, bool B_KC, int NB, bool K_TAIL>
+__device__ __forceinline__ void gemm_core_f32_quarter(f32x4 (&acc)[NB], const float* a_ptr, long a_k, const float* b_ptr, long b_k,
+                                                      long b_half, int K, float* smem) {
+  static_assert(!K_TAIL || (!A_KC && !B_KC), "ragged K: x-contiguous operands");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  const int l16 = lane & 15, lg = lane >> 4;
+  const int n_steps = (K + kFQK - 1) / kFQK;
+  const int kt = tid >> 3;                             // K_TAIL: this thread's k inside a step
+  const lds_f32_ptr lds = (lds_f32_ptr)smem;
+  constexpr int kStages = (1 + NB) * kFQStage;
+  constexpr int kAhead = NB == 1 ? 4 : 2;              // steps under way (GEMM-1: two, or fewer than four workgroups fit a CU)
+  const int kc_st = (tid >> 3) * kFQLd + (tid & 1) * 8 + ((tid & 7) >> 1) * 2, xc_st = kt * kFQLd + (tid & 7) * 4;
+  const int k0 = (lg & 1) * 4 + (lg >> 1);
+  const int a_rd = A_KC ? (wm * 16 + l16) * kFQLd + lg * 8 : k0 * kFQLd + wm * 16 + l16;
+  const int b_rd = B_KC ? (wn * 16 + l16) * kFQLd + lg * 8 : k0 * kFQLd + wn * 16 + l16;
+  struct Regs { f32x4 a, b[NB]; };
+  auto load = [&](Regs& r, int s) __attribute__((always_inline)) {
+    const long k = K_TAIL ? min(s * kFQK + kt, K - 1) - kt : min(s, n_steps - 1) * kFQK;
+    r.a = *reinterpret_cast<const f32x4*>(a_ptr + k * a_k);
+#pragma unroll
+    for (int h = 0; h < NB; ++h) r.b[h] = *reinterpret_cast<const f32x4*>(b_ptr + k * b_k + h * b_half);
+  };
+  auto put = [&](lds_f32_ptr st, const f32x4& v, bool kc) __attribute__((always_inline)) {
+    if (kc) {
+      *(lds_f32x2_ptr)(st + kc_st) = f32x2{v[0], v[2]};
+      *(lds_f32x2_ptr)(st + kc_st + 16) = f32x2{v[1], v[3]};
+    } else {
+      *(lds_f32x4_ptr)(st + xc_st) = v;
+    }
+  };
+  auto stage = [&](const Regs& r, int s, int buf) __attribute__((always_inline)) {
+    const lds_f32_ptr st = lds + buf * kStages;
+    const bool in = !K_TAIL || s * kFQK + kt < K;
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    put(st, in ? r.a : z, A_KC);
+#pragma unroll
+    for (int h = 0; h < NB; ++h) put(st + (1 + h) * kFQStage, in ? r.b[h] : z, B_KC);
+  };
+  auto fragment = [&](float (&f)[8], lds_f32_ptr st, bool kc) __attribute__((always_inline)) {
+    if (kc) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const f32x4 v = *(lds_f32x4_ptr)(st + q * 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f[q * 4 + i] = v[i];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) f[i] = st[((i >> 1) * 8 + (i & 1) * 2) * kFQLd];
+    }
+  };
+  auto step = [&](Regs& r, int s, int buf) __attribute__((always_inline)) {
+    const lds_f32_ptr st = lds + buf * kStages;
+    float a[8], b[NB][8];
+    fragment(a, st + a_rd, A_KC);
+#pragma unroll
+    for (int h = 0; h < NB; ++h) fragment(b[h], st + (1 + h) * kFQStage + b_rd, B_KC);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int h = 0; h < NB; ++h) acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[h][i], acc[h], 0, 0, 0);
+    if (K_TAIL) __builtin_amdgcn_sched_barrier(0);     // the zeroing of one step must not be moved ahead of the other's wait
+    stage(r, s + 1, buf ^ 1);
+    load(r, s + 1 + kAhead);
+    __syncthreads();                                   // at the last step also: LDS free for the next tile
+    if (K_TAIL) __builtin_amdgcn_sched_barrier(0);
+  };
+  if (n_steps <= 0) return;
+  Regs r[kAhead];
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) load(r[i], i);
+  stage(r[0], 0, 0);
+  if (K_TAIL) __builtin_amdgcn_sched_barrier(0);
+  load(r[0], kAhead);
+  __syncthreads();
+  for (int s = 0; s < n_steps; s += kAhead) {          // an odd count (ragged K only) ends with a step of zeros
+    step(r[1], s, 0);
+    step(r[2 % kAhead], s + 1, 1);
+    if constexpr (kAhead == 4) {
+      if (s + 2 >= n_steps) break;
+      step(r[3], s + 2, 0);
+      step(r[0], s + 3, 1);
+    }
+  }
+}
+
+// Tiles of a launch of G workgroups, four to a CU: whole tiles in full sweeps, the rest as quarters where that shortens the
+// launch.  The fullest CU decides: ceil(4 rem / G) whole tiles or ceil(16 rem / G) quarters.  A quarter fetches twice the
+// operand bytes per product, an eighth on its time; kFQFixed: a weight gradient over 60 rows per expert (560 tiles) is faster
+// whole (a step of T = 300 91.9 us against 93.1), GEMMs of K = 1024 are not (forward of T = 600, 528 tiles: 161 -> 147).
+template <typename Whole, typename Quarter>
+__device__ __forceinline__ void f32_sweeps(int total, int K, Whole&& whole, Quarter&& quarter) {
+  const int G = gridDim.x, rem = total % G;
+  const bool split = (16 * rem + G - 1) / G * (9 * K + 8 * kFQFixed) < (4 * rem + G - 1) / G * (32 * K + 8 * kFQFixed);
+  const int n_whole = split ? total - rem : total;
+  for (int it = 0; it * G < n_whole; ++it) {
+    const int tile = xcd_spread_tile(it, blockIdx.x, G, n_whole);
+    if (tile >= 0) whole(tile);
+  }
+  if (!split) return;
+  for (int it = 0; it * G < 4 * rem; ++it) {
+    const int i = xcd_spread_tile(it, blockIdx.x, G, 4 * rem);
+    if (i >= 0) quarter(n_whole + (i >> 2), (i >> 1) & 1, i & 1);
+  }
+}
+
 // Rows of a wave's block in the order of the result registers.
 __device__ __forceinline__ int f32_acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
+
+// One result: v, for SwiGLU the pre-activations (v, u).
+template <int EPI>
+__device__ __forceinline__ void store_f32(const GemmParamsF32& p, size_t grow, int c, float v, float u) {
+  if (EPI == kEpiSwiglu) {
+    p.C[grow * p.ldc + c] = v * sigmoidf_(v) * u;
+    if (p.C2) {
+      p.C2[grow * (size_t)(2 * p.N) + c] = v;
+      p.C2[grow * (size_t)(2 * p.N) + p.N + c] = u;
+    }
+  } else {
+    p.C[grow * p.ldc + c] = v;
+  }
+}
 
 template <int EPI>
 __device__ __forceinline__ void gemm_tile_f32(const GemmParamsF32& p, int mtile, int ntile, float* smem) {
@@ -170,31 +309,45 @@ __device__ __forceinline__ void gemm_tile_f32(const GemmParamsF32& p, int mtile,
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int m = wm * 32 + f32_acc_row(r, lane);
-    if (m >= rows) continue;
-    const size_t grow = (size_t)(row0 + m);
-    if (EPI == kEpiSwiglu) {
-      const float g = acc[0][r], u = acc[NB - 1][r];
-      p.C[grow * p.ldc + c] = g * sigmoidf_(g) * u;
-      if (p.C2) {
-        p.C2[grow * (size_t)(2 * p.N) + c] = g;
-        p.C2[grow * (size_t)(2 * p.N) + p.N + c] = u;
-      }
-    } else {
-      p.C[grow * p.ldc + c] = acc[0][r];
-    }
+    if (m < rows) store_f32<EPI>(p, (size_t)(row0 + m), c, acc[0][r], acc[NB - 1][r]);
+  }
+}
+
+// Quarter (qm, qn) of the same tile.
+template <int EPI>
+__device__ __forceinline__ void gemm_quarter_f32(const GemmParamsF32& p, int mtile, int ntile, int qm, int qn, float* smem) {
+  constexpr int NB = (EPI == kEpiSwiglu) ? 2 : 1;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  const int e = p.tiles.expert[mtile];
+  const int row0 = p.tiles.row0[mtile] + qm * 32;
+  const int rows = p.tiles.rows[mtile] - qm * 32;
+  if (rows <= 0) return;
+  const int n0 = ntile * kFBN + qn * 32;
+  f32x4 acc[NB];
+#pragma unroll
+  for (int h = 0; h < NB; ++h)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[h][r] = 0.f;
+  gemm_core_f32_quarter<true, false, NB, false>(acc, p.A + (size_t)(row0 + min(tid >> 3, rows - 1)) * p.lda + (tid & 7) * 4, 1,
+                                                p.B + (size_t)e * p.strideB + (size_t)(tid >> 3) * p.ldb + n0 + (tid & 7) * 4,
+                                                p.ldb, p.N, p.K, smem);
+  const int c = n0 + wn * 16 + (lane & 15);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int m = wm * 16 + 4 * (lane >> 4) + r;
+    if (m < rows) store_f32<EPI>(p, (size_t)(row0 + m), c, acc[0][r], acc[NB - 1][r]);
   }
 }
 
 template <int EPI>
 __global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(GemmParamsF32 p) {
   __shared__ __attribute__((aligned(16))) float smem[EPI == kEpiSwiglu ? kFLdsFloats2 : kFLdsFloats1];
-  const int total = p.tiles.meta[kMetaMTiles] * p.n_ntiles;
-  const int G = gridDim.x;
-  for (int it = 0; it * G < total; ++it) {
-    const int tile = xcd_spread_tile(it, blockIdx.x, G, total);
-    if (tile < 0) continue;
-    gemm_tile_f32<EPI>(p, tile / p.n_ntiles, tile % p.n_ntiles, smem);
-  }
+  f32_sweeps(p.tiles.meta[kMetaMTiles] * p.n_ntiles, p.K,
+             [&](int t) __attribute__((always_inline)) { gemm_tile_f32<EPI>(p, t / p.n_ntiles, t % p.n_ntiles, smem); },
+             [&](int t, int qm, int qn) __attribute__((always_inline)) {
+               gemm_quarter_f32<EPI>(p, t / p.n_ntiles, t % p.n_ntiles, qm, qn, smem);
+             });
 }
 
 }  // namespace moe

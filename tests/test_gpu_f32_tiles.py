@@ -30,3 +30,22 @@ def test_edges_of_the_fp32_tiles(H, I, keep_xp):
     single = run_forward(cfg, inp, mode=moe.MODE_PERSISTENT, store_h1=True, keep_xp=keep_xp)
     assert torch.equal(single.out, run.out)
     check_backward(run_backward(cfg, inp, run), oracle.backward(inp["dy"], ref, inp["w_gate_up"], inp["w_down"]), ref["counts"], "f32")
+
+
+# 66 M tiles by 16 column tiles are one sweep of 1024 workgroups and 32 tiles that run as quarters; 64 by 4 fill the chip
+# once and stay whole; 66 by 1 are quarters only.
+@pytest.mark.parametrize("H,I,rows", [(1024, 64, [65] * 32 + [0, 31, 33]), (256, 64, [64] * 60 + [1, 63, 32, 33])])
+def test_whole_tiles_and_quarters(H, I, rows):
+    from gpu_common import check_backward, check_forward, run_backward, run_forward, small_config
+    cfg = small_config("f32_quarters", sum(rows), H, I, len(rows), len(rows), 0, 1, "f32", 73)
+    inp = make_inputs(cfg, with_dy=True)
+    inp["logits"][:] = -10.0
+    inp["logits"][np.arange(cfg.T), np.random.default_rng(5).permutation(np.repeat(np.arange(len(rows)), rows))] = 1.0
+    ref = oracle.forward(inp["x"], inp["logits"], inp["w_gate_up"], inp["w_down"], cfg.k)
+    assert ref["counts"].tolist() == rows
+    run = run_forward(cfg, inp, store_h1=True)
+    check_forward(run, ref, "f32", store_h1=True)
+    # the single launch multiplies whole tiles only: the same chain of sums
+    single = run_forward(cfg, inp, mode=moe.MODE_PERSISTENT, store_h1=True)
+    assert torch.equal(single.out, run.out)
+    check_backward(run_backward(cfg, inp, run), oracle.backward(inp["dy"], ref, inp["w_gate_up"], inp["w_down"]), ref["counts"], "f32")

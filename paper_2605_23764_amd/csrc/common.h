@@ -25,6 +25,7 @@ enum MetaWord {
   kMetaRows = 1,     // R: rows in expert-contiguous order
   kMetaStatus = 2,   // scheduler status (0 ok, MOE_ERR_SCHED_TIMEOUT)
   kMetaMaxRows = 3,  // rows of the largest expert
+  kMetaActive = 14,  // experts with rows
   kMetaWords = 16
 };
 

@@ -69,7 +69,8 @@ constexpr int kMaxMT = kBM / 64;                     // 32-row MFMA sub-tiles pe
 // those of a 256-row tile, and the MFMA work grows by the real rows only.
 constexpr int kWideRows = kBM + 64;
 constexpr int kBLinesPerWave = kBLines / 4;          // 8
-constexpr int kStreamMaxRows = 64;                   // rows of the largest expert up to which a launch runs as a weight stream
+constexpr int kStreamRows = 64;                      // rows of the largest expert up to which a launch runs as a weight stream,
+constexpr int kStreamMaxRows = 128;                  // ... and up to which it does where that takes a single round (see the kernel)
 
 struct GemmParams {
   const __bf16* A;    // [rows, lda] activations, expert-contiguous rows, k-contiguous
@@ -974,7 +975,7 @@ __device__ __forceinline__ int xcd_spread_tile(int it, int b, int G, int total) 
 // XCD j % 8 (workgroups are dealt to the XCDs round-robin by id); inside an XCD
 // the work items run N-tile-major with the two siblings adjacent, so the CUs that
 // stream the same weight panel do so at the same time behind the same L2.
-// A launch whose largest expert has at most kStreamMaxRows rows runs as a weight stream instead (gemm_stream.h).
+// A launch with few rows per expert runs as a weight stream instead (gemm_stream.h).
 template <int LAY, int EPI>
 __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_rows, char* smem);
 
@@ -985,10 +986,16 @@ void grouped_gemm_bf16_kernel(GemmParams p) {
   // Both words of the map and the grid size are fetched together: left to itself the compiler sinks what only the tiles need
   // below the branch, where it waits for memory a second time.  Layers of 33..144 MB of weights, 40 and 100 rows per expert:
   // 1 us of a forward of 40..70 us, streams included (with the two words alone: nothing gained).
-  int n_m = p.tiles.meta[kMetaMTiles], max_rows = p.tiles.meta[kMetaMaxRows], G = gridDim.x;
-  asm volatile("" : "+s"(n_m), "+s"(max_rows), "+s"(G));
+  int n_m = p.tiles.meta[kMetaMTiles], max_rows = p.tiles.meta[kMetaMaxRows], n_act = p.tiles.meta[kMetaActive], G = gridDim.x;
+  asm volatile("" : "+s"(n_m), "+s"(max_rows), "+s"(n_act), "+s"(G));
   if constexpr (EPI != kEpiScatter) {
-    if (max_rows <= kStreamMaxRows) {
+    // 65..128 rows per expert: as a stream where its items of 128 columns are a single round, i.e. where tiles of 256 columns
+    // leave half of the chip idle (T = 777, H = 1088, I = 704, 10 experts: training step 133 -> 115 us; 1600 rows, H = 7168,
+    // I = 512, 4 experts: forward 141 -> 96, backward 212 -> 159; T = 400, H = 2048, I = 1408, 16 experts: gate_grad and act_grad,
+    // backward 206 -> 194).  With more items than workgroups the tiles win (the same layer's GEMM-1: forward 95 as tiles, 106 as
+    // a stream; H = 7168, I = 2048, 32 experts: 603 and 669), and above 128 rows too (150 rows, 16 experts: 54 and 60).
+    constexpr int kOut128 = EPI == kEpiSwiglu ? 64 : 128;
+    if (max_rows <= kStreamRows || (max_rows <= kStreamMaxRows && n_act * ((p.N + kOut128 - 1) / kOut128) <= G)) {
       stream_gemm_bf16<LAY, EPI>(p, max_rows, smem);
       return;
     }

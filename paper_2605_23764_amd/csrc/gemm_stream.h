@@ -1,20 +1,20 @@
 // Grouped bf16 GEMMs for a few rows per expert (serving batches, small training batches): the weight stream.
 //
 // With at most 64 rows per expert a weight element meets one or two MFMA row blocks, so the launch is a read of the
-// weights at HBM rate and nothing else; the tile of gemm_bf16.h (256 weight columns, 64 KB of weights under way per CU)
+// weights at HBM rate and nothing else (up to 128 rows, where a launch is a single round: grouped_gemm_bf16_kernel); the tile of gemm_bf16.h (256 weight columns, 64 KB of weights under way per CU)
 // then has too few work items to fill the chip evenly (T = 1 at H = 2048, I = 1408: 44 items on four of the eight dies)
 // and too little in flight.  Here
 //   * an item is some weight columns of one expert over the whole K (never split: results are the same bits as the other
 //     kernel's, whose MFMAs sum in the same order), dealt evenly to all workgroups.  Three widths (stream_gemm_bf16 has the rule):
-//       columns              a stage holds              ring: up to 32 rows / up to 64    weights under way
-//       256 (GEMM-1 only)    64 k x 256 = 32 KB         4 / 3 stages                      96 / 64 KB
-//       128                  64 k x 128 = 16 KB         7 / 6                             96 / 80 KB
-//       64 (up to 32 rows)   128 k x 64 = 16 KB         7 (up to 16 rows) / 6             96 / 80 KB
+//       columns                a stage holds (weights)   ring: up to 16 / 32 / 64 / 128 rows   weights under way
+//       256 (GEMM-1 only)      64 k x 256 = 32 KB        4 / 4 / 3 / -  stages                 96 .. 64 KB
+//       128                    64 k x 128 = 16 KB        7 / 7 / 6 / 4                         96 .. 48 KB
+//       64                     128 k x 64 = 16 KB        7 / 6 / 4 / 3                         96 .. 32 KB
 //   * a workgroup runs its items as ONE stream of such stages through the ring in LDS; the next item's first stages are
 //     requested while the last ones of this item are multiplied, so nothing drains between items;
-//   * activation rows ride along in the same stage (4 or 8 KB, from the L2), gathered through the permutation if need be;
+//   * activation rows ride along in the same stage (4 to 32 KB, from the L2), gathered through the permutation if need be;
 //   * one barrier per stage; each of the four waves multiplies one 32-column block (256 columns: two; 64 columns: two of the
-//     waves one each).  For SwiGLU a block is 16 gate and the 16 matching up columns: both meet in one lane's accumulators.
+//     waves one each, above 32 rows two waves a block, half of the rows each).  For SwiGLU a block is 16 gate and the 16 matching up columns: both meet in one lane's accumulators.
 // Results are written straight from the accumulators (8 bytes per lane): they are a thousandth of the bytes read.
 // The weights are read non-temporally (each line once, by one workgroup; 64 columns: not, two items share a line): 5 to 9 %
 // of a launch.
@@ -25,12 +25,13 @@
 // Measured, layer (routing and Combine included), against the tiles of gemm_bf16.h: H = 7168, I = 2048, 32 of 256 experts,
 // k = 8: T = 4 168 -> 101 us, T = 32 428 -> 354, T = 256 524 -> 461, T = 1000 548 -> 505; H = 2048, I = 1408, 16 experts,
 // k = 4: T = 1 60 -> 38.5, T = 8 74 -> 62, T = 64 76 -> 67.  Above 64 rows the activations' share of a stage grows past a
-// third and the other kernel's 256 rows per weight fetch win.
+// third and the other kernel's 256 rows per weight fetch win, unless its tiles leave CUs idle.
 #pragma once
 #include "gemm_bf16.h"
 
 namespace moe {
 
+constexpr int kStreamRing = 144 * 1024;              // LDS of the stages
 constexpr int kStreamGather = 2048;                  // token indices kept in LDS (rows beyond are looked up in memory)
 
 // CW weight columns per item; AL activation lines (8 rows x 64 k) per wave and stage.
@@ -38,21 +39,18 @@ template <int CW, int AL>
 struct StreamShape {
   static constexpr int kKB = CW == 64 ? 128 : 64;                // k per stage
   static constexpr int kRows = (CW == 64 ? 16 : 32) * AL;        // activation rows a stage holds
-  static constexpr int kMT = kRows > 32 ? 2 : 1;                 // 32-row blocks
+  static constexpr int kMT = kRows > 32 ? kRows / 32 : 1;        // 32-row blocks
+  static constexpr int kWaveRows = CW == 64 && kMT > 1 ? 2 : 1;  // 64 columns: the waves share two column blocks and split the rows
+  static constexpr int kMTW = kMT / kWaveRows;                   // row blocks per wave
   static constexpr int kNB = CW == 256 ? 2 : 1;                  // 32-column blocks per wave
   static constexpr int kBLoads = CW == 256 ? 8 : 4;              // weight lines per wave and stage
   static constexpr int kALine0 = 4 * kBLoads;                    // the stage's activation lines follow its weight lines
   static constexpr int kStage = (kALine0 + 4 * AL) * kLine;
-  static constexpr int kDepth = CW == 256 ? (AL == 1 ? 4 : 3) : AL == 1 ? 7 : 6;
+  static constexpr int kDepth = kStreamRing / kStage;
   static constexpr int kLoads = kBLoads + AL;                    // wave-wide loads per wave and stage
-  static constexpr int kRing = kDepth * kStage;
 };
 
-constexpr int stream_max(int a, int b) { return a > b ? a : b; }
-// LDS offset of the tables, behind the largest ring (144 KB)
-constexpr int kStreamTables = stream_max(stream_max(StreamShape<256, 1>::kRing, StreamShape<256, 2>::kRing),
-                                         stream_max(stream_max(StreamShape<128, 1>::kRing, StreamShape<128, 2>::kRing),
-                                                    stream_max(StreamShape<64, 1>::kRing, StreamShape<64, 2>::kRing)));
+constexpr int kStreamTables = kStreamRing;           // LDS offset of the tables, behind the ring
 constexpr int kStreamGatherOff = kStreamTables + 3 * kMaxE * 4;
 static_assert(kStreamGatherOff + kStreamGather * 4 <= kGemmLdsBytes, "LDS budget");
 
@@ -177,7 +175,8 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
 
   // ---- operand reads: offsets of this lane inside a stage ----
   const int blk = CW != 64 ? wave : wave & 1;                    // this wave's (first) 32-column block; the second: blk + 4
-  const bool active = CW != 64 || wave < 2;
+  const bool active = CW != 64 || S::kWaveRows == 2 || wave < 2;
+  const int mt0 = S::kWaveRows == 2 ? (wave >> 1) * S::kMTW : 0;  // this wave's first row block
   uint32_t b_rd;
   if (LAY == kLayNN) {
     const int g = lane >> 4, i = lane & 15, kk = i >> 2;
@@ -191,23 +190,24 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
   } else {
     b_rd = (uint32_t)((blk * 4 + (l32 >> 3)) * (CW != 64 ? 1 : 2) * kLine + (l32 & 7) * 128);
   }
-  const int ar = l32 & (S::kRows - 1);                           // 16-row stages: the upper lanes repeat the rows
-  const uint32_t a_rd = (uint32_t)(S::kALine0 * kLine + (ar >> 3) * (CW != 64 ? 1 : 2) * kLine + (ar & 7) * 128);
+  const int ar = l32 & (S::kRows < 32 ? S::kRows - 1 : 31);      // 16-row stages: the upper lanes repeat the rows
+  constexpr int kABlock = (CW != 64 ? 4 : 8) * kLine;            // activation lines of 32 rows
+  const uint32_t a_rd = (uint32_t)(S::kALine0 * kLine + mt0 * kABlock + (ar >> 3) * (CW != 64 ? 1 : 2) * kLine + (ar & 7) * 128);
   const int a_sw = (ar >> 1) & 7, b_sw = (l32 >> 1) & 7;
 
-  f32x16 acc[S::kNB][S::kMT];
+  f32x16 acc[S::kNB][S::kMTW];
   auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int nb = 0; nb < S::kNB; ++nb)
 #pragma unroll
-      for (int mt = 0; mt < S::kMT; ++mt)
+      for (int mt = 0; mt < S::kMTW; ++mt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[nb][mt][r] = 0.f;
   };
   clear();
 
   auto half_stage = [&](lds_cptr st, int h) __attribute__((always_inline)) {   // 64 k: four MFMA slices
-    bf16x8 wf[S::kNB][4], xf[4][S::kMT];
+    bf16x8 wf[S::kNB][4], xf[4][S::kMTW];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int ks = h * 4 + s;
@@ -223,13 +223,13 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
         wf[0][s] = *(lds_bf16x8_cptr)(st + b_rd + h * kLine + (uint32_t)(((s * 2 + lh) ^ b_sw) << 4));
       }
 #pragma unroll
-      for (int mt = 0; mt < S::kMT; ++mt)
-        xf[s][mt] = *(lds_bf16x8_cptr)(st + a_rd + h * kLine + mt * 4 * kLine + (uint32_t)(((s * 2 + lh) ^ a_sw) << 4));
+      for (int mt = 0; mt < S::kMTW; ++mt)
+        xf[s][mt] = *(lds_bf16x8_cptr)(st + a_rd + h * kLine + mt * kABlock + (uint32_t)(((s * 2 + lh) ^ a_sw) << 4));
     }
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int mt = 0; mt < S::kMT; ++mt)
+      for (int mt = 0; mt < S::kMTW; ++mt)
 #pragma unroll
         for (int nb = 0; nb < S::kNB; ++nb) acc[nb][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[nb][s], xf[s][mt], acc[nb][mt], 0, 0, 0);
   };
@@ -255,8 +255,8 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
     const int row0 = __builtin_amdgcn_readfirstlane(s_row0[ae]), rows = __builtin_amdgcn_readfirstlane(s_rows[ae]);
     // lane: row l32 of each 32-row block; register group q: staged columns q * 8 + lh * 4 .. + 3 of the wave's block
 #pragma unroll
-    for (int mt = 0; mt < S::kMT; ++mt) {
-      const int m = mt * 32 + l32;
+    for (int mt = 0; mt < S::kMTW; ++mt) {
+      const int m = (mt0 + mt) * 32 + l32;
       const size_t grow = (size_t)(row0 + m);
       if (m < rows) {
         if (EPI == kEpiSwiglu) {
@@ -305,7 +305,7 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
   }
 }
 
-// Whole launch of a grouped GEMM whose largest expert has max_rows <= kStreamMaxRows rows.
+// Whole launch of a grouped GEMM whose largest expert has max_rows <= kStreamMaxRows rows (above kStreamRows: a single round).
 template <int LAY, int EPI>
 __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_rows, char* smem) {
   // experts with rows, in expert order (every wave counts, wave 0 writes), and the tokens of the first rows
@@ -355,10 +355,16 @@ __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_ro
       return;
     }
   }
-  if (max_rows > 32) stream_items<LAY, EPI, 128, 2>(p, n_act, smem);
-  else if (!narrow) stream_items<LAY, EPI, 128, 1>(p, n_act, smem);
-  else if (max_rows > 16) stream_items<LAY, EPI, 64, 2>(p, n_act, smem);
-  else stream_items<LAY, EPI, 64, 1>(p, n_act, smem);
+  if (narrow) {
+    if (max_rows > 64) stream_items<LAY, EPI, 64, 8>(p, n_act, smem);
+    else if (max_rows > 32) stream_items<LAY, EPI, 64, 4>(p, n_act, smem);
+    else if (max_rows > 16) stream_items<LAY, EPI, 64, 2>(p, n_act, smem);
+    else stream_items<LAY, EPI, 64, 1>(p, n_act, smem);
+  } else {
+    if (max_rows > 64) stream_items<LAY, EPI, 128, 4>(p, n_act, smem);
+    else if (max_rows > 32) stream_items<LAY, EPI, 128, 2>(p, n_act, smem);
+    else stream_items<LAY, EPI, 128, 1>(p, n_act, smem);
+  }
 }
 
 }  // namespace moe

@@ -265,7 +265,7 @@ __device__ __forceinline__ void build_tile_map(int E_local, const int32_t* cnt, 
   // ---- per expert (lane = expert, kPasses passes): rows before it, tall slots and pair slots before it ----
   int off[kPasses], tall_ex[kPasses], pair_ex[kPasses], single_ex[kPasses];
   int cost[kPasses];     // cost of the expert's left-over single tile, 0 = none
-  int n_rows = 0, n_tall = 0, n_pair = 0, n_left = 0, max_rows = 0;
+  int n_rows = 0, n_tall = 0, n_pair = 0, n_left = 0, max_rows = 0, n_active = 0;
 #pragma unroll
   for (int p = 0; p < kPasses; ++p) {
     off[p] = tall_ex[p] = pair_ex[p] = single_ex[p] = cost[p] = 0;
@@ -273,6 +273,7 @@ __device__ __forceinline__ void build_tile_map(int E_local, const int32_t* cnt, 
     const int e = p * kWave + lane;
     const int c = e < E_local ? cnt[e] : 0;
     max_rows = max(max_rows, c);
+    n_active += __popcll(__ballot(c > 0));
     const ExpertTiling t = expert_tiling(c, wide_max, granule, tall);
     const int nt = t.is_tall ? t.n : 0, np = t.is_tall ? 0 : (t.n >> 1), n1 = t.is_tall ? 0 : (t.n & 1);
     if (n1) cost[p] = single_cost_of_rows(tile_row_count(t, t.n - 1, c));
@@ -399,6 +400,7 @@ __device__ __forceinline__ void build_tile_map(int E_local, const int32_t* cnt, 
   if (lane == 0) {
     if (offsets) offsets[E_local] = n_rows;
     tiles.meta[kMetaMaxRows] = max_rows;
+    tiles.meta[kMetaActive] = n_active;
     tiles.meta[kMetaMTiles] = n_entries;
     tiles.meta[kMetaRows] = n_rows;
     tiles.meta[kMetaStatus] = 0;

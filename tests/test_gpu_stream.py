@@ -55,6 +55,24 @@ def _columns(n_act, N, swiglu, G):
     return cw, items[cw]
 
 
+MEDIUM = [
+    # 33..128 rows in a single round: 64 columns per item (stages of 64 and 128 rows, K = 2.5 and 1.5 stages) ...
+    ("narrow_64", 320, 192, [64, 33, 1, 0]),
+    ("narrow_128", 320, 192, [128, 97, 65, 0, 1]),
+    # ... 128 columns (20 experts with rows: 64 columns would be 440, 260 and 260 items; act_grad 220 of 64) ...
+    ("one_round_128", 832, 704, [128, 97, 65, 2, 0] * 5),
+    # ... and what takes the tiles: 260 items of 128 columns in GEMM-1, 129 rows
+    ("two_rounds", 192, 832, [65, 128] * 10),
+    ("rows_129", 192, 128, [129, 5]),
+]
+
+
+@pytest.mark.parametrize("keep_xp", [True, False])
+@pytest.mark.parametrize("case", MEDIUM, ids=[c[0] for c in MEDIUM])
+def test_single_round_above_32_rows(case, keep_xp):
+    _run(*case, keep_xp)
+
+
 @pytest.mark.parametrize("keep_xp", [True, False])
 @pytest.mark.parametrize("case", DEEP, ids=[c[0] for c in DEEP])
 def test_several_items_per_workgroup(case, keep_xp):

@@ -9,6 +9,8 @@
 // ascend in token id, so every index is a pure function of the routing result
 // (no atomics decide an order).
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 namespace moe {
@@ -70,17 +72,18 @@ __device__ __forceinline__ float row_sum_f32(float v) {
 
 constexpr int kHistBatch = 16;             // histogram rows fetched per round trip
 constexpr int kRouteTokensPerWave = 4;    // one token per 16-lane row
-constexpr int kRouteKeys = kMaxE / 16;    // experts per lane
+constexpr int kRouteKeys = kMaxE / 16;    // experts per lane, at most
 
 // Logits of the wave's four tokens as order-preserving keys: lane s of row r holds
-// experts 16s .. 16s+15 of token t_first + r (0 = absent).
-__device__ __forceinline__ void route_load(const RouteParams& p, int t_first, int lane, uint32_t (&key)[kRouteKeys]) {
+// experts KP s .. KP s + KP - 1 of token t_first + r (0 = absent).
+template <int KP>
+__device__ __forceinline__ void route_load(const RouteParams& p, int t_first, int lane, uint32_t (&key)[KP]) {
   const int t = min(t_first + (lane >> 4), p.T - 1);   // tokens past the end repeat the last one; results are not stored
   const float* row = p.logits + (size_t)t * p.E;
-  const int e0 = (lane & 15) * kRouteKeys;
-  if ((p.E & 3) == 0) {
+  const int e0 = (lane & 15) * KP;
+  if (KP >= 4 && (p.E & 3) == 0) {
 #pragma unroll
-    for (int i = 0; i < kRouteKeys; i += 4) {
+    for (int i = 0; i + 3 < KP; i += 4) {
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
       const bool in = e0 + i < p.E;
       if (in) v = *reinterpret_cast<const float4*>(row + e0 + i);
@@ -91,7 +94,7 @@ __device__ __forceinline__ void route_load(const RouteParams& p, int t_first, in
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < kRouteKeys; ++i) key[i] = e0 + i < p.E ? float_order_key(row[e0 + i]) : 0u;
+    for (int i = 0; i < KP; ++i) key[i] = e0 + i < p.E ? float_order_key(row[e0 + i]) : 0u;
   }
 }
 
@@ -102,24 +105,25 @@ __device__ __forceinline__ void route_load(const RouteParams& p, int t_first, in
 // retires the key and files (id, logit) as slot j in LDS.  Afterwards lane s < k of
 // a row picks up slot s and the row computes the softmax over the k selected logits.
 // s_idx / s_val: [4][kMaxK] words of LDS for this wave.
-__device__ __forceinline__ void route_select(const RouteParams& p, int t_first, int lane, uint32_t (&key)[kRouteKeys],
+template <int KP>
+__device__ __forceinline__ void route_select(const RouteParams& p, int t_first, int lane, uint32_t (&key)[KP],
                                              int32_t* s_idx, float* s_val) {
   const int row = lane >> 4, s = lane & 15;
   for (int j = 0; j < p.k; ++j) {
     uint32_t local = key[0];
     int li = 0;
 #pragma unroll
-    for (int i = 1; i < kRouteKeys; ++i)
+    for (int i = 1; i < KP; ++i)
       if (key[i] > local) { local = key[i]; li = i; }
     const uint32_t best = row_max_u32(local);
     const uint64_t bal = __ballot(local == best);
     const uint32_t in_row = (uint32_t)(bal >> (row * 16)) & 0xFFFFu;
     const bool winner = s == __builtin_ctz(in_row);   // in_row != 0: the row maximum is some lane's local maximum
 #pragma unroll
-    for (int i = 0; i < kRouteKeys; ++i)
+    for (int i = 0; i < KP; ++i)
       if (winner && i == li) key[i] = 0u;
     if (winner) {
-      s_idx[row * kMaxK + j] = s * kRouteKeys + li;
+      s_idx[row * kMaxK + j] = s * KP + li;
       s_val[row * kMaxK + j] = float_from_order_key(best);
     }
   }
@@ -138,6 +142,19 @@ __device__ __forceinline__ void route_select(const RouteParams& p, int t_first, 
     p.topk_idx[(size_t)t * p.k + s] = idx;
     p.topk_w[(size_t)t * p.k + s] = pj / sum;
   }
+}
+
+// f(number of experts per lane) for E experts: the least of 1, 2, 4, 8, 16 that holds them.  A round of the selection walks a
+// lane's experts, so with 16 to a lane for any E its cost was that of 256 experts
+// (16 experts, T = 65..256: a layer of H = 2048 66.8 -> 64.4 us, 80 -> 77.7; a training step of T = 777, 24 experts 114.9 -> 112.2).
+template <typename F>
+__device__ __forceinline__ void with_route_keys(int E, F&& f) {
+  static_assert(kRouteKeys == 16, "cases");
+  if (E <= 16) f(std::integral_constant<int, 1>{});
+  else if (E <= 32) f(std::integral_constant<int, 2>{});
+  else if (E <= 64) f(std::integral_constant<int, 4>{});
+  else if (E <= 128) f(std::integral_constant<int, 8>{});
+  else f(std::integral_constant<int, 16>{});
 }
 
 // Bitmask of the local experts a token selected, from its k indices.
@@ -166,16 +183,19 @@ __device__ __forceinline__ void route_chunk(const RouteParams& p, int sub, int32
   const int n_waves = blockDim.x / kWave;
   const int t0 = sub * kSub;
   const int step = n_waves * kRouteTokensPerWave;
-  uint32_t key[kRouteKeys], key_next[kRouteKeys];
-  int i = wave * kRouteTokensPerWave;
-  if (i < kSub && t0 + i < p.T) route_load(p, t0 + i, lane, key);
-  for (; i < kSub && t0 + i < p.T; i += step) {
-    const bool more = i + step < kSub && t0 + i + step < p.T;
-    if (more) route_load(p, t0 + i + step, lane, key_next);
-    route_select(p, t0 + i, lane, key, s_idx + i * kMaxK, s_val + i * kMaxK);
+  with_route_keys(p.E, [&](auto kp) __attribute__((always_inline)) {
+    constexpr int KP = decltype(kp)::value;
+    uint32_t key[KP], key_next[KP];
+    int i = wave * kRouteTokensPerWave;
+    if (i < kSub && t0 + i < p.T) route_load<KP>(p, t0 + i, lane, key);
+    for (; i < kSub && t0 + i < p.T; i += step) {
+      const bool more = i + step < kSub && t0 + i + step < p.T;
+      if (more) route_load<KP>(p, t0 + i + step, lane, key_next);
+      route_select<KP>(p, t0 + i, lane, key, s_idx + i * kMaxK, s_val + i * kMaxK);
 #pragma unroll
-    for (int q = 0; q < kRouteKeys; ++q) key[q] = key_next[q];
-  }
+      for (int q = 0; q < KP; ++q) key[q] = key_next[q];
+    }
+  });
   __syncthreads();
   if (wave == 0) {
     uint64_t mask[kMaskWords];

@@ -365,20 +365,26 @@ SchedParams<BF16> sched_params(const Ctx& c, const void* x, const float* logits,
   return sp;
 }
 
-// Routing, two launches: the router (top-k, softmax, per-chunk histograms), then prefix sums + M-tile map +
-// stable ranks.  The second launch also zeroes the tile scheduler's counters and writes its task tables (one
+// Routing, one launch for up to 64 tokens, otherwise two: the router (top-k, softmax, per-chunk histograms), then prefix sums +
+// M-tile map + stable ranks.  The second launch also zeroes the tile scheduler's counters and writes its task tables (one
 // workgroup, beside the rank groups), so that either launch mode can follow.
 template <bool BF16>
 int run_route_t(const Ctx& c, const float* logits, bool tables, void* zero_out) {
   SchedParams<BF16> sp = sched_params<BF16>(c, nullptr, logits, nullptr, nullptr, nullptr);
   sp.skip_tables = tables ? 0 : 1;
   const RouteParams& rp = sp.route;
+  const bool one = c.s.T <= kRouteOneT;   // one workgroup does it all in one launch (see route_one)
+  const int fill_threads = one ? kRouteOneThreads : kScanRankWaves * kWave;
   int fill_wgs = 0;
   if (zero_out) {
     sp.zero_dst = static_cast<uint4*>(zero_out);
     sp.zero_n16 = (size_t)c.s.T * c.s.H * elem_bytes(c.s) / 16;
-    const size_t want = (sp.zero_n16 + kScanRankWaves * kWave - 1) / (kScanRankWaves * kWave);
+    const size_t want = (sp.zero_n16 + fill_threads - 1) / fill_threads;
     fill_wgs = (int)(want < (size_t)c.n_cu * 4 ? want : (size_t)c.n_cu * 4);
+  }
+  if (one) {
+    hipLaunchKernelGGL(route_one_kernel<BF16>, dim3(1 + fill_wgs), dim3(kRouteOneThreads), 0, c.stream, sp);
+    return launch_status();
   }
   hipLaunchKernelGGL(route_kernel, dim3(rp.n_sub), dim3(512), 0, c.stream, rp);
   hipLaunchKernelGGL(sched_prepare_kernel<BF16>, dim3(1 + (rp.n_groups + kScanRankWaves - 1) / kScanRankWaves + fill_wgs),

@@ -360,6 +360,22 @@ __global__ __launch_bounds__(kScanRankWaves * kWave) void sched_prepare_kernel(S
   if (group < sp.route.n_groups) rank_chunk(sp.route, group, s_lds + wave * kRankLdsWords);
 }
 
+// Both routing launches as one, for few tokens (route_one): workgroup 0 routes, further ones only fill.
+template <bool BF16>
+__global__ __launch_bounds__(kRouteOneThreads) void route_one_kernel(SchedParams<BF16> sp) {
+  if (blockIdx.x > 0) {
+    const size_t stride = (size_t)(gridDim.x - 1) * blockDim.x;
+    for (size_t i = (size_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x; i < sp.zero_n16; i += stride)
+      sp.zero_dst[i] = make_uint4(0, 0, 0, 0);
+    return;
+  }
+  route_one(sp.route);
+  if (sp.skip_tables) return;
+  __threadfence_block();
+  __syncthreads();   // tile map (written by wave 0) complete before every wave reads it
+  build_task_tables<BF16>(sp);
+}
+
 // Vector tasks of a 4-wave worker: 16-byte vectors per lane and pass matched to the row length (a row of H = 7168
 // bf16 is 14 per lane, of H = 2048 four): a pass wider than the row spends its instructions on vectors that do not
 // exist (COMBINE) or falls through to a one-vector-at-a-time tail (PERMUTE).

@@ -555,6 +555,69 @@ __global__ __launch_bounds__(512) void route_kernel(RouteParams p) {
   route_chunk(p, blockIdx.x, s_idx, s_val);
 }
 
+// The whole routing of up to 64 tokens by ONE workgroup of 16 waves, nothing but results in memory: a wave routes four tokens,
+// the tokens that selected an expert stand as one 64-bit mask per expert in LDS, and the masks give counts (wave 0 builds the
+// tile map from them) and, beside that, offsets and stable ranks (wave 1, lane = token).
+// Two launches of 5..9 us with one to two workgroups each became one; measured with both, a layer of T tokens: H = 2048, 16
+// experts, T = 1 38.9 -> 36.1 us, T = 64 66.7 -> 65.4; H = 256, I = 128, 256 experts, T = 32 28.2 -> 23.4, T = 64 29.2 -> 26.8.  The
+// line is one pass of the 16 waves: with a second one T = 128 lost 3..5 us (72 -> 75, 29.8 -> 34.4), T = 256 10..18.
+constexpr int kRouteOneT = kWave, kRouteOneThreads = kRouteOneT / kRouteTokensPerWave * kWave;
+__device__ __forceinline__ void route_one(const RouteParams& p) {
+  __shared__ int32_t s_idx[kRouteOneT * kMaxK];
+  __shared__ float s_val[kRouteOneT * kMaxK];
+  __shared__ unsigned long long s_mask[kMaxE];
+  __shared__ int32_t s_first[kMaxE], s_cnt[kMaxE];
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  for (int e = threadIdx.x; e < p.E_local; e += blockDim.x) s_mask[e] = 0ull;
+  const int t0 = wave * kRouteTokensPerWave;
+  if (t0 < p.T)
+    with_route_keys(p.E, [&](auto kp) __attribute__((always_inline)) {
+      uint32_t key[decltype(kp)::value];
+      route_load(p, t0, lane, key);
+      route_select(p, t0, lane, key, s_idx + t0 * kMaxK, s_val + t0 * kMaxK);
+    });
+  __syncthreads();
+  // the local expert of slot j of token `lane`, or -1
+  auto local_of = [&](int j) __attribute__((always_inline)) {
+    const int l = lane < p.T ? s_idx[lane * kMaxK + j] - p.expert_base : -1;
+    return l < p.E_local ? l : -1;
+  };
+  for (int j = wave; j < p.k; j += kRouteOneThreads / kWave) {
+    const int l = local_of(j);
+    if (l >= 0) atomicOr(&s_mask[l], 1ull << lane);
+  }
+  __syncthreads();
+  if (wave == 0) {
+    for (int e = lane; e < p.E_local; e += kWave) s_cnt[e] = __popcll(s_mask[e]);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    build_tile_map(p.E_local, s_cnt, p.wide_max, p.granule, p.tall, p.counts, p.offsets, p.tiles);
+  } else if (wave == 1) {
+    int run = 0;   // rows of the experts before this block of 64
+    for (int e0 = 0; e0 < p.E_local; e0 += kWave) {
+      const int c = e0 + lane < p.E_local ? __popcll(s_mask[e0 + lane]) : 0;
+      const int incl = wave_incl_scan(c, lane);
+      if (e0 + lane < p.E_local) s_first[e0 + lane] = run + incl - c;
+      run += __shfl(incl, kWave - 1, kWave);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int j = 0; j < p.k; ++j) {
+      const int l = local_of(j);
+      int r = -1;
+      if (l >= 0) {
+        r = s_first[l] + __popcll(s_mask[l] & ((1ull << lane) - 1ull));
+        p.token_of[r] = lane;
+        p.slot_of[r] = j;
+      }
+      if (lane < p.T) p.row_of[(size_t)lane * p.k + j] = r;
+    }
+  }
+}
+
 // The two steps that need nothing but the finished histogram table run side by side in one launch
 // (sched_prepare_kernel): workgroup 0 sums the table into counts, offsets and the M-tile map; every other
 // workgroup ranks 4 groups of 64 tokens, one per wave.  Grid: 1 + ceil(n_groups / 4) workgroups of 256 threads.

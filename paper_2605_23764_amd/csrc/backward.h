@@ -193,13 +193,21 @@ __global__ __launch_bounds__(256) void grouped_dgrad_f32_kernel(GemmBwdParamsF32
   f32_sweeps(p.tiles.meta[kMetaMTiles] * p.n_ntiles, p.K, whole, quarter);
 }
 
-// w2_grad and w1_grad: C_e[M, N] = A_e[rows_e, M]^T * B_e[rows_e, N]; zeros for experts without rows.
-__global__ __launch_bounds__(256) void grouped_wgrad_f32_kernel(GemmBwdParamsF32 p) {
+// w2_grad and w1_grad: C_e[M, N] = A_e[rows_e, M]^T * B_e[rows_e, N]; zeros for experts without rows.  A launch does one or
+// both (NG), the second one's tiles behind the first one's: one partly filled last sweep instead of two (T = 256, H = 256,
+// I = 128, 8 experts: training step 56.3 -> 52 us; T = 1500, H = 512, I = 448, 10 experts: backward 126 -> 116).
+template <int NG>
+struct WgradGroupF32 { GemmBwdParamsF32 p[NG]; };
+template <int NG>
+__global__ __launch_bounds__(256) void grouped_wgrad_f32_kernel(WgradGroupF32<NG> w) {
   __shared__ __attribute__((aligned(16))) float smem[kFLdsFloats1];
-  const int per_e = p.n_mtiles * p.n_ntiles;
+  const int per0 = w.p[0].n_mtiles * w.p[0].n_ntiles, total0 = w.p[0].E_local * per0;
+  const int per1 = w.p[NG - 1].n_mtiles * w.p[NG - 1].n_ntiles, total1 = NG > 1 ? w.p[NG - 1].E_local * per1 : 0;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
-  auto whole = [&](int tile) __attribute__((always_inline)) {
+  auto whole = [&](int t) __attribute__((always_inline)) {
+    const int i = NG > 1 ? __builtin_amdgcn_readfirstlane(t >= total0 ? 1 : 0) : 0, tile = i ? t - total0 : t, per_e = i ? per1 : per0;
+    const GemmBwdParamsF32& p = w.p[i];
     const int e = tile / per_e, rem = tile % per_e;
     const int m0 = (rem / p.n_ntiles) * kFBM, n0 = (rem % p.n_ntiles) * kFBN;
     const int seg0 = p.offsets[e], cnt = p.offsets[e + 1] - seg0;
@@ -213,7 +221,9 @@ __global__ __launch_bounds__(256) void grouped_wgrad_f32_kernel(GemmBwdParamsF32
 #pragma unroll
     for (int r = 0; r < 16; ++r) c_base[(size_t)f32_acc_row(r, lane) * p.ldc] = acc[0][r];
   };
-  auto quarter = [&](int tile, int qm, int qn) __attribute__((always_inline)) {
+  auto quarter = [&](int t, int qm, int qn) __attribute__((always_inline)) {
+    const int i = NG > 1 ? __builtin_amdgcn_readfirstlane(t >= total0 ? 1 : 0) : 0, tile = i ? t - total0 : t, per_e = i ? per1 : per0;
+    const GemmBwdParamsF32& p = w.p[i];
     const int e = tile / per_e, rem = tile % per_e;
     const int m0 = (rem / p.n_ntiles) * kFBM + qm * 32, n0 = (rem % p.n_ntiles) * kFBN + qn * 32;
     const int seg0 = p.offsets[e], cnt = p.offsets[e + 1] - seg0;
@@ -225,7 +235,7 @@ __global__ __launch_bounds__(256) void grouped_wgrad_f32_kernel(GemmBwdParamsF32
 #pragma unroll
     for (int r = 0; r < 4; ++r) c_base[(size_t)r * p.ldc] = acc[0][r];
   };
-  f32_sweeps(p.E_local * per_e, p.offsets[p.E_local] / p.E_local, whole, quarter);
+  f32_sweeps(total0 + total1, w.p[0].offsets[w.p[0].E_local] / w.p[0].E_local, whole, quarter);
 }
 
 }  // namespace moe

@@ -466,13 +466,15 @@ struct BwdCtx {
   int mode;          // MOE_MODE_PERSISTENT: act_grad and gate_grad as one launch under the tile scheduler
 };
 
-// Weight gradient of one GEMM: experts with up to 384 rows go to the register-stationary kernel when
-// the output splits into full 256 x 128 tiles, everything else to the general kernel.
+// Weight gradients (bf16): experts with up to 384 rows go to the register-stationary kernel when the output splits into full
+// 256 x 128 tiles, everything else to the general kernel: on one stream both gradients' in one launch behind dH1.  The
+// register-stationary launches stay where their operands are fresh (w2_grad's behind the backward Dispatch): moved together
+// they cost the training step at T = 8192, H = 7168, I = 2048 1 %.
 bool wgrad_panel_fits(int M, int N) { return M % kWpM == 0 && N % kWpN == 0; }
 
-// p.gather != nullptr: the register-stationary kernel reads the rows of p.A through it; the general kernel
-// reads `a_general`, in which the caller has placed the rows of the experts that kernel takes.
-void launch_wgrad_bf16(GemmParams p, int grid, int n_cu, hipStream_t stream, const __bf16* a_general = nullptr) {
+// First the register-stationary kernel, if it fits; p is then what the general kernel gets.  p.gather != nullptr: the first
+// reads the rows of A through it, the second a_general, in which the caller has placed the rows of the experts it takes.
+void launch_wgrad_panel(GemmParams& p, int grid, int n_cu, hipStream_t stream, const __bf16* a_general) {
   p.k_lo = 0;
   if (wgrad_panel_fits(p.M, p.N)) {
     // the kernel splits every expert's tile row into column ranges so that each CU gets about four items
@@ -480,7 +482,17 @@ void launch_wgrad_bf16(GemmParams p, int grid, int n_cu, hipStream_t stream, con
     p.k_lo = kWpMaxRows + 1;
   }
   if (p.gather) { p.A = a_general; p.gather = nullptr; }
-  hipLaunchKernelGGL(grouped_wgrad2_bf16_kernel, dim3(2 * grid), dim3(kGemmThreads), 0, stream, p);
+}
+void launch_wgrad_panel(GemmBwdParamsF32&, int, int, hipStream_t, const float*) {}
+
+// One weight gradient, or (q) two as one launch.
+void launch_wgrad_general(const GemmParams& p, const GemmParams* q, int grid, hipStream_t stream) {
+  if (q) hipLaunchKernelGGL(grouped_wgrad2_bf16_kernel<2>, dim3(2 * grid), dim3(kGemmThreads), 0, stream, WgradGroup<2>{{p, *q}});
+  else hipLaunchKernelGGL(grouped_wgrad2_bf16_kernel<1>, dim3(2 * grid), dim3(kGemmThreads), 0, stream, WgradGroup<1>{{p}});
+}
+void launch_wgrad_general(const GemmBwdParamsF32& p, const GemmBwdParamsF32* q, int grid, hipStream_t stream) {
+  if (q) hipLaunchKernelGGL(grouped_wgrad_f32_kernel<2>, dim3(grid), dim3(256), 0, stream, WgradGroupF32<2>{{p, *q}});
+  else hipLaunchKernelGGL(grouped_wgrad_f32_kernel<1>, dim3(grid), dim3(256), 0, stream, WgradGroupF32<1>{{p}});
 }
 
 template <typename T>
@@ -545,17 +557,20 @@ int run_backward(const BwdCtx& c, const void* dy, const void* x, const void* w_g
   pg.tiles = c.tiles;
   pg.offsets = c.sv.offsets; pg.E_local = s.E_local;
 
-  // w2_grad: dW_down[e] = A_e^T dYp_e (needs only dYp: runs first, while dYp is fresh in the caches)
+  // w2_grad: dW_down[e] = A_e^T dYp_e (needs only dYp: the register-stationary kernel runs first, while dYp is fresh in the
+  // caches; on one stream the general kernel waits for w1_grad's part)
+  P p2{};
+  p2.A = static_cast<const T*>(c.sv.A); p2.B = dYp; p2.C = static_cast<T*>(dw_down);
+  p2.strideC = (long)s.I * s.H; p2.M = s.I; p2.N = s.H;
+  p2.lda = s.I; p2.ldb = s.H; p2.ldc = s.H;
+  p2.n_ntiles = ceil_div(s.H, tn);
+  if constexpr (!BF16) p2.n_mtiles = ceil_div(s.I, bm);
+  p2.E_local = s.E_local; p2.offsets = c.sv.offsets;
+  if constexpr (BF16) p2.tickets = tickets;
+  p2.tiles = c.tiles;
   auto launch_w2 = [&](hipStream_t st) {
-    P p{};
-    p.A = static_cast<const T*>(c.sv.A); p.B = dYp; p.C = static_cast<T*>(dw_down);
-    p.strideC = (long)s.I * s.H; p.M = s.I; p.N = s.H;
-    p.lda = s.I; p.ldb = s.H; p.ldc = s.H;
-    p.n_ntiles = ceil_div(s.H, tn);
-    if constexpr (!BF16) p.n_mtiles = ceil_div(s.I, bm);
-    p.E_local = s.E_local; p.offsets = c.sv.offsets;
-    if constexpr (BF16) { p.tickets = tickets; p.tiles = c.tiles; launch_wgrad_bf16(p, grid, c.n_cu, st); }
-    else hipLaunchKernelGGL(grouped_wgrad_f32_kernel, dim3(grid), dim3(256), 0, st, p);
+    launch_wgrad_panel(p2, grid, c.n_cu, st, xp_ws);
+    if (side) launch_wgrad_general(p2, nullptr, grid, st);   // one stream: together with w1_grad
   };
   if (!side) launch_w2(c.stream);
   // called right behind the launch that completes dH1: w2_grad goes to the other stream, w1_grad may follow there
@@ -623,8 +638,10 @@ int run_backward(const BwdCtx& c, const void* dy, const void* x, const void* w_g
         p.A = xp_ws;
       }
     }
-    if constexpr (BF16) { p.tickets = tickets + kNumXcd; p.tiles = c.tiles; launch_wgrad_bf16(p, grid, c.n_cu, sw, xp_ws); }
-    else hipLaunchKernelGGL(grouped_wgrad_f32_kernel, dim3(grid), dim3(256), 0, sw, p);
+    if constexpr (BF16) p.tickets = tickets + kNumXcd;
+    p.tiles = c.tiles;
+    launch_wgrad_panel(p, grid, c.n_cu, sw, xp_ws);
+    launch_wgrad_general(side ? p : p2, side ? nullptr : &p, grid, sw);
   }
   // backward Combine: dX[t] = sum over local slots of dXp[row_of[t,j]]
   {

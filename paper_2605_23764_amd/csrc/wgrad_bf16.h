@@ -238,20 +238,21 @@ __device__ __forceinline__ void wgrad_tile_of(int r, int n_mt, int n_nt, int& mt
 // G consecutive tiles over the G workgroups is then balanced by construction (all tiles of a sweep belong to
 // one expert or to two of neighbouring size), and the last, partly filled sweep holds the cheapest tiles.  An
 // XCD takes a contiguous eighth of every sweep, so the CUs that share operand panels sit behind one L2.
-__global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void grouped_wgrad2_bf16_kernel(GemmParams p) {
-  __shared__ __attribute__((aligned(1024))) char smem[kWgLdsBytes];
-  __shared__ int s_rows[kMaxE];      // rows of expert e if this kernel takes it, else -1
-  __shared__ int s_order[kMaxE];     // the experts it takes, most rows first
-  __shared__ int s_box[1];           // number of such experts
-  const int n_mt = (p.M + kWgBM - 1) / kWgBM, n_nt = (p.N + kWgBN - 1) / kWgBN;
-  const int per_e = n_mt * n_nt;
-  // nothing to do when the other kernel takes every expert (p.tiles.meta: the M-tile map's header, or nullptr)
-  if (p.k_lo > 0 && p.tiles.meta && __builtin_amdgcn_readfirstlane(p.tiles.meta[kMetaMaxRows]) < p.k_lo) return;
+//
+// A launch does one or two (NG) weight gradients, the second one's tiles behind the first one's: both on one stream as one
+// launch have one partly filled last sweep (T = 777, H = 1088, I = 704, 10 experts: 300 and 540 tiles on 512 workgroups, training
+// step 112.3 -> 106.2 us; T = 4096, H = 2048, I = 1408, 16 experts, backward 728 -> 720).  One is a kernel of its own: with the
+// second behind a switch it was up to 1.4 % slower.
+template <int NG>
+struct WgradGroup { GemmParams p[NG]; };
+
+// Experts of p that this kernel takes, most rows first, into s_order; returns how many.  Whole workgroup; s_rows: kMaxE words.
+__device__ __forceinline__ int wgrad_order_experts(const GemmParams& p, int* s_rows, int* s_order, int* s_box) {
   for (int e = threadIdx.x; e < p.E_local; e += kGemmThreads) {
     const int cnt = p.offsets[e + 1] - p.offsets[e];
     s_rows[e] = cnt >= p.k_lo ? cnt : -1;
   }
+  if (threadIdx.x == 0) s_box[0] = 0;
   __syncthreads();
   int n_mine = 0;
   for (int e = threadIdx.x; e < p.E_local; e += kGemmThreads) {
@@ -264,20 +265,41 @@ void grouped_wgrad2_bf16_kernel(GemmParams p) {
     if (cnt >= 0) s_order[rank] = e;
     n_mine += cnt >= 0;
   }
-  if (threadIdx.x == 0) s_box[0] = 0;
-  __syncthreads();
   if (n_mine) atomicAdd(&s_box[0], n_mine);
   __syncthreads();
-  const int total = s_box[0] * per_e;
+  return __builtin_amdgcn_readfirstlane(s_box[0]);
+}
+
+template <int NG>
+__global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void grouped_wgrad2_bf16_kernel(WgradGroup<NG> w) {
+  __shared__ __attribute__((aligned(1024))) char smem[kWgLdsBytes];
+  __shared__ int s_order[NG][kMaxE]; // the experts it takes, most rows first
+  __shared__ int s_box[NG];          // number of such experts
+  int n_mt[NG], n_nt[NG], total[NG], all = 0;
+#pragma unroll
+  for (int i = 0; i < NG; ++i) {
+    const GemmParams& p = w.p[i];
+    n_mt[i] = (p.M + kWgBM - 1) / kWgBM;
+    n_nt[i] = (p.N + kWgBN - 1) / kWgBN;
+    total[i] = 0;
+    // nothing to do when the other kernel takes every expert (p.tiles.meta: the M-tile map's header)
+    if (!(p.k_lo > 0 && __builtin_amdgcn_readfirstlane(p.tiles.meta[kMetaMaxRows]) < p.k_lo))
+      total[i] = wgrad_order_experts(p, reinterpret_cast<int*>(smem), s_order[i], &s_box[i]) * n_mt[i] * n_nt[i];
+    all += total[i];
+  }
+  __syncthreads();                   // the stages are not in use as tables any more
   const int G = gridDim.x;
-  for (int it = 0; it * G < total; ++it) {
-    const int tile = xcd_spread_tile(it, blockIdx.x, G, total);
-    if (tile < 0) continue;
-    const int r = tile / per_e;
-    const int e = __builtin_amdgcn_readfirstlane(s_order[r]);
+  for (int it = 0; it * G < all; ++it) {
+    const int t = xcd_spread_tile(it, blockIdx.x, G, all);
+    if (t < 0) continue;
+    const int i = NG > 1 ? __builtin_amdgcn_readfirstlane(t >= total[0] ? 1 : 0) : 0;
+    const int tile = i ? t - total[0] : t, nm = i ? n_mt[NG - 1] : n_mt[0], nn = i ? n_nt[NG - 1] : n_nt[0];
+    const int r = tile / (nm * nn);
+    const int e = __builtin_amdgcn_readfirstlane(s_order[i][r]);
     int mt, nt;
-    wgrad_tile_of(tile - r * per_e, n_mt, n_nt, mt, nt);
-    wgrad_tile_bf16(p, e, __builtin_amdgcn_readfirstlane(mt), __builtin_amdgcn_readfirstlane(nt), smem);
+    wgrad_tile_of(tile - r * nm * nn, nm, nn, mt, nt);
+    wgrad_tile_bf16(w.p[i], e, __builtin_amdgcn_readfirstlane(mt), __builtin_amdgcn_readfirstlane(nt), smem);
   }
 }
 

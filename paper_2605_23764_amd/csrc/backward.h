@@ -190,7 +190,7 @@ __global__ __launch_bounds__(256) void grouped_dgrad_f32_kernel(GemmBwdParamsF32
       if (m < rows) store_dgrad_f32<EPI>(p, (size_t)(row0 + m), c, acc[0][r]);
     }
   };
-  f32_sweeps(p.tiles.meta[kMetaMTiles] * p.n_ntiles, p.K, whole, quarter);
+  f32_sweeps(p.tiles.meta[kMetaMTiles] * p.n_ntiles, p.K, p.tiles.meta[kMetaMaxRows] <= 32, whole, quarter);
 }
 
 // w2_grad and w1_grad: C_e[M, N] = A_e[rows_e, M]^T * B_e[rows_e, N]; zeros for experts without rows.  A launch does one or
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(256) void grouped_wgrad_f32_kernel(WgradGroupF32<NG
 #pragma unroll
     for (int r = 0; r < 4; ++r) c_base[(size_t)r * p.ldc] = acc[0][r];
   };
-  f32_sweeps(total0 + total1, w.p[0].offsets[w.p[0].E_local] / w.p[0].E_local, whole, quarter);
+  f32_sweeps(total0 + total1, w.p[0].offsets[w.p[0].E_local] / w.p[0].E_local, false, whole, quarter);
 }
 
 }  // namespace moe

@@ -41,6 +41,11 @@ static_assert(kFQStage <= kFStage, "a quarter's stages fit where a tile's do");
 constexpr int kFLdsFloats1 = 2 * 2 * kFStage;     // two stages of two operands (20 KB)
 constexpr int kFLdsFloats2 = 2 * 3 * kFStage;     // two weight column blocks (30 KB)
 
+constexpr int kFSLd = 64 + 4;                     // a strip's weight stage: floats per k
+// LDS of a serialized launch: two stages of tiles or of strips (22 KB; two weight column blocks 39 KB, four workgroups a CU)
+constexpr int f32_lds_floats(int nb) { return 2 * (16 * kFQLd + nb * kFQK * kFSLd); }
+static_assert(f32_lds_floats(1) >= kFLdsFloats1 && f32_lds_floats(2) >= kFLdsFloats2 && 4 * 4 * f32_lds_floats(2) <= 160 * 1024, "LDS budget");
+
 struct GemmParamsF32 {
   const float* A;   // [rows, lda]
   const float* B;   // per expert [K, ldb]
@@ -250,23 +255,98 @@ __device__ __forceinline__ void gemm_core_f32_quarter(f32x4 (&acc)[NB], const fl
   }
 }
 
+// A strip, 16 rows x 64 columns, for launches whose experts have at most 16 rows each: wave w owns columns 16 w .. + 15 (GEMM-1:
+// of the gate and of the up block) and nothing is multiplied for rows that are not there, K step 32.  Such a launch reads
+// weights: 256-byte pieces, two steps of 8 KB (GEMM-1: 16) under way per workgroup.  Forward layout only; the same chain of
+// sums as the other tiles.  Against quarters (whose second 16 rows do not exist here, and which read 128-byte pieces): forward of
+// T = 20, H = 2048, I = 1408, 16 of 64 experts 145 -> 95 us (554 MB of weights where all have rows, 78 us at 7.1 TB/s), T = 100 180 -> 118;
+// T = 30, H = 1024, I = 704, 16 experts 61.6 -> 42; T = 8, 64 experts 115 -> 75.  With two quarters per tile up to 32 rows: T = 64
+// 62.6 -> 52.7, a training step of T = 64, H = 512, I = 448, 10 of 16 experts 75 -> 63.5.
+template <int NB>
+__device__ __forceinline__ void gemm_core_f32_strip(f32x4 (&acc)[NB], const float* a_ptr, const float* b_ptr, long b_k, long b_half,
+                                                    int K, float* smem) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lg = lane >> 4;
+  const int n_steps = K / kFQK;                        // even: K is a multiple of 64
+  const lds_f32_ptr lds = (lds_f32_ptr)smem;
+  constexpr int kAStage = 16 * kFQLd, kBStage = kFQK * kFSLd, kStages = kAStage + NB * kBStage;
+  static_assert(2 * kStages <= f32_lds_floats(NB), "LDS budget");
+  const bool has_a = wave < 2;                         // 128 threads fetch the 16 rows
+  const int a_st = (tid >> 3) * kFQLd + (tid & 1) * 8 + ((tid & 7) >> 1) * 2;
+  const int b_st = kAStage + (tid >> 4) * kFSLd + (tid & 15) * 4;
+  const int k0 = (lg & 1) * 4 + (lg >> 1);
+  const int a_rd = l16 * kFQLd + lg * 8, b_rd = kAStage + k0 * kFSLd + wave * 16 + l16;
+  struct Regs { f32x4 a, b[NB][2]; } r[2];             // two steps under way (four: no faster, and too many registers)
+  auto load = [&](Regs& q, int s) __attribute__((always_inline)) {
+    const long k = (long)min(s, n_steps - 1) * kFQK;
+    q.a = *reinterpret_cast<const f32x4*>(a_ptr + k);
+#pragma unroll
+    for (int h = 0; h < NB; ++h)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        q.b[h][i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(b_ptr + (k + 16 * i) * b_k + h * b_half));
+  };
+  auto stage = [&](const Regs& q, int buf) __attribute__((always_inline)) {
+    const lds_f32_ptr st = lds + buf * kStages;
+    if (has_a) {
+      *(lds_f32x2_ptr)(st + a_st) = f32x2{q.a[0], q.a[2]};
+      *(lds_f32x2_ptr)(st + a_st + 16) = f32x2{q.a[1], q.a[3]};
+    }
+#pragma unroll
+    for (int h = 0; h < NB; ++h)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) *(lds_f32x4_ptr)(st + b_st + h * kBStage + i * 16 * kFSLd) = q.b[h][i];
+  };
+  auto step = [&](Regs& q, int s, int buf) __attribute__((always_inline)) {
+    const lds_f32_ptr st = lds + buf * kStages;
+    f32x4 a[2];
+    float b[NB][8];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) a[i] = *(lds_f32x4_ptr)(st + a_rd + i * 4);
+#pragma unroll
+    for (int h = 0; h < NB; ++h)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) b[h][i] = st[b_rd + h * kBStage + ((i >> 1) * 8 + (i & 1) * 2) * kFSLd];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int h = 0; h < NB; ++h) acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i >> 2][i & 3], b[h][i], acc[h], 0, 0, 0);
+    stage(q, buf ^ 1);
+    load(q, s + 3);
+    __syncthreads();                                   // at the last step also: LDS free for the next tile
+  };
+  if (n_steps <= 0) return;
+  load(r[0], 0);
+  load(r[1], 1);
+  stage(r[0], 0);
+  load(r[0], 2);
+  __syncthreads();
+  for (int s = 0; s < n_steps; s += 2) {
+    step(r[1], s, 0);
+    step(r[0], s + 1, 1);
+  }
+}
+
 // Tiles of a launch of G workgroups, four to a CU: whole tiles in full sweeps, the rest as quarters where that shortens the
-// launch.  The fullest CU decides: ceil(4 rem / G) whole tiles or ceil(16 rem / G) quarters.  A quarter fetches twice the
+// launch.  The fullest CU decides: ceil(4 rem / G) whole tiles or ceil(16 rem / G) quarters (half_rows: no tile has more than 32
+// rows, two quarters each).  A quarter fetches twice the
 // operand bytes per product, an eighth on its time; kFQFixed: a weight gradient over 60 rows per expert (560 tiles) is faster
 // whole (a step of T = 300 91.9 us against 93.1), GEMMs of K = 1024 are not (forward of T = 600, 528 tiles: 161 -> 147).
 template <typename Whole, typename Quarter>
-__device__ __forceinline__ void f32_sweeps(int total, int K, Whole&& whole, Quarter&& quarter) {
-  const int G = gridDim.x, rem = total % G;
-  const bool split = (16 * rem + G - 1) / G * (9 * K + 8 * kFQFixed) < (4 * rem + G - 1) / G * (32 * K + 8 * kFQFixed);
+__device__ __forceinline__ void f32_sweeps(int total, int K, bool half_rows, Whole&& whole, Quarter&& quarter) {
+  const int G = gridDim.x, rem = total % G, nq = half_rows ? 2 : 4;
+  const bool split = (4 * nq * rem + G - 1) / G * (9 * K + 8 * kFQFixed) < (4 * rem + G - 1) / G * (32 * K + 8 * kFQFixed);
   const int n_whole = split ? total - rem : total;
   for (int it = 0; it * G < n_whole; ++it) {
     const int tile = xcd_spread_tile(it, blockIdx.x, G, n_whole);
     if (tile >= 0) whole(tile);
   }
   if (!split) return;
-  for (int it = 0; it * G < 4 * rem; ++it) {
-    const int i = xcd_spread_tile(it, blockIdx.x, G, 4 * rem);
-    if (i >= 0) quarter(n_whole + (i >> 2), (i >> 1) & 1, i & 1);
+  for (int it = 0; it * G < nq * rem; ++it) {
+    const int i = xcd_spread_tile(it, blockIdx.x, G, nq * rem);
+    if (i >= 0) quarter(n_whole + (half_rows ? i >> 1 : i >> 2), half_rows ? 0 : (i >> 1) & 1, i & 1);
   }
 }
 
@@ -340,10 +420,44 @@ __device__ __forceinline__ void gemm_quarter_f32(const GemmParamsF32& p, int mti
   }
 }
 
+// The same tile of an expert with at most 16 rows.
 template <int EPI>
-__global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(GemmParamsF32 p) {
-  __shared__ __attribute__((aligned(16))) float smem[EPI == kEpiSwiglu ? kFLdsFloats2 : kFLdsFloats1];
-  f32_sweeps(p.tiles.meta[kMetaMTiles] * p.n_ntiles, p.K,
+__device__ __forceinline__ void gemm_strip_f32(const GemmParamsF32& p, int mtile, int ntile, float* smem) {
+  constexpr int NB = (EPI == kEpiSwiglu) ? 2 : 1;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int e = p.tiles.expert[mtile], row0 = p.tiles.row0[mtile], rows = p.tiles.rows[mtile];
+  if (rows <= 0) return;
+  const int n0 = ntile * kFBN;
+  f32x4 acc[NB];
+#pragma unroll
+  for (int h = 0; h < NB; ++h)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[h][r] = 0.f;
+  gemm_core_f32_strip<NB>(acc, p.A + (size_t)(row0 + min((tid >> 3) & 15, rows - 1)) * p.lda + (tid & 7) * 4,
+                          p.B + (size_t)e * p.strideB + (size_t)(tid >> 4) * p.ldb + n0 + (tid & 15) * 4, p.ldb, p.N, p.K, smem);
+  const int c = n0 + (tid >> 6) * 16 + (lane & 15);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int m = 4 * (lane >> 4) + r;
+    if (m < rows) store_f32<EPI>(p, (size_t)(row0 + m), c, acc[0][r], acc[NB - 1][r]);
+  }
+}
+
+template <int EPI>
+__global__ __launch_bounds__(256, EPI == kEpiSwiglu ? 4 : 1) void grouped_gemm_f32_kernel(GemmParamsF32 p) {
+  __shared__ __attribute__((aligned(16))) float smem[f32_lds_floats(EPI == kEpiSwiglu ? 2 : 1)];
+  const int total = p.tiles.meta[kMetaMTiles] * p.n_ntiles;
+  const int max_rows = p.tiles.meta[kMetaMaxRows], G = gridDim.x;
+  // strips where two quarters per tile would not find a CU each (T = 4, H = 2048, I = 1408, about four experts with rows: 51 us a
+  // layer with quarters, 59 with strips; T = 20, 12 experts: 145 and 95)
+  if (max_rows <= 16 && 8 * total > G) {
+    for (int it = 0; it * G < total; ++it) {
+      const int t = xcd_spread_tile(it, blockIdx.x, G, total);
+      if (t >= 0) gemm_strip_f32<EPI>(p, t / p.n_ntiles, t % p.n_ntiles, smem);
+    }
+    return;
+  }
+  f32_sweeps(total, p.K, max_rows <= 32,
              [&](int t) __attribute__((always_inline)) { gemm_tile_f32<EPI>(p, t / p.n_ntiles, t % p.n_ntiles, smem); },
              [&](int t, int qm, int qn) __attribute__((always_inline)) {
                gemm_quarter_f32<EPI>(p, t / p.n_ntiles, t % p.n_ntiles, qm, qn, smem);

@@ -23,7 +23,7 @@
 // non-temporal hint; 128 bytes 5.1), 1 KB pieces 6.3..6.7, one linear stream 7.1; with the MFMAs taken out the launch is no
 // faster, without the activation loads 2 %.
 // Measured, layer (routing and Combine included), against the tiles of gemm_bf16.h: H = 7168, I = 2048, 32 of 256 experts,
-// k = 8: T = 4 168 -> 101 us, T = 32 428 -> 354, T = 256 524 -> 461, T = 1000 548 -> 505; H = 2048, I = 1408, 16 experts,
+// k = 8: T = 4 168 -> 101 us, T = 32 428 -> 354 (now 328, see the rule), T = 256 524 -> 461, T = 1000 548 -> 505; H = 2048, I = 1408, 16 experts,
 // k = 4: T = 1 60 -> 38.5, T = 8 74 -> 62, T = 64 76 -> 67.  Above 64 rows the activations' share of a stage grows past a
 // third and the other kernel's 256 rows per weight fetch win, unless its tiles leave CUs idle.
 #pragma once
@@ -66,15 +66,16 @@ __device__ __forceinline__ void stream_wait(int stages) {
   }
 }
 
+// Items id0 .. id1 - 1 (expert by expert among those with rows, then by columns).
 template <int LAY, int EPI, int CW, int AL>
-__device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, char* smem) {
+__device__ __forceinline__ void stream_items(const GemmParams& p, int id0, int id1, char* smem) {
   typedef StreamShape<CW, AL> S;
   constexpr int kOut = EPI == kEpiSwiglu ? CW / 2 : CW;          // output columns per item
   constexpr int kRPL = CW == 64 ? 8 : 4;                         // NN: k-rows per 1 KB line
   static_assert(CW != 256 || (LAY == kLayNN && EPI == kEpiSwiglu), "256 columns: gate and up halves");
   const int G = gridDim.x;
   const int n_ct = (p.N + kOut - 1) / kOut;
-  const int total = n_act * n_ct;
+  const int total = id1 - id0;
   // 128 columns: neighbouring items on different dies, as the dispatcher deals them; 64 columns: on one die, whose L2 then
   // serves both halves of a line that two items share
   auto tile_of = [&](int it) __attribute__((always_inline)) {
@@ -100,7 +101,7 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int n_act, cha
   struct { const char *a_base, *b_base; uint32_t a_off[AL], b_off[LAY == kLayNT ? 4 : S::kNB]; int step, item, slot; } q;
   q.step = 0; q.item = 0; q.slot = 0;
   auto item_of = [&](int it, int& ae, int& ct) __attribute__((always_inline)) {
-    const int id = tile_of(it);
+    const int id = id0 + tile_of(it);
     ae = __builtin_amdgcn_readfirstlane(id / n_ct);
     ct = __builtin_amdgcn_readfirstlane(id - ae * n_ct);
   };
@@ -345,25 +346,32 @@ __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_ro
   const bool narrow = n_act * ((p.N + kOut64 - 1) / kOut64) <= (int)gridDim.x;
   if constexpr (LAY == kLayNN && EPI == kEpiSwiglu) {
     // GEMM-1: 256 columns (128 gate, 128 up: 256-byte pieces instead of 128; T = 256, H = 7168 515 -> 475 us a layer, T = 64,
-    // H = 2048 73 -> 67), unless 128 make shorter rounds (20 experts with rows, 320 items of 256 on 256 workgroups: 352 against
-    // 356 at T = 32; a round costs its columns)
-    const int G = gridDim.x;
-    const int rounds256 = (n_act * ((p.N + 127) / 128) + G - 1) / G, rounds128 = (n_act * ((p.N + 63) / 64) + G - 1) / G;
-    if (!narrow && 2 * rounds256 <= rounds128) {
-      if (max_rows > 32) stream_items<LAY, EPI, 256, 2>(p, n_act, smem);
-      else stream_items<LAY, EPI, 256, 1>(p, n_act, smem);
+    // H = 2048 73 -> 67).  Where that leaves a last round at most half full, its items run as two of 128 columns each: a round
+    // costs its columns, and whole rounds keep the longer pieces (about 20 experts with rows, 320 items on 256 workgroups: T = 32
+    // 350 us a layer with 128 columns throughout, 328 so; T = 24 318 -> 295; 32 experts, H = 4096, I = 1536, T = 64 224 -> 210).
+    // With less than one round, or columns that don't divide: 128 throughout.
+    const int G = gridDim.x, n256 = n_act * ((p.N + 127) / 128), rest = n256 % G;
+    if (!narrow && (2 * rest > G || rest == 0 || (n256 > G && p.N % 128 == 0))) {
+      const int whole = 2 * rest > G ? n256 : n256 - rest;
+      if (max_rows > 32) stream_items<LAY, EPI, 256, 2>(p, 0, whole, smem);
+      else stream_items<LAY, EPI, 256, 1>(p, 0, whole, smem);
+      if (whole == n256) return;
+      __syncthreads();                                           // the ring has been read out by all
+      if (max_rows > 32) stream_items<LAY, EPI, 128, 2>(p, 2 * whole, 2 * n256, smem);
+      else stream_items<LAY, EPI, 128, 1>(p, 2 * whole, 2 * n256, smem);
       return;
     }
   }
+  const int total = n_act * ((p.N + (narrow ? kOut64 : 2 * kOut64) - 1) / (narrow ? kOut64 : 2 * kOut64));
   if (narrow) {
-    if (max_rows > 64) stream_items<LAY, EPI, 64, 8>(p, n_act, smem);
-    else if (max_rows > 32) stream_items<LAY, EPI, 64, 4>(p, n_act, smem);
-    else if (max_rows > 16) stream_items<LAY, EPI, 64, 2>(p, n_act, smem);
-    else stream_items<LAY, EPI, 64, 1>(p, n_act, smem);
+    if (max_rows > 64) stream_items<LAY, EPI, 64, 8>(p, 0, total, smem);
+    else if (max_rows > 32) stream_items<LAY, EPI, 64, 4>(p, 0, total, smem);
+    else if (max_rows > 16) stream_items<LAY, EPI, 64, 2>(p, 0, total, smem);
+    else stream_items<LAY, EPI, 64, 1>(p, 0, total, smem);
   } else {
-    if (max_rows > 64) stream_items<LAY, EPI, 128, 4>(p, n_act, smem);
-    else if (max_rows > 32) stream_items<LAY, EPI, 128, 2>(p, n_act, smem);
-    else stream_items<LAY, EPI, 128, 1>(p, n_act, smem);
+    if (max_rows > 64) stream_items<LAY, EPI, 128, 4>(p, 0, total, smem);
+    else if (max_rows > 32) stream_items<LAY, EPI, 128, 2>(p, 0, total, smem);
+    else stream_items<LAY, EPI, 128, 1>(p, 0, total, smem);
   }
 }
 

@@ -45,6 +45,16 @@ DEEP = [
 ]
 
 
+# GEMM-1: 320 items of 256 columns are one round of 256 workgroups and 64 items that run as 128 of 128 columns
+MIXED = [("gemm1_256_then_128_rows_32", 576, 640, ONE_32 * 8), ("gemm1_256_then_128_rows_64", 128, 640, ONE_64 * 8)]
+
+
+@pytest.mark.parametrize("keep_xp", [True, False])
+@pytest.mark.parametrize("case", MIXED, ids=[c[0] for c in MIXED])
+def test_whole_rounds_wide_and_the_rest_narrow(case, keep_xp):
+    _run(*case, keep_xp)
+
+
 def _columns(n_act, N, swiglu, G):
     """Columns per item and number of items that the launch's rule (csrc/gemm_stream.h, stream_gemm_bf16) gives."""
     items = {cw: n_act * -(-N // (cw // 2 if swiglu else cw)) for cw in (64, 128, 256)}

@@ -257,12 +257,12 @@ __device__ __forceinline__ void gemm_core_f32_quarter(f32x4 (&acc)[NB], const fl
 
 // A strip, 16 rows x 64 columns, for launches whose experts have at most 16 rows each: wave w owns columns 16 w .. + 15 (GEMM-1:
 // of the gate and of the up block) and nothing is multiplied for rows that are not there, K step 32.  Such a launch reads
-// weights: 256-byte pieces, two steps of 8 KB (GEMM-1: 16) under way per workgroup.  Forward layout only; the same chain of
+// weights: 256-byte pieces, AHEAD steps of 8 KB (GEMM-1: 16) under way per workgroup.  Forward layout only; the same chain of
 // sums as the other tiles.  Against quarters (whose second 16 rows do not exist here, and which read 128-byte pieces): forward of
 // T = 20, H = 2048, I = 1408, 16 of 64 experts 145 -> 95 us (554 MB of weights where all have rows, 78 us at 7.1 TB/s), T = 100 180 -> 118;
 // T = 30, H = 1024, I = 704, 16 experts 61.6 -> 42; T = 8, 64 experts 115 -> 75.  With two quarters per tile up to 32 rows: T = 64
 // 62.6 -> 52.7, a training step of T = 64, H = 512, I = 448, 10 of 16 experts 75 -> 63.5.
-template <int NB>
+template <int NB, int AHEAD>
 __device__ __forceinline__ void gemm_core_f32_strip(f32x4 (&acc)[NB], const float* a_ptr, const float* b_ptr, long b_k, long b_half,
                                                     int K, float* smem) {
   const int tid = threadIdx.x, lane = tid & 63;
@@ -277,7 +277,7 @@ __device__ __forceinline__ void gemm_core_f32_strip(f32x4 (&acc)[NB], const floa
   const int b_st = kAStage + (tid >> 4) * kFSLd + (tid & 15) * 4;
   const int k0 = (lg & 1) * 4 + (lg >> 1);
   const int a_rd = l16 * kFQLd + lg * 8, b_rd = kAStage + k0 * kFSLd + wave * 16 + l16;
-  struct Regs { f32x4 a, b[NB][2]; } r[2];             // two steps under way (four: no faster, and too many registers)
+  struct Regs { f32x4 a, b[NB][2]; } r[AHEAD];
   auto load = [&](Regs& q, int s) __attribute__((always_inline)) {
     const long k = (long)min(s, n_steps - 1) * kFQK;
     q.a = *reinterpret_cast<const f32x4*>(a_ptr + k);
@@ -314,18 +314,23 @@ __device__ __forceinline__ void gemm_core_f32_strip(f32x4 (&acc)[NB], const floa
 #pragma unroll
       for (int h = 0; h < NB; ++h) acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i >> 2][i & 3], b[h][i], acc[h], 0, 0, 0);
     stage(q, buf ^ 1);
-    load(q, s + 3);
+    load(q, s + 1 + AHEAD);
     __syncthreads();                                   // at the last step also: LDS free for the next tile
   };
   if (n_steps <= 0) return;
-  load(r[0], 0);
-  load(r[1], 1);
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) load(r[i], i);
   stage(r[0], 0);
-  load(r[0], 2);
+  load(r[0], AHEAD);
   __syncthreads();
-  for (int s = 0; s < n_steps; s += 2) {
+  for (int s = 0; s < n_steps; s += AHEAD) {
     step(r[1], s, 0);
-    step(r[0], s + 1, 1);
+    step(r[2 % AHEAD], s + 1, 1);
+    if constexpr (AHEAD == 4) {
+      if (s + 2 >= n_steps) break;
+      step(r[3], s + 2, 0);
+      step(r[0], s + 3, 1);
+    }
   }
 }
 
@@ -421,7 +426,8 @@ __device__ __forceinline__ void gemm_quarter_f32(const GemmParamsF32& p, int mti
 }
 
 // The same tile of an expert with at most 16 rows.
-template <int EPI>
+// AHEAD: steps under way, two where four workgroups share a CU (four are no faster there and take too many registers).
+template <int EPI, int AHEAD = 2>
 __device__ __forceinline__ void gemm_strip_f32(const GemmParamsF32& p, int mtile, int ntile, float* smem) {
   constexpr int NB = (EPI == kEpiSwiglu) ? 2 : 1;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -433,7 +439,7 @@ __device__ __forceinline__ void gemm_strip_f32(const GemmParamsF32& p, int mtile
   for (int h = 0; h < NB; ++h)
 #pragma unroll
     for (int r = 0; r < 4; ++r) acc[h][r] = 0.f;
-  gemm_core_f32_strip<NB>(acc, p.A + (size_t)(row0 + min((tid >> 3) & 15, rows - 1)) * p.lda + (tid & 7) * 4,
+  gemm_core_f32_strip<NB, AHEAD>(acc, p.A + (size_t)(row0 + min((tid >> 3) & 15, rows - 1)) * p.lda + (tid & 7) * 4,
                           p.B + (size_t)e * p.strideB + (size_t)(tid >> 4) * p.ldb + n0 + (tid & 15) * 4, p.ldb, p.N, p.K, smem);
   const int c = n0 + (tid >> 6) * 16 + (lane & 15);
 #pragma unroll
@@ -441,6 +447,15 @@ __device__ __forceinline__ void gemm_strip_f32(const GemmParamsF32& p, int mtile
     const int m = 4 * (lane >> 4) + r;
     if (m < rows) store_f32<EPI>(p, (size_t)(row0 + m), c, acc[0][r], acc[NB - 1][r]);
   }
+}
+
+// A tile as a task of the single launch, whose one workgroup per CU has registers for four steps under way.  Tiles of at most 16
+// rows as strips: T = 20, H = 2048, I = 1408, 16 of 64 experts, single launch 219 -> 141 us, T = 1 86 -> 58; T = 8, H = 1024, I = 704,
+// 64 experts 173 -> 130; with 375 rows per expert the longer code costs 1 % (378 -> 384).
+template <int EPI>
+__device__ __forceinline__ void gemm_task_f32(const GemmParamsF32& p, int mtile, int ntile, float* smem) {
+  if (__builtin_amdgcn_readfirstlane(p.tiles.rows[mtile]) <= 16) gemm_strip_f32<EPI, 4>(p, mtile, ntile, smem);
+  else gemm_tile_f32<EPI>(p, mtile, ntile, smem);
 }
 
 template <int EPI>

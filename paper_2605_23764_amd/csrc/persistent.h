@@ -412,11 +412,11 @@ __device__ __forceinline__ void run_tile_task(const SchedParams<BF16>& sp, const
     sched_trigger(sp, kEvPerTile + m, wave, scope);
   } else if (type == kTaskGemm1) {
     if constexpr (BF16) gemm_map_tile_bf16<kLayNN, kEpiSwiglu>(sp.g1, m, idx, tile_is_tall(__builtin_amdgcn_readfirstlane(sp.route.tiles.rows[m])), smem);
-    else gemm_tile_f32<kEpiSwiglu>(sp.g1, m, idx, reinterpret_cast<float*>(smem));
+    else gemm_task_f32<kEpiSwiglu>(sp.g1, m, idx, reinterpret_cast<float*>(smem));
     sched_trigger(sp, kEvPerTile + sp.max_mtiles + m, wave, scope);
   } else {
     if constexpr (BF16) gemm_map_tile_bf16<kLayNN, SCATTER ? kEpiScatter : kEpiStore>(sp.g2, m, idx, narrow || tile_is_tall(__builtin_amdgcn_readfirstlane(sp.route.tiles.rows[m])), smem);
-    else gemm_tile_f32<kEpiStore>(sp.g2, m, idx, reinterpret_cast<float*>(smem));
+    else gemm_task_f32<kEpiStore>(sp.g2, m, idx, reinterpret_cast<float*>(smem));
     // COMBINE waits for every GEMM-2 tile, so completions are counted here and published once per
     // worker after its queue has drained: a device-scope release per tile would write back the
     // XCD's whole L2 each time (about 30 us per tile in a trace)

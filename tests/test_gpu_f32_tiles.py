@@ -56,7 +56,7 @@ def _whole_tiles_and_quarters(name, H, I, rows):
     assert ref["counts"].tolist() == rows
     run = run_forward(cfg, inp, store_h1=True)
     check_forward(run, ref, "f32", store_h1=True)
-    # the single launch multiplies whole tiles only: the same chain of sums
+    # the single launch multiplies whole tiles, or strips where a tile has at most 16 rows: the same chain of sums
     single = run_forward(cfg, inp, mode=moe.MODE_PERSISTENT, store_h1=True)
     assert torch.equal(single.out, run.out)
     check_backward(run_backward(cfg, inp, run), oracle.backward(inp["dy"], ref, inp["w_gate_up"], inp["w_down"]), ref["counts"], "f32")

@@ -1,4 +1,4 @@
-"""Grouped GEMMs as a weight stream (largest expert of at most 64 rows): the edges of its shapes, against the fp64 oracle
+"""Grouped GEMMs as a weight stream (largest expert of at most 64 rows, 128 where that is a single round): the edges of its shapes, against the fp64 oracle
 and bit for bit against the single launch, which runs the same products through the ordinary tiles (both sum K in the
 same order)."""
 import numpy as np
@@ -19,7 +19,7 @@ CASES = [
     ("wide_32", 448, 832, [32, 2, 31, 0] * 12),             # 256 columns (GEMM-1), 128 (act_grad), 64; N = 3.5 and 6.5 tiles of 128
     ("wide_64", 320, 448, [64, 33, 1, 0, 50]),              # two row blocks
     ("many_rows", 128, 192, [40] * 64),                     # more rows than the token table in LDS holds
-    ("above", 192, 128, [65, 3]),                           # the first size that takes the ordinary tiles
+    ("above", 192, 128, [65, 3]),                           # above 64 rows, a single round
 ]
 
 

@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "stream_rule.h"
 
 namespace moe {
 
@@ -69,8 +70,6 @@ constexpr int kMaxMT = kBM / 64;                     // 32-row MFMA sub-tiles pe
 // those of a 256-row tile, and the MFMA work grows by the real rows only.
 constexpr int kWideRows = kBM + 64;
 constexpr int kBLinesPerWave = kBLines / 4;          // 8
-constexpr int kStreamRows = 64;                      // rows of the largest expert up to which a launch runs as a weight stream,
-constexpr int kStreamMaxRows = 128;                  // ... and up to which it does where that takes a single round (see the kernel)
 
 struct GemmParams {
   const __bf16* A;    // [rows, lda] activations, expert-contiguous rows, k-contiguous
@@ -989,13 +988,7 @@ void grouped_gemm_bf16_kernel(GemmParams p) {
   int n_m = p.tiles.meta[kMetaMTiles], max_rows = p.tiles.meta[kMetaMaxRows], n_act = p.tiles.meta[kMetaActive], G = gridDim.x;
   asm volatile("" : "+s"(n_m), "+s"(max_rows), "+s"(n_act), "+s"(G));
   if constexpr (EPI != kEpiScatter) {
-    // 65..128 rows per expert: as a stream where its items of 128 columns are a single round, i.e. where tiles of 256 columns
-    // leave half of the chip idle (T = 777, H = 1088, I = 704, 10 experts: training step 133 -> 115 us; 1600 rows, H = 7168,
-    // I = 512, 4 experts: forward 141 -> 96, backward 212 -> 159; T = 400, H = 2048, I = 1408, 16 experts: gate_grad and act_grad,
-    // backward 206 -> 194).  With more items than workgroups the tiles win (the same layer's GEMM-1: forward 95 as tiles, 106 as
-    // a stream; H = 7168, I = 2048, 32 experts: 603 and 669), and above 128 rows too (150 rows, 16 experts: 54 and 60).
-    constexpr int kOut128 = EPI == kEpiSwiglu ? 64 : 128;
-    if (max_rows <= kStreamRows || (max_rows <= kStreamMaxRows && n_act * ((p.N + kOut128 - 1) / kOut128) <= G)) {
+    if (stream_takes(max_rows, n_act, p.N, EPI == kEpiSwiglu, G)) {
       stream_gemm_bf16<LAY, EPI>(p, max_rows, smem);
       return;
     }

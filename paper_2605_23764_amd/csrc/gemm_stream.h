@@ -1,11 +1,11 @@
 // Grouped bf16 GEMMs for a few rows per expert (serving batches, small training batches): the weight stream.
 //
 // With at most 64 rows per expert a weight element meets one or two MFMA row blocks, so the launch is a read of the
-// weights at HBM rate and nothing else (up to 128 rows, where a launch is a single round: grouped_gemm_bf16_kernel); the tile of gemm_bf16.h (256 weight columns, 64 KB of weights under way per CU)
+// weights at HBM rate and nothing else (up to 128 rows, where a launch is a single round: stream_takes); the tile of gemm_bf16.h (256 weight columns, 64 KB of weights under way per CU)
 // then has too few work items to fill the chip evenly (T = 1 at H = 2048, I = 1408: 44 items on four of the eight dies)
 // and too little in flight.  Here
 //   * an item is some weight columns of one expert over the whole K (never split: results are the same bits as the other
-//     kernel's, whose MFMAs sum in the same order), dealt evenly to all workgroups.  Three widths (stream_gemm_bf16 has the rule):
+//     kernel's, whose MFMAs sum in the same order), dealt evenly to all workgroups.  Three widths (stream_form has the rule):
 //       columns                a stage holds (weights)   ring: up to 16 / 32 / 64 / 128 rows   weights under way
 //       256 (GEMM-1 only)      64 k x 256 = 32 KB        4 / 4 / 3 / -  stages                 96 .. 64 KB
 //       128                    64 k x 128 = 16 KB        7 / 7 / 6 / 4                         96 .. 48 KB
@@ -306,7 +306,15 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int id0, int i
   }
 }
 
-// Whole launch of a grouped GEMM whose largest expert has max_rows <= kStreamMaxRows rows (above kStreamRows: a single round).
+// The same with stages of ROWS activation rows.
+template <int LAY, int EPI, int CW, int ROWS>
+__device__ __forceinline__ void stream_rows(const GemmParams& p, int id0, int id1, char* smem) {
+  constexpr int AL = ROWS / (CW == 64 ? 16 : 32);
+  static_assert(StreamShape<CW, AL>::kRows == ROWS, "rows of a stage");
+  stream_items<LAY, EPI, CW, AL>(p, id0, id1, smem);
+}
+
+// Whole launch of a grouped GEMM that stream_takes.
 template <int LAY, int EPI>
 __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_rows, char* smem) {
   // experts with rows, in expert order (every wave counts, wave 0 writes), and the tokens of the first rows
@@ -338,40 +346,27 @@ __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_ro
   }
   __syncthreads();
   n_act = __builtin_amdgcn_readfirstlane(n_act);
-  // 128 columns per item; 64 only where that still is a single round, i.e. where the chip would be at most half full
-  // (T = 1, H = 2048, I = 1408, four experts: GEMM-1 88 items -> 176): 64 columns are 128-byte pieces of a row, 64-byte
-  // pieces for SwiGLU (half gate, half up), which stream 10..30 % slower once all CUs are busy (T = 64: 84 us a layer
-  // against 73).
-  constexpr int kOut64 = EPI == kEpiSwiglu ? 32 : 64;
-  const bool narrow = n_act * ((p.N + kOut64 - 1) / kOut64) <= (int)gridDim.x;
+  const StreamForm f = stream_form(max_rows, n_act, p.N, EPI == kEpiSwiglu, gridDim.x);
   if constexpr (LAY == kLayNN && EPI == kEpiSwiglu) {
-    // GEMM-1: 256 columns (128 gate, 128 up: 256-byte pieces instead of 128; T = 256, H = 7168 515 -> 475 us a layer, T = 64,
-    // H = 2048 73 -> 67).  Where that leaves a last round at most half full, its items run as two of 128 columns each: a round
-    // costs its columns, and whole rounds keep the longer pieces (about 20 experts with rows, 320 items on 256 workgroups: T = 32
-    // 350 us a layer with 128 columns throughout, 328 so; T = 24 318 -> 295; 32 experts, H = 4096, I = 1536, T = 64 224 -> 210).
-    // With less than one round, or columns that don't divide: 128 throughout.
-    const int G = gridDim.x, n256 = n_act * ((p.N + 127) / 128), rest = n256 % G;
-    if (!narrow && (2 * rest > G || rest == 0 || (n256 > G && p.N % 128 == 0))) {
-      const int whole = 2 * rest > G ? n256 : n256 - rest;
-      if (max_rows > 32) stream_items<LAY, EPI, 256, 2>(p, 0, whole, smem);
-      else stream_items<LAY, EPI, 256, 1>(p, 0, whole, smem);
-      if (whole == n256) return;
+    if (f.cols == 256) {
+      if (f.rows == 64) stream_rows<LAY, EPI, 256, 64>(p, 0, f.whole, smem);
+      else stream_rows<LAY, EPI, 256, 32>(p, 0, f.whole, smem);
+      if (f.whole == f.items) return;
       __syncthreads();                                           // the ring has been read out by all
-      if (max_rows > 32) stream_items<LAY, EPI, 128, 2>(p, 2 * whole, 2 * n256, smem);
-      else stream_items<LAY, EPI, 128, 1>(p, 2 * whole, 2 * n256, smem);
+      if (f.rows == 64) stream_rows<LAY, EPI, 128, 64>(p, 2 * f.whole, 2 * f.items, smem);
+      else stream_rows<LAY, EPI, 128, 32>(p, 2 * f.whole, 2 * f.items, smem);
       return;
     }
   }
-  const int total = n_act * ((p.N + (narrow ? kOut64 : 2 * kOut64) - 1) / (narrow ? kOut64 : 2 * kOut64));
-  if (narrow) {
-    if (max_rows > 64) stream_items<LAY, EPI, 64, 8>(p, 0, total, smem);
-    else if (max_rows > 32) stream_items<LAY, EPI, 64, 4>(p, 0, total, smem);
-    else if (max_rows > 16) stream_items<LAY, EPI, 64, 2>(p, 0, total, smem);
-    else stream_items<LAY, EPI, 64, 1>(p, 0, total, smem);
+  if (f.cols == 64) {
+    if (f.rows == 128) stream_rows<LAY, EPI, 64, 128>(p, 0, f.items, smem);
+    else if (f.rows == 64) stream_rows<LAY, EPI, 64, 64>(p, 0, f.items, smem);
+    else if (f.rows == 32) stream_rows<LAY, EPI, 64, 32>(p, 0, f.items, smem);
+    else stream_rows<LAY, EPI, 64, 16>(p, 0, f.items, smem);
   } else {
-    if (max_rows > 64) stream_items<LAY, EPI, 128, 4>(p, 0, total, smem);
-    else if (max_rows > 32) stream_items<LAY, EPI, 128, 2>(p, 0, total, smem);
-    else stream_items<LAY, EPI, 128, 1>(p, 0, total, smem);
+    if (f.rows == 128) stream_rows<LAY, EPI, 128, 128>(p, 0, f.items, smem);
+    else if (f.rows == 64) stream_rows<LAY, EPI, 128, 64>(p, 0, f.items, smem);
+    else stream_rows<LAY, EPI, 128, 32>(p, 0, f.items, smem);
   }
 }
 

@@ -50,6 +50,9 @@ def run_forward(cfg: MoeConfig, inp: dict, mode=moe.MODE_SERIALIZED, store_h1=Fa
         w_down=to_device(inp["w_down"], cfg.dtype),
     )
     saved = moe.alloc_saved(shape, store_h1=store_h1, keep_xp=keep_xp)
+    for t in (saved.Xp, saved.H1, saved.A, saved.Yp):
+        if t is not None:
+            t.fill_(float("nan"))   # a row that the forward leaves out must not pass with what was in memory before
     ws = moe.alloc_workspace(shape)
     out = torch.full((cfg.T, cfg.H), float("nan"), dtype=tdt, device="cuda")
     moe.moe_ffn_forward(shape, dev["x"], dev["logits"], dev["w_gate_up"], dev["w_down"], out, saved, ws, mode)

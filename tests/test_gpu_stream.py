@@ -7,6 +7,7 @@ import torch
 
 import oracle
 import paper_2605_23764_amd as moe
+import stream_rule
 from workloads import make_inputs
 
 pytestmark = pytest.mark.gpu
@@ -53,6 +54,23 @@ MIXED = [("gemm1_256_then_128_rows_32", 576, 640, ONE_32 * 8), ("gemm1_256_then_
 @pytest.mark.parametrize("case", MIXED, ids=[c[0] for c in MIXED])
 def test_whole_rounds_wide_and_the_rest_narrow(case, keep_xp):
     _run(*case, keep_xp)
+
+
+# 65..128 rows at the upper edge of a single round of 128-column items, where items of 256 columns (stages of 64 rows) would be
+# more than half a round: I / 64 odd; the last: its even neighbour, exactly half a round
+ABOVE_64 = [("i64", 128, 64, 160), ("i320", 128, 320, 48), ("i704_22", 192, 704, 22), ("i704_23", 128, 704, 23), ("i832", 128, 832, 19),
+            ("i1600", 192, 1600, 10), ("i704_20", 128, 704, 20)]
+
+
+@pytest.mark.parametrize("keep_xp", [True, False])
+@pytest.mark.parametrize("largest", [65, 128])
+@pytest.mark.parametrize("case", ABOVE_64, ids=[c[0] for c in ABOVE_64])
+def test_rows_above_64_at_the_edge_of_a_round(case, largest, keep_xp):
+    name, H, I, n_act = case
+    G = -(-torch.cuda.get_device_properties(0).multi_processor_count // 8) * 8
+    if G == 256:
+        assert stream_rule.form(largest, n_act, I, True, G)[:2] == (128, 128)
+    _run(f"{name}_{largest}", H, I, ([largest, 1, 64, 33, largest, 16] * 27)[:n_act], keep_xp)
 
 
 def _columns(n_act, N, swiglu, G):

@@ -71,7 +71,7 @@ def sim(tmp_path_factory):
     d = tmp_path_factory.mktemp("lds_order")
     (d / "hip").mkdir()
     (d / "hip" / "hip_runtime.h").write_text("#pragma once\n")
-    for name in ("common.h", "gemm_bf16.h"):
+    for name in ("common.h", "gemm_bf16.h", "stream_rule.h"):
         with open(os.path.join(CSRC, name)) as f:
             (d / name).write_text(recorded(f.read()))
     exe = str(d / "lds_copy_order")

@@ -5,7 +5,7 @@
 // then has too few work items to fill the chip evenly (T = 1 at H = 2048, I = 1408: 44 items on four of the eight dies)
 // and too little in flight.  Here
 //   * an item is some weight columns of one expert over the whole K (never split: results are the same bits as the other
-//     kernel's, whose MFMAs sum in the same order), dealt evenly to all workgroups.  Three widths (stream_form has the rule):
+//     kernel's, whose MFMAs sum in the same order), dealt evenly to all workgroups.  Three widths (stream_rule.h has the rule):
 //       columns                a stage holds (weights)   ring: up to 16 / 32 / 64 / 128 rows   weights under way
 //       256 (GEMM-1 only)      64 k x 256 = 32 KB        4 / 4 / 3 / -  stages                 96 .. 64 KB
 //       128                    64 k x 128 = 16 KB        7 / 7 / 6 / 4                         96 .. 48 KB
@@ -314,7 +314,12 @@ __device__ __forceinline__ void stream_rows(const GemmParams& p, int id0, int id
   stream_items<LAY, EPI, CW, AL>(p, id0, id1, smem);
 }
 
-// Whole launch of a grouped GEMM that stream_takes.
+// Whole launch of a grouped GEMM that stream_takes, in the form of stream_form.  The comparisons of max_rows below are those of
+// stream_stage_rows.
+static_assert(stream_stage_rows(64, 16) == 16 && stream_stage_rows(64, 17) == 32 && stream_stage_rows(64, 32) == 32 &&
+              stream_stage_rows(64, 33) == 64 && stream_stage_rows(64, 64) == 64 && stream_stage_rows(64, 65) == 128, "64 columns");
+static_assert(stream_stage_rows(128, 32) == 32 && stream_stage_rows(128, 33) == 64 && stream_stage_rows(128, 64) == 64 &&
+              stream_stage_rows(128, 65) == 128 && stream_stage_rows(256, 32) == 32 && stream_stage_rows(256, 33) == 64, "128, 256");
 template <int LAY, int EPI>
 __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_rows, char* smem) {
   // experts with rows, in expert order (every wave counts, wave 0 writes), and the tokens of the first rows
@@ -346,27 +351,32 @@ __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_ro
   }
   __syncthreads();
   n_act = __builtin_amdgcn_readfirstlane(n_act);
-  const StreamForm f = stream_form(max_rows, n_act, p.N, EPI == kEpiSwiglu, gridDim.x);
+  const int G = gridDim.x;
+  const bool narrow = stream_narrow(n_act, p.N, EPI == kEpiSwiglu, G);
   if constexpr (LAY == kLayNN && EPI == kEpiSwiglu) {
-    if (f.cols == 256) {
-      if (f.rows == 64) stream_rows<LAY, EPI, 256, 64>(p, 0, f.whole, smem);
-      else stream_rows<LAY, EPI, 256, 32>(p, 0, f.whole, smem);
-      if (f.whole == f.items) return;
+    const int n256 = n_act * stream_tiles(p.N, 128), n128 = n_act * stream_tiles(p.N, 64);
+    if (!narrow && stream_wide(max_rows, n256, n128, p.N, G)) {
+      const int whole = stream_whole(n256, n128, G);
+      if (max_rows > 32) stream_rows<LAY, EPI, 256, 64>(p, 0, whole, smem);
+      else stream_rows<LAY, EPI, 256, 32>(p, 0, whole, smem);
+      if (whole == n256) return;
       __syncthreads();                                           // the ring has been read out by all
-      if (f.rows == 64) stream_rows<LAY, EPI, 128, 64>(p, 2 * f.whole, 2 * f.items, smem);
-      else stream_rows<LAY, EPI, 128, 32>(p, 2 * f.whole, 2 * f.items, smem);
+      if (max_rows > 32) stream_rows<LAY, EPI, 128, 64>(p, 2 * whole, 2 * n256, smem);
+      else stream_rows<LAY, EPI, 128, 32>(p, 2 * whole, 2 * n256, smem);
       return;
     }
   }
-  if (f.cols == 64) {
-    if (f.rows == 128) stream_rows<LAY, EPI, 64, 128>(p, 0, f.items, smem);
-    else if (f.rows == 64) stream_rows<LAY, EPI, 64, 64>(p, 0, f.items, smem);
-    else if (f.rows == 32) stream_rows<LAY, EPI, 64, 32>(p, 0, f.items, smem);
-    else stream_rows<LAY, EPI, 64, 16>(p, 0, f.items, smem);
+  constexpr int kOut64 = EPI == kEpiSwiglu ? 32 : 64;
+  const int total = n_act * stream_tiles(p.N, narrow ? kOut64 : 2 * kOut64);
+  if (narrow) {
+    if (max_rows > 64) stream_rows<LAY, EPI, 64, 128>(p, 0, total, smem);
+    else if (max_rows > 32) stream_rows<LAY, EPI, 64, 64>(p, 0, total, smem);
+    else if (max_rows > 16) stream_rows<LAY, EPI, 64, 32>(p, 0, total, smem);
+    else stream_rows<LAY, EPI, 64, 16>(p, 0, total, smem);
   } else {
-    if (f.rows == 128) stream_rows<LAY, EPI, 128, 128>(p, 0, f.items, smem);
-    else if (f.rows == 64) stream_rows<LAY, EPI, 128, 64>(p, 0, f.items, smem);
-    else stream_rows<LAY, EPI, 128, 32>(p, 0, f.items, smem);
+    if (max_rows > 64) stream_rows<LAY, EPI, 128, 128>(p, 0, total, smem);
+    else if (max_rows > 32) stream_rows<LAY, EPI, 128, 64>(p, 0, total, smem);
+    else stream_rows<LAY, EPI, 128, 32>(p, 0, total, smem);
   }
 }
 

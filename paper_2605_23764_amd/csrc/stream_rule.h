@@ -21,31 +21,50 @@ constexpr bool stream_takes(int max_rows, int n_act, int N, bool swiglu, int G) 
   return max_rows <= kStreamRows || (max_rows <= kStreamMaxRows && n_act * stream_tiles(N, swiglu ? 64 : 128) <= G);
 }
 
+// 128 columns per item; 64 only where that still is a single round, i.e. where the chip would be at most half full
+// (T = 1, H = 2048, I = 1408, four experts: GEMM-1 88 items -> 176): 64 columns are 128-byte pieces of a row, 64-byte
+// pieces for SwiGLU (half gate, half up), which stream 10..30 % slower once all CUs are busy (T = 64: 84 us a layer
+// against 73).
+constexpr bool stream_narrow(int n_act, int N, bool swiglu, int G) { return n_act * stream_tiles(N, swiglu ? 32 : 64) <= G; }
+
+// GEMM-1: 256 columns (128 gate, 128 up: 256-byte pieces instead of 128; T = 256, H = 7168 515 -> 475 us a layer, T = 64,
+// H = 2048 73 -> 67) where no workgroup gets more columns that way than with 128 throughout: a round costs its columns.  Where a
+// last round of at most half the workgroups is the reason that one would, its items run as two of 128 columns each behind the
+// whole rounds (about 20 experts with rows, 320 items on 256 workgroups: T = 32 350 us a layer with 128 columns throughout, 328 so;
+// T = 24 318 -> 295; 32 experts, H = 4096, I = 1536, T = 64 224 -> 210).  Otherwise (less than one round; N / 64 odd, where every
+// expert's last item is half empty) 128 throughout.  256 columns there took, H = 2048, 35 rows an expert, I = 1600: 10 experts 69.6
+// us a layer against 60.7, 30 experts 138.0 and 133.6; I = 704, 22 experts 73.2 and 64.9; 8 rows an expert 2..10 % more.  Only four
+// rounds against seven and more than 32 rows went the other way, by 1 % (I = 1984, 57 experts 287.0 and 289.4).
+// A stage of this form holds 64 rows.  n256, n128: the launch's items of either width.
+constexpr bool stream_wide_throughout(int n256, int n128, int G) {
+  // 2 * ceil(n256 / G) <= ceil(n128 / G), from the last round's items and the 128-column halves that have no columns
+  const int rest = n256 % G, missing = 2 * n256 - n128;
+  return 2 * (rest ? rest : G) - missing > G;
+}
+constexpr bool stream_wide(int max_rows, int n256, int n128, int N, int G) {
+  return max_rows <= kStreamRows && (stream_wide_throughout(n256, n128, G) || (n256 > G && N % 128 == 0));
+}
+// Items that run with 256 columns; the others as two of 128 each.
+constexpr int stream_whole(int n256, int n128, int G) { return stream_wide_throughout(n256, n128, G) ? n256 : n256 - n256 % G; }
+
+// Activation rows that a stage holds, for every form at least max_rows.
+constexpr int stream_stage_rows(int cols, int max_rows) {
+  return cols == 64 && max_rows <= 16 ? 16 : max_rows <= 32 ? 32 : cols == 256 || max_rows <= 64 ? 64 : 128;
+}
+
+// All of it, as stream_gemm_bf16 puts it together.
 struct StreamForm {
   int cols;    // weight columns per item: 64, 128 or 256
-  int rows;    // activation rows that a stage holds, for every form at least max_rows
+  int rows;    // activation rows that a stage holds
   int items;   // items of `cols` columns
   int whole;   // the first of them, which run as such; the others run as two of 128 columns each
 };
-
 constexpr StreamForm stream_form(int max_rows, int n_act, int N, bool swiglu, int G) {
-  // 128 columns per item; 64 only where that still is a single round, i.e. where the chip would be at most half full
-  // (T = 1, H = 2048, I = 1408, four experts: GEMM-1 88 items -> 176): 64 columns are 128-byte pieces of a row, 64-byte
-  // pieces for SwiGLU (half gate, half up), which stream 10..30 % slower once all CUs are busy (T = 64: 84 us a layer
-  // against 73).
   const int n64 = n_act * stream_tiles(N, swiglu ? 32 : 64), n128 = n_act * stream_tiles(N, swiglu ? 64 : 128);
-  if (n64 <= G) return {64, max_rows <= 16 ? 16 : max_rows <= 32 ? 32 : max_rows <= 64 ? 64 : 128, n64, n64};
-  // GEMM-1: 256 columns (128 gate, 128 up: 256-byte pieces instead of 128; T = 256, H = 7168 515 -> 475 us a layer, T = 64,
-  // H = 2048 73 -> 67).  Where that leaves a last round at most half full, its items run as two of 128 columns each: a round
-  // costs its columns, and whole rounds keep the longer pieces (about 20 experts with rows, 320 items on 256 workgroups: T = 32
-  // 350 us a layer with 128 columns throughout, 328 so; T = 24 318 -> 295; 32 experts, H = 4096, I = 1536, T = 64 224 -> 210).
-  // A stage of this form holds 64 rows.
-  if (swiglu && max_rows <= kStreamRows) {
-    const int n256 = n_act * stream_tiles(N, 128), rest = n256 % G;
-    if (2 * rest > G || rest == 0 || (n256 > G && N % 128 == 0))
-      return {256, max_rows <= 32 ? 32 : 64, n256, 2 * rest > G ? n256 : n256 - rest};
-  }
-  return {128, max_rows <= 32 ? 32 : max_rows <= 64 ? 64 : 128, n128, n128};
+  const int n256 = n_act * stream_tiles(N, 128);
+  if (stream_narrow(n_act, N, swiglu, G)) return {64, stream_stage_rows(64, max_rows), n64, n64};
+  if (swiglu && stream_wide(max_rows, n256, n128, N, G)) return {256, stream_stage_rows(256, max_rows), n256, stream_whole(n256, n128, G)};
+  return {128, stream_stage_rows(128, max_rows), n128, n128};
 }
 
 }  // namespace moe

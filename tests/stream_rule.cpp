@@ -29,3 +29,19 @@ extern "C" int stream_faults(int G, int* first) {
         }
   return n;
 }
+
+// Launches of at most 64 rows in which some workgroup gets more columns than with 128 columns per item throughout.
+extern "C" int stream_longer(int G, int* first) {
+  auto rounds = [&](int items) { return (items + G - 1) / G; };
+  int n = 0;
+  for (int swiglu = 0; swiglu < 2; ++swiglu)
+    for (int N = 64; N <= 8192; N += 64)
+      for (int n_act = 1; n_act <= 256; ++n_act)
+        for (int max_rows = 1; max_rows <= moe::kStreamRows; ++max_rows) {
+          const moe::StreamForm f = moe::stream_form(max_rows, n_act, N, swiglu, G);
+          const int out128 = swiglu ? 64 : 128, by128 = 128 * rounds(n_act * ((N + out128 - 1) / out128));
+          if (f.cols * rounds(f.whole) + 128 * rounds(2 * (f.items - f.whole)) <= by128) continue;
+          if (n++ == 0) { first[0] = max_rows; first[1] = n_act; first[2] = N; first[3] = swiglu; }
+        }
+  return n;
+}

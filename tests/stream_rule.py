@@ -36,3 +36,9 @@ def faults(G):
     """Number of launches whose form cannot hold them, and one of them (max_rows, n_act, N, swiglu)."""
     first = (ctypes.c_int * 4)()
     return library().stream_faults(G, first), tuple(first)
+
+
+def longer(G):
+    """Number of launches with longer rounds than items of 128 columns throughout would have, and one of them."""
+    first = (ctypes.c_int * 4)()
+    return library().stream_longer(G, first), tuple(first)

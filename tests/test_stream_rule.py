@@ -13,6 +13,13 @@ def test_every_form_holds_its_launch(G):
     assert n == 0, f"{n} launches, one of them (max_rows, experts with rows, N, swiglu) = {first}: {stream_rule.form(*first, G)}"
 
 
+@pytest.mark.parametrize("G", [248, 256, 304])
+def test_no_form_makes_rounds_longer(G):
+    """A round costs its columns: no workgroup has more of them than with 128 columns per item throughout."""
+    n, first = stream_rule.longer(G)
+    assert n == 0, f"{n} launches, one of them (max_rows, experts with rows, N, swiglu) = {first}: {stream_rule.form(*first, G)}"
+
+
 @pytest.mark.parametrize("N,n_act", [(64, 160), (192, 70), (320, 48), (448, 35), (576, 27), (704, 22), (832, 19), (960, 17), (1088, 15),
                                      (1216, 13), (1344, 12), (1472, 11), (1600, 10), (3264, 5)])
 def test_stages_of_128_rows_above_64_rows(N, n_act):

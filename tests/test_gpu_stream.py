@@ -1,6 +1,6 @@
-"""Grouped GEMMs as a weight stream (largest expert of at most 64 rows, 128 where that is a single round): the edges of its shapes, against the fp64 oracle
-and bit for bit against the single launch, which runs the same products through the ordinary tiles (both sum K in the
-same order)."""
+"""Grouped GEMMs as a weight stream (largest expert of at most 64 rows, 128 where that is a single round): the edges of its
+shapes, against the fp64 oracle and bit for bit against the single launch, which runs the same products through the ordinary
+tiles (both sum K in the same order).  Where a test means one form of the stream, it asks the rule which one it gets."""
 import numpy as np
 import pytest
 import torch
@@ -11,6 +11,18 @@ import stream_rule
 from workloads import make_inputs
 
 pytestmark = pytest.mark.gpu
+
+
+def _forms(rows, H, I):
+    """Forms (tests/stream_rule.py) of GEMM-1, GEMM-2, act_grad and gate_grad on this device; None: tiles."""
+    G = -(-torch.cuda.get_device_properties(0).multi_processor_count // 8) * 8
+    n_act = sum(r > 0 for r in rows)
+    return [stream_rule.form(max(rows), n_act, N, swiglu, G) for N, swiglu in ((I, True), (H, False), (I, False), (H, False))], G
+
+
+def _shape(form):
+    return form and (form.cols, form.rows)
+
 
 CASES = [
     # name, H, I, rows per expert (repeated over the experts)
@@ -53,13 +65,16 @@ MIXED = [("gemm1_256_then_128_rows_32", 576, 640, ONE_32 * 8), ("gemm1_256_then_
 @pytest.mark.parametrize("keep_xp", [True, False])
 @pytest.mark.parametrize("case", MIXED, ids=[c[0] for c in MIXED])
 def test_whole_rounds_wide_and_the_rest_narrow(case, keep_xp):
+    _, H, I, rows = case
+    forms, G = _forms(rows, H, I)
+    assert _shape(forms[0]) == (256, 32 if max(rows) <= 32 else 64) and forms[0].whole == G and G < forms[0].items < 2 * G
     _run(*case, keep_xp)
 
 
 # 65..128 rows at the upper edge of a single round of 128-column items, where items of 256 columns (stages of 64 rows) would be
-# more than half a round: I / 64 odd; the last: its even neighbour, exactly half a round
+# more than half a round: I / 64 odd; the last: I / 64 even, where they never are
 ABOVE_64 = [("i64", 128, 64, 160), ("i320", 128, 320, 48), ("i704_22", 192, 704, 22), ("i704_23", 128, 704, 23), ("i832", 128, 832, 19),
-            ("i1600", 192, 1600, 10), ("i704_20", 128, 704, 20)]
+            ("i1600", 192, 1600, 10), ("i1408", 128, 1408, 11)]
 
 
 @pytest.mark.parametrize("keep_xp", [True, False])
@@ -67,38 +82,30 @@ ABOVE_64 = [("i64", 128, 64, 160), ("i320", 128, 320, 48), ("i704_22", 192, 704,
 @pytest.mark.parametrize("case", ABOVE_64, ids=[c[0] for c in ABOVE_64])
 def test_rows_above_64_at_the_edge_of_a_round(case, largest, keep_xp):
     name, H, I, n_act = case
-    G = -(-torch.cuda.get_device_properties(0).multi_processor_count // 8) * 8
-    if G == 256:
-        assert stream_rule.form(largest, n_act, I, True, G)[:2] == (128, 128)
-    _run(f"{name}_{largest}", H, I, ([largest, 1, 64, 33, largest, 16] * 27)[:n_act], keep_xp)
-
-
-def _columns(n_act, N, swiglu, G):
-    """Columns per item and number of items that the launch's rule (csrc/gemm_stream.h, stream_gemm_bf16) gives."""
-    items = {cw: n_act * -(-N // (cw // 2 if swiglu else cw)) for cw in (64, 128, 256)}
-    if items[64] <= G:
-        cw = 64
-    else:
-        cw = 256 if swiglu and 2 * -(-items[256] // G) <= -(-items[128] // G) else 128
-    return cw, items[cw]
+    rows = ([largest, 1, 64, 33, largest, 16] * 27)[:n_act]
+    assert _shape(_forms(rows, H, I)[0][0]) == (128, 128)
+    _run(f"{name}_{largest}", H, I, rows, keep_xp)
 
 
 MEDIUM = [
+    # name, H, I, rows per expert; (columns per item, rows of a stage) of GEMM-1, GEMM-2, act_grad, gate_grad, None: tiles
     # 33..128 rows in a single round: 64 columns per item (stages of 64 and 128 rows, K = 2.5 and 1.5 stages) ...
-    ("narrow_64", 320, 192, [64, 33, 1, 0]),
-    ("narrow_128", 320, 192, [128, 97, 65, 0, 1]),
+    ("narrow_64", 320, 192, [64, 33, 1, 0], [(64, 64)] * 4),
+    ("narrow_128", 320, 192, [128, 97, 65, 0, 1], [(64, 128)] * 4),
     # ... 128 columns (20 experts with rows: 64 columns would be 440, 260 and 260 items; act_grad 220 of 64) ...
-    ("one_round_128", 832, 704, [128, 97, 65, 2, 0] * 5),
+    ("one_round_128", 832, 704, [128, 97, 65, 2, 0] * 5, [(128, 128), (128, 128), (64, 128), (128, 128)]),
     # ... and what takes the tiles: 260 items of 128 columns in GEMM-1, 129 rows
-    ("two_rounds", 192, 832, [65, 128] * 10),
-    ("rows_129", 192, 128, [129, 5]),
+    ("two_rounds", 192, 832, [65, 128] * 10, [None, (64, 128), (128, 128), (64, 128)]),
+    ("rows_129", 192, 128, [129, 5], [None] * 4),
 ]
 
 
 @pytest.mark.parametrize("keep_xp", [True, False])
 @pytest.mark.parametrize("case", MEDIUM, ids=[c[0] for c in MEDIUM])
 def test_single_round_above_32_rows(case, keep_xp):
-    _run(*case, keep_xp)
+    name, H, I, rows, want = case
+    assert [_shape(f) for f in _forms(rows, H, I)[0]] == want
+    _run(name, H, I, rows, keep_xp)
 
 
 @pytest.mark.parametrize("keep_xp", [True, False])
@@ -107,12 +114,10 @@ def test_several_items_per_workgroup(case, keep_xp):
     """Each workgroup runs more than one item: stages of the next one requested while the last ones of this one are
     multiplied, stores between the loads, and a last round that only some workgroups have an item in."""
     name, H, I, rows, columns = case
-    G = -(-torch.cuda.get_device_properties(0).multi_processor_count // 8) * 8
-    n_act = sum(r > 0 for r in rows)
-    for want, (N, swiglu) in zip(columns, ((I, True), (H, False), (I, False), (H, False))):
+    forms, G = _forms(rows, H, I)
+    for want, f in zip(columns, forms):
         if want is not None:
-            cw, items = _columns(n_act, N, swiglu, G)
-            assert cw == want and items > G and items % G, (name, N, cw, items, G)
+            assert f.cols == want and f.whole == f.items > G and f.items % G, (name, f, G)
     _run(name, H, I, rows, keep_xp)
 
 

@@ -102,6 +102,22 @@ def loads_ahead_of_first_branch(asm: str, kernel: str):
     return groups
 
 
+def innermost_loops(asm: str, kernel: str):
+    """Instructions of each of the kernel's loops that contains no other loop."""
+    start = asm.index(f"\n{kernel}:")
+    lines = [raw.split(";")[0].strip() for raw in asm[start:asm.index(".Lfunc_end", start)].splitlines()]
+    labels, loops = {}, []
+    for i, line in enumerate(lines):
+        m = re.match(r"(\.LBB\w+):", line)
+        if m:
+            labels[m.group(1)] = i
+        m = re.match(r"s_c?branch\w*\s+(\.LBB\w+)", line)
+        if m and m.group(1) in labels:
+            loops.append((labels[m.group(1)], i))
+    inner = [(a, b) for a, b in loops if not any((a, b) != (c, d) and a <= c and d <= b for c, d in loops)]
+    return [[line for line in lines[a:b + 1] if line and not line.startswith(".")] for a, b in inner]
+
+
 def main():
     n, bad = check_register_fed_loads(device_assembly())
     print(f"{n} assembly loads with register destinations, {len(bad)} instructions inside a request-to-retire window touch them")

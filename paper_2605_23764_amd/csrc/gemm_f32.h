@@ -63,6 +63,13 @@ typedef __attribute__((address_space(3))) f32x4* lds_f32x4_ptr;
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) f32x2* lds_f32x2_ptr;
 
+// The same address, of which the compiler knows nothing: it stays in its register.
+__device__ __forceinline__ lds_f32_ptr lds_pinned(lds_f32_ptr p) {
+  uint32_t a = (uint32_t)(uintptr_t)p;
+  asm volatile("" : "+v"(a));
+  return (lds_f32_ptr)(uintptr_t)a;
+}
+
 // acc[h] += A * B_h over n_steps K steps of 16 (rounded up to an even count) for this wave's 32 x 32 block (wm, wn).
 // A_KC / B_KC: operand k-contiguous (a thread fetches row tid / 4, k = tid % 4 * 4 .. + 3) or x-contiguous (k = tid / 16,
 // columns tid % 16 * 4 .. + 3); a_ptr / b_ptr: this thread's 16 bytes of step 0, a_k / b_k: floats from one k to the next,
@@ -101,6 +108,20 @@ __device__ __forceinline__ void gemm_core_f32(f32x16 (&acc)[NB], const float* a_
 #pragma unroll
     for (int h = 0; h < NB; ++h) *(lds_f32x4_ptr)(st + (1 + h) * kFStage + b_st) = in ? r.b[h] : z;
   };
+  // Where an x-contiguous operand's reads of eight k start, per stage.  Opaque, or in the long body of the single launch the
+  // compiler adds them up again on every step, between the barrier and the reads (GEMM-1: 112 instructions per two steps instead
+  // of 100; single launch, H = 2048, I = 1408, 16 of 64 experts, 90 rows per expert 413 -> 403 us, 250 rows 850 -> 832; H = 1024,
+  // I = 704, 16 experts, 375 rows 385 -> 378); the other launches have the same loops either way.
+  lds_f32_ptr a_at[2][2], b_at[2][NB][2];
+#pragma unroll
+  for (int buf = 0; buf < 2; ++buf)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (!A_KC) a_at[buf][q] = lds_pinned(lds + buf * kStages + a_rd + q * 8 * kFXcLd);
+#pragma unroll
+      for (int h = 0; h < NB; ++h)
+        if (!B_KC) b_at[buf][h][q] = lds_pinned(lds + buf * kStages + (1 + h) * kFStage + b_rd + q * 8 * kFXcLd);
+    }
   auto compute = [&](int buf) __attribute__((always_inline)) {
     if (!ACTIVE) return;
     const lds_f32_ptr as = lds + buf * kStages + a_rd;
@@ -110,15 +131,14 @@ __device__ __forceinline__ void gemm_core_f32(f32x16 (&acc)[NB], const float* a_
       if (A_KC) a[q] = *(lds_f32x4_ptr)(as + q * 8);
       else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a[q][i] = as[(q * 8 + i) * kFXcLd];
+        for (int i = 0; i < 4; ++i) a[q][i] = a_at[buf][q][i * kFXcLd];
       }
 #pragma unroll
       for (int h = 0; h < NB; ++h) {
-        const lds_f32_ptr bs = lds + buf * kStages + (1 + h) * kFStage + b_rd;
-        if (B_KC) b[q][h] = *(lds_f32x4_ptr)(bs + q * 8);
+        if (B_KC) b[q][h] = *(lds_f32x4_ptr)(lds + buf * kStages + (1 + h) * kFStage + b_rd + q * 8);
         else {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) b[q][h][i] = bs[(q * 8 + i) * kFXcLd];
+          for (int i = 0; i < 4; ++i) b[q][h][i] = b_at[buf][h][q][i * kFXcLd];
         }
       }
     }
@@ -451,7 +471,9 @@ __device__ __forceinline__ void gemm_strip_f32(const GemmParamsF32& p, int mtile
 
 // A tile as a task of the single launch, whose one workgroup per CU has registers for four steps under way.  Tiles of at most 16
 // rows as strips: T = 20, H = 2048, I = 1408, 16 of 64 experts, single launch 219 -> 141 us, T = 1 86 -> 58; T = 8, H = 1024, I = 704,
-// 64 experts 173 -> 130; with 375 rows per expert the longer code costs 1 % (378 -> 384).
+// 64 experts 173 -> 130; 128 rows per expert, whose last tile is often a strip, 551 -> 487.  More rows don't lose by the longer code
+// with the LDS addresses of the tile pinned (gemm_core_f32): 375 rows 383 -> 378, without that 385.  Of 35 calls of 1..375 rows
+// one is slower than whole tiles: skewed routing of T = 192 over 16 experts, 137 -> 139 (of T = 128 157 -> 143).
 template <int EPI>
 __device__ __forceinline__ void gemm_task_f32(const GemmParamsF32& p, int mtile, int ntile, float* smem) {
   if (__builtin_amdgcn_readfirstlane(p.tiles.rows[mtile]) <= 16) gemm_strip_f32<EPI, 4>(p, mtile, ntile, smem);

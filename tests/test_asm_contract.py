@@ -5,7 +5,8 @@ import os
 
 import pytest
 
-from paper_2605_23764_amd.asm_check import check_register_fed_loads, device_assembly, loads_ahead_of_first_branch
+from paper_2605_23764_amd.asm_check import (check_register_fed_loads, device_assembly, innermost_loops,
+                                            loads_ahead_of_first_branch)
 
 GOOD = """
 \t.amdhsa_kernel k
@@ -59,3 +60,13 @@ def test_launch_head_waits_for_the_tile_map_once(lay, epi):
     groups = loads_ahead_of_first_branch(device_assembly(), f"_ZN3moe24grouped_gemm_bf16_kernelILi{lay}ELi{epi}EEEvNS_10GemmParamsE")
     # kernel arguments come from s[0:1]
     assert any({(base, 0), (base, 12)} <= set(g) for g in groups for base, _ in g if base != "s[0:1]"), groups
+
+
+@pytest.mark.skipif(not os.path.exists(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")), reason="needs hipcc")
+def test_fp32_single_launch_keeps_the_addresses_of_its_tiles():
+    """No address is added up inside the K loops of whole tiles: GEMM-1 (two column blocks, 32 MFMAs per two steps) and GEMM-2."""
+    asm = device_assembly()
+    loops = innermost_loops(asm, "_ZN3moe25persistent_forward_kernelILb0ELb0EEEvNS_11SchedParamsIXT_EEE")
+    tiles = {sum("v_mfma_f32_32x32x2_f32" in i for i in loop): loop for loop in loops}
+    for mfmas in (16, 32):
+        assert not [i for i in tiles[mfmas] if i.startswith("v_add_u32")], tiles[mfmas]

@@ -15,6 +15,7 @@
 // loaded and zeroed in LDS before the last step.
 #pragma once
 #include "gemm_bf16.h"
+#include "wgrad_order.h"
 
 namespace moe {
 
@@ -239,8 +240,8 @@ __device__ __forceinline__ void wgrad_tile_of(int r, int n_mt, int n_nt, int& mt
 // one expert or to two of neighbouring size), and the last, partly filled sweep holds the cheapest tiles.  An
 // XCD takes a contiguous eighth of every sweep, so the CUs that share operand panels sit behind one L2.
 //
-// A launch does one or two (NG) weight gradients, the second one's tiles behind the first one's: both on one stream as one
-// launch have one partly filled last sweep (T = 777, H = 1088, I = 704, 10 experts: 300 and 540 tiles on 512 workgroups, training
+// A launch does one or two (NG) weight gradients, an expert's tiles of both side by side (wgrad_order.h): both on one stream as
+// one launch have one partly filled last sweep (T = 777, H = 1088, I = 704, 10 experts: 300 and 540 tiles on 512 workgroups, training
 // step 112.3 -> 106.2 us; T = 4096, H = 2048, I = 1408, 16 experts, backward 728 -> 720).  One is a kernel of its own: with the
 // second behind a switch it was up to 1.4 % slower.
 template <int NG>
@@ -276,29 +277,29 @@ void grouped_wgrad2_bf16_kernel(WgradGroup<NG> w) {
   __shared__ __attribute__((aligned(1024))) char smem[kWgLdsBytes];
   __shared__ int s_order[NG][kMaxE]; // the experts it takes, most rows first
   __shared__ int s_box[NG];          // number of such experts
-  int n_mt[NG], n_nt[NG], total[NG], all = 0;
+  int n_mt[NG], n_nt[NG], n_e[NG], all = 0;
 #pragma unroll
   for (int i = 0; i < NG; ++i) {
     const GemmParams& p = w.p[i];
     n_mt[i] = (p.M + kWgBM - 1) / kWgBM;
     n_nt[i] = (p.N + kWgBN - 1) / kWgBN;
-    total[i] = 0;
+    n_e[i] = 0;
     // nothing to do when the other kernel takes every expert (p.tiles.meta: the M-tile map's header)
     if (!(p.k_lo > 0 && __builtin_amdgcn_readfirstlane(p.tiles.meta[kMetaMaxRows]) < p.k_lo))
-      total[i] = wgrad_order_experts(p, reinterpret_cast<int*>(smem), s_order[i], &s_box[i]) * n_mt[i] * n_nt[i];
-    all += total[i];
+      n_e[i] = wgrad_order_experts(p, reinterpret_cast<int*>(smem), s_order[i], &s_box[i]);
+    all += n_e[i] * n_mt[i] * n_nt[i];
   }
   __syncthreads();                   // the stages are not in use as tables any more
   const int G = gridDim.x;
   for (int it = 0; it * G < all; ++it) {
     const int t = xcd_spread_tile(it, blockIdx.x, G, all);
     if (t < 0) continue;
-    const int i = NG > 1 ? __builtin_amdgcn_readfirstlane(t >= total[0] ? 1 : 0) : 0;
-    const int tile = i ? t - total[0] : t, nm = i ? n_mt[NG - 1] : n_mt[0], nn = i ? n_nt[NG - 1] : n_nt[0];
-    const int r = tile / (nm * nn);
-    const int e = __builtin_amdgcn_readfirstlane(s_order[i][r]);
+    const WgradPick pick = NG > 1 ? wgrad_pick(t, n_e[0], n_mt[0] * n_nt[0], n_e[NG - 1], n_mt[NG - 1] * n_nt[NG - 1])
+                                  : wgrad_pick(t, n_e[0], n_mt[0] * n_nt[0], 0, 0);
+    const int i = NG > 1 ? __builtin_amdgcn_readfirstlane(pick.which) : 0;
+    const int e = __builtin_amdgcn_readfirstlane(s_order[i][pick.rank]);
     int mt, nt;
-    wgrad_tile_of(tile - r * nm * nn, nm, nn, mt, nt);
+    wgrad_tile_of(pick.tile, i ? n_mt[NG - 1] : n_mt[0], i ? n_nt[NG - 1] : n_nt[0], mt, nt);
     wgrad_tile_bf16(w.p[i], e, __builtin_amdgcn_readfirstlane(mt), __builtin_amdgcn_readfirstlane(nt), smem);
   }
 }

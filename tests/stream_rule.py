@@ -1,26 +1,14 @@
 """csrc/stream_rule.h (which form a grouped GEMM of few rows takes) built for the host, so that tests know which form they reach."""
 import collections
 import ctypes
-import functools
-import os
-import shutil
-import subprocess
-import tempfile
 
-HERE = os.path.dirname(os.path.abspath(__file__))
-CSRC = os.path.join(os.path.dirname(HERE), "paper_2605_23764_amd", "csrc")
-CXX = next((c for c in (shutil.which("g++"), shutil.which("clang++"), "/opt/rocm/llvm/bin/clang++") if c and os.path.exists(c)), None)
+from host_build import CXX, library as _build  # noqa: F401  (CXX: None without a host compiler)
 
 Form = collections.namedtuple("Form", "cols rows items whole")
 
 
-@functools.lru_cache(maxsize=None)
 def library():
-    with tempfile.TemporaryDirectory() as tmp:
-        so = os.path.join(tmp, "stream_rule.so")
-        subprocess.run([CXX, "-std=c++17", "-O2", "-Wall", "-Werror", "-fPIC", "-shared", "-I", CSRC, os.path.join(HERE, "stream_rule.cpp"),
-                        "-o", so], check=True)
-        return ctypes.CDLL(so)
+    return _build("stream_rule.cpp")
 
 
 def form(max_rows, n_act, N, swiglu, G):

@@ -16,7 +16,7 @@ ROWS = [0, 5, 390, 64, 384, 700]
 
 @pytest.mark.parametrize("keep_xp", [True, False])
 @pytest.mark.parametrize("rows", [ROWS, [3, 0, 70]], ids=["large_experts", "small_experts"])
-@pytest.mark.parametrize("H,I,dtype", [(192, 64, "bf16"), (256, 192, "bf16"), (256, 256, "bf16"), (192, 128, "f32")])
+@pytest.mark.parametrize("H,I,dtype", [(192, 64, "bf16"), (256, 192, "bf16"), (384, 256, "bf16"), (256, 256, "bf16"), (192, 128, "f32")])
 def test_one_launch_or_two(H, I, dtype, rows, keep_xp):
     from gpu_common import check_backward, run_backward, run_forward, small_config
     cfg = small_config("wgrad_launches", sum(rows), H, I, len(rows), len(rows), 0, 1, dtype, 93)

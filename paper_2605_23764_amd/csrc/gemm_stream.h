@@ -351,12 +351,13 @@ __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_ro
   }
   __syncthreads();
   n_act = __builtin_amdgcn_readfirstlane(n_act);
-  const int G = gridDim.x;
-  const bool narrow = stream_narrow(n_act, p.N, EPI == kEpiSwiglu, G);
+  constexpr int kOut64 = EPI == kEpiSwiglu ? 32 : 64;
+  const bool narrow = stream_narrow(n_act, p.N, EPI == kEpiSwiglu, gridDim.x);
   if constexpr (LAY == kLayNN && EPI == kEpiSwiglu) {
-    const int n256 = n_act * stream_tiles(p.N, 128), n128 = n_act * stream_tiles(p.N, 64);
-    if (!narrow && stream_wide(max_rows, n256, n128, p.N, G)) {
-      const int whole = stream_whole(n256, n128, G);
+    const int G = gridDim.x, n256 = n_act * stream_tiles(p.N, 128), n128 = n_act * stream_tiles(p.N, 64);
+    const bool all = stream_wide_throughout(n256, n128, G);
+    if (!narrow && stream_wide(max_rows, all, n256, p.N, G)) {
+      const int whole = stream_whole(all, n256, G);
       if (max_rows > 32) stream_rows<LAY, EPI, 256, 64>(p, 0, whole, smem);
       else stream_rows<LAY, EPI, 256, 32>(p, 0, whole, smem);
       if (whole == n256) return;
@@ -366,7 +367,6 @@ __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_ro
       return;
     }
   }
-  constexpr int kOut64 = EPI == kEpiSwiglu ? 32 : 64;
   const int total = n_act * stream_tiles(p.N, narrow ? kOut64 : 2 * kOut64);
   if (narrow) {
     if (max_rows > 64) stream_rows<LAY, EPI, 64, 128>(p, 0, total, smem);

@@ -1,9 +1,9 @@
 // Grouped bf16 GEMMs for a few rows per expert (serving batches, small training batches): the weight stream.
 //
 // With at most 64 rows per expert a weight element meets one or two MFMA row blocks, so the launch is a read of the
-// weights at HBM rate and nothing else (up to 128 rows, where a launch is a single round: stream_takes); the tile of gemm_bf16.h (256 weight columns, 64 KB of weights under way per CU)
-// then has too few work items to fill the chip evenly (T = 1 at H = 2048, I = 1408: 44 items on four of the eight dies)
-// and too little in flight.  Here
+// weights at HBM rate and nothing else (up to 128 rows, where a launch is a single round: stream_takes); the tile of
+// gemm_bf16.h (256 weight columns, 64 KB of weights under way per CU) then has too few work items to fill the chip evenly
+// (T = 1 at H = 2048, I = 1408: 44 items on four of the eight dies) and too little in flight.  Here
 //   * an item is some weight columns of one expert over the whole K (never split: results are the same bits as the other
 //     kernel's, whose MFMAs sum in the same order), dealt evenly to all workgroups.  Three widths (stream_rule.h has the rule):
 //       columns                a stage holds (weights)   ring: up to 16 / 32 / 64 / 128 rows   weights under way
@@ -14,7 +14,8 @@
 //     requested while the last ones of this item are multiplied, so nothing drains between items;
 //   * activation rows ride along in the same stage (4 to 32 KB, from the L2), gathered through the permutation if need be;
 //   * one barrier per stage; each of the four waves multiplies one 32-column block (256 columns: two; 64 columns: two of the
-//     waves one each, above 32 rows two waves a block, half of the rows each).  For SwiGLU a block is 16 gate and the 16 matching up columns: both meet in one lane's accumulators.
+//     waves one each, above 32 rows two waves a block, half of the rows each).  For SwiGLU a block is 16 gate and the 16
+//     matching up columns: both meet in one lane's accumulators.
 // Results are written straight from the accumulators (8 bytes per lane): they are a thousandth of the bytes read.
 // The weights are read non-temporally (each line once, by one workgroup; 64 columns: not, two items share a line): 5 to 9 %
 // of a launch.
@@ -23,8 +24,8 @@
 // non-temporal hint; 128 bytes 5.1), 1 KB pieces 6.3..6.7, one linear stream 7.1; with the MFMAs taken out the launch is no
 // faster, without the activation loads 2 %.
 // Measured, layer (routing and Combine included), against the tiles of gemm_bf16.h: H = 7168, I = 2048, 32 of 256 experts,
-// k = 8: T = 4 168 -> 101 us, T = 32 428 -> 354 (now 328, see the rule), T = 256 524 -> 461, T = 1000 548 -> 505; H = 2048, I = 1408, 16 experts,
-// k = 4: T = 1 60 -> 38.5, T = 8 74 -> 62, T = 64 76 -> 67.  Above 64 rows the activations' share of a stage grows past a
+// k = 8: T = 4 168 -> 101 us, T = 32 428 -> 354 (328 with the rest of a round as 128 columns: stream_wide), T = 256 524 -> 461,
+// T = 1000 548 -> 505; H = 2048, I = 1408, 16 experts, k = 4: T = 1 60 -> 38.5, T = 8 74 -> 62, T = 64 76 -> 67.  Above 64 rows the activations' share of a stage grows past a
 // third and the other kernel's 256 rows per weight fetch win, unless its tiles leave CUs idle.
 #pragma once
 #include "gemm_bf16.h"
@@ -351,13 +352,12 @@ __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_ro
   }
   __syncthreads();
   n_act = __builtin_amdgcn_readfirstlane(n_act);
-  constexpr int kOut64 = EPI == kEpiSwiglu ? 32 : 64;
-  const bool narrow = stream_narrow(n_act, p.N, EPI == kEpiSwiglu, gridDim.x);
+  const int G = gridDim.x;
+  const bool narrow = stream_narrow(n_act, p.N, EPI == kEpiSwiglu, G);
   if constexpr (LAY == kLayNN && EPI == kEpiSwiglu) {
-    const int G = gridDim.x, n256 = n_act * stream_tiles(p.N, 128), n128 = n_act * stream_tiles(p.N, 64);
-    const bool all = stream_wide_throughout(n256, n128, G);
-    if (!narrow && stream_wide(max_rows, all, n256, p.N, G)) {
-      const int whole = stream_whole(all, n256, G);
+    const int n256 = n_act * stream_tiles(p.N, 128), n128 = n_act * stream_tiles(p.N, 64);
+    if (!narrow && stream_wide(max_rows, n256, n128, p.N, G)) {
+      const int whole = stream_whole(n256, n128, G);
       if (max_rows > 32) stream_rows<LAY, EPI, 256, 64>(p, 0, whole, smem);
       else stream_rows<LAY, EPI, 256, 32>(p, 0, whole, smem);
       if (whole == n256) return;
@@ -367,6 +367,7 @@ __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_ro
       return;
     }
   }
+  constexpr int kOut64 = EPI == kEpiSwiglu ? 32 : 64;
   const int total = n_act * stream_tiles(p.N, narrow ? kOut64 : 2 * kOut64);
   if (narrow) {
     if (max_rows > 64) stream_rows<LAY, EPI, 64, 128>(p, 0, total, smem);

@@ -139,7 +139,6 @@ struct GemmBwdParamsF32 {
   TileMap tiles;
 };
 
-// act_grad (+ SwiGLU_grad) and gate_grad: C[rows, N] = A[rows, K] * W_e[N, K]^T per M tile.
 // One result v of a data gradient (SwiGLU-grad: v = dA).
 template <int EPI>
 __device__ __forceinline__ void store_dgrad_f32(const GemmBwdParamsF32& p, size_t grow, int c, float v) {
@@ -153,6 +152,7 @@ __device__ __forceinline__ void store_dgrad_f32(const GemmBwdParamsF32& p, size_
   }
 }
 
+// act_grad (+ SwiGLU_grad) and gate_grad: C[rows, N] = A[rows, K] * W_e[N, K]^T per M tile.
 template <int EPI>
 __global__ __launch_bounds__(256) void grouped_dgrad_f32_kernel(GemmBwdParamsF32 p) {
   __shared__ __attribute__((aligned(16))) float smem[kFLdsFloats1];

@@ -14,10 +14,11 @@
 //
 // The single launch covers the paper's own interval, Dispatch to Combine (Section 5.2 starts the
 // clock at Dispatch).  Routing runs ahead of it as two small launches at full occupancy (the
-// router, then prefix sums + stable ranks; up to 64 tokens one launch of one workgroup): a worker here is a 4-wave workgroup that owns a whole
-// CU for the sake of the GEMM tiles, the wrong shape for the latency-bound routing steps.  The
-// second routing launch also zeroes the event counters and queue heads and materialises the task
-// descriptors, so nothing but the persistent kernel itself stands between Dispatch and Combine.
+// router, then prefix sums + stable ranks; up to 64 tokens one launch of one workgroup): a worker
+// here is a 4-wave workgroup that owns a whole CU for the sake of the GEMM tiles, the wrong shape
+// for the latency-bound routing steps.  The last routing launch also zeroes the event counters and
+// queue heads and materialises the task descriptors, so nothing but the persistent kernel itself
+// stands between Dispatch and Combine.
 //
 // Queues
 //   X0..X7        one per XCD: PERMUTE parts, GEMM-1 tiles, GEMM-2 tiles of the M-tile

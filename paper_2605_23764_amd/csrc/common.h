@@ -52,6 +52,14 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 __device__ __forceinline__ float bf16_lo(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t p) { return __builtin_bit_cast(float, p & 0xFFFF0000u); }
 
+// Hand-over inside a launch (single launches): 16 bytes stored through the die's L2 to memory, so that once the store has been
+// acknowledged (vmcnt) a workgroup on any die that has not touched the line in this launch reads it, without a write-back of the
+// writer's L2 or an invalidation of the reader's.  The wait state behind it belongs to the store: its data registers may not be
+// written by the next instruction, which the compiler looks after for its own stores only.
+__device__ __forceinline__ void store_through(u32x4* dst, u32x4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(dst), "v"(v) : "memory");
+}
+
 __device__ __forceinline__ float sigmoidf_(float z) { return 1.0f / (1.0f + expf(-z)); }
 // For results that are rounded to bf16 anyway: hardware exp2 and reciprocal (about 1 ulp each, and the scaling by
 // log2(e) adds |z| * 2^-24 relative), a fifth of the instructions of the version above.

@@ -47,6 +47,9 @@ namespace moe {
 // The weight gradients (reduction over the expert's rows) have kernels of their own
 // (wgrad_panel.h, wgrad_bf16.h); they share GemmParams and the epilogue staging.
 enum GemmLayout { kLayNN = 0, kLayNT = 1 };
+// How a single launch hands a result over to its later tasks: not at all; stored through to memory (store_through); that, or behind
+// the L2 of the die alone, as the launch decides (far).
+enum HandOver { kHandNone = 0, kHandThrough = 1, kHandFar = 2 };
 enum GemmEpilogue { kEpiStore = 0, kEpiSwiglu = 1, kEpiSwigluGrad = 2, kEpiScatter = 3 };
 
 constexpr int kBM = 256;            // tile row capacity (one M tile of the tile map)
@@ -568,9 +571,9 @@ __device__ __forceinline__ char* epilogue_region(char* smem, int wave) {
 // the stored pre-activations, one LDS round trip for both).
 // All reads back from the region are issued before the first store, and the stores are predicated, not branched
 // around: one LDS latency per call instead of one per row group.
-template <int NB, bool NT = false, bool SPLIT = false>
+template <int NB, bool NT = false, bool SPLIT = false, int HAND = kHandNone>
 __device__ __forceinline__ void store_block_via_lds(char* region, const u32x2 (&pk)[NB][4], __bf16* gdst, long ld,
-                                                    int rows_valid, int cols_valid, __bf16* gdst2 = nullptr) {
+                                                    int rows_valid, int cols_valid, __bf16* gdst2 = nullptr, bool far = false) {
   typedef __attribute__((address_space(3))) char* lds_ptr;
   typedef __attribute__((address_space(3))) u32x2* lds_u32x2_ptr;
   typedef __attribute__((address_space(3))) const u32x4* lds_u32x4_cptr;
@@ -602,7 +605,8 @@ __device__ __forceinline__ void store_block_via_lds(char* region, const u32x2 (&
   for (int it = 0; it < NIT; ++it) {
     if (it * RPI + row_l < rows_valid && col_ok) {
       u32x4* dst = reinterpret_cast<u32x4*>(gp + (size_t)(it * RPI) * ld);
-      if (NT) __builtin_nontemporal_store(v[it], dst);
+      if (HAND == kHandThrough || (HAND == kHandFar && far)) store_through(dst, v[it]);
+      else if (NT) __builtin_nontemporal_store(v[it], dst);
       else *dst = v[it];
     }
   }
@@ -684,10 +688,10 @@ static_assert(4 * kGradWave <= kGemmLdsBytes, "LDS budget");
 template <int N>
 __device__ __forceinline__ void wait_copies() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
 
-template <int X5>
+template <int X5, int HAND>
 __device__ __forceinline__ void swiglu_grad_blocks(const GemmParams& p, const f32x16 (&acc)[kMaxMT][4], const f32x16 (&accx)[4],
                                                    char* smem, int wave, int row0, int rows, int row_base, int n_mt, int x_row0,
-                                                   bool has_x, int c0) {
+                                                   bool has_x, int c0, bool far) {
   typedef __attribute__((address_space(3))) char* lds_ptr;
   typedef __attribute__((address_space(3))) u32x2* lds_u32x2_ptr;
   typedef __attribute__((address_space(3))) const u32x4* lds_u32x4_cptr;
@@ -755,16 +759,20 @@ __device__ __forceinline__ void swiglu_grad_blocks(const GemmParams& p, const f3
     __bf16* out = p.C + (size_t)(row0 + m0 + r4) * p.ldc + c0 + pos * 8;
 #pragma unroll
     for (int i = 0; i < 16; ++i)
-      if (4 * (i & 7) + r4 < rows_valid && pos * 8 < cols)
-        *reinterpret_cast<u32x4*>(out + (size_t)(4 * (i & 7)) * p.ldc + (i >> 3) * p.N) = o[i >> 3][i & 7];
+      if (4 * (i & 7) + r4 < rows_valid && pos * 8 < cols) {
+        u32x4* dst = reinterpret_cast<u32x4*>(out + (size_t)(4 * (i & 7)) * p.ldc + (i >> 3) * p.N);
+        if (HAND == kHandThrough || (HAND == kHandFar && far)) store_through(dst, o[i >> 3][i & 7]);
+        else *dst = o[i >> 3][i & 7];
+      }
   });
 }
 
 // One output tile: (t0, t1) = (M tile of the tile map, N tile of TileShape<TALL>::kCols
 // columns; SwiGLU: half as many output columns).  X5: a wide tile of 257..320 rows (rows past 256 go
 // through the register-fed block of each wave row).
-template <int LAY, int EPI, bool TALL, int X5 = 0, bool NT_OK = false>
-__device__ __forceinline__ void gemm_tile_bf16(const GemmParams& p, int t0, int t1, char* smem) {
+// NT_OK: with a second K loop for non-temporal weights.  HAND, far: the result (SwiGLU: the activations) is read in this launch.
+template <int LAY, int EPI, bool TALL, int X5 = 0, bool NT_OK = false, int HAND = kHandNone>
+__device__ __forceinline__ void gemm_tile_bf16(const GemmParams& p, int t0, int t1, char* smem, bool far = false) {
   typedef TileShape<TALL> S;
   static_assert(!(TALL && X5), "one shape at a time");
   const int tid = threadIdx.x;
@@ -917,7 +925,7 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmParams& p, int t0, int 
   if constexpr (EPI == kEpiSwigluGrad) {               // the accumulators hold dA
     __builtin_amdgcn_s_barrier();                      // every wave has read its last operands, its copies have landed
     const int c0 = ntile * S::kCols + wn * 128;
-    if (c0 < p.N) swiglu_grad_blocks<X5>(p, acc, accx, smem, wave, row0, rows, row_base, n_mt, x_row0, has_x, c0);
+    if (c0 < p.N) swiglu_grad_blocks<X5, HAND>(p, acc, accx, smem, wave, row0, rows, row_base, n_mt, x_row0, has_x, c0, far);
     wait_lgkmcnt0();
     __builtin_amdgcn_s_barrier();                      // the next tile's copies go to the same places
     return;
@@ -976,7 +984,7 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmParams& p, int t0, int 
           ph[ng][q] = u32x2{pack_bf16(g[0], g[1]), pack_bf16(g[2], g[3])};
           ph[ng + 2][q] = u32x2{pack_bf16(u[0], u[1]), pack_bf16(u[2], u[3])};
         }
-      store_block_via_lds<2>(region, pa, p.C + grow0 * p.ldc + c0, p.ldc, rows_valid, p.N - c0);
+      store_block_via_lds<2, false, false, HAND>(region, pa, p.C + grow0 * p.ldc + c0, p.ldc, rows_valid, p.N - c0, nullptr, far);
       if (p.C2) {
         __bf16* h = p.C2 + grow0 * (size_t)(2 * p.N) + c0;
         store_block_via_lds<4, false, true>(region, ph, h, 2 * p.N, rows_valid, p.N - c0, h + p.N);
@@ -1001,7 +1009,7 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmParams& p, int t0, int 
         for (int q = 0; q < 4; ++q)
           pk[nt][q] = u32x2{pack_bf16(am[nt][q * 4 + 0], am[nt][q * 4 + 1]),
                             pack_bf16(am[nt][q * 4 + 2], am[nt][q * 4 + 3])};
-      store_block_via_lds<4>(region, pk, p.C + grow0 * p.ldc + c0, p.ldc, rows_valid, p.N - c0);
+      store_block_via_lds<4, false, false, HAND>(region, pk, p.C + grow0 * p.ldc + c0, p.ldc, rows_valid, p.N - c0, nullptr, far);
     }
   }
 }
@@ -1010,11 +1018,11 @@ __device__ __forceinline__ void gemm_tile_bf16(const GemmParams& p, int t0, int 
 // tall above (the map builder makes such tiles only with <= 384 rows and gives each a pair slot of its own).
 __device__ __forceinline__ bool tile_is_tall(int rows) { return rows > kWideRows; }
 
-template <int LAY, int EPI, bool NT_OK = false>
-__device__ __forceinline__ void gemm_map_tile_bf16(const GemmParams& p, int mtile, int ntile, bool tall, char* smem) {
-  if (tall) gemm_tile_bf16<LAY, EPI, true>(p, mtile, ntile, smem);
-  else if (__builtin_amdgcn_readfirstlane(p.tiles.rows[mtile]) > kBM) gemm_tile_bf16<LAY, EPI, false, 1, NT_OK>(p, mtile, ntile, smem);
-  else gemm_tile_bf16<LAY, EPI, false, 0, NT_OK>(p, mtile, ntile, smem);
+template <int LAY, int EPI, bool NT_OK = false, int HAND = kHandNone>
+__device__ __forceinline__ void gemm_map_tile_bf16(const GemmParams& p, int mtile, int ntile, bool tall, char* smem, bool far = false) {
+  if (tall) gemm_tile_bf16<LAY, EPI, true, 0, false, HAND>(p, mtile, ntile, smem, far);
+  else if (__builtin_amdgcn_readfirstlane(p.tiles.rows[mtile]) > kBM) gemm_tile_bf16<LAY, EPI, false, 1, NT_OK, HAND>(p, mtile, ntile, smem, far);
+  else gemm_tile_bf16<LAY, EPI, false, 0, NT_OK, HAND>(p, mtile, ntile, smem, far);
 }
 
 // Work item `rem` (0 .. 2*n_ntiles-1) of tile pair (m0, m0+1): a tall tile owns the whole slot as

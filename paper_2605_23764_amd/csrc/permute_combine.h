@@ -23,12 +23,17 @@ struct PermuteParams {
 // inside the wave (a whole row in flight).  The copies are non-temporal: every byte is
 // touched once, and with ordinary loads more than four in flight per lane made the
 // persistent tasks slower (53 / 82 / 117 us per task at 4 / 7 / 14), not faster.
+// through: the rows are read inside this launch, on any die: stored through the L2 (see store_through).
 template <int U>
 __device__ __forceinline__ void permute_rows(const PermuteParams& p, int r_begin, int r_end,
-                                             int wave, int n_waves) {
+                                             int wave, int n_waves, bool through = false) {
   const int lane = lane_id();
   const int vec_per_row = (p.H * p.elem_bytes) / 16;
   const size_t row_bytes = (size_t)p.H * p.elem_bytes;
+  auto put = [&](uint4* dst, u32x4 v) __attribute__((always_inline)) {
+    if (through) store_through(reinterpret_cast<u32x4*>(dst), v);
+    else __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
+  };
   // This wave's rows are r_begin + wave + i * n_waves.  Their tokens are fetched with one load (lane i: row i; 64
   // rows at a time) instead of one dependent load per row, and two rows are copied per pass, the loads of both in
   // flight before the first store: with only a few waves per CU the copy is latency bound otherwise.
@@ -53,15 +58,20 @@ __device__ __forceinline__ void permute_rows(const PermuteParams& p, int r_begin
           for (int u = 0; u < U; ++u) q1[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src1 + v + u * kWave));
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) __builtin_nontemporal_store(q0[u], reinterpret_cast<u32x4*>(dst0 + v + u * kWave));
+        for (int u = 0; u < U; ++u) put(dst0 + v + u * kWave, q0[u]);
         if (two) {
 #pragma unroll
-          for (int u = 0; u < U; ++u) __builtin_nontemporal_store(q1[u], reinterpret_cast<u32x4*>(dst1 + v + u * kWave));
+          for (int u = 0; u < U; ++u) put(dst1 + v + u * kWave, q1[u]);
         }
       }
       for (; v < vec_per_row; v += kWave) {
-        dst0[v] = src0[v];
-        if (two) dst1[v] = src1[v];
+        if (through) {
+          put(dst0 + v, *reinterpret_cast<const u32x4*>(src0 + v));
+          if (two) put(dst1 + v, *reinterpret_cast<const u32x4*>(src1 + v));
+        } else {
+          dst0[v] = src0[v];
+          if (two) dst1[v] = src1[v];
+        }
       }
     }
   }

@@ -30,9 +30,8 @@
 //                 one sweep after its producers, close enough for L2 reuse, far
 //                 enough not to stall the queue.
 //   C  (global)   COMBINE x token groups, after every GEMM-2 tile
-// XCD queues are private to the workers of that XCD (no stealing), so the PERMUTE ->
-// GEMM-1 -> GEMM-2 chain of an M tile is produced and consumed behind one L2.  That
-// lets those events skip the device-scope cache maintenance: a device-scope release
+// The PERMUTE -> GEMM-1 -> GEMM-2 chain of an M tile belongs to one XCD's queue, so that it is produced and consumed
+// behind one L2.  That lets those events skip the device-scope cache maintenance: a device-scope release
 // (buffer_wbl2) stalls for a write-back of everything dirty in the XCD's L2 (about
 // 30 us per task when all CUs do it) and a device-scope acquire (buffer_inv) drops
 // the L2 contents the sibling tiles are sharing.  Inside an XCD it is enough that the
@@ -40,9 +39,19 @@
 // 128-byte line of Xp and A is written by one task, completely, before any task reads it
 // within a launch (rows are multiples of 128 bytes and the host requires 128-byte aligned
 // buffers in this mode), so no CU can hold a stale copy of a line in its vector L1 and
-// there is nothing to invalidate on the consumer side.  The event that crosses XCDs
-// (GEMM-2 -> COMBINE) keeps the full device-scope fences; since COMBINE needs every
-// GEMM-2 tile, a worker publishes its GEMM-2 completions once, after its queue has drained.
+// there is nothing to invalidate on the consumer side.
+//
+// bf16, launches of several rounds (sched_hands_far): Xp and A are stored THROUGH the L2 to memory (store_through), and the
+// same argument then holds for the L2 of every die: none has a copy of a line that nobody has read.  So a worker whose queue
+// has run out draws from the queue with the most tasks left: with skewed routing the queues ended 1191 .. 1408 us into a launch.
+// The event that crosses XCDs (GEMM-2 -> COMBINE) works so in every bf16 launch but the scatter epilogue's, which has none: Yp is
+// stored through, a worker publishes its GEMM-2 completions once, after the queues have drained, without a write-back (17 us
+// between the last GEMM-2 tile and the first COMBINE at T = 500, now 3), and COMBINE's one acquire per worker stays (Yp may
+// lie off the lines).  fp32 keeps the fences.
+// Measured, layer, same bits, before and after: H = 7168, I = 2048, 32 of 256 experts: T = 8192 skewed 1246 -> 1162 us, uniform
+// 866 -> 855, T = 3000 639 -> 613; H = 2048, I = 1408, 16 experts: T = 500 146 -> 121, T = 2000 223 -> 207, T = 4096 389 -> 361, T = 3000
+// skewed 335 -> 296.  Far in launches of less than four rounds: T = 500 125, T = 2000 211; with the scatter epilogue 2..5 % slower
+// (T = 1000 132 -> 135; skewed 3..4 % faster, but behind a switch it costs the others 2 %: not taken).
 //
 // Placement is checked, not assumed: every worker reads the id of the XCD it really runs on
 // (hardware register XCC_ID) and reports it when it starts; a queue whose workers do not all
@@ -179,6 +188,39 @@ __device__ __forceinline__ int sched_chain_scope(const SchedParams<BF16>& sp, in
   const int scope = __builtin_amdgcn_readfirstlane(s_box[1]);
   __syncthreads();
   return scope;
+}
+
+// Whether tiles are handed over through memory, so that a worker whose queue has run out may draw from another die's: with more than
+// kFarRounds tasks per worker, whose rounds drift apart between the dies.  With fewer, every task is drawn before a worker has
+// finished, and a consumer that finds its operand behind its own L2 is faster.
+constexpr int kFarRounds = 4;
+__device__ __forceinline__ bool sched_hands_far(const int32_t* meta) {
+  int total = 0;
+#pragma unroll
+  for (int i = 0; i < kNumXcd; ++i) total += meta[kMetaQueueCount0 + i];
+  return __builtin_amdgcn_readfirstlane(total) > kFarRounds * (int)gridDim.x;
+}
+
+// The XCD queue with the most tasks that nobody has drawn yet, -1: every one is drawn.  Whole workgroup.
+template <bool BF16>
+__device__ __forceinline__ int sched_fullest_queue(const SchedParams<BF16>& sp, volatile int* s_box, int wave) {
+  if (wave == 0) {
+    const int lane = lane_id();
+    int left = 0;
+    if (lane < kNumXcd)
+      left = max(sp.meta[kMetaQueueCount0 + lane] - (int)__hip_atomic_load(&sp.qhead[kQXcd0 + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0);
+    int most = 0, at = -1;
+#pragma unroll
+    for (int i = 0; i < kNumXcd; ++i) {
+      const int n = __builtin_amdgcn_readlane(left, i);
+      if (n > most) { most = n; at = i; }
+    }
+    s_box[1] = at;
+  }
+  __syncthreads();
+  const int at = __builtin_amdgcn_readfirstlane(s_box[1]);
+  __syncthreads();
+  return at;
 }
 
 // Wait until events[ev] >= threshold (bounded).  Returns false on timeout after
@@ -391,7 +433,7 @@ __device__ __forceinline__ void with_row_vectors(int vec_per_row, F&& f) {
 // (kEpiScatter), and the launch has no COMBINE tasks: nothing waits for the whole chip's GEMM-2 tiles.
 template <bool BF16, bool SCATTER = false>
 __device__ __forceinline__ void run_tile_task(const SchedParams<BF16>& sp, const TaskDesc& td, char* smem, volatile int* s_box,
-                                              int wave, int q, long long& t_start, uint32_t& gemm2_done, int& scope) {
+                                              int wave, int q, bool far, long long& t_start, uint32_t& gemm2_done, int& scope) {
   const int type_n = __builtin_amdgcn_readfirstlane(td.type_n);
   const int type = type_n & kTaskTypeMask, idx = type_n >> 8, m = __builtin_amdgcn_readfirstlane(td.m);
   const bool narrow = (type_n & kTaskNarrow) != 0;
@@ -408,19 +450,19 @@ __device__ __forceinline__ void run_tile_task(const SchedParams<BF16>& sp, const
     const int row0 = sp.route.tiles.row0[m], rows = sp.route.tiles.rows[m];
     const int r0 = row0 + idx * sp.perm_rows;
     with_row_vectors(sp.perm.H * sp.perm.elem_bytes / 16, [&](auto uv) {
-      permute_rows<decltype(uv)::value>(sp.perm, r0, min(r0 + sp.perm_rows, row0 + rows), wave, blockDim.x / kWave);
+      permute_rows<decltype(uv)::value>(sp.perm, r0, min(r0 + sp.perm_rows, row0 + rows), wave, blockDim.x / kWave, BF16 && far);
     });
     sched_trigger(sp, kEvPerTile + m, wave, scope);
   } else if (type == kTaskGemm1) {
-    if constexpr (BF16) gemm_map_tile_bf16<kLayNN, kEpiSwiglu>(sp.g1, m, idx, tile_is_tall(__builtin_amdgcn_readfirstlane(sp.route.tiles.rows[m])), smem);
+    if constexpr (BF16) gemm_map_tile_bf16<kLayNN, kEpiSwiglu, false, SCATTER ? kHandNone : kHandFar>(sp.g1, m, idx, tile_is_tall(__builtin_amdgcn_readfirstlane(sp.route.tiles.rows[m])), smem, far);
     else gemm_task_f32<kEpiSwiglu>(sp.g1, m, idx, reinterpret_cast<float*>(smem));
     sched_trigger(sp, kEvPerTile + sp.max_mtiles + m, wave, scope);
   } else {
-    if constexpr (BF16) gemm_map_tile_bf16<kLayNN, SCATTER ? kEpiScatter : kEpiStore>(sp.g2, m, idx, narrow || tile_is_tall(__builtin_amdgcn_readfirstlane(sp.route.tiles.rows[m])), smem);
+    if constexpr (BF16) gemm_map_tile_bf16<kLayNN, SCATTER ? kEpiScatter : kEpiStore, false, SCATTER ? kHandNone : kHandThrough>(sp.g2, m, idx, narrow || tile_is_tall(__builtin_amdgcn_readfirstlane(sp.route.tiles.rows[m])), smem);
     else gemm_task_f32<kEpiStore>(sp.g2, m, idx, reinterpret_cast<float*>(smem));
     // COMBINE waits for every GEMM-2 tile, so completions are counted here and published once per
-    // worker after its queue has drained: a device-scope release per tile would write back the
-    // XCD's whole L2 each time (about 30 us per tile in a trace)
+    // worker after the queues have drained (fp32: a device-scope release per tile would write back the
+    // XCD's whole L2 each time, about 30 us per tile in a trace)
     ++gemm2_done;
   }
 }
@@ -439,23 +481,27 @@ void persistent_forward_kernel(SchedParams<BF16> sp) {
   const int q = blockIdx.x % kNumXcd;   // workgroups are dealt to XCDs round-robin: one XCD per class (checked: sched_arrive)
   sched_arrive(sp, q, wave);
   {
-    const int count = __builtin_amdgcn_readfirstlane(sp.meta[kMetaQueueCount0 + q]);
     uint32_t gemm2_done = 0;
     int scope = -1;
-    for (;;) {
-      const int t = sched_fetch(sp.qhead, kQXcd0 + q, s_box, wave);
-      if (t >= count) break;
-      const TaskDesc td = sp.tasks[(size_t)q * sp.max_tasks_per_q + t];
+    const bool far = BF16 && !SCATTER && sched_hands_far(sp.meta);
+    for (int qq = q; qq >= 0;) {
+      const int count = __builtin_amdgcn_readfirstlane(sp.meta[kMetaQueueCount0 + qq]);
+      const int t = sched_fetch(sp.qhead, kQXcd0 + qq, s_box, wave);
+      if (t >= count) {
+        qq = far ? sched_fullest_queue(sp, s_box, wave) : -1;
+        continue;
+      }
+      const TaskDesc td = sp.tasks[(size_t)qq * sp.max_tasks_per_q + t];
       MOE_TRACE_FETCH(td.type_n & kTaskTypeMask, td.m, td.type_n >> 8)
       long long t_start = 0;
-      run_tile_task<BF16, SCATTER>(sp, td, smem, s_box, wave, q, t_start, gemm2_done, scope);
+      run_tile_task<BF16, SCATTER>(sp, td, smem, s_box, wave, q, far, t_start, gemm2_done, scope);
 #if defined(MOE_SCHED_TRACE)
       tr_.t_start = t_start;
 #endif
       MOE_TRACE_END(sp)
     }
     if (SCATTER) return;   // no COMBINE tasks; the adds are complete when the launch is
-    if (gemm2_done) sched_trigger(sp, kEvGemm2, wave, kScopeDevice, gemm2_done);
+    if (gemm2_done) sched_trigger(sp, kEvGemm2, wave, BF16 ? scope : kScopeDevice, gemm2_done);
   }
 
   // ---- queue C: combine ----
@@ -506,17 +552,21 @@ void persistent_dgrad_kernel(SchedParams<true> sp) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int q = blockIdx.x % kNumXcd;   // workgroups are dealt to XCDs round-robin by id (checked: sched_arrive)
   sched_arrive(sp, q, wave);
-  const int count = __builtin_amdgcn_readfirstlane(sp.meta[kMetaQueueCount0 + q]);
+  const bool far = sched_hands_far(sp.meta);
   int scope = -1;
-  for (;;) {
-    const int t = sched_fetch(sp.qhead, kQXcd0 + q, s_box, wave);
-    if (t >= count) break;
-    const TaskDesc td = sp.tasks[(size_t)q * sp.max_tasks_per_q + t];
+  for (int qq = q; qq >= 0;) {
+    const int count = __builtin_amdgcn_readfirstlane(sp.meta[kMetaQueueCount0 + qq]);
+    const int t = sched_fetch(sp.qhead, kQXcd0 + qq, s_box, wave);
+    if (t >= count) {
+      qq = far ? sched_fullest_queue(sp, s_box, wave) : -1;
+      continue;
+    }
+    const TaskDesc td = sp.tasks[(size_t)qq * sp.max_tasks_per_q + t];
     const int type_n = __builtin_amdgcn_readfirstlane(td.type_n);
     const int type = type_n & kTaskTypeMask, idx = type_n >> 8, m = __builtin_amdgcn_readfirstlane(td.m);
     const bool tall = (type_n & kTaskNarrow) != 0 || tile_is_tall(__builtin_amdgcn_readfirstlane(sp.route.tiles.rows[m]));
     if (type == kTaskGemm1) {
-      gemm_map_tile_bf16<kLayNT, kEpiSwigluGrad>(sp.g1, m, idx, tall, smem);
+      gemm_map_tile_bf16<kLayNT, kEpiSwigluGrad, false, kHandFar>(sp.g1, m, idx, tall, smem, far);
       if (scope < 0) scope = sched_chain_scope(sp, q, s_box, wave);
       sched_trigger(sp, kEvPerTile + sp.max_mtiles + m, wave, scope);
     } else {

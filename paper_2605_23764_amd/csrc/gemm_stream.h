@@ -53,9 +53,22 @@ struct StreamShape {
 
 constexpr int kStreamTables = kStreamRing;           // LDS offset of the tables, behind the ring
 constexpr int kStreamGatherOff = kStreamTables + 3 * kMaxE * 4;
-static_assert(kStreamGatherOff + kStreamGather * 4 <= kGemmLdsBytes, "LDS budget");
+constexpr int kStreamBox = kStreamGatherOff + kStreamGather * 4;   // two words of the single launch (persistent.h)
+static_assert(kStreamBox + 8 <= kGemmLdsBytes, "LDS budget");
+
+// Who runs a stream: a launch of its own; or both GEMMs of a layer one after the other in the single launch (stream_layer in
+// persistent.h), whose results are stored through to memory and whose second stream starts with the weights, before the
+// activations are there.
+enum StreamRole { kStreamAlone = 0, kStreamFirst = 1, kStreamSecond = 2 };
 
 typedef __attribute__((address_space(3))) int32_t* lds_i32_ptr;
+// 8 bytes of a result; THROUGH: as store_through does.
+template <bool THROUGH>
+__device__ __forceinline__ void store8(__bf16* dst, u32x2 v) {
+  if constexpr (THROUGH) asm volatile("global_store_dwordx2 %0, %1, off sc1\n\ts_nop 1" : : "v"(dst), "v"(v) : "memory");
+  else *reinterpret_cast<u32x2*>(dst) = v;
+}
+
 // Waits until at most `stages` stages requested after the wanted one are under way (fewer near the end of the stream).
 template <int LPS, int MOST>
 __device__ __forceinline__ void stream_wait(int stages) {
@@ -67,9 +80,10 @@ __device__ __forceinline__ void stream_wait(int stages) {
   }
 }
 
-// Items id0 .. id1 - 1 (expert by expert among those with rows, then by columns).
-template <int LAY, int EPI, int CW, int AL>
-__device__ __forceinline__ void stream_items(const GemmParams& p, int id0, int id1, char* smem) {
+// Items id0 .. id1 - 1 (expert by expert among those with rows, then by columns), the share of workgroup b.  kStreamSecond: ready()
+// waits until the activations may be read; false, it has given up, and nothing is stored.
+template <int LAY, int EPI, int CW, int AL, int ROLE, typename Ready>
+__device__ __forceinline__ void stream_items(const GemmParams& p, int id0, int id1, int b, char* smem, Ready&& ready) {
   typedef StreamShape<CW, AL> S;
   constexpr int kOut = EPI == kEpiSwiglu ? CW / 2 : CW;          // output columns per item
   constexpr int kRPL = CW == 64 ? 8 : 4;                         // NN: k-rows per 1 KB line
@@ -80,8 +94,8 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int id0, int i
   // 128 columns: neighbouring items on different dies, as the dispatcher deals them; 64 columns: on one die, whose L2 then
   // serves both halves of a line that two items share
   auto tile_of = [&](int it) __attribute__((always_inline)) {
-    const int id = it * G + (int)blockIdx.x;
-    return CW != 64 ? (id < total ? id : -1) : xcd_spread_tile(it, blockIdx.x, G, total);
+    const int id = it * G + b;
+    return CW != 64 ? (id < total ? id : -1) : xcd_spread_tile(it, b, G, total);
   };
   int n_items = (total + G - 1) / G;
   if (n_items > 0 && tile_of(n_items - 1) < 0) --n_items;
@@ -155,21 +169,22 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int id0, int i
       }
     }
   };
-  auto request = [&]() __attribute__((always_inline)) {
+  auto request = [&](bool rows = true, bool weights = true) __attribute__((always_inline)) {   // both constant in a call
     if (q.step == 0) set_item();
     const int k0 = q.step * S::kKB;
     const uint32_t st = uniform_u32(lds0 + (uint32_t)(q.slot * S::kStage));
     // k past the end (an odd number of 64s with 128 to a stage): the last 64 again, not multiplied
     const char* a_k = uniform_ptr(q.a_base + (size_t)(CW != 64 ? k0 : min(k0 + (wave & 1) * 64, p.K - 64)) * 2);
 #pragma unroll
-    for (int i = 0; i < AL; ++i) lds_dma16(a_k, q.a_off[i], st + (S::kALine0 + wave + 4 * i) * kLine);
+    for (int i = 0; i < AL; ++i)
+      if (rows) lds_dma16(a_k, q.a_off[i], st + (S::kALine0 + wave + 4 * i) * kLine);
 #pragma unroll
     for (int i = 0; i < S::kBLoads; ++i) {
       const char* b_k;
       if (CW == 256) b_k = q.b_base + (size_t)(k0 + (wave * 4 + (i >> 1)) * 4) * ldb_bytes;
       else if (LAY == kLayNN) b_k = q.b_base + (size_t)min(k0 + (wave * 4 + i) * kRPL, p.K - kRPL) * ldb_bytes;
       else b_k = q.b_base + (size_t)(CW == 128 ? k0 : min(k0 + (i & 1) * 64, p.K - 64)) * 2;
-      lds_dma16<CW != 64>(uniform_ptr(b_k), q.b_off[LAY == kLayNT ? i : CW == 256 ? i & 1 : 0], st + (wave * S::kBLoads + i) * kLine);
+      if (weights) lds_dma16<CW != 64>(uniform_ptr(b_k), q.b_off[LAY == kLayNT ? i : CW == 256 ? i & 1 : 0], st + (wave * S::kBLoads + i) * kLine);
     }
     q.slot = q.slot == S::kDepth - 1 ? 0 : q.slot + 1;
     if (++q.step == n_steps) { q.step = 0; ++q.item; }
@@ -236,7 +251,19 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int id0, int i
         for (int nb = 0; nb < S::kNB; ++nb) acc[nb][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[nb][s], xf[s][mt], acc[nb][mt], 0, 0, 0);
   };
 
-  for (int g = 0; g < S::kDepth - 1 && g < n_total; ++g) request();
+  if constexpr (ROLE == kStreamSecond) {
+    const auto q0 = q;
+    for (int g = 0; g < S::kDepth - 1 && g < n_total; ++g) request(false, true);
+    if (!ready()) {
+      wait_vmcnt<0>();
+      return;
+    }
+    q = q0;
+    for (int g = 0; g < S::kDepth - 1 && g < n_total; ++g) request(true, false);
+    wait_vmcnt<0>();                                             // the waits below count whole stages in order
+  } else {
+    for (int g = 0; g < S::kDepth - 1 && g < n_total; ++g) request();
+  }
   int step = 0, item = 0, slot = 0;
   for (int g = 0; g < n_total; ++g) {
     stream_wait<S::kLoads, S::kDepth - 2>(n_total - 1 - g);      // this wave's part of stage g has landed
@@ -274,7 +301,7 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int id0, int i
               u[x] = acc[nb][mt][qg * 4 + 8 + x];
               a[x] = gt[x] * sigmoid_bf16_(gt[x]) * u[x];
             }
-            *reinterpret_cast<u32x2*>(p.C + grow * p.ldc + c) = u32x2{pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3])};
+            store8<ROLE != kStreamAlone>(p.C + grow * p.ldc + c, u32x2{pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3])});
             if (p.C2) {
               __bf16* h = p.C2 + grow * (size_t)(2 * p.N) + c;
               *reinterpret_cast<u32x2*>(h) = u32x2{pack_bf16(gt[0], gt[1]), pack_bf16(gt[2], gt[3])};
@@ -297,7 +324,7 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int id0, int i
               *reinterpret_cast<u32x2*>(o) = u32x2{pack_bf16(dg[0], dg[1]), pack_bf16(dg[2], dg[3])};
               *reinterpret_cast<u32x2*>(o + p.N) = u32x2{pack_bf16(du[0], du[1]), pack_bf16(du[2], du[3])};
             } else {
-              *reinterpret_cast<u32x2*>(p.C + grow * p.ldc + c) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+              store8<ROLE != kStreamAlone>(p.C + grow * p.ldc + c, u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])});
             }
           }
         }
@@ -308,11 +335,11 @@ __device__ __forceinline__ void stream_items(const GemmParams& p, int id0, int i
 }
 
 // The same with stages of ROWS activation rows.
-template <int LAY, int EPI, int CW, int ROWS>
-__device__ __forceinline__ void stream_rows(const GemmParams& p, int id0, int id1, char* smem) {
+template <int LAY, int EPI, int CW, int ROWS, int ROLE, typename Ready>
+__device__ __forceinline__ void stream_rows(const GemmParams& p, int id0, int id1, int b, char* smem, Ready&& ready) {
   constexpr int AL = ROWS / (CW == 64 ? 16 : 32);
   static_assert(StreamShape<CW, AL>::kRows == ROWS, "rows of a stage");
-  stream_items<LAY, EPI, CW, AL>(p, id0, id1, smem);
+  stream_items<LAY, EPI, CW, AL, ROLE>(p, id0, id1, b, smem, ready);
 }
 
 // Whole launch of a grouped GEMM that stream_takes, in the form of stream_form.  The comparisons of max_rows below are those of
@@ -321,9 +348,9 @@ static_assert(stream_stage_rows(64, 16) == 16 && stream_stage_rows(64, 17) == 32
               stream_stage_rows(64, 33) == 64 && stream_stage_rows(64, 64) == 64 && stream_stage_rows(64, 65) == 128, "64 columns");
 static_assert(stream_stage_rows(128, 32) == 32 && stream_stage_rows(128, 33) == 64 && stream_stage_rows(128, 64) == 64 &&
               stream_stage_rows(128, 65) == 128 && stream_stage_rows(256, 32) == 32 && stream_stage_rows(256, 33) == 64, "128, 256");
-template <int LAY, int EPI>
-__device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_rows, char* smem) {
-  // experts with rows, in expert order (every wave counts, wave 0 writes), and the tokens of the first rows
+// Tables in LDS: experts with rows, in expert order (every wave counts, wave 0 writes), and the tokens of the first rows if the
+// activations are gathered.  Returns the number of such experts.
+__device__ __forceinline__ int stream_tables(const int32_t* offsets, int E_local, const int32_t* gather, char* smem) {
   const int lane = lane_id();
   const lds_i32_ptr s_expert = (lds_i32_ptr)(smem + kStreamTables), s_row0 = s_expert + kMaxE, s_rows = s_row0 + kMaxE;
   int n_act = 0, R = 0;
@@ -331,8 +358,8 @@ __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_ro
 #pragma unroll
   for (int i = 0; i < kMaxE / kWave; ++i) {
     const int e = i * kWave + lane;
-    lo[i] = e < p.E_local ? p.offsets[e] : 0;
-    hi[i] = e < p.E_local ? p.offsets[e + 1] : 0;
+    lo[i] = e < E_local ? offsets[e] : 0;
+    hi[i] = e < E_local ? offsets[e + 1] : 0;
   }
 #pragma unroll
   for (int i = 0; i < kMaxE / kWave; ++i) {
@@ -345,40 +372,51 @@ __device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_ro
     }
     n_act += __popcll(bal);
   }
-  if (LAY == kLayNN && p.gather) {
-    R = p.offsets[p.E_local];
+  if (gather) {
+    R = offsets[E_local];
     const lds_i32_ptr s_tok = (lds_i32_ptr)(smem + kStreamGatherOff);
-    for (int i = threadIdx.x; i < min(R, kStreamGather); i += kGemmThreads) s_tok[i] = p.gather[i];
+    for (int i = threadIdx.x; i < min(R, kStreamGather); i += kGemmThreads) s_tok[i] = gather[i];
   }
   __syncthreads();
-  n_act = __builtin_amdgcn_readfirstlane(n_act);
+  return __builtin_amdgcn_readfirstlane(n_act);
+}
+
+// The share of workgroup b, in the form of stream_form (the roles of the single launch: up to 64 rows).
+template <int LAY, int EPI, int ROLE, typename Ready>
+__device__ __forceinline__ void stream_share(const GemmParams& p, int max_rows, int n_act, int b, char* smem, Ready&& ready) {
   const int G = gridDim.x;
   const bool narrow = stream_narrow(n_act, p.N, EPI == kEpiSwiglu, G);
   if constexpr (LAY == kLayNN && EPI == kEpiSwiglu) {
     const int n256 = n_act * stream_tiles(p.N, 128), n128 = n_act * stream_tiles(p.N, 64);
     if (!narrow && stream_wide(max_rows, n256, n128, p.N, G)) {
       const int whole = stream_whole(n256, n128, G);
-      if (max_rows > 32) stream_rows<LAY, EPI, 256, 64>(p, 0, whole, smem);
-      else stream_rows<LAY, EPI, 256, 32>(p, 0, whole, smem);
+      if (max_rows > 32) stream_rows<LAY, EPI, 256, 64, ROLE>(p, 0, whole, b, smem, ready);
+      else stream_rows<LAY, EPI, 256, 32, ROLE>(p, 0, whole, b, smem, ready);
       if (whole == n256) return;
       __syncthreads();                                           // the ring has been read out by all
-      if (max_rows > 32) stream_rows<LAY, EPI, 128, 64>(p, 2 * whole, 2 * n256, smem);
-      else stream_rows<LAY, EPI, 128, 32>(p, 2 * whole, 2 * n256, smem);
+      if (max_rows > 32) stream_rows<LAY, EPI, 128, 64, ROLE>(p, 2 * whole, 2 * n256, b, smem, ready);
+      else stream_rows<LAY, EPI, 128, 32, ROLE>(p, 2 * whole, 2 * n256, b, smem, ready);
       return;
     }
   }
   constexpr int kOut64 = EPI == kEpiSwiglu ? 32 : 64;
   const int total = n_act * stream_tiles(p.N, narrow ? kOut64 : 2 * kOut64);
   if (narrow) {
-    if (max_rows > 64) stream_rows<LAY, EPI, 64, 128>(p, 0, total, smem);
-    else if (max_rows > 32) stream_rows<LAY, EPI, 64, 64>(p, 0, total, smem);
-    else if (max_rows > 16) stream_rows<LAY, EPI, 64, 32>(p, 0, total, smem);
-    else stream_rows<LAY, EPI, 64, 16>(p, 0, total, smem);
+    if (ROLE == kStreamAlone && max_rows > 64) stream_rows<LAY, EPI, 64, 128, ROLE>(p, 0, total, b, smem, ready);
+    else if (max_rows > 32) stream_rows<LAY, EPI, 64, 64, ROLE>(p, 0, total, b, smem, ready);
+    else if (max_rows > 16) stream_rows<LAY, EPI, 64, 32, ROLE>(p, 0, total, b, smem, ready);
+    else stream_rows<LAY, EPI, 64, 16, ROLE>(p, 0, total, b, smem, ready);
   } else {
-    if (max_rows > 64) stream_rows<LAY, EPI, 128, 128>(p, 0, total, smem);
-    else if (max_rows > 32) stream_rows<LAY, EPI, 128, 64>(p, 0, total, smem);
-    else stream_rows<LAY, EPI, 128, 32>(p, 0, total, smem);
+    if (ROLE == kStreamAlone && max_rows > 64) stream_rows<LAY, EPI, 128, 128, ROLE>(p, 0, total, b, smem, ready);
+    else if (max_rows > 32) stream_rows<LAY, EPI, 128, 64, ROLE>(p, 0, total, b, smem, ready);
+    else stream_rows<LAY, EPI, 128, 32, ROLE>(p, 0, total, b, smem, ready);
   }
+}
+
+template <int LAY, int EPI>
+__device__ __forceinline__ void stream_gemm_bf16(const GemmParams& p, int max_rows, char* smem) {
+  const int n_act = stream_tables(p.offsets, p.E_local, LAY == kLayNN ? p.gather : nullptr, smem);
+  stream_share<LAY, EPI, kStreamAlone>(p, max_rows, n_act, blockIdx.x, smem, [] { return true; });
 }
 
 }  // namespace moe

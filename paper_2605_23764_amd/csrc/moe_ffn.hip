@@ -18,6 +18,7 @@
 #include "persistent.h"
 #include "probe.h"
 #include "route.h"
+#include "stream_layer.h"
 #include "wgrad_bf16.h"
 #include "wgrad_panel.h"
 
@@ -115,9 +116,10 @@ struct Ctx {
 // No MoeSaved (inference) or MoeSaved without Xp (the backward then reads x through the permutation as
 // well): nobody reads a permuted copy of x, so bf16 GEMM-1 applies the permutation while loading (32-bit
 // offsets: x must span < 4 GB) and the PERMUTE step is dropped.
-bool gathers_x(const Ctx& c) {
-  return !c.keep_xp && c.s.dtype == MOE_BF16 && (size_t)c.s.T * c.s.H * 2 < ((size_t)1 << 32);
-}
+bool x_spans_32_bits(const Ctx& c) { return (size_t)c.s.T * c.s.H * 2 < ((size_t)1 << 32); }
+bool gathers_x(const Ctx& c) { return !c.keep_xp && c.s.dtype == MOE_BF16 && x_spans_32_bits(c); }
+// Single launch of up to 64 tokens, where no expert has more rows than a stream takes: as streams instead of tile tasks.
+bool streams_layer(const Ctx& c) { return c.s.dtype == MOE_BF16 && c.s.T <= kStreamRows && x_spans_32_bits(c); }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 // Single-launch modes hand tiles over between CUs behind one L2 without invalidating the CUs' vector L1;
@@ -333,6 +335,7 @@ SchedParams<BF16> sched_params(const Ctx& c, const void* x, const float* logits,
   sp.comb = combine_params(c, out);
   sp.no_permute = 0;
   sp.skip_tables = 0;
+  sp.no_tasks = BF16 && streams_layer(c);
   sp.zero_dst = nullptr;
   sp.zero_n16 = 0;
   if constexpr (BF16) {
@@ -372,6 +375,7 @@ template <bool BF16>
 int run_route_t(const Ctx& c, const float* logits, bool tables, void* zero_out) {
   SchedParams<BF16> sp = sched_params<BF16>(c, nullptr, logits, nullptr, nullptr, nullptr);
   sp.skip_tables = tables ? 0 : 1;
+  if (zero_out) sp.no_tasks = 0;          // the scatter epilogue follows, which runs as tasks
   const RouteParams& rp = sp.route;
   const bool one = c.s.T <= kRouteOneT;   // one workgroup does it all in one launch (see route_one)
   const int fill_threads = one ? kRouteOneThreads : kScanRankWaves * kWave;
@@ -400,8 +404,26 @@ int run_route(const Ctx& c, const float* logits, bool tables = true, void* zero_
 }
 
 // Dispatch to Combine as ONE launch of tile tasks (after run_route on the same MoeSaved).
+int run_stream_layer(const Ctx& c, const void* x, const void* w_gate_up, const void* w_down, void* out) {
+  StreamLayerParams p;
+  p.g1 = gemm1_params<GemmParams, __bf16>(c, w_gate_up);
+  p.g1.A = static_cast<const __bf16*>(x);
+  p.g1.gather = c.sv.token_of;
+  p.g2 = gemm2_params<GemmParams, __bf16>(c, w_down);
+  p.perm = permute_params(c, x);
+  p.comb = combine_params(c, out);
+  p.events = reinterpret_cast<uint32_t*>(c.ws + c.L.events);
+  p.meta = reinterpret_cast<int32_t*>(c.ws + c.L.meta);
+  p.copy = c.keep_xp ? 1 : 0;
+  p.spin_limit = g_spin_limit;
+  p.timeout_status = MOE_ERR_SCHED_TIMEOUT;
+  hipLaunchKernelGGL(stream_layer_kernel, dim3(gemm_grid(c)), dim3(kGemmThreads), 0, c.stream, p);
+  return launch_status();
+}
+
 template <bool BF16>
 int run_persistent(const Ctx& c, const void* x, const void* w_gate_up, const void* w_down, void* out) {
+  if (BF16 && streams_layer(c)) return run_stream_layer(c, x, w_gate_up, w_down, out);
   const SchedParams<BF16> sp = sched_params<BF16>(c, x, nullptr, w_gate_up, w_down, out);
   hipLaunchKernelGGL(persistent_forward_kernel<BF16>, dim3(gemm_grid(c)), dim3(kGemmThreads), 0, c.stream, sp);
   return launch_status();

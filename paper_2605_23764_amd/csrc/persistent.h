@@ -119,6 +119,7 @@ struct SchedParams {
   int no_permute;          // nobody needs Xp: GEMM-1 gathers its rows from x through token_of
   int force_device_scope;  // test hook: behave as if a worker had reported a foreign XCD
   int skip_tables;         // routing launch: the serialized operators follow, nobody reads counters or task tables
+  int no_tasks;            // routing launch: the single launch that follows has counters but no tasks (stream_layer.h)
   uint4* zero_dst;         // routing launch, optional: zero_n16 16-byte vectors that further workgroups of the launch
   size_t zero_n16;         // set to zero (the layer output ahead of a GEMM-2 that adds its rows into it)
   uint32_t spin_limit;     // polls before a wait gives up (MOE_ERR_SCHED_TIMEOUT)
@@ -273,6 +274,7 @@ __device__ __forceinline__ void build_task_tables(const SchedParams<BF16>& sp) {
   for (int i = threadIdx.x; i < sp.n_events; i += blockDim.x) sp.events[i] = 0;
   if (threadIdx.x < kNumQueues) sp.qhead[threadIdx.x] = 0;
   if (threadIdx.x == 0) sp.meta[kMetaFallbackWorkers] = 0;
+  if (sp.no_tasks) return;
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), n_waves = blockDim.x / kWave;
   const int n_mtiles = sp.meta[kMetaMTiles];

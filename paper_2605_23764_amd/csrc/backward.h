@@ -18,7 +18,7 @@ struct BwdDispatchParams {
   float* d_topk_w;         // [T,k]
   int T, H, k;
   // The backward's M-tile map, rebuilt from the saved rows per expert, and the counters the later kernels draw
-  // tickets from: nothing in this kernel needs them, so its last workgroup makes them on the side (one wave).
+  // tickets from: nothing in this kernel needs them, so its first workgroup makes them on the side (one wave).
   const int32_t* counts;   // [E_local]
   int E_local, wide_max, granule, tall;
   TileMap tiles;
@@ -109,20 +109,25 @@ __device__ __forceinline__ void bwd_dispatch_token(const BwdDispatchParams& p, i
   }
 }
 
+// Workgroup 0 makes the map and the counters (true); it is the first to start, so its serial chain runs under the rows of the others.
 template <bool BF16>
-__global__ __launch_bounds__(256) void bwd_dispatch_kernel(BwdDispatchParams p) {
+__device__ __forceinline__ bool bwd_dispatch(const BwdDispatchParams& p) {
   const int n_waves = blockDim.x / kWave;
   const int wave = threadIdx.x / kWave;
-  const int n_blocks = (int)gridDim.x - 1;
-  if ((int)blockIdx.x == n_blocks) {
+  if (blockIdx.x == 0) {
     if (wave == 0) {
       for (int i = threadIdx.x; i < p.n_zero; i += kWave) p.zero[i] = 0;
       build_tile_map(p.E_local, p.counts, p.wide_max, p.granule, p.tall, nullptr, nullptr, p.tiles);
     }
-    return;
+    return true;
   }
-  for (int t = blockIdx.x * n_waves + wave; t < p.T; t += n_blocks * n_waves) bwd_dispatch_token<BF16>(p, t);
+  const int n_blocks = (int)gridDim.x - 1;
+  for (int t = ((int)blockIdx.x - 1) * n_waves + wave; t < p.T; t += n_blocks * n_waves) bwd_dispatch_token<BF16>(p, t);
+  return false;
 }
+
+template <bool BF16>
+__global__ __launch_bounds__(256) void bwd_dispatch_kernel(BwdDispatchParams p) { bwd_dispatch<BF16>(p); }
 
 // ---- fp32 backward GEMMs on the tile of gemm_f32.h (H and I are multiples of 64: every tile is full in N, and in M
 // except for the last rows of an expert's segment) ----

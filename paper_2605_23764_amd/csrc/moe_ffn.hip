@@ -378,7 +378,7 @@ int run_route_t(const Ctx& c, const float* logits, bool tables, void* zero_out) 
   if (zero_out) sp.no_tasks = 0;          // the scatter epilogue follows, which runs as tasks
   const RouteParams& rp = sp.route;
   const bool one = c.s.T <= kRouteOneT;   // one workgroup does it all in one launch (see route_one)
-  const int fill_threads = one ? kRouteOneThreads : kScanRankWaves * kWave;
+  const int fill_threads = one ? kRouteOneThreads : kScanWaves * kWave;
   int fill_wgs = 0;
   if (zero_out) {
     sp.zero_dst = static_cast<uint4*>(zero_out);
@@ -391,8 +391,8 @@ int run_route_t(const Ctx& c, const float* logits, bool tables, void* zero_out) 
     return launch_status();
   }
   hipLaunchKernelGGL(route_kernel, dim3(rp.n_sub), dim3(512), 0, c.stream, rp);
-  hipLaunchKernelGGL(sched_prepare_kernel<BF16>, dim3(1 + (rp.n_groups + kScanRankWaves - 1) / kScanRankWaves + fill_wgs),
-                     dim3(kScanRankWaves * kWave), 0, c.stream, sp);
+  hipLaunchKernelGGL(sched_prepare_kernel<BF16>, dim3(1 + (rp.n_groups + kRankWaves - 1) / kRankWaves + fill_wgs),
+                     dim3(kScanWaves * kWave), 0, c.stream, sp);
   return launch_status();
 }
 // tables = false: the caller knows that one launch per operator follows (the task tables take workgroup 0 of the
@@ -532,16 +532,52 @@ int run_backward(const BwdCtx& c, const void* dy, const void* x, const void* w_g
 
   uint32_t* tickets = reinterpret_cast<uint32_t*>(c.ws + c.L.tickets);   // [0, 8): w2_grad, [8, 16): w1_grad
 
-  // backward Dispatch; its extra workgroup rebuilds the M-tile map from the saved counts and zeroes the tickets
+  // backward Dispatch; its first workgroup rebuilds the M-tile map from the saved counts and zeroes the tickets
   BwdDispatchParams bd;
   bd.dY = dy; bd.Yp = c.sv.Yp; bd.dYp = dYp; bd.row_of = c.sv.row_of; bd.topk_w = c.sv.topk_w;
   bd.d_topk_w = d_topk_w; bd.T = s.T; bd.H = s.H; bd.k = s.k;
   bd.counts = c.sv.counts; bd.E_local = s.E_local; bd.wide_max = tile_wide_max(s); bd.granule = BF16 ? kRowGranule : kFBM;
   bd.tall = tile_tall(s); bd.tiles = c.tiles; bd.zero = tickets; bd.n_zero = 2 * kNumXcd;
+  const bool chain = BF16 && c.mode == MOE_MODE_PERSISTENT;   // act_grad and gate_grad as one launch of tile tasks
+  using P = typename std::conditional<BF16, GemmParams, GemmBwdParamsF32>::type;
+  // act_grad + SwiGLU_grad: dH1 = swiglu'(dYp W_down^T ; H1)
+  P pa{};
+  pa.A = dYp; pa.B = static_cast<const T*>(w_down); pa.C = dH1; pa.G = static_cast<const T*>(c.sv.H1);
+  pa.strideB = (long)s.I * s.H; pa.K = s.H; pa.N = s.I;
+  pa.lda = s.H; pa.ldb = s.H; pa.ldc = 2 * s.I;
+  pa.n_ntiles = ceil_div(s.I, tn);
+  pa.tiles = c.tiles;
+  pa.offsets = c.sv.offsets; pa.E_local = s.E_local;
+  // gate_grad: dXp = dH1 W_gate_up^T
+  P pg{};
+  pg.A = dH1; pg.B = static_cast<const T*>(w_gate_up); pg.C = dXp;
+  pg.strideB = (long)s.H * 2 * s.I; pg.K = 2 * s.I; pg.N = s.H;
+  pg.lda = 2 * s.I; pg.ldb = 2 * s.I; pg.ldc = s.H;
+  pg.n_ntiles = ceil_div(s.H, tn);
+  pg.tiles = c.tiles;
+  pg.offsets = c.sv.offsets; pg.E_local = s.E_local;
+  SchedParams<true> sp{};
+  if constexpr (BF16) {
+    sp.route.tiles = c.tiles;
+    sp.g1 = pa; sp.g2 = pg;
+    sp.events = reinterpret_cast<uint32_t*>(c.ws + c.L.events);
+    sp.qhead = reinterpret_cast<uint32_t*>(c.ws + c.L.qhead);
+    sp.tasks = reinterpret_cast<TaskDesc*>(c.ws + c.L.tasks);
+    sp.meta = c.tiles.meta;
+    sp.max_mtiles = (int)max_mtiles(s);
+    sp.max_tasks_per_q = (int)max_tasks_per_queue(s);
+    sp.n_events = (int)n_events(s);
+    sp.force_device_scope = g_force_device_scope;
+    sp.perm_rows = perm_task_rows(s);
+    sp.workers_per_q = grid / kNumXcd;
+    sp.spin_limit = g_spin_limit;
+    sp.timeout_status = MOE_ERR_SCHED_TIMEOUT;
+  }
   {
     long want = ((long)s.T + 3) / 4;
     int g = (int)(want < (long)c.n_cu * 8 ? want : (long)c.n_cu * 8);
-    hipLaunchKernelGGL(bwd_dispatch_kernel<BF16>, dim3(g + 1), dim3(256), 0, c.stream, bd);
+    if (chain) hipLaunchKernelGGL(bwd_dispatch_tables_kernel, dim3(g + 1), dim3(256), 0, c.stream, bd, sp);
+    else hipLaunchKernelGGL(bwd_dispatch_kernel<BF16>, dim3(g + 1), dim3(256), 0, c.stream, bd);
   }
   // Two streams: the weight-gradient branch of the graph (w2_grad behind the backward Dispatch, w1_grad behind
   // act_grad) is enqueued on its own stream, so that its workgroups take the CUs that the last tiles of the
@@ -560,24 +596,7 @@ int run_backward(const BwdCtx& c, const void* dy, const void* x, const void* w_g
     if (hipEventRecord(ev[0], c.stream) != hipSuccess || hipStreamWaitEvent(sw, ev[0], 0) != hipSuccess) return MOE_ERR_LAUNCH;
   }
 
-  using P = typename std::conditional<BF16, GemmParams, GemmBwdParamsF32>::type;
   T* xp_ws = reinterpret_cast<T*>(c.ws + c.L.Xp);
-  // act_grad + SwiGLU_grad: dH1 = swiglu'(dYp W_down^T ; H1)
-  P pa{};
-  pa.A = dYp; pa.B = static_cast<const T*>(w_down); pa.C = dH1; pa.G = static_cast<const T*>(c.sv.H1);
-  pa.strideB = (long)s.I * s.H; pa.K = s.H; pa.N = s.I;
-  pa.lda = s.H; pa.ldb = s.H; pa.ldc = 2 * s.I;
-  pa.n_ntiles = ceil_div(s.I, tn);
-  pa.tiles = c.tiles;
-  pa.offsets = c.sv.offsets; pa.E_local = s.E_local;
-  // gate_grad: dXp = dH1 W_gate_up^T
-  P pg{};
-  pg.A = dH1; pg.B = static_cast<const T*>(w_gate_up); pg.C = dXp;
-  pg.strideB = (long)s.H * 2 * s.I; pg.K = 2 * s.I; pg.N = s.H;
-  pg.lda = 2 * s.I; pg.ldb = 2 * s.I; pg.ldc = s.H;
-  pg.n_ntiles = ceil_div(s.H, tn);
-  pg.tiles = c.tiles;
-  pg.offsets = c.sv.offsets; pg.E_local = s.E_local;
 
   // w2_grad: dW_down[e] = A_e^T dYp_e (needs only dYp: the register-stationary kernel runs first, while dYp is fresh in the
   // caches; on one stream the general kernel waits for w1_grad's part)
@@ -602,23 +621,7 @@ int run_backward(const BwdCtx& c, const void* dy, const void* x, const void* w_g
     return hipEventRecord(ev[1], c.stream) == hipSuccess && hipStreamWaitEvent(sw, ev[1], 0) == hipSuccess;
   };
   if constexpr (BF16) {
-    if (c.mode == MOE_MODE_PERSISTENT) {
-      SchedParams<true> sp{};
-      sp.route.tiles = c.tiles;
-      sp.g1 = pa; sp.g2 = pg;
-      sp.events = reinterpret_cast<uint32_t*>(c.ws + c.L.events);
-      sp.qhead = reinterpret_cast<uint32_t*>(c.ws + c.L.qhead);
-      sp.tasks = reinterpret_cast<TaskDesc*>(c.ws + c.L.tasks);
-      sp.meta = c.tiles.meta;
-      sp.max_mtiles = (int)max_mtiles(s);
-      sp.max_tasks_per_q = (int)max_tasks_per_queue(s);
-      sp.n_events = (int)n_events(s);
-      sp.force_device_scope = g_force_device_scope;
-      sp.perm_rows = perm_task_rows(s);
-      sp.workers_per_q = grid / kNumXcd;
-      sp.spin_limit = g_spin_limit;
-      sp.timeout_status = MOE_ERR_SCHED_TIMEOUT;
-      hipLaunchKernelGGL(dgrad_prepare_kernel, dim3(1), dim3(kGemmThreads), 0, c.stream, sp);
+    if (chain) {
       hipLaunchKernelGGL(persistent_dgrad_kernel, dim3(grid), dim3(kGemmThreads), 0, c.stream, sp);
       if (!fork_behind_dh1()) return MOE_ERR_LAUNCH;
     } else {

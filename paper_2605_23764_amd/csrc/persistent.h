@@ -60,6 +60,7 @@
 #pragma once
 #include <type_traits>
 
+#include "backward.h"
 #include "common.h"
 #include "gemm_bf16.h"
 #include "gemm_f32.h"
@@ -263,6 +264,7 @@ __device__ __forceinline__ void sched_trigger(const SchedParams<BF16>& sp, int e
   if (wave == 0) wave_atomic_add(&sp.events[ev], inc);
 }
 
+constexpr int kTableRows = 1024;
 // Zero the counters and queue heads, then materialise the per-XCD task tables from the fresh tile map.
 // Whole workgroup, after the tile map is complete: a wave per queue, the lanes of the wave fill a block
 // of descriptors in parallel (block offsets are wave-uniform running sums).
@@ -271,6 +273,7 @@ __device__ __forceinline__ void sched_trigger(const SchedParams<BF16>& sp, int e
 template <bool BF16, bool BWD = false>
 __device__ __forceinline__ void build_task_tables(const SchedParams<BF16>& sp) {
   __shared__ int s_extra[kNumXcd];   // per queue: GEMM-2 tasks added by halving its last round
+  __shared__ int s_rows[kTableRows];   // rows of the map's first entries: the queues are built along chains of look-ups
   for (int i = threadIdx.x; i < sp.n_events; i += blockDim.x) sp.events[i] = 0;
   if (threadIdx.x < kNumQueues) sp.qhead[threadIdx.x] = 0;
   if (threadIdx.x == 0) sp.meta[kMetaFallbackWorkers] = 0;
@@ -279,9 +282,12 @@ __device__ __forceinline__ void build_task_tables(const SchedParams<BF16>& sp) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), n_waves = blockDim.x / kWave;
   const int n_mtiles = sp.meta[kMetaMTiles];
   const int nN1 = sp.g1.n_ntiles, nN2 = sp.g2.n_ntiles;
+  for (int m = threadIdx.x; m < min(n_mtiles, kTableRows); m += blockDim.x) s_rows[m] = sp.route.tiles.rows[m];
+  __syncthreads();
+  auto rows_of = [&](int m) __attribute__((always_inline)) { return m < kTableRows ? s_rows[m] : sp.route.tiles.rows[m]; };
   // the tile map lists M tiles in pairs (siblings of one expert where possible); queue q owns pairs q, q+8, ...
   const int n_pairs = (n_mtiles + 1) >> 1;
-  auto parts_of = [&](int m) { return (sp.route.tiles.rows[m] + sp.perm_rows - 1) / sp.perm_rows; };
+  auto parts_of = [&](int m) { return (rows_of(m) + sp.perm_rows - 1) / sp.perm_rows; };
   constexpr int kTallAbove = BF16 ? kWideRows : (1 << 30);   // a bf16 tile with more rows runs in the tall shape
   const bool permute = !(sp.no_permute || BWD);
   for (int q = wave; q < kNumXcd; q += n_waves) {
@@ -304,9 +310,9 @@ __device__ __forceinline__ void build_task_tables(const SchedParams<BF16>& sp) {
     for (int j = 0; j < Pq + lag; ++j) {
       if (j < Pq) {
         const int m0 = 2 * (q + kNumXcd * j);
-        const int rows0 = sp.route.tiles.rows[m0];
+        const int rows0 = rows_of(m0);
         const bool tall = rows0 > kTallAbove;
-        const int n_sib = rows0 <= 0 ? 0 : tall ? 1 : ((m0 + 1 < n_mtiles && sp.route.tiles.rows[m0 + 1] > 0) ? 2 : 1);   // 0: empty slot
+        const int n_sib = rows0 <= 0 ? 0 : tall ? 1 : ((m0 + 1 < n_mtiles && rows_of(m0 + 1) > 0) ? 2 : 1);   // 0: empty slot
         const int n_nt = tall ? (sp.g1.N + kTallCols1 - 1) / kTallCols1 : nN1;
         const int parts0 = parts_of(m0), parts1 = n_sib > 1 ? parts_of(m0 + 1) : 0;
         for (int i = lane; i < n_nt * n_sib; i += kWave) {
@@ -318,8 +324,8 @@ __device__ __forceinline__ void build_task_tables(const SchedParams<BF16>& sp) {
       }
       if (j >= lag) {
         const int m0 = 2 * (q + kNumXcd * (j - lag));
-        const bool tall = sp.route.tiles.rows[m0] > kTallAbove;
-        const int n_sib = sp.route.tiles.rows[m0] <= 0 ? 0 : tall ? 1 : ((m0 + 1 < n_mtiles && sp.route.tiles.rows[m0 + 1] > 0) ? 2 : 1);
+        const bool tall = rows_of(m0) > kTallAbove;
+        const int n_sib = rows_of(m0) <= 0 ? 0 : tall ? 1 : ((m0 + 1 < n_mtiles && rows_of(m0 + 1) > 0) ? 2 : 1);
         const int n_nt = tall ? (sp.g2.N + 127) / 128 : nN2;
         const int g1_tiles = tall ? (sp.g1.N + kTallCols1 - 1) / kTallCols1 : nN1;   // GEMM-1 tiles that complete a row block of A
         for (int i = lane; i < n_nt * n_sib; i += kWave) {
@@ -346,7 +352,7 @@ __device__ __forceinline__ void build_task_tables(const SchedParams<BF16>& sp) {
         int cnt = 0;
         if (lane < tail) {
           td = tq[n - tail + lane];
-          const bool wide = sp.route.tiles.rows[td.m] <= kTallAbove;
+          const bool wide = rows_of(td.m) <= kTallAbove;
           cnt = wide && 2 * (td.type_n >> 8) + 1 < n_half ? 2 : 1;
           if (wide) td.type_n = kTaskGemm2 | kTaskNarrow | ((2 * (td.type_n >> 8)) << 8);
         }
@@ -372,7 +378,7 @@ __device__ __forceinline__ void build_task_tables(const SchedParams<BF16>& sp) {
   if (wave == 0) {
     int total = 0;
     for (int m = lane; m < n_mtiles; m += kWave) {
-      const int rows = sp.route.tiles.rows[m];
+      const int rows = rows_of(m);
       total += rows > kTallAbove ? (sp.g2.N + 127) / 128 : (rows > 0 ? nN2 : 0);
     }
     if (lane < kNumXcd) total += s_extra[lane];
@@ -384,8 +390,8 @@ __device__ __forceinline__ void build_task_tables(const SchedParams<BF16>& sp) {
 // Second routing launch (both launch modes): prefix sums and M-tile map by workgroup 0, stable ranks by the
 // others, plus, in workgroup 0, the tile scheduler's counters and task tables.
 template <bool BF16>
-__global__ __launch_bounds__(kScanRankWaves * kWave) void sched_prepare_kernel(SchedParams<BF16> sp) {
-  __shared__ int32_t s_lds[kScanRankWaves * kRankLdsWords];   // rank: 4 * kMaxE words per wave; scan: (5 * kMaxE + 66) words
+__global__ __launch_bounds__(kScanWaves * kWave) void sched_prepare_kernel(SchedParams<BF16> sp) {
+  __shared__ int32_t s_lds[kScanRankLds];
   if (blockIdx.x == 0) {
     scan_all(sp.route, s_lds, s_lds + kMaxE + 64);
     __threadfence_block();
@@ -393,7 +399,7 @@ __global__ __launch_bounds__(kScanRankWaves * kWave) void sched_prepare_kernel(S
     if (!sp.skip_tables) build_task_tables<BF16>(sp);
     return;
   }
-  const int rank_wgs = (sp.route.n_groups + kScanRankWaves - 1) / kScanRankWaves;
+  const int rank_wgs = (sp.route.n_groups + kRankWaves - 1) / kRankWaves;
   if ((int)blockIdx.x > rank_wgs) {       // fill workgroups: the launch lasts as long as workgroup 0's chain anyway
     const size_t stride = (size_t)(gridDim.x - 1 - rank_wgs) * blockDim.x;
     for (size_t i = (size_t)(blockIdx.x - 1 - rank_wgs) * blockDim.x + threadIdx.x; i < sp.zero_n16; i += stride)
@@ -401,8 +407,8 @@ __global__ __launch_bounds__(kScanRankWaves * kWave) void sched_prepare_kernel(S
     return;
   }
   const int wave = threadIdx.x / kWave;
-  const int group = (blockIdx.x - 1) * kScanRankWaves + wave;
-  if (group < sp.route.n_groups) rank_chunk(sp.route, group, s_lds + wave * kRankLdsWords);
+  const int group = (blockIdx.x - 1) * kRankWaves + wave;
+  if (wave < kRankWaves && group < sp.route.n_groups) rank_chunk(sp.route, group, s_lds + wave * kRankLdsWords);
 }
 
 // Both routing launches as one, for few tokens (route_one): workgroup 0 routes, further ones only fill.
@@ -542,8 +548,12 @@ void persistent_forward_kernel(SchedParams<BF16> sp) {
 // 256 CUs at H = 7168, I = 2048, 32 experts of ~254 rows).  sp.g1 = act_grad, sp.g2 = gate_grad,
 // sp.route.tiles = the backward's M-tile map; the other members of sp are unused.
 
-// One workgroup: zero the counters, then build the per-XCD task tables from the finished tile map.
-__global__ __launch_bounds__(kGemmThreads) void dgrad_prepare_kernel(SchedParams<true> sp) {
+// Backward Dispatch whose first workgroup, behind the tile map, zeroes the counters and builds the per-XCD task tables of the
+// launch below: it is done long before the rows are (as a launch of its own it took 10 us).
+__global__ __launch_bounds__(kGemmThreads) void bwd_dispatch_tables_kernel(BwdDispatchParams p, SchedParams<true> sp) {
+  if (!bwd_dispatch<true>(p)) return;
+  __threadfence_block();
+  __syncthreads();   // tile map (written by wave 0) complete before every wave reads it
   build_task_tables<true, true>(sp);
 }
 

@@ -620,8 +620,10 @@ __device__ __forceinline__ void route_one(const RouteParams& p) {
 
 // The two steps that need nothing but the finished histogram table run side by side in one launch
 // (sched_prepare_kernel): workgroup 0 sums the table into counts, offsets and the M-tile map; every other
-// workgroup ranks 4 groups of 64 tokens, one per wave.  Grid: 1 + ceil(n_groups / 4) workgroups of 256 threads.
-constexpr int kScanRankWaves = 4;
-static_assert(kScanRankWaves * kRankLdsWords >= (kScanRankWaves + 1) * kMaxE + 2 + 64, "LDS of the scan step");
+// workgroup ranks 4 groups of 64 tokens, one per wave.  Grid: 1 + ceil(n_groups / 4) workgroups of 512 threads: workgroup 0, the
+// launch's critical path, walks the table and builds the task tables (a queue per wave) with eight waves; with as many rank waves to
+// a workgroup the walks of one CU delayed each other (T = 8192, 32 experts, without tables 16 us, with eight 18).
+constexpr int kScanWaves = 8, kRankWaves = 4;
+constexpr int kScanRankLds = kRankWaves * kRankLdsWords > (kScanWaves + 1) * kMaxE + 66 ? kRankWaves * kRankLdsWords : (kScanWaves + 1) * kMaxE + 66;
 
 }  // namespace moe

@@ -372,8 +372,8 @@ SchedParams<BF16> sched_params(const Ctx& c, const void* x, const float* logits,
 // M-tile map + stable ranks.  The second launch also zeroes the tile scheduler's counters and writes its task tables (one
 // workgroup, beside the rank groups), so that either launch mode can follow.
 template <bool BF16>
-int run_route_t(const Ctx& c, const float* logits, bool tables, void* zero_out) {
-  SchedParams<BF16> sp = sched_params<BF16>(c, nullptr, logits, nullptr, nullptr, nullptr);
+int run_route_t(const Ctx& c, const float* logits, bool tables, void* zero_out, const void* copy_x) {
+  SchedParams<BF16> sp = sched_params<BF16>(c, copy_x, logits, nullptr, nullptr, nullptr);
   sp.skip_tables = tables ? 0 : 1;
   if (zero_out) sp.no_tasks = 0;          // the scatter epilogue follows, which runs as tasks
   const RouteParams& rp = sp.route;
@@ -391,6 +391,14 @@ int run_route_t(const Ctx& c, const float* logits, bool tables, void* zero_out) 
     return launch_status();
   }
   hipLaunchKernelGGL(route_kernel, dim3(rp.n_sub), dim3(512), 0, c.stream, rp);
+  if (copy_x) {
+    // tokens per workgroup: a workgroup per CU, as long as each has a token
+    int tokens = kSub;
+    while (tokens > 4 && (c.s.T + tokens - 1) / tokens < c.n_cu) tokens >>= 1;
+    hipLaunchKernelGGL(sched_prepare_copy_kernel<BF16>, dim3(1 + (c.s.T + tokens - 1) / tokens), dim3(kRankCopyThreads), 0, c.stream, sp,
+                       tokens);
+    return launch_status();
+  }
   hipLaunchKernelGGL(sched_prepare_kernel<BF16>, dim3(1 + (rp.n_groups + kRankWaves - 1) / kRankWaves + fill_wgs),
                      dim3(kScanWaves * kWave), 0, c.stream, sp);
   return launch_status();
@@ -398,9 +406,10 @@ int run_route_t(const Ctx& c, const float* logits, bool tables, void* zero_out) 
 // tables = false: the caller knows that one launch per operator follows (the task tables take workgroup 0 of the
 // second launch, which is the launch's critical path, about as long again as the prefix sums and the tile map).
 // zero_out: the layer output, zeroed by further workgroups of the second launch (scatter epilogue follows).
-int run_route(const Ctx& c, const float* logits, bool tables = true, void* zero_out = nullptr) {
-  return c.s.dtype == MOE_BF16 ? run_route_t<true>(c, logits, tables, zero_out)
-                               : run_route_t<false>(c, logits, tables, zero_out);
+// copy_x: Dispatch in the second launch as well (more than kRouteOneT tokens, no tables, nothing to zero).
+int run_route(const Ctx& c, const float* logits, bool tables = true, void* zero_out = nullptr, const void* copy_x = nullptr) {
+  return c.s.dtype == MOE_BF16 ? run_route_t<true>(c, logits, tables, zero_out, copy_x)
+                               : run_route_t<false>(c, logits, tables, zero_out, copy_x);
 }
 
 // Dispatch to Combine as ONE launch of tile tasks (after run_route on the same MoeSaved).
@@ -865,8 +874,9 @@ int moe_ffn_forward_scatter(const MoeShape* shape, const void* d_x, const float*
 }
 
 // Dispatch -> GEMM-1 + SwiGLU -> GEMM-2 -> Combine on routing results that are already in `saved` / the workspace.
+// dispatched: the permuted copy is there already (run_route).
 static int run_dispatch_to_combine(const Ctx& c, const void* d_x, const void* d_w_gate_up, const void* d_w_down,
-                                   void* d_out, int mode) {
+                                   void* d_out, int mode, bool dispatched = false) {
   if (mode != MOE_MODE_SERIALIZED && mode != MOE_MODE_PERSISTENT) return MOE_ERR_INVALID_ARG;
   const void* ptrs[] = {d_x, d_w_gate_up, d_w_down, d_out};
   for (const void* q : ptrs)
@@ -879,7 +889,7 @@ static int run_dispatch_to_combine(const Ctx& c, const void* d_x, const void* d_
                                  : run_persistent<false>(c, d_x, d_w_gate_up, d_w_down, d_out);
   }
   int st;
-  if (!gathers_x(c) && (st = run_permute(c, d_x)) != MOE_OK) return st;
+  if (!dispatched && !gathers_x(c) && (st = run_permute(c, d_x)) != MOE_OK) return st;
   if ((st = run_gemm1(c, d_w_gate_up, gathers_x(c) ? d_x : nullptr)) != MOE_OK) return st;
   if ((st = run_gemm2(c, d_w_down)) != MOE_OK) return st;
   return run_combine(c, d_out);
@@ -908,8 +918,9 @@ int moe_ffn_forward(const MoeShape* shape, const void* d_x, const float* d_logit
     if (!q || !aligned16(q)) return MOE_ERR_INVALID_ARG;
   if (mode == MOE_MODE_PERSISTENT && (!aligned128(c.ws) || !aligned128(c.sv.Xp) || !aligned128(c.sv.A)))
     return MOE_ERR_INVALID_ARG;   // before anything is enqueued
-  if ((st = run_route(c, d_logits, mode == MOE_MODE_PERSISTENT)) != MOE_OK) return st;
-  return run_dispatch_to_combine(c, d_x, d_w_gate_up, d_w_down, d_out, mode);
+  const bool copies = mode == MOE_MODE_SERIALIZED && !gathers_x(c) && c.s.T > kRouteOneT;
+  if ((st = run_route(c, d_logits, mode == MOE_MODE_PERSISTENT, nullptr, copies ? d_x : nullptr)) != MOE_OK) return st;
+  return run_dispatch_to_combine(c, d_x, d_w_gate_up, d_w_down, d_out, mode, copies);
 }
 
 int moe_ffn_backward(const MoeShape* shape, const void* d_dy, const void* d_x, const void* d_w_gate_up,

@@ -77,6 +77,30 @@ __device__ __forceinline__ void permute_rows(const PermuteParams& p, int r_begin
   }
 }
 
+// The row of token t to the rows of its local slots (lane j: the row of slot j, or -1), by one wave: read once.
+template <int U>
+__device__ __forceinline__ void permute_token(const PermuteParams& p, int t, int rowv) {
+  const int lane = lane_id();
+  const uint64_t local = __ballot(rowv >= 0);
+  if (local == 0) return;
+  const int vec_per_row = (p.H * p.elem_bytes) / 16;
+  const size_t row_bytes = (size_t)p.H * p.elem_bytes;
+  const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const char*>(p.x) + (size_t)t * row_bytes);
+  for (int v0 = lane; v0 < vec_per_row; v0 += U * kWave) {
+    u32x4 q[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (v0 + u * kWave < vec_per_row) q[u] = __builtin_nontemporal_load(src + v0 + u * kWave);
+    for (uint64_t m = local; m != 0; m &= m - 1) {
+      const int r = __builtin_amdgcn_readlane(rowv, __builtin_amdgcn_readfirstlane(__builtin_ctzll(m)));
+      u32x4* dst = reinterpret_cast<u32x4*>(static_cast<char*>(p.Xp) + (size_t)r * row_bytes);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (v0 + u * kWave < vec_per_row) __builtin_nontemporal_store(q[u], dst + v0 + u * kWave);
+    }
+  }
+}
+
 __global__ __launch_bounds__(256) void permute_kernel(PermuteParams p) {
   const int R = p.meta[kMetaRows];
   const int n_waves = blockDim.x / kWave;

@@ -387,6 +387,16 @@ __device__ __forceinline__ void build_task_tables(const SchedParams<BF16>& sp) {
   }
 }
 
+// Vector tasks of a 4-wave worker: 16-byte vectors per lane and pass matched to the row length (a row of H = 7168
+// bf16 is 14 per lane, of H = 2048 four): a pass wider than the row spends its instructions on vectors that do not
+// exist (COMBINE) or falls through to a one-vector-at-a-time tail (PERMUTE).
+template <typename F>
+__device__ __forceinline__ void with_row_vectors(int vec_per_row, F&& f) {
+  if (vec_per_row >= 14 * kWave) f(std::integral_constant<int, 14>{});
+  else if (vec_per_row >= 7 * kWave) f(std::integral_constant<int, 7>{});
+  else f(std::integral_constant<int, 4>{});
+}
+
 // Second routing launch (both launch modes): prefix sums and M-tile map by workgroup 0, stable ranks by the
 // others, plus, in workgroup 0, the tile scheduler's counters and task tables.
 template <bool BF16>
@@ -411,6 +421,21 @@ __global__ __launch_bounds__(kScanWaves * kWave) void sched_prepare_kernel(Sched
   if (wave < kRankWaves && group < sp.route.n_groups) rank_chunk(sp.route, group, s_lds + wave * kRankLdsWords);
 }
 
+// The same with Dispatch in it (serialized launches that keep or need a permuted copy): the other workgroups rank `tokens` tokens each
+// and copy their rows.
+template <bool BF16>
+__global__ __launch_bounds__(kRankCopyThreads) void sched_prepare_copy_kernel(SchedParams<BF16> sp, int tokens) {
+  __shared__ int32_t s_lds[(kScanWaves + 1) * kMaxE + 66];
+  static_assert(kRankCopyThreads == kScanWaves * kWave, "workgroup 0 scans with all its waves");
+  if (blockIdx.x == 0) {
+    scan_all(sp.route, s_lds, s_lds + kMaxE + 64);
+    return;
+  }
+  rank_copy(sp.route, ((int)blockIdx.x - 1) * tokens, tokens, [&](int t, int rowv) __attribute__((always_inline)) {
+    with_row_vectors(sp.perm.H * sp.perm.elem_bytes / 16, [&](auto uv) { permute_token<decltype(uv)::value>(sp.perm, t, rowv); });
+  });
+}
+
 // Both routing launches as one, for few tokens (route_one): workgroup 0 routes, further ones only fill.
 template <bool BF16>
 __global__ __launch_bounds__(kRouteOneThreads) void route_one_kernel(SchedParams<BF16> sp) {
@@ -425,16 +450,6 @@ __global__ __launch_bounds__(kRouteOneThreads) void route_one_kernel(SchedParams
   __threadfence_block();
   __syncthreads();   // tile map (written by wave 0) complete before every wave reads it
   build_task_tables<BF16>(sp);
-}
-
-// Vector tasks of a 4-wave worker: 16-byte vectors per lane and pass matched to the row length (a row of H = 7168
-// bf16 is 14 per lane, of H = 2048 four): a pass wider than the row spends its instructions on vectors that do not
-// exist (COMBINE) or falls through to a one-vector-at-a-time tail (PERMUTE).
-template <typename F>
-__device__ __forceinline__ void with_row_vectors(int vec_per_row, F&& f) {
-  if (vec_per_row >= 14 * kWave) f(std::integral_constant<int, 14>{});
-  else if (vec_per_row >= 7 * kWave) f(std::integral_constant<int, 7>{});
-  else f(std::integral_constant<int, 4>{});
 }
 
 // SCATTER (bf16): GEMM-2 tiles add their weighted rows into the zeroed layer output from their epilogue

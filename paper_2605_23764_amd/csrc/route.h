@@ -626,4 +626,63 @@ __device__ __forceinline__ void route_one(const RouteParams& p) {
 constexpr int kScanWaves = 8, kRankWaves = 4;
 constexpr int kScanRankLds = kRankWaves * kRankLdsWords > (kScanWaves + 1) * kMaxE + 66 ? kRankWaves * kRankLdsWords : (kScanWaves + 1) * kMaxE + 66;
 
+// Stable ranks of `tokens` (a divisor of kSub) tokens from t0 on, and Dispatch of their rows in the same breath, by a workgroup of
+// 512 threads: thread = (token of the sub-chunk, slot).  The table walk is spread over all lanes of the workgroup (sums in LDS, whole
+// numbers, so their order does not matter); f(token, lane j < 16: row of slot j or -1) then copies, a token per wave.
+constexpr int kRankCopyThreads = kSub * kMaxK;
+template <typename F>
+__device__ __forceinline__ void rank_copy(const RouteParams& p, int t0, int tokens, F&& copy) {
+  __shared__ int32_t s_total[kMaxE], s_base[kMaxE], s_row[kSub * kMaxK];
+  __shared__ uint32_t s_mask[kMaxE];
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  constexpr int kWaves = kRankCopyThreads / kWave;
+  const int sub = t0 / kSub, i = threadIdx.x / kMaxK, j = threadIdx.x % kMaxK, t = sub * kSub + i;
+  const bool slot = t < p.T && j < p.k;
+  const int idx = slot ? p.topk_idx[(size_t)t * p.k + j] : -1;
+  for (int e = threadIdx.x; e < p.E_local; e += kRankCopyThreads) { s_total[e] = 0; s_base[e] = 0; s_mask[e] = 0u; }
+  __syncthreads();
+  const int ew = p.E_local >= kWave ? kWave : (p.E_local <= 1 ? 1 : 1 << (32 - __builtin_clz(p.E_local - 1)));
+  const int parts = kWaves * (kWave / ew), part = wave * (kWave / ew) + (lane >> __builtin_ctz(ew)), el = lane & (ew - 1);
+  constexpr int kBatch = 8;
+  for (int e = el; e < p.E_local; e += ew) {
+    int total = 0, before = 0;
+    for (int c0 = part * kBatch; c0 < p.n_sub; c0 += kBatch * parts) {
+      int v[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) v[u] = c0 + u < p.n_sub ? p.chunk_cnt[(size_t)(c0 + u) * p.E_local + e] : 0;
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        total += v[u];
+        before += c0 + u < sub ? v[u] : 0;
+      }
+    }
+    if (total) atomicAdd(&s_total[e], total);
+    if (before) atomicAdd(&s_base[e], before);
+  }
+  const int l = slot && idx >= p.expert_base && idx - p.expert_base < p.E_local ? idx - p.expert_base : -1;
+  if (l >= 0) atomicOr(&s_mask[l], 1u << i);
+  __syncthreads();
+  if (wave == 0) {
+    int run = 0;   // rows of the experts before this block of 64
+    for (int e0 = 0; e0 < p.E_local; e0 += kWave) {
+      const int c = e0 + lane < p.E_local ? s_total[e0 + lane] : 0;
+      const int incl = wave_incl_scan(c, lane);
+      if (e0 + lane < p.E_local) s_base[e0 + lane] += run + incl - c;
+      run += __shfl(incl, kWave - 1, kWave);
+    }
+  }
+  __syncthreads();
+  const int r = l >= 0 ? s_base[l] + __popc(s_mask[l] & ((1u << i) - 1u)) : -1;
+  s_row[threadIdx.x] = r;
+  if (slot && t >= t0 && t < t0 + tokens) {
+    p.row_of[(size_t)t * p.k + j] = r;
+    if (r >= 0) {
+      p.token_of[r] = t;
+      p.slot_of[r] = j;
+    }
+  }
+  __syncthreads();
+  for (int n = t0 + wave; n < min(t0 + tokens, p.T); n += kWaves) copy(n, lane < kMaxK ? s_row[(n - sub * kSub) * kMaxK + lane] : -1);
+}
+
 }  // namespace moe

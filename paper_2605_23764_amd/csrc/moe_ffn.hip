@@ -42,7 +42,6 @@ inline int tile_wide_max(const MoeShape& s) { return s.dtype == MOE_BF16 ? kWide
 inline int perm_task_rows(const MoeShape& s) { return (size_t)s.H * elem_bytes(s) >= 8192 ? kPermRows : 2 * kPermRows; }
 inline long r_max(const MoeShape& s) { return (long)s.T * (s.k < s.E_local ? s.k : s.E_local); }
 inline int n_sub(const MoeShape& s) { return (s.T + kSub - 1) / kSub; }
-inline int n_groups(const MoeShape& s) { return (s.T + kChunk - 1) / kChunk; }
 // pair slots of the tile map: a tall tile (> BM rows) takes two entries, a wide tile of a split expert has > BM/2 rows
 inline long max_mtiles(const MoeShape& s) { return 2 * (r_max(s) / tile_bm(s)) + 2 * s.E_local + kMapSlack; }
 inline int tile_tall(const MoeShape& s) { return s.dtype == MOE_BF16 ? kTallRows : 0; }
@@ -195,7 +194,6 @@ RouteParams route_params(const Ctx& c, const float* logits) {
   p.tiles = tile_map(c);
   p.T = c.s.T; p.E = c.s.E; p.E_local = c.s.E_local; p.expert_base = c.s.expert_base; p.k = c.s.k;
   p.n_sub = n_sub(c.s);
-  p.n_groups = n_groups(c.s);
   p.BM = tile_bm(c.s);
   p.granule = c.s.dtype == MOE_BF16 ? kRowGranule : kFBM;
   p.tall = tile_tall(c.s);
@@ -395,11 +393,11 @@ int run_route_t(const Ctx& c, const float* logits, bool tables, void* zero_out, 
     // tokens per workgroup: a workgroup per CU, as long as each has a token
     int tokens = kSub;
     while (tokens > 4 && (c.s.T + tokens - 1) / tokens < c.n_cu) tokens >>= 1;
-    hipLaunchKernelGGL(sched_prepare_copy_kernel<BF16>, dim3(1 + (c.s.T + tokens - 1) / tokens), dim3(kRankCopyThreads), 0, c.stream, sp,
+    hipLaunchKernelGGL(sched_prepare_copy_kernel<BF16>, dim3(1 + (c.s.T + tokens - 1) / tokens), dim3(kRankThreads), 0, c.stream, sp,
                        tokens);
     return launch_status();
   }
-  hipLaunchKernelGGL(sched_prepare_kernel<BF16>, dim3(1 + (rp.n_groups + kRankWaves - 1) / kRankWaves + fill_wgs),
+  hipLaunchKernelGGL(sched_prepare_kernel<BF16>, dim3(1 + rp.n_sub + fill_wgs),
                      dim3(kScanWaves * kWave), 0, c.stream, sp);
   return launch_status();
 }

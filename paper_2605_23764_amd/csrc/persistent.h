@@ -401,7 +401,8 @@ __device__ __forceinline__ void with_row_vectors(int vec_per_row, F&& f) {
 // others, plus, in workgroup 0, the tile scheduler's counters and task tables.
 template <bool BF16>
 __global__ __launch_bounds__(kScanWaves * kWave) void sched_prepare_kernel(SchedParams<BF16> sp) {
-  __shared__ int32_t s_lds[kScanRankLds];
+  __shared__ int32_t s_lds[kScanLds];
+  static_assert(kRankThreads == kScanWaves * kWave, "workgroup 0 scans with all its waves");
   if (blockIdx.x == 0) {
     scan_all(sp.route, s_lds, s_lds + kMaxE + 64);
     __threadfence_block();
@@ -409,29 +410,26 @@ __global__ __launch_bounds__(kScanWaves * kWave) void sched_prepare_kernel(Sched
     if (!sp.skip_tables) build_task_tables<BF16>(sp);
     return;
   }
-  const int rank_wgs = (sp.route.n_groups + kRankWaves - 1) / kRankWaves;
+  const int rank_wgs = sp.route.n_sub;
   if ((int)blockIdx.x > rank_wgs) {       // fill workgroups: the launch lasts as long as workgroup 0's chain anyway
     const size_t stride = (size_t)(gridDim.x - 1 - rank_wgs) * blockDim.x;
     for (size_t i = (size_t)(blockIdx.x - 1 - rank_wgs) * blockDim.x + threadIdx.x; i < sp.zero_n16; i += stride)
       sp.zero_dst[i] = make_uint4(0, 0, 0, 0);
     return;
   }
-  const int wave = threadIdx.x / kWave;
-  const int group = (blockIdx.x - 1) * kRankWaves + wave;
-  if (wave < kRankWaves && group < sp.route.n_groups) rank_chunk(sp.route, group, s_lds + wave * kRankLdsWords);
+  rank_tokens(sp.route, ((int)blockIdx.x - 1) * kSub, kSub, [](int, int) {});
 }
 
 // The same with Dispatch in it (serialized launches that keep or need a permuted copy): the other workgroups rank `tokens` tokens each
 // and copy their rows.
 template <bool BF16>
-__global__ __launch_bounds__(kRankCopyThreads) void sched_prepare_copy_kernel(SchedParams<BF16> sp, int tokens) {
-  __shared__ int32_t s_lds[(kScanWaves + 1) * kMaxE + 66];
-  static_assert(kRankCopyThreads == kScanWaves * kWave, "workgroup 0 scans with all its waves");
+__global__ __launch_bounds__(kRankThreads) void sched_prepare_copy_kernel(SchedParams<BF16> sp, int tokens) {
+  __shared__ int32_t s_lds[kScanLds];
   if (blockIdx.x == 0) {
     scan_all(sp.route, s_lds, s_lds + kMaxE + 64);
     return;
   }
-  rank_copy(sp.route, ((int)blockIdx.x - 1) * tokens, tokens, [&](int t, int rowv) __attribute__((always_inline)) {
+  rank_tokens(sp.route, ((int)blockIdx.x - 1) * tokens, tokens, [&](int t, int rowv) __attribute__((always_inline)) {
     with_row_vectors(sp.perm.H * sp.perm.elem_bytes / 16, [&](auto uv) { permute_token<decltype(uv)::value>(sp.perm, t, rowv); });
   });
 }

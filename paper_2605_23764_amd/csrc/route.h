@@ -4,7 +4,7 @@
 // Three steps, each a device function:
 //   route_chunk  top-k + softmax for the 64 tokens of a chunk, per-chunk expert histogram
 //   scan_all     prefix sums over chunks and experts, counts/offsets, M-tile map
-//   rank_chunk   stable row of every local slot, inverse maps
+//   rank_tokens  stable row of every local slot, inverse maps
 // The permutation is a stable counting sort keyed by expert: rows of one expert
 // ascend in token id, so every index is a pure function of the routing result
 // (no atomics decide an order).
@@ -28,7 +28,6 @@ struct RouteParams {
   TileMap tiles;
   int T, E, E_local, expert_base, k;
   int n_sub;     // ceil(T / kSub) histogram rows
-  int n_groups;  // ceil(T / kChunk) rank groups
   int BM;        // M-tile row capacity of the plain wide shape
   int wide_max;  // rows a single wide M tile can take (>= BM: the bf16 kernels feed one more row block per wave row from registers)
   int tall;      // row capacity of a tall M tile (0 = the kernels have no tall shape)
@@ -463,92 +462,6 @@ __device__ __forceinline__ void scan_all(const RouteParams& p, int32_t* s_cnt, i
   if (wave == 0) build_tile_map(p.E_local, s_cnt, p.wide_max, p.granule, p.tall, p.counts, p.offsets, p.tiles);
 }
 
-constexpr int kRankLdsWords = 4 * kMaxE;   // LDS words rank_chunk needs per wave
-
-// Rows of the local slots of one group of kChunk tokens, by one wave (lane = token):
-// row = (rows of lower experts) + (tokens of earlier sub-chunks selecting e) + (earlier lanes of the
-// token's own sub-chunk selecting e).
-// The first two terms come straight from the histogram table (lane = expert: one
-// pass over its rows gives every expert's total and its count in earlier sub-chunks;
-// a wave scan of the totals gives the expert offsets), so a group needs nothing but
-// the finished table.  The lanes that selected expert e are collected as a 64-bit
-// mask per expert in LDS (an OR, so the result does not depend on the order of the
-// updates); a slot's rank inside its sub-chunk is the number of lower lanes of that
-// sub-chunk in its expert's mask.
-// s_lds: kRankLdsWords int32 of LDS owned by this wave.
-__device__ __forceinline__ void rank_chunk(const RouteParams& p, int group, int32_t* s_lds) {
-  const int lane = lane_id();
-  const int t = group * kChunk + lane;
-  const bool live = t < p.T;
-  unsigned long long* s_mask = reinterpret_cast<unsigned long long*>(s_lds);   // [E_local]
-  int32_t* s_base = s_lds + 2 * kMaxE;                                           // [2][E_local] first row per half
-  const int sub0 = group * (kChunk / kSub);
-  // The table walk is a chain of round trips to the L2, so it is spread over all 64 lanes: with fewer than 64
-  // local experts, `parts` lanes share an expert and take every parts-th batch of rows (E_local = 32: 8 round
-  // trips instead of 16 at T = 8192); their partial sums are added with a butterfly.
-  const int ew = p.E_local >= kWave ? kWave : (p.E_local <= 1 ? 1 : 1 << (32 - __builtin_clz(p.E_local - 1)));
-  const int parts = kWave / ew, part = lane >> __builtin_ctz(ew), el = lane & (ew - 1);
-  int run = 0;   // rows of the experts before this block of ew
-  for (int e0 = 0; e0 < p.E_local; e0 += ew) {
-    const int e = e0 + el;
-    int total = 0, before = 0, own0 = 0;
-    if (e < p.E_local) {
-      for (int c0 = part * kHistBatch; c0 < p.n_sub; c0 += kHistBatch * parts) {
-        int v[kHistBatch];
-#pragma unroll
-        for (int u = 0; u < kHistBatch; ++u) v[u] = c0 + u < p.n_sub ? p.chunk_cnt[(size_t)(c0 + u) * p.E_local + e] : 0;
-#pragma unroll
-        for (int u = 0; u < kHistBatch; ++u) {
-          total += v[u];
-          before += c0 + u < sub0 ? v[u] : 0;
-          own0 = c0 + u == sub0 ? v[u] : own0;
-        }
-      }
-    }
-    for (int off = ew; off < kWave; off <<= 1) {   // own0 is non-zero in one part only
-      total += __shfl_xor(total, off, kWave);
-      before += __shfl_xor(before, off, kWave);
-      own0 += __shfl_xor(own0, off, kWave);
-    }
-    const int incl = wave_incl_scan(part == 0 ? total : 0, lane);   // lanes 0..ew-1: running sum over the experts
-    if (part == 0 && e < p.E_local) {
-      const int first = run + incl - total + before;
-      s_mask[e] = 0ull;
-      s_base[e] = first;
-      s_base[kMaxE + e] = first + own0;
-    }
-    run += __shfl(incl, kWave - 1, kWave);
-  }
-  int32_t le[kMaxK];
-#pragma unroll
-  for (int j = 0; j < kMaxK; ++j) {
-    const int idx = (live && j < p.k) ? p.topk_idx[(size_t)t * p.k + j] : -1;
-    const int l = idx - p.expert_base;
-    le[j] = (idx >= 0 && l >= 0 && l < p.E_local) ? l : -1;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int j = 0; j < kMaxK; ++j)
-    if (le[j] >= 0) atomicOr(&s_mask[le[j]], 1ull << lane);
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  const int half = lane / kSub;
-  // lower lanes of this lane's own sub-chunk
-  const unsigned long long lt = ((1ull << lane) - 1ull) & (half ? ~((1ull << kSub) - 1ull) : ~0ull);
-#pragma unroll
-  for (int j = 0; j < kMaxK; ++j) {
-    if (j >= p.k) break;
-    int r = -1;
-    if (le[j] >= 0) {
-      r = s_base[half * kMaxE + le[j]] + __popcll(s_mask[le[j]] & lt);
-      p.token_of[r] = t;
-      p.slot_of[r] = j;
-    }
-    if (live) p.row_of[(size_t)t * p.k + j] = r;
-  }
-}
-
 __global__ __launch_bounds__(512) void route_kernel(RouteParams p) {
   __shared__ int32_t s_idx[kSub * kMaxK];
   __shared__ float s_val[kSub * kMaxK];
@@ -618,28 +531,30 @@ __device__ __forceinline__ void route_one(const RouteParams& p) {
   }
 }
 
-// The two steps that need nothing but the finished histogram table run side by side in one launch
-// (sched_prepare_kernel): workgroup 0 sums the table into counts, offsets and the M-tile map; every other
-// workgroup ranks 4 groups of 64 tokens, one per wave.  Grid: 1 + ceil(n_groups / 4) workgroups of 512 threads: workgroup 0, the
-// launch's critical path, walks the table and builds the task tables (a queue per wave) with eight waves; with as many rank waves to
-// a workgroup the walks of one CU delayed each other (T = 8192, 32 experts, without tables 16 us, with eight 18).
-constexpr int kScanWaves = 8, kRankWaves = 4;
-constexpr int kScanRankLds = kRankWaves * kRankLdsWords > (kScanWaves + 1) * kMaxE + 66 ? kRankWaves * kRankLdsWords : (kScanWaves + 1) * kMaxE + 66;
+// The two steps that need nothing but the finished histogram table run side by side in one launch of 512-thread workgroups
+// (sched_prepare_kernel): workgroup 0, the launch's critical path, sums the table into counts, offsets and the M-tile map; every
+// other one ranks a few tokens.
+constexpr int kScanWaves = 8;
+constexpr int kScanLds = (kScanWaves + 1) * kMaxE + 66;
 
-// Stable ranks of `tokens` (a divisor of kSub) tokens from t0 on, and Dispatch of their rows in the same breath, by a workgroup of
-// 512 threads: thread = (token of the sub-chunk, slot).  The table walk is spread over all lanes of the workgroup (sums in LDS, whole
-// numbers, so their order does not matter); f(token, lane j < 16: row of slot j or -1) then copies, a token per wave.
-constexpr int kRankCopyThreads = kSub * kMaxK;
+// Rows of the local slots of `tokens` (a divisor of kSub) tokens from t0 on, by a workgroup of 512 threads, thread = (token of the
+// sub-chunk, slot): row = (rows of lower experts) + (tokens of earlier sub-chunks selecting e) + (lower tokens of the own sub-chunk
+// selecting e).  The first two terms come straight from the histogram table, whose walk is spread over all lanes of the workgroup
+// (sums in LDS, whole numbers, so their order does not matter; fewer than 64 local experts: several lanes to an expert); the tokens
+// of the sub-chunk that selected expert e stand as a mask per expert, so the third is a population count.
+// done(token, lane j < 16: row of slot j or -1) follows, a token per wave: Dispatch, where the launch copies rows as well.
+// With a wave per 64 tokens, four to a workgroup: T = 8192, 256 local experts, H = 256, forward 170 us, with this 115.
+constexpr int kRankThreads = kSub * kMaxK;
 template <typename F>
-__device__ __forceinline__ void rank_copy(const RouteParams& p, int t0, int tokens, F&& copy) {
+__device__ __forceinline__ void rank_tokens(const RouteParams& p, int t0, int tokens, F&& done) {
   __shared__ int32_t s_total[kMaxE], s_base[kMaxE], s_row[kSub * kMaxK];
   __shared__ uint32_t s_mask[kMaxE];
   const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  constexpr int kWaves = kRankCopyThreads / kWave;
+  constexpr int kWaves = kRankThreads / kWave;
   const int sub = t0 / kSub, i = threadIdx.x / kMaxK, j = threadIdx.x % kMaxK, t = sub * kSub + i;
   const bool slot = t < p.T && j < p.k;
   const int idx = slot ? p.topk_idx[(size_t)t * p.k + j] : -1;
-  for (int e = threadIdx.x; e < p.E_local; e += kRankCopyThreads) { s_total[e] = 0; s_base[e] = 0; s_mask[e] = 0u; }
+  for (int e = threadIdx.x; e < p.E_local; e += kRankThreads) { s_total[e] = 0; s_base[e] = 0; s_mask[e] = 0u; }
   __syncthreads();
   const int ew = p.E_local >= kWave ? kWave : (p.E_local <= 1 ? 1 : 1 << (32 - __builtin_clz(p.E_local - 1)));
   const int parts = kWaves * (kWave / ew), part = wave * (kWave / ew) + (lane >> __builtin_ctz(ew)), el = lane & (ew - 1);
@@ -682,7 +597,7 @@ __device__ __forceinline__ void rank_copy(const RouteParams& p, int t0, int toke
     }
   }
   __syncthreads();
-  for (int n = t0 + wave; n < min(t0 + tokens, p.T); n += kWaves) copy(n, lane < kMaxK ? s_row[(n - sub * kSub) * kMaxK + lane] : -1);
+  for (int n = t0 + wave; n < min(t0 + tokens, p.T); n += kWaves) done(n, lane < kMaxK ? s_row[(n - sub * kSub) * kMaxK + lane] : -1);
 }
 
 }  // namespace moe

@@ -275,12 +275,13 @@ constexpr int kMaxBrokenTiles = 14;   // tiles of at most 7 broken pair slots
 __device__ __forceinline__ int single_cost_of_rows(int rows) {
   return max((rows + 63) & ~63, 128);   // small tiles still stream the expert's whole weight panel
 }
-__device__ __forceinline__ void build_tile_map(int E_local, const int32_t* cnt, int wide_max, int granule, int tall,
-                                               int32_t* counts, int32_t* offsets, const TileMap& tiles) {
-  __shared__ int32_t s_broken[3][16];   // expert, first row, rows of the tiles of broken pair slots
+// kPasses: 64 experts each.  A chain of once-executed code by one wave, so its length counts: layers of up to 64 local experts have a
+// body of a quarter of the instructions (build_tile_map).
+template <int kPasses>
+__device__ __forceinline__ void build_tile_map_of(int E_local, const int32_t* cnt, int wide_max, int granule, int tall,
+                                                  int32_t* counts, int32_t* offsets, const TileMap& tiles, int32_t (&s_broken)[3][16]) {
   const int lane = lane_id();
   const bool balance = tall > 0;
-  constexpr int kPasses = kMaxE / kWave;
   // ---- per expert (lane = expert, kPasses passes): rows before it, tall slots and pair slots before it ----
   int off[kPasses], tall_ex[kPasses], pair_ex[kPasses], single_ex[kPasses];
   int cost[kPasses];     // cost of the expert's left-over single tile, 0 = none
@@ -424,6 +425,13 @@ __device__ __forceinline__ void build_tile_map(int E_local, const int32_t* cnt, 
     tiles.meta[kMetaRows] = n_rows;
     tiles.meta[kMetaStatus] = 0;
   }
+}
+
+__device__ __forceinline__ void build_tile_map(int E_local, const int32_t* cnt, int wide_max, int granule, int tall,
+                                               int32_t* counts, int32_t* offsets, const TileMap& tiles) {
+  __shared__ int32_t s_broken[3][16];   // expert, first row, rows of the tiles of broken pair slots
+  if (E_local <= kWave) build_tile_map_of<1>(E_local, cnt, wide_max, granule, tall, counts, offsets, tiles, s_broken);
+  else build_tile_map_of<kMaxE / kWave>(E_local, cnt, wide_max, granule, tall, counts, offsets, tiles, s_broken);
 }
 
 // Whole-problem step by ONE workgroup: rows per expert (column sums of the

@@ -354,24 +354,29 @@ __device__ __forceinline__ int stream_tables(const int32_t* offsets, int E_local
   const int lane = lane_id();
   const lds_i32_ptr s_expert = (lds_i32_ptr)(smem + kStreamTables), s_row0 = s_expert + kMaxE, s_rows = s_row0 + kMaxE;
   int n_act = 0, R = 0;
-  int lo[kMaxE / kWave], hi[kMaxE / kWave];
+  auto fill = [&](auto passes) __attribute__((always_inline)) {   // 64 experts each
+    constexpr int P = decltype(passes)::value;
+    int lo[P], hi[P];
 #pragma unroll
-  for (int i = 0; i < kMaxE / kWave; ++i) {
-    const int e = i * kWave + lane;
-    lo[i] = e < E_local ? offsets[e] : 0;
-    hi[i] = e < E_local ? offsets[e + 1] : 0;
-  }
-#pragma unroll
-  for (int i = 0; i < kMaxE / kWave; ++i) {
-    const uint64_t bal = __ballot(hi[i] > lo[i]);
-    const int at = n_act + __popcll(bal & ((1ull << lane) - 1));
-    if (threadIdx.x < kWave && hi[i] > lo[i]) {
-      s_expert[at] = i * kWave + lane;
-      s_row0[at] = lo[i];
-      s_rows[at] = hi[i] - lo[i];
+    for (int i = 0; i < P; ++i) {
+      const int e = i * kWave + lane;
+      lo[i] = e < E_local ? offsets[e] : 0;
+      hi[i] = e < E_local ? offsets[e + 1] : 0;
     }
-    n_act += __popcll(bal);
-  }
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const uint64_t bal = __ballot(hi[i] > lo[i]);
+      const int at = n_act + __popcll(bal & ((1ull << lane) - 1));
+      if (threadIdx.x < kWave && hi[i] > lo[i]) {
+        s_expert[at] = i * kWave + lane;
+        s_row0[at] = lo[i];
+        s_rows[at] = hi[i] - lo[i];
+      }
+      n_act += __popcll(bal);
+    }
+  };
+  if (E_local <= kWave) fill(std::integral_constant<int, 1>{});
+  else fill(std::integral_constant<int, kMaxE / kWave>{});
   if (gather) {
     R = offsets[E_local];
     const lds_i32_ptr s_tok = (lds_i32_ptr)(smem + kStreamGatherOff);

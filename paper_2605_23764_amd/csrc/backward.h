@@ -159,8 +159,7 @@ __device__ __forceinline__ void store_dgrad_f32(const GemmBwdParamsF32& p, size_
 
 // act_grad (+ SwiGLU_grad) and gate_grad: C[rows, N] = A[rows, K] * W_e[N, K]^T per M tile.
 template <int EPI>
-__global__ __launch_bounds__(256) void grouped_dgrad_f32_kernel(GemmBwdParamsF32 p) {
-  __shared__ __attribute__((aligned(16))) float smem[kFLdsFloats1];
+__device__ __forceinline__ void dgrad_f32(const GemmBwdParamsF32& p, int b, float* smem) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
   auto whole = [&](int tile) __attribute__((always_inline)) {
@@ -195,7 +194,13 @@ __global__ __launch_bounds__(256) void grouped_dgrad_f32_kernel(GemmBwdParamsF32
       if (m < rows) store_dgrad_f32<EPI>(p, (size_t)(row0 + m), c, acc[0][r]);
     }
   };
-  f32_sweeps(p.tiles.meta[kMetaMTiles] * p.n_ntiles, p.K, p.tiles.meta[kMetaMaxRows] <= 32, whole, quarter);
+  f32_sweeps(b, p.tiles.meta[kMetaMTiles] * p.n_ntiles, p.K, p.tiles.meta[kMetaMaxRows] <= 32, whole, quarter);
+}
+
+template <int EPI>
+__global__ __launch_bounds__(256) void grouped_dgrad_f32_kernel(GemmBwdParamsF32 p) {
+  __shared__ __attribute__((aligned(16))) float smem[kFLdsFloats1];
+  dgrad_f32<EPI>(p, blockIdx.x, smem);
 }
 
 // w2_grad and w1_grad: C_e[M, N] = A_e[rows_e, M]^T * B_e[rows_e, N]; zeros for experts without rows.  A launch does one or
@@ -204,8 +209,7 @@ __global__ __launch_bounds__(256) void grouped_dgrad_f32_kernel(GemmBwdParamsF32
 template <int NG>
 struct WgradGroupF32 { GemmBwdParamsF32 p[NG]; };
 template <int NG>
-__global__ __launch_bounds__(256) void grouped_wgrad_f32_kernel(WgradGroupF32<NG> w) {
-  __shared__ __attribute__((aligned(16))) float smem[kFLdsFloats1];
+__device__ __forceinline__ void wgrad_f32(const WgradGroupF32<NG>& w, int b, float* smem) {
   const int per0 = w.p[0].n_mtiles * w.p[0].n_ntiles, total0 = w.p[0].E_local * per0;
   const int per1 = w.p[NG - 1].n_mtiles * w.p[NG - 1].n_ntiles, total1 = NG > 1 ? w.p[NG - 1].E_local * per1 : 0;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -240,7 +244,24 @@ __global__ __launch_bounds__(256) void grouped_wgrad_f32_kernel(WgradGroupF32<NG
 #pragma unroll
     for (int r = 0; r < 4; ++r) c_base[(size_t)r * p.ldc] = acc[0][r];
   };
-  f32_sweeps(total0 + total1, w.p[0].offsets[w.p[0].E_local] / w.p[0].E_local, false, whole, quarter);
+  f32_sweeps(b, total0 + total1, w.p[0].offsets[w.p[0].E_local] / w.p[0].E_local, false, whole, quarter);
+}
+
+template <int NG>
+__global__ __launch_bounds__(256) void grouped_wgrad_f32_kernel(WgradGroupF32<NG> w) {
+  __shared__ __attribute__((aligned(16))) float smem[kFLdsFloats1];
+  wgrad_f32<NG>(w, blockIdx.x, smem);
+}
+
+// gate_grad and both weight gradients, which only share inputs, as one launch behind dH1 (small layers, one stream): workgroups that gate_grad's
+// last sweep leaves idle go on with the weight gradients.  Its sweeps are dealt in the other order inside a die, so that it is not
+// the same workgroups that get one more tile of both.
+__global__ __launch_bounds__(256) void grouped_grads_f32_kernel(GemmBwdParamsF32 gate, WgradGroupF32<2> w) {
+  __shared__ __attribute__((aligned(16))) float smem[kFLdsFloats1];
+  const int b = blockIdx.x;
+  dgrad_f32<kEpiStore>(gate, ((int)(gridDim.x >> 3) - 1 - (b >> 3)) * 8 + (b & 7), smem);
+  __syncthreads();                         // the stages have been read out
+  wgrad_f32<2>(w, b, smem);
 }
 
 }  // namespace moe

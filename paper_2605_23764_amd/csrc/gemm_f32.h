@@ -360,17 +360,17 @@ __device__ __forceinline__ void gemm_core_f32_strip(f32x4 (&acc)[NB], const floa
 // operand bytes per product, an eighth on its time; kFQFixed: a weight gradient over 60 rows per expert (560 tiles) is faster
 // whole (a step of T = 300 91.9 us against 93.1), GEMMs of K = 1024 are not (forward of T = 600, 528 tiles: 161 -> 147).
 template <typename Whole, typename Quarter>
-__device__ __forceinline__ void f32_sweeps(int total, int K, bool half_rows, Whole&& whole, Quarter&& quarter) {
+__device__ __forceinline__ void f32_sweeps(int b, int total, int K, bool half_rows, Whole&& whole, Quarter&& quarter) {
   const int G = gridDim.x, rem = total % G, nq = half_rows ? 2 : 4;
   const bool split = (4 * nq * rem + G - 1) / G * (9 * K + 8 * kFQFixed) < (4 * rem + G - 1) / G * (32 * K + 8 * kFQFixed);
   const int n_whole = split ? total - rem : total;
   for (int it = 0; it * G < n_whole; ++it) {
-    const int tile = xcd_spread_tile(it, blockIdx.x, G, n_whole);
+    const int tile = xcd_spread_tile(it, b, G, n_whole);
     if (tile >= 0) whole(tile);
   }
   if (!split) return;
   for (int it = 0; it * G < nq * rem; ++it) {
-    const int i = xcd_spread_tile(it, blockIdx.x, G, nq * rem);
+    const int i = xcd_spread_tile(it, b, G, nq * rem);
     if (i >= 0) quarter(n_whole + (half_rows ? i >> 1 : i >> 2), half_rows ? 0 : (i >> 1) & 1, i & 1);
   }
 }
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(256, EPI == kEpiSwiglu ? 4 : 1) void grouped_gemm_f
     }
     return;
   }
-  f32_sweeps(total, p.K, max_rows <= 32,
+  f32_sweeps(blockIdx.x, total, p.K, max_rows <= 32,
              [&](int t) __attribute__((always_inline)) { gemm_tile_f32<EPI>(p, t / p.n_ntiles, t % p.n_ntiles, smem); },
              [&](int t, int qm, int qn) __attribute__((always_inline)) {
                gemm_quarter_f32<EPI>(p, t / p.n_ntiles, t % p.n_ntiles, qm, qn, smem);

@@ -138,9 +138,11 @@ int moe_ffn_workspace_bytes(const MoeShape* shape, size_t* fwd_bytes, size_t* bw
  *   d_workspace, workspace_bytes  >= moe_ffn_workspace_bytes(...).fwd_bytes
  *   mode       MoeMode.  MOE_MODE_PERSISTENT: the router and the prefix-sum / rank step run as two
  *              launches, then ONE launch runs every Dispatch, GEMM-1, GEMM-2 and Combine tile task.
- *              Its workers hand tiles over through the L2 of the accelerator die (XCD) they share;
+ *              Its workers hand tiles over through the L2 of the accelerator die (XCD) they share, in bf16
+ *              launches of several tasks per worker through memory, so that idle workers take other dies' tasks;
  *              they verify at run time (hardware XCC id) that the workers of a queue all sit on one die
- *              and use device-wide fences for that queue otherwise.
+ *              and use device-wide fences for that queue otherwise.  Up to 64 tokens (bf16) that one launch
+ *              runs both GEMMs as weight streams instead of tile tasks.
  * Returns after enqueueing.  A scheduler timeout (MOE_MODE_PERSISTENT only) is
  * reported by moe_ffn_last_status().
  */
@@ -294,8 +296,8 @@ int moe_ffn_forward_scatter(const MoeShape* shape, const void* d_x, const float*
 /* Dispatch to Combine, the interval the paper times (Section 5.2), on the routing results moe_route left in the
  * SAME `saved` and workspace: Dispatch permute, GEMM-1 + SwiGLU, GEMM-2, Combine.  mode MOE_MODE_SERIALIZED: one
  * launch per operator (Section 2.3's kernel-by-kernel execution); MOE_MODE_PERSISTENT: exactly one launch of
- * tile tasks with event counters (Sections 4.3-4.4; alignment rule at the top of this file), which consumes
- * the counters and queues moe_route prepared: one call per moe_route call (a second one finds every ticket
+ * tile tasks with event counters (Sections 4.3-4.4; alignment rule at the top of this file; up to 64 tokens in
+ * bf16 of weight streams), which consumes the counters and queues moe_route prepared: one call per moe_route call (a second one finds every ticket
  * taken and does nothing).  Results are bit-identical.  moe_ffn_forward(mode) = moe_route + this, except that
  * its routing launches leave the counters and queues out when mode is MOE_MODE_SERIALIZED (nobody reads them
  * then): MOE_MODE_PERSISTENT here needs a moe_route call, or a MOE_MODE_PERSISTENT forward's routing, in front. */

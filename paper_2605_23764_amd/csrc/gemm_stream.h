@@ -53,12 +53,11 @@ struct StreamShape {
 
 constexpr int kStreamTables = kStreamRing;           // LDS offset of the tables, behind the ring
 constexpr int kStreamGatherOff = kStreamTables + 3 * kMaxE * 4;
-constexpr int kStreamBox = kStreamGatherOff + kStreamGather * 4;   // two words of the single launch (persistent.h)
-static_assert(kStreamBox + 8 <= kGemmLdsBytes, "LDS budget");
+constexpr int kStreamBox = kStreamGatherOff + kStreamGather * 4;   // three words of the single launch (stream_layer.h)
+static_assert(kStreamBox + 12 <= kGemmLdsBytes, "LDS budget");
 
-// Who runs a stream: a launch of its own; or both GEMMs of a layer one after the other in the single launch (stream_layer in
-// persistent.h), whose results are stored through to memory and whose second stream starts with the weights, before the
-// activations are there.
+// Who runs a stream: a launch of its own; or both GEMMs of a layer one after the other in the single launch (stream_layer.h),
+// whose results are stored through to memory and whose second stream starts with the weights, before the activations are there.
 enum StreamRole { kStreamAlone = 0, kStreamFirst = 1, kStreamSecond = 2 };
 
 typedef __attribute__((address_space(3))) int32_t* lds_i32_ptr;

@@ -46,21 +46,18 @@ void stream_layer_kernel(StreamLayerParams sp) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int G = gridDim.x, W = G / kNumXcd, b = blockIdx.x, q = b % kNumXcd;
   const int max_rows = __builtin_amdgcn_readfirstlane(sp.meta[kMetaMaxRows]);
-  uint32_t* const draw = sp.events + kEvStreamDraw;                // words 0..7: GEMM-1, 8..15: GEMM-2
-  // lanes 0 and 1: the next share of either GEMM of class c
-  auto draw_both = [&](int c) __attribute__((always_inline)) {
-    uint32_t t = 0;
-    if (lane < 2) t = __hip_atomic_fetch_add(draw + 8 * lane + c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return t;
-  };
+  // words 0..7: shares of GEMM-1 drawn, 8..15: of GEMM-2, 16..23: workgroups started
+  uint32_t* const draw = sp.events + kEvStreamDraw;
   uint32_t mine = 0;
-  if (wave == 0) mine = draw_both(q);
+  if (wave == 0 && lane < 3) mine = __hip_atomic_fetch_add(draw + 8 * lane + q, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int n_act = stream_tables(sp.g1.offsets, sp.g1.E_local, sp.g1.gather, smem);
   if (wave == 0) {
     s_box[0] = __builtin_amdgcn_readlane((int)mine, 0);
     s_box[1] = __builtin_amdgcn_readlane((int)mine, 1);
+    s_box[2] = __builtin_amdgcn_readlane((int)mine, 2);
   }
   __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(s_box[2]) >= W) return;       // a second launch on the same routing: nothing is left to do
   const int first1 = __builtin_amdgcn_readfirstlane(s_box[0]), first2 = __builtin_amdgcn_readfirstlane(s_box[1]);
   if (sp.copy) {
     const int R = sp.meta[kMetaRows], nw = blockDim.x / kWave;

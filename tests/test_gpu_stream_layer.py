@@ -67,6 +67,19 @@ def test_up_to_64_tokens(case, keep_xp):
     assert torch.equal(run.out, _launches(run)[1])
 
 
+def test_second_launch_on_the_same_routing_does_nothing():
+    from gpu_common import run_forward
+    cfg = _config((33, 1088, 704, 24, 10, 6, 3), 76)
+    run = run_forward(cfg, make_inputs(cfg))
+    args = (run.shape, run.dev["x"], run.dev["w_gate_up"], run.dev["w_down"])
+    moe.moe_route(run.shape, run.dev["logits"], run.saved, run.workspace)
+    out, again = torch.empty_like(run.out), torch.full_like(run.out, 7.0)
+    moe.moe_dispatch_to_combine(*args, out, run.saved, run.workspace, moe.MODE_PERSISTENT)
+    moe.moe_dispatch_to_combine(*args, again, run.saved, run.workspace, moe.MODE_PERSISTENT)
+    assert torch.equal(out, run.out) and bool((again == 7.0).all())
+    assert moe.moe_ffn_last_status(run.shape, run.workspace) == 0
+
+
 def test_expired_wait_is_reported_and_the_next_call_is_right():
     """Without polls a wait that is not met at once expires: the launch ends, the status says so, and the next call on the workspace
     is right."""

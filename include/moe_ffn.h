@@ -286,7 +286,8 @@ int moe_grouped_gemm_scatter(const MoeShape* shape, const void* d_w_down, const 
 /* The forward pass with that epilogue: routing (whose second launch also zeroes out), Dispatch (or GEMM-1
  * reading x through the permutation when saved is NULL or saved->Xp is NULL), GEMM-1 + SwiGLU, GEMM-2 adding
  * into out; no Combine.  mode MOE_MODE_SERIALIZED: one launch per operator; MOE_MODE_PERSISTENT: Dispatch to
- * GEMM-2 as one launch of tile tasks without COMBINE tasks, so no task waits for the whole chip (alignment
+ * GEMM-2 as one launch of tile tasks without COMBINE tasks, so no task waits for the whole chip; up to 64 tokens
+ * instead the single launch of moe_ffn_forward, bit for bit, with Yp in the workspace (alignment
  * rule and moe_ffn_last_status as for moe_ffn_forward).  Other arguments as moe_ffn_forward; same limits as
  * moe_grouped_gemm_scatter. */
 int moe_ffn_forward_scatter(const MoeShape* shape, const void* d_x, const float* d_logits, const void* d_w_gate_up,

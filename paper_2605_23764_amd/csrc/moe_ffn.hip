@@ -411,7 +411,8 @@ int run_route(const Ctx& c, const float* logits, bool tables = true, void* zero_
 }
 
 // Dispatch to Combine as ONE launch of tile tasks (after run_route on the same MoeSaved).
-int run_stream_layer(const Ctx& c, const void* x, const void* w_gate_up, const void* w_down, void* out) {
+// own_yp: GEMM-2's rows go to the workspace, the caller's Yp stays as it is.
+int run_stream_layer(const Ctx& c, const void* x, const void* w_gate_up, const void* w_down, void* out, bool own_yp = false) {
   StreamLayerParams p;
   p.g1 = gemm1_params<GemmParams, __bf16>(c, w_gate_up);
   p.g1.A = static_cast<const __bf16*>(x);
@@ -419,6 +420,10 @@ int run_stream_layer(const Ctx& c, const void* x, const void* w_gate_up, const v
   p.g2 = gemm2_params<GemmParams, __bf16>(c, w_down);
   p.perm = permute_params(c, x);
   p.comb = combine_params(c, out);
+  if (own_yp) {
+    p.g2.C = reinterpret_cast<__bf16*>(c.ws + c.L.Yp);
+    p.comb.Yp = c.ws + c.L.Yp;
+  }
   p.events = reinterpret_cast<uint32_t*>(c.ws + c.L.events);
   p.meta = reinterpret_cast<int32_t*>(c.ws + c.L.meta);
   p.copy = c.keep_xp ? 1 : 0;
@@ -872,6 +877,12 @@ int moe_ffn_forward_scatter(const MoeShape* shape, const void* d_x, const float*
     if (!q || !aligned16(q)) return MOE_ERR_INVALID_ARG;
   if (mode == MOE_MODE_PERSISTENT) {
     if (!aligned128(c.ws) || !aligned128(c.sv.Xp) || !aligned128(c.sv.A)) return MOE_ERR_INVALID_ARG;
+    // up to 64 tokens the streams with Combine at their end are faster than tile tasks with the adds (H = 2048, T = 2 70 -> 47 us, T = 64
+    // 85 -> 79; H = 7168, T = 40 436 -> 381)
+    if (streams_layer(c)) {
+      if ((st = run_route(c, d_logits)) != MOE_OK) return st;
+      return run_stream_layer(c, d_x, d_w_gate_up, d_w_down, d_out, true);
+    }
     if ((st = run_route(c, d_logits, true, d_out)) != MOE_OK) return st;
     return run_persistent_scatter(c, d_x, d_w_gate_up, d_w_down, d_out);
   }

@@ -67,6 +67,23 @@ def test_up_to_64_tokens(case, keep_xp):
     assert torch.equal(run.out, _launches(run)[1])
 
 
+@pytest.mark.parametrize("case", [CASES[1], CASES[2], CASES[5], CASES[7]], ids=["T%d_H%d_I%d" % CASES[i][:3] for i in (1, 2, 5, 7)])
+def test_scatter_call_runs_the_same_streams(case):
+    """The single launch of the scatter call: out of moe_ffn_forward bit for bit, the caller's Yp untouched."""
+    from gpu_common import run_forward
+    cfg = _config(case, 77)
+    run = run_forward(cfg, make_inputs(cfg))
+    args = (run.shape, run.dev["x"], run.dev["logits"], run.dev["w_gate_up"], run.dev["w_down"])
+    for saved in (moe.alloc_saved(run.shape, store_h1=True), None):
+        out = torch.full_like(run.out, float("nan"))
+        if saved is not None:
+            saved.Yp.fill_(3.0)
+        moe.moe_ffn_forward_scatter(*args, out, saved, run.workspace, moe.MODE_PERSISTENT)
+        assert torch.equal(out, run.out)
+        assert saved is None or bool((saved.Yp == 3.0).all())
+        assert moe.moe_ffn_last_status(run.shape, run.workspace) == 0
+
+
 def test_second_launch_on_the_same_routing_does_nothing():
     from gpu_common import run_forward
     cfg = _config((33, 1088, 704, 24, 10, 6, 3), 76)

@@ -59,6 +59,9 @@ void stream_layer_kernel(StreamLayerParams sp) {
   __syncthreads();
   if (__builtin_amdgcn_readfirstlane(s_box[2]) >= W) return;       // a second launch on the same routing: nothing is left to do
   const int first1 = __builtin_amdgcn_readfirstlane(s_box[0]), first2 = __builtin_amdgcn_readfirstlane(s_box[1]);
+  // Every wave has read the box before wave 0 writes it again: with a drawn share of GEMM-1 that is somebody else's by now (>= W, as for
+  // a workgroup that starts late) there is no work, and with it no barrier, in front of that.  Every later read has one behind it.
+  __syncthreads();
   if (sp.copy) {
     const int R = sp.meta[kMetaRows], nw = blockDim.x / kWave;
     for (int r0 = b * nw; r0 < R; r0 += G * nw) permute_rows<4>(sp.perm, r0, min(R, r0 + nw), wave, nw);

@@ -70,12 +70,14 @@ void stream_layer_kernel(StreamLayerParams sp) {
   auto counts = [&](const uint32_t* c) __attribute__((always_inline)) {
     return lane < kNumXcd ? __hip_atomic_load(c + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (uint32_t)W;
   };
-  // The share drawn at the start, then what nobody has drawn.  done: one count per share.
+  // The share drawn at the start, then what nobody has drawn.  done: one count per share.  work: false, it has given up (all waves
+  // alike); its share stays uncounted, so that every wait for the results expires as well and nobody goes on with rows that were
+  // never stored (out is left as it was), and the workgroup is done.
   auto shares = [&](uint32_t* dr, int first, uint32_t* done, auto&& work) __attribute__((always_inline)) {
     int t = first, c = q;
     for (;;) {
       if (t < W) {
-        work(t * kNumXcd + c);
+        if (!work(t * kNumXcd + c)) return false;
         wait_own_stores();
         __syncthreads();                   // ... every wave's, and the ring has been read out
       }
@@ -94,7 +96,7 @@ void stream_layer_kernel(StreamLayerParams sp) {
       t = __builtin_amdgcn_readfirstlane(s_box[0]);
       c = __builtin_amdgcn_readfirstlane(s_box[1]);
       __syncthreads();
-      if (c < 0) return;
+      if (c < 0) return true;
     }
   };
   auto wait_all = [&](const uint32_t* done) __attribute__((always_inline)) {   // bounded; false: given up, status set
@@ -116,15 +118,17 @@ void stream_layer_kernel(StreamLayerParams sp) {
   };
   shares(draw, first1, sp.events + kEvStreamDone1, [&](int v) __attribute__((always_inline)) {
     stream_share<kLayNN, kEpiSwiglu, kStreamFirst>(sp.g1, max_rows, n_act, v, smem, [] { return true; });
+    return true;
   });
   int a_ready = -1;                        // -1: not asked yet
-  shares(draw + 8, first2, sp.events + kEvStreamDone2, [&](int v) __attribute__((always_inline)) {
+  const bool stored = shares(draw + 8, first2, sp.events + kEvStreamDone2, [&](int v) __attribute__((always_inline)) {
     stream_share<kLayNN, kEpiStore, kStreamSecond>(sp.g2, max_rows, n_act, v, smem, [&]() __attribute__((always_inline)) {
       if (a_ready < 0) a_ready = wait_all(sp.events + kEvStreamDone1);
       return a_ready != 0;
     });
+    return a_ready != 0;
   });
-  if (b >= sp.comb.T || !wait_all(sp.events + kEvStreamDone2)) return;
+  if (!stored || b >= sp.comb.T || !wait_all(sp.events + kEvStreamDone2)) return;
   for (int t = b + wave * G; t < sp.comb.T; t += G * (int)(blockDim.x / kWave)) {
     int rowv;
     float wv;

@@ -98,18 +98,20 @@ def test_second_launch_on_the_same_routing_does_nothing():
 
 
 def test_expired_wait_is_reported_and_the_next_call_is_right():
-    """Without polls a wait that is not met at once expires: the launch ends, the status says so, and the next call on the workspace
-    is right."""
+    """Without polls a wait that is not met at once expires: the launch ends, the status says so, out is as it was (GEMM-1 leaves 80 of 256
+    workgroups without a share, whose waits for the others' expire; no token is combined then), and the next call on the workspace is right."""
     from gpu_common import run_forward
     cfg = _config((64, 2048, 704, 16, 16, 0, 4), 73)
     run = run_forward(cfg, make_inputs(cfg), mode=moe.MODE_PERSISTENT)
     args = (run.shape, run.dev["x"], run.dev["logits"], run.dev["w_gate_up"], run.dev["w_down"])
-    out = torch.empty_like(run.out)
+    out = torch.full_like(run.out, 7.0)
     try:
         moe.moe_ffn_debug_set_spin_limit(0)
-        moe.moe_ffn_forward(*args, out, run.saved, run.workspace, moe.MODE_PERSISTENT)
-        torch.cuda.synchronize()
-        assert moe.moe_ffn_last_status(run.shape, run.workspace) == -5
+        for forward in (moe.moe_ffn_forward, moe.moe_ffn_forward_scatter):
+            forward(*args, out, run.saved, run.workspace, moe.MODE_PERSISTENT)
+            torch.cuda.synchronize()
+            assert moe.moe_ffn_last_status(run.shape, run.workspace) == -5
+            assert bool((out == 7.0).all()), forward.__name__
     finally:
         moe.moe_ffn_debug_set_spin_limit(1 << 20)
     moe.moe_ffn_forward(*args, out, run.saved, run.workspace, moe.MODE_PERSISTENT)

@@ -7,6 +7,11 @@ statement, `s_waitcnt vmcnt(n)`, which names the registers) no instruction may r
 source is arranged so that the compiler has no reason to (the window lies inside one loop trip and ends in the naming
 wait), but nothing in the language enforces it; this module checks the generated code.
 
+A second contract: no wave passes a barrier with LDS writes of its own under way (barrier_violations).  The language has it
+for __syncthreads, but the compiler has been seen to lose the wait of a barrier at the head of a loop where the writes are
+outstanding only along the way back: waves then read tables that others were still filling.  Barriers placed by hand
+(__builtin_amdgcn_s_barrier) never had one.  Reads may be under way at those: the GEMM pipelines do so by design.
+
     python -m paper_2605_23764_amd.asm_check        # compiles the device code to assembly and checks it
 """
 from __future__ import annotations
@@ -118,12 +123,88 @@ def innermost_loops(asm: str, kernel: str):
     return [[line for line in lines[a:b + 1] if line and not line.startswith(".")] for a, b in inner]
 
 
+_DS_WRITE = re.compile(r"ds_(write|or|and|xor|add|sub|inc|dec|min|max|cmpst|wrxchg|mskor|append|consume)")
+
+
+def barrier_violations(asm: str):
+    """Returns (number of barriers, list of (kernel, line of the barrier, line of an LDS write or atomic that a wave may pass it
+    with)), over every path of the control flow.  A wave's LDS operations complete in order, so a write is complete once
+    `s_waitcnt lgkmcnt(n)` has been passed with n or more LDS operations issued behind it."""
+    lines = [raw.split(";")[0].strip() for raw in asm.splitlines()]
+    kernels = set(re.findall(r"\.amdhsa_kernel\s+(\w+)", asm))
+    n_barriers, bad, i = 0, [], 0
+    while i < len(lines):
+        if not (lines[i].endswith(":") and lines[i][:-1] in kernels):
+            i += 1
+            continue
+        name, first = lines[i][:-1], i + 1
+        while not lines[i].startswith((".Lfunc_end", ".amdhsa_kernel")):
+            i += 1
+        # blocks of instructions (line, text); labels; where each may go on
+        blocks, labels, target = [[]], {}, None
+        jumps = {}
+        for no in range(first, i):
+            line = lines[no]
+            m = re.match(r"(\.LBB\w+):", line)
+            if m:
+                blocks.append([])
+                labels[m.group(1)] = len(blocks) - 1
+            if not line or line.startswith(".") or line.endswith(":"):
+                continue
+            blocks[-1].append((no + 1, line))
+            m = re.search(r"\((\.LBB\w+)-\.Lpost_getpc", line)      # a long branch: the address is added up, then s_setpc_b64
+            target = m.group(1) if m else target
+            op = line.split()
+            if op[0].startswith(("s_cbranch", "s_branch", "s_setpc", "s_endpgm")):
+                to = [target] if op[0].startswith("s_setpc") else op[1:2]
+                jumps[len(blocks) - 1] = (to, op[0].startswith("s_cbranch"))
+                blocks.append([])
+
+        def flow(b, behind, report=None):
+            # behind: None, nothing under way; else (LDS operations issued behind the youngest such write, its line)
+            for no, line in blocks[b]:
+                if _DS_WRITE.match(line):
+                    behind = (0, no)
+                elif line.startswith("ds_") and behind:
+                    behind = (behind[0] + 1, behind[1])
+                elif line.startswith("s_waitcnt"):
+                    m = re.search(r"lgkmcnt\((\d+)\)", line)
+                    if m and behind and behind[0] >= int(m.group(1)):
+                        behind = None
+                elif line.startswith("s_barrier") and report is not None:
+                    report.append((no, behind))
+            return behind
+
+        entry, seen, work = {0: None}, {0}, [0]
+        while work:
+            b = work.pop()
+            out = flow(b, entry[b])
+            to, falls = jumps.get(b, ([], True))
+            for s in [labels[t] for t in to] + ([b + 1] if falls and b + 1 < len(blocks) else []):
+                old = entry.get(s)
+                new = out if old is None or (out is not None and out[0] < old[0]) else old
+                if s not in seen or new != old:
+                    seen.add(s)
+                    entry[s] = new
+                    work.append(s)
+        for b in sorted(seen):
+            found = []
+            flow(b, entry[b], found)
+            n_barriers += len(found)
+            bad += [(name, no, behind[1]) for no, behind in found if behind]
+    return n_barriers, bad
+
+
 def main():
     n, bad = check_register_fed_loads(device_assembly())
     print(f"{n} assembly loads with register destinations, {len(bad)} instructions inside a request-to-retire window touch them")
     for no, line, regs in bad[:20]:
         print(f"  line {no}: {line}   (v{regs})")
-    sys.exit(1 if bad or n == 0 else 0)
+    n_barriers, late = barrier_violations(device_assembly())
+    print(f"{n_barriers} barriers, {len(late)} passed with LDS writes under way")
+    for kernel, no, write in late[:20]:
+        print(f"  {kernel}: barrier in line {no}, write in line {write}")
+    sys.exit(1 if bad or late or n == 0 else 0)
 
 
 if __name__ == "__main__":

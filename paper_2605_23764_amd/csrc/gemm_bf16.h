@@ -610,6 +610,9 @@ __device__ __forceinline__ void store_block_via_lds(char* region, const u32x2 (&
       else *dst = v[it];
     }
   }
+  // A wave with no column to store (an N of 64 or 128 beyond whole tiles) has waited for none of its staging, and behind the next
+  // tile's first barrier other waves' copies go to the same places.  With columns, the stores have waited for it.
+  wait_lgkmcnt0();
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
@@ -656,6 +659,7 @@ __device__ __forceinline__ void scatter_block_via_lds(char* region, const u32x2 
       }
     }
   }
+  wait_lgkmcnt0();                                     // see store_block_via_lds
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }

@@ -1,11 +1,11 @@
 """The generated code keeps the contract of the assembly loads with register destinations (register-fed row block
 of the wide GEMM tile): nothing touches their destination registers between the request and the wait that retires
-them.  CPU only: the device code is compiled to assembly and read; the checker itself is tried on planted text."""
+them; and no wave passes a barrier with LDS writes of its own under way.  CPU only: the device code is compiled to assembly and read; the checker itself is tried on planted text."""
 import os
 
 import pytest
 
-from paper_2605_23764_amd.asm_check import (check_register_fed_loads, device_assembly, innermost_loops,
+from paper_2605_23764_amd.asm_check import (barrier_violations, check_register_fed_loads, device_assembly, innermost_loops,
                                             loads_ahead_of_first_branch)
 
 GOOD = """
@@ -42,6 +42,49 @@ def test_checker_accepts_a_clean_window_and_names_planted_mistakes():
     # the compiler's own wait does not end the window: only the assembly wait that names the registers does
     n, bad = check_register_fed_loads(GOOD.replace("\ts_barrier\n", "\ts_barrier\n\tv_mov_b32_e32 v61, v11\n"))
     assert len(bad) == 1 and bad[0][2] == [11]
+
+
+LOOP = """
+\t.amdhsa_kernel k
+k:
+\tds_write_b32 v1, v2
+\ts_waitcnt lgkmcnt(0)
+.LBB0_1:
+\ts_barrier
+\tds_read_b32 v3, v4
+\ts_waitcnt lgkmcnt(0)
+\ts_barrier
+\ts_cbranch_scc1 .LBB0_3
+\tds_or_b32 v1, v2
+\tds_read_b32 v3, v4
+\ts_waitcnt lgkmcnt(1)
+\ts_branch .LBB0_1
+.LBB0_3:
+\ts_endpgm
+.Lfunc_end0:
+"""
+
+
+def test_barrier_checker_follows_the_loop():
+    assert barrier_violations(LOOP) == (2, [])
+    # outstanding along the way back alone
+    n, bad = barrier_violations(LOOP.replace("\ts_waitcnt lgkmcnt(1)\n", ""))
+    assert n == 2 and bad == [("k", 7, 12)]
+    # on the way in; a wait that is not long enough; a wait for something else
+    for plant in (LOOP.replace("v2\n\ts_waitcnt lgkmcnt(0)\n.LBB0_1", "v2\n.LBB0_1"), LOOP.replace("lgkmcnt(1)", "lgkmcnt(2)"),
+                  LOOP.replace("lgkmcnt(1)", "vmcnt(0)")):
+        assert len(barrier_violations(plant)[1]) == 1, plant
+    # the way back as a long branch
+    far = LOOP.replace("\ts_branch .LBB0_1", "\ts_add_u32 s8, s8, (.LBB0_1-.Lpost_getpc0)&4294967295\n\ts_setpc_b64 s[8:9]")
+    assert barrier_violations(far) == (2, [])
+    assert barrier_violations(far.replace("\ts_waitcnt lgkmcnt(1)\n", ""))[1] == [("k", 7, 12)]
+
+
+@pytest.mark.skipif(not os.path.exists(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")), reason="needs hipcc")
+def test_no_barrier_is_passed_with_lds_writes_under_way():
+    n, bad = barrier_violations(device_assembly())
+    assert n > 500, n
+    assert not bad, bad[:5]
 
 
 @pytest.mark.skipif(not os.path.exists(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")), reason="needs hipcc")

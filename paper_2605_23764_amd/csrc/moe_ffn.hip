@@ -41,7 +41,12 @@ inline int tile_wide_max(const MoeShape& s) { return s.dtype == MOE_BF16 ? kWide
 // and trigger, is a few us: T = 4096, H = 2048 ran 2 % faster with 32-row tasks, H = 7168 the same with 16 or 32)
 inline int perm_task_rows(const MoeShape& s) { return (size_t)s.H * elem_bytes(s) >= 8192 ? kPermRows : 2 * kPermRows; }
 inline long r_max(const MoeShape& s) { return (long)s.T * (s.k < s.E_local ? s.k : s.E_local); }
-inline int n_sub(const MoeShape& s) { return (s.T + kSub - 1) / kSub; }
+inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
+inline int n_sub(const MoeShape& s) { return ceil_div(s.T, kSub); }
+// Sub-chunks per rank workgroup (route.h, rank_tokens): one as long as all such workgroups fit on the chip at a time.
+// Each walks the whole histogram table: with one throughout, the routing of 256 experts takes 154, 322, 1057 and 3782 us at T = 32768,
+// 65536, 131072 and 262144 (32 of 256 experts: 44, 74, 184, 555), by this rule 155, 283, 562 and 1179 (44, 72, 126, 240); 16 experts level.
+inline int rank_subs(const MoeShape& s, int n_cu) { return ceil_div(n_sub(s), 4 * n_cu); }
 // pair slots of the tile map: a tall tile (> BM rows) takes two entries, a wide tile of a split expert has > BM/2 rows
 inline long max_mtiles(const MoeShape& s) { return 2 * (r_max(s) / tile_bm(s)) + 2 * s.E_local + kMapSlack; }
 inline int tile_tall(const MoeShape& s) { return s.dtype == MOE_BF16 ? kTallRows : 0; }
@@ -194,6 +199,7 @@ RouteParams route_params(const Ctx& c, const float* logits) {
   p.tiles = tile_map(c);
   p.T = c.s.T; p.E = c.s.E; p.E_local = c.s.E_local; p.expert_base = c.s.expert_base; p.k = c.s.k;
   p.n_sub = n_sub(c.s);
+  p.subs = rank_subs(c.s, c.n_cu);
   p.BM = tile_bm(c.s);
   p.granule = c.s.dtype == MOE_BF16 ? kRowGranule : kFBM;
   p.tall = tile_tall(c.s);
@@ -390,14 +396,14 @@ int run_route_t(const Ctx& c, const float* logits, bool tables, void* zero_out, 
   }
   hipLaunchKernelGGL(route_kernel, dim3(rp.n_sub), dim3(512), 0, c.stream, rp);
   if (copy_x) {
-    // tokens per workgroup: a workgroup per CU, as long as each has a token
+    // tokens per workgroup: a workgroup per CU, as long as each has a token (then rp.subs is 1)
     int tokens = kSub;
-    while (tokens > 4 && (c.s.T + tokens - 1) / tokens < c.n_cu) tokens >>= 1;
-    hipLaunchKernelGGL(sched_prepare_copy_kernel<BF16>, dim3(1 + (c.s.T + tokens - 1) / tokens), dim3(kRankThreads), 0, c.stream, sp,
+    while (tokens > 4 && ceil_div(c.s.T, tokens) < c.n_cu) tokens >>= 1;
+    hipLaunchKernelGGL(sched_prepare_copy_kernel<BF16>, dim3(1 + ceil_div(c.s.T, tokens * rp.subs)), dim3(kRankThreads), 0, c.stream, sp,
                        tokens);
     return launch_status();
   }
-  hipLaunchKernelGGL(sched_prepare_kernel<BF16>, dim3(1 + rp.n_sub + fill_wgs),
+  hipLaunchKernelGGL(sched_prepare_kernel<BF16>, dim3(1 + ceil_div(rp.n_sub, rp.subs) + fill_wgs),
                      dim3(kScanWaves * kWave), 0, c.stream, sp);
   return launch_status();
 }
@@ -545,7 +551,6 @@ int run_backward(const BwdCtx& c, const void* dy, const void* x, const void* w_g
   T* dXp = reinterpret_cast<T*>(c.ws + c.L.dXp);
   const int bm = tile_bm(s);
   const int tn = BF16 ? kBN : kFBN;
-  auto ceil_div = [](int a, int b) { return (a + b - 1) / b; };
   const int grid = (c.n_cu + 7) / 8 * 8 * (BF16 ? 1 : 4);   // fp32: four 256-thread workgroups per CU
 
   uint32_t* tickets = reinterpret_cast<uint32_t*>(c.ws + c.L.tickets);   // [0, 8): w2_grad, [8, 16): w1_grad

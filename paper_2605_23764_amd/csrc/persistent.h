@@ -410,14 +410,14 @@ __global__ __launch_bounds__(kScanWaves * kWave) void sched_prepare_kernel(Sched
     if (!sp.skip_tables) build_task_tables<BF16>(sp);
     return;
   }
-  const int rank_wgs = sp.route.n_sub;
+  const int rank_wgs = (sp.route.n_sub + sp.route.subs - 1) / sp.route.subs;
   if ((int)blockIdx.x > rank_wgs) {       // fill workgroups: the launch lasts as long as workgroup 0's chain anyway
     const size_t stride = (size_t)(gridDim.x - 1 - rank_wgs) * blockDim.x;
     for (size_t i = (size_t)(blockIdx.x - 1 - rank_wgs) * blockDim.x + threadIdx.x; i < sp.zero_n16; i += stride)
       sp.zero_dst[i] = make_uint4(0, 0, 0, 0);
     return;
   }
-  rank_tokens(sp.route, ((int)blockIdx.x - 1) * kSub, kSub, [](int, int) {});
+  rank_tokens(sp.route, ((int)blockIdx.x - 1) * sp.route.subs * kSub, kSub, [](int, int) {});
 }
 
 // The same with Dispatch in it (serialized launches that keep or need a permuted copy): the other workgroups rank `tokens` tokens each
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(kRankThreads) void sched_prepare_copy_kernel(SchedP
     scan_all(sp.route, s_lds, s_lds + kMaxE + 64);
     return;
   }
-  rank_tokens(sp.route, ((int)blockIdx.x - 1) * tokens, tokens, [&](int t, int rowv) __attribute__((always_inline)) {
+  rank_tokens(sp.route, ((int)blockIdx.x - 1) * sp.route.subs * tokens, tokens, [&](int t, int rowv) __attribute__((always_inline)) {
     with_row_vectors(sp.perm.H * sp.perm.elem_bytes / 16, [&](auto uv) { permute_token<decltype(uv)::value>(sp.perm, t, rowv); });
   });
 }

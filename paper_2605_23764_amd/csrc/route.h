@@ -28,6 +28,7 @@ struct RouteParams {
   TileMap tiles;
   int T, E, E_local, expert_base, k;
   int n_sub;     // ceil(T / kSub) histogram rows
+  int subs;      // sub-chunks that a rank workgroup takes
   int BM;        // M-tile row capacity of the plain wide shape
   int wide_max;  // rows a single wide M tile can take (>= BM: the bf16 kernels feed one more row block per wave row from registers)
   int tall;      // row capacity of a tall M tile (0 = the kernels have no tall shape)
@@ -550,6 +551,8 @@ constexpr int kScanLds = (kScanWaves + 1) * kMaxE + 66;
 // selecting e).  The first two terms come straight from the histogram table, whose walk is spread over all lanes of the workgroup
 // (sums in LDS, whole numbers, so their order does not matter; fewer than 64 local experts: several lanes to an expert); the tokens
 // of the sub-chunk that selected expert e stand as a mask per expert, so the third is a population count.
+// p.subs > 1 (tokens = kSub, t0 a multiple of it): that many sub-chunks one after the other, whose masks move the rows on, behind one
+// walk of the table: walks for all grow with the square of T (rank_subs has the line and the times).
 // done(token, lane j < 16: row of slot j or -1) follows, a token per wave: Dispatch, where the launch copies rows as well.
 // With a wave per 64 tokens, four to a workgroup: T = 8192, 256 local experts, H = 256, forward 170 us, with this 115.
 constexpr int kRankThreads = kSub * kMaxK;
@@ -559,9 +562,16 @@ __device__ __forceinline__ void rank_tokens(const RouteParams& p, int t0, int to
   __shared__ uint32_t s_mask[kMaxE];
   const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   constexpr int kWaves = kRankThreads / kWave;
-  const int sub = t0 / kSub, i = threadIdx.x / kMaxK, j = threadIdx.x % kMaxK, t = sub * kSub + i;
-  const bool slot = t < p.T && j < p.k;
-  const int idx = slot ? p.topk_idx[(size_t)t * p.k + j] : -1;
+  const int i = threadIdx.x / kMaxK, j = threadIdx.x % kMaxK;
+  const int sub_end = min(t0 / kSub + p.subs, p.n_sub);
+  int sub = t0 / kSub;
+  // the local expert of this thread's slot, -1: none
+  auto selected = [&]() __attribute__((always_inline)) {
+    const int t = sub * kSub + i;
+    const int idx = t < p.T && j < p.k ? p.topk_idx[(size_t)t * p.k + j] : -1;
+    return idx >= p.expert_base && idx - p.expert_base < p.E_local ? idx - p.expert_base : -1;
+  };
+  int l = selected();
   for (int e = threadIdx.x; e < p.E_local; e += kRankThreads) { s_total[e] = 0; s_base[e] = 0; s_mask[e] = 0u; }
   __syncthreads();
   const int ew = p.E_local >= kWave ? kWave : (p.E_local <= 1 ? 1 : 1 << (32 - __builtin_clz(p.E_local - 1)));
@@ -582,7 +592,6 @@ __device__ __forceinline__ void rank_tokens(const RouteParams& p, int t0, int to
     if (total) atomicAdd(&s_total[e], total);
     if (before) atomicAdd(&s_base[e], before);
   }
-  const int l = slot && idx >= p.expert_base && idx - p.expert_base < p.E_local ? idx - p.expert_base : -1;
   if (l >= 0) atomicOr(&s_mask[l], 1u << i);
   __syncthreads();
   if (wave == 0) {
@@ -595,17 +604,31 @@ __device__ __forceinline__ void rank_tokens(const RouteParams& p, int t0, int to
     }
   }
   __syncthreads();
-  const int r = l >= 0 ? s_base[l] + __popc(s_mask[l] & ((1u << i) - 1u)) : -1;
-  s_row[threadIdx.x] = r;
-  if (slot && t >= t0 && t < t0 + tokens) {
-    p.row_of[(size_t)t * p.k + j] = r;
-    if (r >= 0) {
-      p.token_of[r] = t;
-      p.slot_of[r] = j;
+  for (;;) {                               // no barrier at the head: the compiler has lost its wait for the masks of the way back there
+    const int t = sub * kSub + i;
+    const int r = l >= 0 ? s_base[l] + __popc(s_mask[l] & ((1u << i) - 1u)) : -1;
+    s_row[threadIdx.x] = r;
+    const int end = min(p.subs > 1 ? (sub + 1) * kSub : t0 + tokens, p.T);
+    if (t >= t0 && t < end && j < p.k) {
+      p.row_of[(size_t)t * p.k + j] = r;
+      if (r >= 0) {
+        p.token_of[r] = t;
+        p.slot_of[r] = j;
+      }
     }
+    __syncthreads();
+    for (int n = max(t0, sub * kSub) + wave; n < end; n += kWaves) done(n, lane < kMaxK ? s_row[(n - sub * kSub) * kMaxK + lane] : -1);
+    if (++sub >= sub_end) return;
+    // the next sub-chunk's rows begin behind this one's; the masks were last read in front of the barrier above
+    for (int e = threadIdx.x; e < p.E_local; e += kRankThreads) {
+      s_base[e] += __popc(s_mask[e]);
+      s_mask[e] = 0u;
+    }
+    l = selected();
+    __syncthreads();
+    if (l >= 0) atomicOr(&s_mask[l], 1u << i);
+    __syncthreads();
   }
-  __syncthreads();
-  for (int n = t0 + wave; n < min(t0 + tokens, p.T); n += kWaves) done(n, lane < kMaxK ? s_row[(n - sub * kSub) * kMaxK + lane] : -1);
 }
 
 }  // namespace moe

@@ -98,6 +98,7 @@ class GpuBackward:
     dw_gate_up: torch.Tensor
     dw_down: torch.Tensor
     dtopk_w: torch.Tensor
+    workspace: torch.Tensor = None
 
 
 def run_backward(cfg: MoeConfig, inp: dict, run: GpuRun, mode=moe.MODE_SERIALIZED, wgrad_stream=None) -> GpuBackward:
@@ -120,7 +121,7 @@ def run_backward(cfg: MoeConfig, inp: dict, run: GpuRun, mode=moe.MODE_SERIALIZE
     # the two-stream call has joined the other stream back into this one: this stream alone is waited for
     torch.cuda.current_stream().synchronize() if wgrad_stream is not None else torch.cuda.synchronize()
     assert moe.moe_ffn_last_status(run.shape, ws) == 0
-    return GpuBackward(dx, dw1, dw2, dtw)
+    return GpuBackward(dx, dw1, dw2, dtw, ws)
 
 
 def check_backward(bwd: GpuBackward, ref_b: dict, counts: np.ndarray, dtype: str):

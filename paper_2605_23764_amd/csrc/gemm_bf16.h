@@ -689,6 +689,7 @@ __device__ __forceinline__ void swiglu_grad4(const float (&da)[4], u32x2 gv, u32
 constexpr int kGradBlock = 32 * 256;                   // bytes of a 32 x 128 block
 constexpr int kGradWave = 4 * kGradBlock;
 static_assert(4 * kGradWave <= kGemmLdsBytes, "LDS budget");
+// wait_vmcnt without a barrier behind it: the compiler may not move the LDS reads that follow in front of it either.
 template <int N>
 __device__ __forceinline__ void wait_copies() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
 

@@ -120,10 +120,12 @@ struct Ctx {
 // No MoeSaved (inference) or MoeSaved without Xp (the backward then reads x through the permutation as
 // well): nobody reads a permuted copy of x, so bf16 GEMM-1 applies the permutation while loading (32-bit
 // offsets: x must span < 4 GB) and the PERMUTE step is dropped.
-bool x_spans_32_bits(const Ctx& c) { return (size_t)c.s.T * c.s.H * 2 < ((size_t)1 << 32); }
-bool gathers_x(const Ctx& c) { return !c.keep_xp && c.s.dtype == MOE_BF16 && x_spans_32_bits(c); }
-// Single launch of up to 64 tokens, where no expert has more rows than a stream takes: as streams instead of tile tasks.
-bool streams_layer(const Ctx& c) { return c.s.dtype == MOE_BF16 && c.s.T <= kStreamRows && x_spans_32_bits(c); }
+bool gathers_x(const Ctx& c) {
+  return !c.keep_xp && c.s.dtype == MOE_BF16 && (size_t)c.s.T * c.s.H * 2 < ((size_t)1 << 32);
+}
+// Single launch of up to 64 tokens, where no expert has more rows than a stream takes: as streams instead of tile tasks.  (The offsets of
+// the gathered rows fit: H is at most 2^18.)
+bool streams_layer(const Ctx& c) { return c.s.dtype == MOE_BF16 && c.s.T <= kStreamRows; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 // Single-launch modes hand tiles over between CUs behind one L2 without invalidating the CUs' vector L1;
@@ -372,14 +374,13 @@ SchedParams<BF16> sched_params(const Ctx& c, const void* x, const float* logits,
   return sp;
 }
 
-// Routing, one launch for up to 64 tokens, otherwise two: the router (top-k, softmax, per-chunk histograms), then prefix sums +
+// Routing, one launch for up to 64 tokens, otherwise two: the router (top-k, softmax, a histogram per sub-chunk), then prefix sums +
 // M-tile map + stable ranks.  The second launch also zeroes the tile scheduler's counters and writes its task tables (one
-// workgroup, beside the rank groups), so that either launch mode can follow.
+// workgroup, beside the rank workgroups), so that either launch mode can follow.
 template <bool BF16>
 int run_route_t(const Ctx& c, const float* logits, bool tables, void* zero_out, const void* copy_x) {
   SchedParams<BF16> sp = sched_params<BF16>(c, copy_x, logits, nullptr, nullptr, nullptr);
   sp.skip_tables = tables ? 0 : 1;
-  if (zero_out) sp.no_tasks = 0;          // the scatter epilogue follows, which runs as tasks
   const RouteParams& rp = sp.route;
   const bool one = c.s.T <= kRouteOneT;   // one workgroup does it all in one launch (see route_one)
   const int fill_threads = one ? kRouteOneThreads : kScanWaves * kWave;
@@ -416,7 +417,7 @@ int run_route(const Ctx& c, const float* logits, bool tables = true, void* zero_
                                : run_route_t<false>(c, logits, tables, zero_out, copy_x);
 }
 
-// Dispatch to Combine as ONE launch of tile tasks (after run_route on the same MoeSaved).
+// Dispatch to Combine of up to 64 tokens as ONE launch of weight streams (stream_layer.h), after run_route on the same MoeSaved.
 // own_yp: GEMM-2's rows go to the workspace, the caller's Yp stays as it is.
 int run_stream_layer(const Ctx& c, const void* x, const void* w_gate_up, const void* w_down, void* out, bool own_yp = false) {
   StreamLayerParams p;
@@ -439,6 +440,7 @@ int run_stream_layer(const Ctx& c, const void* x, const void* w_gate_up, const v
   return launch_status();
 }
 
+// Dispatch to Combine as ONE launch (after run_route on the same MoeSaved): of tile tasks, up to 64 tokens in bf16 of streams.
 template <bool BF16>
 int run_persistent(const Ctx& c, const void* x, const void* w_gate_up, const void* w_down, void* out) {
   if (BF16 && streams_layer(c)) return run_stream_layer(c, x, w_gate_up, w_down, out);

@@ -2,8 +2,8 @@
 // Dispatch; Section 5.1: tile offsets derived from the routing result at run time).
 //
 // Three steps, each a device function:
-//   route_chunk  top-k + softmax for the 64 tokens of a chunk, per-chunk expert histogram
-//   scan_all     prefix sums over chunks and experts, counts/offsets, M-tile map
+//   route_chunk  top-k + softmax for a sub-chunk of 32 tokens, its expert histogram
+//   scan_all     prefix sums over sub-chunks and experts, counts/offsets, M-tile map
 //   rank_tokens  stable row of every local slot, inverse maps
 // The permutation is a stable counting sort keyed by expert: rows of one expert
 // ascend in token id, so every index is a pure function of the routing result
@@ -437,7 +437,7 @@ __device__ __forceinline__ void build_tile_map(int E_local, const int32_t* cnt, 
 
 // Whole-problem step by ONE workgroup: rows per expert (column sums of the
 // histogram table) -> counts, offsets, M-tile map.  The table itself is left as it
-// is: every rank group derives its own prefix from it.
+// is: every rank workgroup derives its own prefix from it.
 // s_cnt: (kMaxE + 2) int32 of LDS; s_part: n_waves * kMaxE int32 of LDS.
 __device__ __forceinline__ void scan_all(const RouteParams& p, int32_t* s_cnt, int32_t* s_part) {
   const int lane = lane_id();

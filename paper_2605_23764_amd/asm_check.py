@@ -12,6 +12,10 @@ for __syncthreads, but the compiler has been seen to lose the wait of a barrier 
 outstanding only along the way back: waves then read tables that others were still filling.  Barriers placed by hand
 (__builtin_amdgcn_s_barrier) never had one.  Reads may be under way at those: the GEMM pipelines do so by design.
 
+A third: a condition that is the same for the whole wave, tested inside a loop that lanes leave one by one and again behind it, is not
+carried out of the loop as a lane mask (stale_lane_masks).  The compiler did that to the copy of two rows at a time: lanes that had
+left the loop a pass earlier stored the tail of a second row where there was none.
+
     python -m paper_2605_23764_amd.asm_check        # compiles the device code to assembly and checks it
 """
 from __future__ import annotations
@@ -123,16 +127,11 @@ def innermost_loops(asm: str, kernel: str):
     return [[line for line in lines[a:b + 1] if line and not line.startswith(".")] for a, b in inner]
 
 
-_DS_WRITE = re.compile(r"ds_(write|or|and|xor|add|sub|inc|dec|min|max|cmpst|wrxchg|mskor|append|consume)")
-
-
-def barrier_violations(asm: str):
-    """Returns (number of barriers, list of (kernel, line of the barrier, line of an LDS write or atomic that a wave may pass it
-    with)), over every path of the control flow.  A wave's LDS operations complete in order, so a write is complete once
-    `s_waitcnt lgkmcnt(n)` has been passed with n or more LDS operations issued behind it."""
+def _control_flow(asm: str):
+    """Per kernel: its name, blocks of instructions [(line, text)], and the blocks that may follow each."""
     lines = [raw.split(";")[0].strip() for raw in asm.splitlines()]
     kernels = set(re.findall(r"\.amdhsa_kernel\s+(\w+)", asm))
-    n_barriers, bad, i = 0, [], 0
+    i = 0
     while i < len(lines):
         if not (lines[i].endswith(":") and lines[i][:-1] in kernels):
             i += 1
@@ -140,14 +139,13 @@ def barrier_violations(asm: str):
         name, first = lines[i][:-1], i + 1
         while not lines[i].startswith((".Lfunc_end", ".amdhsa_kernel")):
             i += 1
-        # blocks of instructions (line, text); labels; where each may go on
-        blocks, labels, target = [[]], {}, None
-        jumps = {}
+        blocks, labels, jumps, target = [[]], {}, {}, None
         for no in range(first, i):
             line = lines[no]
             m = re.match(r"(\.LBB\w+):", line)
             if m:
-                blocks.append([])
+                if blocks[-1]:
+                    blocks.append([])
                 labels[m.group(1)] = len(blocks) - 1
             if not line or line.startswith(".") or line.endswith(":"):
                 continue
@@ -156,9 +154,24 @@ def barrier_violations(asm: str):
             target = m.group(1) if m else target
             op = line.split()
             if op[0].startswith(("s_cbranch", "s_branch", "s_setpc", "s_endpgm")):
-                to = [target] if op[0].startswith("s_setpc") else op[1:2]
-                jumps[len(blocks) - 1] = (to, op[0].startswith("s_cbranch"))
+                jumps[len(blocks) - 1] = ([target] if op[0].startswith("s_setpc") else op[1:2], op[0].startswith("s_cbranch"))
                 blocks.append([])
+        follow = []
+        for n in range(len(blocks)):
+            to, falls = jumps.get(n, ([], True))
+            follow.append([labels[t] for t in to] + ([n + 1] if falls and n + 1 < len(blocks) else []))
+        yield name, blocks, follow
+
+
+_DS_WRITE = re.compile(r"ds_(write|or|and|xor|add|sub|inc|dec|min|max|cmpst|wrxchg|mskor|append|consume)")
+
+
+def barrier_violations(asm: str):
+    """Returns (number of barriers, list of (kernel, line of the barrier, line of an LDS write or atomic that a wave may pass it
+    with)), over every path of the control flow.  A wave's LDS operations complete in order, so a write is complete once
+    `s_waitcnt lgkmcnt(n)` has been passed with n or more LDS operations issued behind it."""
+    n_barriers, bad = 0, []
+    for name, blocks, follow in _control_flow(asm):
 
         def flow(b, behind, report=None):
             # behind: None, nothing under way; else (LDS operations issued behind the youngest such write, its line)
@@ -179,8 +192,7 @@ def barrier_violations(asm: str):
         while work:
             b = work.pop()
             out = flow(b, entry[b])
-            to, falls = jumps.get(b, ([], True))
-            for s in [labels[t] for t in to] + ([b + 1] if falls and b + 1 < len(blocks) else []):
+            for s in follow[b]:
                 old = entry.get(s)
                 new = out if old is None or (out is not None and out[0] < old[0]) else old
                 if s not in seen or new != old:
@@ -195,6 +207,73 @@ def barrier_violations(asm: str):
     return n_barriers, bad
 
 
+def _sgprs(token: str) -> set:
+    m = re.fullmatch(r"s\[(\d+):(\d+)\]", token)
+    if m:
+        return set(range(int(m.group(1)), int(m.group(2)) + 1))
+    m = re.fullmatch(r"s(\d+)", token)
+    return {int(m.group(1))} if m else set()
+
+
+def stale_lane_masks(asm: str):
+    """Branches behind a loop that lanes leave one by one, decided for the whole wave by a lane mask of a compare inside the loop: the mask
+    has zeros for the lanes that were no longer in it.  Returns (number of such loops, list of (kernel, line of the use, line of the
+    compare))."""
+    n_loops, bad = 0, []
+    for name, blocks, follow in _control_flow(asm):
+        before = [[] for _ in blocks]
+        for b, f in enumerate(follow):
+            for s in f:
+                before[s].append(b)
+        for latch, block in enumerate(blocks):
+            if not any(line.startswith("s_andn2_b64 exec, exec") for _, line in block):
+                continue
+            # the smallest loop that this block closes
+            body = None
+            for head in follow[latch]:
+                loop, work = {head, latch}, [latch]
+                while work:
+                    b = work.pop()
+                    if b != head:
+                        new = [q for q in before[b] if q not in loop]
+                        loop.update(new)
+                        work += new
+                if (0 not in loop or head == 0) and (body is None or len(loop) < len(body)):
+                    body = loop
+            if body is None:
+                continue
+            n_loops += 1
+            masks, other = {}, set()
+            for b in body:
+                for no, line in blocks[b]:
+                    op = line.replace(",", " ").split()
+                    if len(op) < 2:
+                        continue
+                    if op[0].startswith("v_cmp") and op[1].startswith("s["):
+                        masks[op[1]] = no
+                    else:
+                        other |= _sgprs(op[1]) if not op[0].startswith("s_c") else set()
+            masks = {m: no for m, no in masks.items() if not _sgprs(m) & other}
+            # from the loop's ends on, until the mask is written again
+            seen = set()
+            work = [(s, frozenset(masks)) for b in body for s in follow[b] if s not in body] if masks else []
+            while work:
+                b, live = work.pop()
+                if b in body or (b, live) in seen:
+                    continue
+                seen.add((b, live))
+                for i, (no, line) in enumerate(blocks[b]):
+                    op = line.replace(",", " ").split()
+                    if op[0] in ("s_and_b64", "s_andn2_b64") and op[1] == "vcc" and "exec" in op[2:4]:
+                        if any(o[1].startswith("s_cbranch_vcc") for o in blocks[b][i + 1:]):
+                            bad += [(name, no, masks[m]) for m in op[2:4] if m in live]
+                    if len(op) > 1 and not op[0].startswith("s_cmp"):
+                        live = frozenset(m for m in live if not _sgprs(m) & _sgprs(op[1]))
+                if live:
+                    work += [(s, live) for s in follow[b]]
+    return n_loops, sorted(set(bad))
+
+
 def main():
     n, bad = check_register_fed_loads(device_assembly())
     print(f"{n} assembly loads with register destinations, {len(bad)} instructions inside a request-to-retire window touch them")
@@ -204,7 +283,11 @@ def main():
     print(f"{n_barriers} barriers, {len(late)} passed with LDS writes under way")
     for kernel, no, write in late[:20]:
         print(f"  {kernel}: barrier in line {no}, write in line {write}")
-    sys.exit(1 if bad or late or n == 0 else 0)
+    n_loops, stale = stale_lane_masks(device_assembly())
+    print(f"{n_loops} loops that lanes leave one by one, {len(stale)} uses of their lane masks for the whole wave behind them")
+    for kernel, no, compare in stale[:20]:
+        print(f"  {kernel}: use in line {no}, compare in line {compare}")
+    sys.exit(1 if bad or late or stale or n == 0 else 0)
 
 
 if __name__ == "__main__":

@@ -48,8 +48,12 @@ __device__ __forceinline__ void permute_rows(const PermuteParams& p, int r_begin
       const uint4* src1 = reinterpret_cast<const uint4*>(static_cast<const char*>(p.x) + (size_t)t1 * row_bytes);
       uint4* dst0 = reinterpret_cast<uint4*>(static_cast<char*>(p.Xp) + (size_t)r0 * row_bytes);
       uint4* dst1 = reinterpret_cast<uint4*>(static_cast<char*>(p.Xp) + (size_t)r1 * row_bytes);
-      int v = lane;
-      for (; v + (U - 1) * kWave < vec_per_row; v += U * kWave) {
+      // Both loops are left by all lanes at once: with `v + (U - 1) * kWave < vec_per_row` per lane, rows whose last pass is full for
+      // some lanes only (3392 floats) took `two` from a lane mask of the first loop to the second, which has zeros for the lanes that had
+      // left it, and the tail of a second row was stored where there was none.
+      int v0 = 0;
+      for (; v0 + U * kWave <= vec_per_row; v0 += U * kWave) {
+        const int v = v0 + lane;
         u32x4 q0[U], q1[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) q0[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src0 + v + u * kWave));
@@ -64,7 +68,9 @@ __device__ __forceinline__ void permute_rows(const PermuteParams& p, int r_begin
           for (int u = 0; u < U; ++u) put(dst1 + v + u * kWave, q1[u]);
         }
       }
-      for (; v < vec_per_row; v += kWave) {
+      for (; v0 < vec_per_row; v0 += kWave) {
+        const int v = v0 + lane;
+        if (v >= vec_per_row) continue;
         if (through) {
           put(dst0 + v, *reinterpret_cast<const u32x4*>(src0 + v));
           if (two) put(dst1 + v, *reinterpret_cast<const u32x4*>(src1 + v));

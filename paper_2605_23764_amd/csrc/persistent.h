@@ -196,7 +196,7 @@ __device__ __forceinline__ int sched_chain_scope(const SchedParams<BF16>& sp, in
 // kFarRounds tasks per worker, whose rounds drift apart between the dies.  With fewer, the hand-over through memory costs more than the
 // drawing gives (T = 500, H = 2048 121 -> 125 us, T = 2000 207 -> 211): a skewed launch of few rounds leaves a die idle whose queue has
 // run out.  PERMUTE tasks count like tiles.  Both forms are one body: against the near one alone it spills 14 vector registers instead
-// of 11 in the forward, 17 instead of 11 in the backward, and 441 scalar ones instead of 295, which launches of few tasks pay as well.
+// of 11 in the forward, 17 instead of 11 in the backward, and 407 scalar ones instead of 295, which launches of few tasks pay as well.
 constexpr int kFarRounds = 4;
 __device__ __forceinline__ bool sched_hands_far(const int32_t* meta) {
   int total = 0;

@@ -1,12 +1,13 @@
 """The generated code keeps the contract of the assembly loads with register destinations (register-fed row block
 of the wide GEMM tile): nothing touches their destination registers between the request and the wait that retires
-them; and no wave passes a barrier with LDS writes of its own under way.  CPU only: the device code is compiled to assembly and read; the checker itself is tried on planted text."""
+them; no wave passes a barrier with LDS writes of its own under way;
+and no lane mask of a loop decides for the whole wave behind it.  CPU only: the device code is compiled to assembly and read; the checker itself is tried on planted text."""
 import os
 
 import pytest
 
 from paper_2605_23764_amd.asm_check import (barrier_violations, check_register_fed_loads, device_assembly, innermost_loops,
-                                            loads_ahead_of_first_branch)
+                                            loads_ahead_of_first_branch, stale_lane_masks)
 
 GOOD = """
 \t.amdhsa_kernel k
@@ -84,6 +85,50 @@ def test_barrier_checker_follows_the_loop():
 def test_no_barrier_is_passed_with_lds_writes_under_way():
     n, bad = barrier_violations(device_assembly())
     assert n > 500, n
+    assert not bad, bad[:5]
+
+
+LANES = """
+\t.amdhsa_kernel k
+k:
+\ts_mov_b64 s[6:7], 0
+\ts_branch .LBB0_2
+.LBB0_1:
+\tv_cmp_le_i32_e32 vcc, s8, v1
+\ts_or_b64 s[6:7], vcc, s[6:7]
+\ts_andn2_b64 exec, exec, s[6:7]
+\ts_cbranch_execz .LBB0_4
+.LBB0_2:
+\tv_cmp_ne_u32_e64 s[4:5], 1, v2
+\ts_and_b64 vcc, exec, s[4:5]
+\ts_cbranch_vccnz .LBB0_1
+\tglobal_store_dword v3, v4, s[2:3]
+\ts_branch .LBB0_1
+.LBB0_4:
+\ts_or_b64 exec, exec, s[6:7]
+\ts_andn2_b64 vcc, exec, s[10:11]
+\ts_cbranch_vccnz .LBB0_5
+\tglobal_store_dword v3, v4, s[2:3]
+.LBB0_5:
+\ts_endpgm
+.Lfunc_end0:
+"""
+
+
+def test_lane_mask_checker_looks_behind_the_loop():
+    assert stale_lane_masks(LANES) == (1, [])
+    stale = LANES.replace("s_andn2_b64 vcc, exec, s[10:11]", "s_and_b64 vcc, exec, s[4:5]")
+    assert stale_lane_masks(stale) == (1, [("k", 19, 12)])
+    # the mask is computed again behind the loop; written by something else; its register is not read as a mask of the wave
+    for fresh in ("v_cmp_ne_u32_e64 s[4:5], 1, v2", "s_mov_b64 s[4:5], 0"):
+        assert stale_lane_masks(stale.replace("\ts_and_b64 vcc, exec, s[4:5]\n\ts_cbranch_vccnz .LBB0_5", f"\t{fresh}\n\ts_and_b64 vcc, exec, s[4:5]\n\ts_cbranch_vccnz .LBB0_5")) == (1, [])
+    assert stale_lane_masks(stale.replace("vcc, exec, s[4:5]\n\ts_cbranch_vccnz .LBB0_5", "s[12:13], exec, s[4:5]\n\ts_cbranch_scc1 .LBB0_5"))[1] == []
+
+
+@pytest.mark.skipif(not os.path.exists(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")), reason="needs hipcc")
+def test_no_lane_mask_of_a_loop_decides_for_the_wave_behind_it():
+    n, bad = stale_lane_masks(device_assembly())
+    assert n > 100, n
     assert not bad, bad[:5]
 
 

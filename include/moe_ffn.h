@@ -143,6 +143,9 @@ int moe_ffn_workspace_bytes(const MoeShape* shape, size_t* fwd_bytes, size_t* bw
  *              they verify at run time (hardware XCC id) that the workers of a queue all sit on one die
  *              and use device-wide fences for that queue otherwise.  Up to 64 tokens (bf16) that one launch
  *              runs both GEMMs as weight streams instead of tile tasks.
+ *              The workers of a launch of tile tasks wait (bounded) until all of them run, so two such launches
+ *              side by side on one GPU, each on a part of it, can end in a scheduler timeout; beside other work, and
+ *              in the launch of up to 64 tokens, every wait is for workgroups that run.
  * Returns after enqueueing.  A scheduler timeout (MOE_MODE_PERSISTENT only) is
  * reported by moe_ffn_last_status().
  */
